@@ -138,17 +138,18 @@ def _prepare_layer(case, seed):
     xc = _hidden(g, sh, Bc * Sc, gain).double()
     if post:
         xc = torch.nn.functional.layer_norm(xc, (d,), emb_g.double(), emb_b.double(), sh.eps)
-    weights, keep = [], []
+    weights, keep, scales = [], [], []
     for _ in range(case["layers"]):
         p = _params(g, sh)
         sc, xc = prep.calibrate(p, xc, sh.arch, sh.H, sh.Dh, sh.eps, HB.MASK_NONE if post else HB.MASK_CAUSAL, Bc, Sc, hero=hero, fp8=fp8)
         t, qk, ps = prep.prepare(p, sc, sh.arch, d, sh.Dh, mode, hero=hero, fp8=fp8)
         keep.append(t)
+        scales.append((qk, ps))
         weights.append(hero.layer_weights(t, qk, ps))
         del p
 
     desc = hero.layer_desc(sh.arch, d, sh.H, sh.Dh, sh.f, sh.eps, mask, mode | (HB.M_FP8 if fp8 else 0))
-    st = {"kind": "layer", "hero": hero, "desc": desc, "weights": weights, "keep": keep, "B": B, "S": S, "post": post,
+    st = {"kind": "layer", "hero": hero, "desc": desc, "weights": weights, "keep": keep, "scales": scales, "B": B, "S": S, "post": post,
           "next": [keep[(l + 1) % len(keep)].get("w_qkv") for l in range(len(keep))],
           "ws": torch.empty(hero.hero_layer_workspace_bytes(desc, B, S), dtype=torch.uint8, device="cuda")}
     h0 = _hidden(g, sh, T, gain)
@@ -201,11 +202,12 @@ def _prepare_embed(case, seed):
     B, S, d = case["B"], case["S"], sh.d
     tok = _randn(g, VOCAB, d) * 0.02
     scale = tok.abs().amax(1) / 127
-    w = 1.0 / (torch.arange(VOCAB, device="cuda") + 10.0)      # word frequencies fall with the rank
+    u = torch.rand(B * S, device="cuda", generator=g, dtype=torch.float64)
+    ids = 10 * (((VOCAB + 10) / 10) ** u - 1)                  # word frequencies fall as 1 / (rank + 10)
     st = {"kind": "embed", "hero": pkg.load(), "tok": (tok / scale[:, None]).round().to(torch.int8), "tok_scale": scale,
           "pos": (0.02 * _randn(g, MAX_POS, d)).to(torch.bfloat16), "type": (0.02 * _randn(g, TYPES, d)).to(torch.bfloat16),
           "g": 1 + 0.1 * _randn(g, d), "b": 0.02 * _randn(g, d), "eps": sh.eps,
-          "ids": torch.multinomial(w, B * S, replacement=True, generator=g).to(torch.int32),
+          "ids": ids.clamp(0, VOCAB - 1).to(torch.int32),
           "pos_ids": torch.arange(S, device="cuda", dtype=torch.int32).repeat(B),
           "y": (torch.empty((B * S, d), dtype=torch.int8, device="cuda"), torch.empty(B * S, device="cuda"))}
     split = torch.randint(S // 4, S, (B, 1), device="cuda", generator=g)
@@ -242,6 +244,127 @@ def run(st):
         hero.hero_layer_fwd(st["desc"], st["weights"][l], B, S, st["ws"], h=st["h"], kv_len=st["kv_len"], k_cache=kc, v_cache=vc,
                             next_read=st["next"][l])
     return [st["h"]] + [c for kv in st["caches"] or [] for c in kv]
+
+
+# ---------------------------------------------------------------------------------------------------- the same in 64 bits
+def _f8(x):
+    """E4M3 values nearest to x, saturating: the codes lie on the grid 2^-9 * integers, 3 bits behind the leading one."""
+    e = torch.floor(torch.log2(x.abs().clamp(min=2.0 ** -6)))
+    u = torch.exp2(e - 3)
+    return ((x / u).round() * u).clamp(-448, 448)
+
+
+def _code(x, fp8):
+    return _f8(x) if fp8 else x.round().clamp(-127, 127)
+
+
+def _ln_quant64(x, g, b, eps, fp8):
+    """LN^quant in 64 bits: codes, token-wise scales and the values themselves."""
+    y = torch.nn.functional.layer_norm(x, x.shape[-1:], g.double(), b.double(), eps)
+    s = y.abs().amax(1) / (448.0 if fp8 else 127.0)
+    s = torch.where(s == 0, torch.ones_like(s), s)
+    return _code(y / s[:, None], fp8), s, y
+
+
+def _attn64(q, k, v, qk, ps, visible, fp8):
+    """Attention of one sequence, [H, S, Dh] against [H, Skv, Dh]; ps: the step of the 8-bit probabilities (None: 16-bit
+    attention).  visible: [S, Skv].  Rows that see nothing are zero."""
+    out = torch.empty_like(q)
+    any_ = visible.any(1)
+    for h in range(q.shape[0]):
+        a = (q[h] @ k[h].t()) * qk
+        a = a.masked_fill(~visible, -torch.inf).masked_fill(~any_[:, None], 0.0)
+        p = torch.softmax(a, 1) * any_[:, None]
+        if ps is not None:
+            p = _f8(p / ps) if fp8 else (p / ps).round().clamp(0, 255)
+        out[h] = p @ v[h]
+    return out
+
+
+def _layer64(case, st, l, x, x_scale):
+    """One layer in 64 bits: x are the input's codes with x_scale, or (pre-LN; a 16-bit QKV) its values.  The 8-bit codes and
+    the 16-bit storage between two modules are the method's own and stay; everything between them is 64 bits."""
+    sh, m, t = MODELS[case["model"]], MODES[case["mode"]], st["keep"][l]
+    (qk, ps), fp8, post = st["scales"][l], case["fmt"] == "fp8", st["post"]
+    B, S, d, H, Dh = st["B"], st["S"], sh.d, sh.H, sh.Dh
+    hp = lambda v: v.to(DTYPES[case["hp"]]).double()
+    D = lambda name: t[name].double()
+    on = lambda bit: bool(m & bit)
+    ln = lambda v, n: _ln_quant64(v, t[n + "_g"], t[n + "_b"], sh.eps, fp8)
+
+    def linear(a, a_scale, w, w_hp, b, i8):
+        y = a @ (D(w) if i8 else D(w_hp)).t()
+        if i8:
+            y = y * D(w + "_s")
+            y = y if a_scale is None else y * a_scale[:, None]
+        return y + D(b)
+
+    h = x
+    if post:
+        xin, xs = x, x_scale
+    else:
+        c, s_, y = ln(h, "ln1")
+        xin, xs = (c, s_) if on(HB.M_QKV) else (hp(y), None)
+    qkv = linear(xin, xs, "w_qkv", "w_qkv_hp", "b_qkv", on(HB.M_QKV))
+    qkv = _code(qkv, fp8) if on(HB.M_ATTN) else hp(qkv)
+    q, k, v = (p.reshape(B, S, H, Dh).transpose(1, 2) for p in qkv.split(d, 1))
+    caches = st["caches"][l] if st["caches"] else None
+    rows = torch.arange(S, device="cuda")[:, None]
+    attn = torch.empty((B, S, H, Dh), dtype=torch.float64, device="cuda")
+    for b in range(B):
+        n = int(st["kv_len"][b]) if st["kv_len"] is not None else S
+        kb, vb = k[b], v[b]
+        if caches:
+            for c, new in zip(caches, (kb, vb)):
+                c[b, :, n - S:n] = new.float().to(c.dtype)
+            kb, vb = (c[b, :, :n].double() for c in caches)
+        cols = torch.arange(kb.shape[1], device="cuda")[None, :]
+        visible = (cols < n) & (rows < n) if post else cols <= rows + (n - S)
+        attn[b] = _attn64(q[b], kb, vb, qk, ps if on(HB.M_ATTN) else None, visible, fp8).transpose(0, 1)
+    attn = attn.reshape(B * S, d)
+    if on(HB.M_ATTN):
+        attn = attn * D("attn_out_scale")
+    attn = _code(attn, fp8) if on(HB.M_ATTN_OUT) else hp(attn)
+    o = linear(attn, None, "w_o", "w_o_bf16", "b_o", on(HB.M_ATTN_OUT))
+    if post:
+        o = _code(o, fp8) * D("S_o") if on(HB.M_ATTN_OUT) else hp(o)
+        c, s_, y = ln((x * x_scale[:, None] if x_scale is not None else x) + o, "ln1")
+    else:
+        h = hp(h + o)
+        c, s_, y = ln(h, "ln2")
+    mid, ms = (c, s_) if on(HB.M_FC1) else (hp(y), None)
+    a = torch.nn.functional.gelu(linear(mid, ms, "w_1", "w_1_hp", "b_1", on(HB.M_FC1)))
+    a = _code(a / D("S_a"), fp8) if on(HB.M_FC2) else hp(a)
+    x2 = linear(a, None, "w_2", "w_2_bf16", "b_2", on(HB.M_FC2))
+    if not post:
+        return hp(h + x2), None, None
+    x2 = _code(x2, fp8) * D("S_x2") if on(HB.M_FC2) else hp(x2)
+    return ln((mid * ms[:, None] if ms is not None else mid) + x2, "ln2")
+
+
+def exact(case, seed):
+    st = prepare(case, seed)
+    if st["kind"] == "gemm":
+        y = (st["A"].double() @ st["Bt"].double().t()) * st["rs"].double()[:, None] * st["cs"].double() + st["bias"].double()
+        if case["epi"] == "gelu":
+            y = torch.nn.functional.gelu(y) / st["out_scale"].double()
+        return _code(y, False) if case["out"] == "i8" else y
+    if st["kind"] == "embed":
+        x = st["tok"][st["ids"].long()].double() * st["tok_scale"][st["ids"].long()].double()[:, None]
+        x = x + st["pos"][st["pos_ids"].long()].double() + st["type"][st["type_ids"].long()].double()
+        return _ln_quant64(x, st["g"], st["b"], st["eps"], False)[:2]
+    if not st["post"]:
+        h = st["h0"].double()
+        for l in range(case["layers"]):
+            h = _layer64(case, st, l, h, None)[0]
+        return [h] + [c for kv in st["caches"] or [] for c in kv]
+    q, s, y = st["x"]
+    i8 = bool(MODES[case["mode"]] & HB.M_QKV)
+    x, xs = (q.double(), s.double()) if i8 else (y.double(), None)
+    for l in range(case["layers"]):
+        q, s, y = _layer64(case, st, l, x, xs)
+        x, xs = (q, s) if i8 else (y, None)
+    return [q, s] if i8 else [q, s, y]
 
 
 # ---------------------------------------------------------------------------------------------------- what a pass needs
