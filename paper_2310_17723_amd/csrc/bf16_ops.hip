@@ -1,9 +1,7 @@
 // 16-bit side of a switched module (paper Sec. 2.3, Table 1: a module marked with a cross runs
-// in FP16 / BF16): hero_hp_gemm and hero_hp_attn (and their BF16-only names hero_bf16_gemm / hero_bf16_attn).
+// in FP16 / BF16): hero_hp_attn (and its BF16-only name hero_bf16_attn); hero_hp_gemm is in int8_gemm.hip.
 // bf16 or fp16 operands, fp32 accumulation on the matrix cores (v_mfma_f32_32x32x16_bf16 / _f16), results in
-// the operands' type.  These kernels make the mixed modes functional; they follow the same operand layouts as
-// the INT8 kernels (both operands K-contiguous, weight fragment first so a lane owns one output row); large
-// GEMMs go to the persistent kernels of int8_gemm.hip.
+// the operands' type.
 #include "hero_common.h"
 
 namespace {
@@ -16,115 +14,6 @@ template <int DT>
 __device__ __forceinline__ v16f mfma_hp(v4i a, v4i b, v16f c) {
     if constexpr (DT == HERO_BF16) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
-}
-
-// ------------------------------------------------------------------------------------------
-// GEMM: C = act(A Wt^T + bias) (+ residual).  128x128 tile, 4 waves of 64x64, slabs of 32
-// bf16 (64 bytes) of K staged through registers into double-buffered, padded LDS.
-// ------------------------------------------------------------------------------------------
-constexpr int GBK = 64;             // bytes of K per slab (32 bf16)
-constexpr int GLD = GBK + 16;
-
-struct BGemmArgs {
-    const uint16_t* A; int64_t lda; const uint16_t* Wt; int64_t ldb;
-    const float* bias; const uint16_t* residual; int64_t ldr; int gelu;
-    uint16_t* C; int64_t ldc; int M, N, K;
-};
-
-template <int DT>
-__global__ __launch_bounds__(256) void bf16_gemm_kernel(BGemmArgs g) {
-    constexpr int BM = 128, BN = 128, TM = 2, TN = 2, NT = 256, CPR = GBK / 16;
-    constexpr int UNITS = BM * CPR / NT;
-    __shared__ __attribute__((aligned(16))) int8_t sA[2][BM * GLD];
-    __shared__ __attribute__((aligned(16))) int8_t sB[2][BN * GLD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int KT = g.K * 2 / GBK, last = KT - 1;
-    const int8_t* pa[UNITS];
-    const int8_t* pb[UNITS];
-    int lo[UNITS];
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-        int idx = tid + u * NT, row = idx / CPR, ch = idx % CPR;
-        pa[u] = (const int8_t*)(g.A + (int64_t)min(m0 + row, g.M - 1) * g.lda) + ch * 16;
-        pb[u] = (const int8_t*)(g.Wt + (int64_t)min(n0 + row, g.N - 1) * g.ldb) + ch * 16;
-        lo[u] = row * GLD + ch * 16;
-    }
-    v4i ra[UNITS], rb[UNITS];
-    auto load = [&](int kt) {
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            ra[u] = *reinterpret_cast<const v4i*>(pa[u] + (int64_t)kt * GBK);
-            rb[u] = *reinterpret_cast<const v4i*>(pb[u] + (int64_t)kt * GBK);
-        }
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            *reinterpret_cast<v4i*>(&sA[buf][lo[u]]) = ra[u];
-            *reinterpret_cast<v4i*>(&sB[buf][lo[u]]) = rb[u];
-        }
-    };
-    v16f acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    load(0);
-    store(0);
-    load(min(1, last));
-    __syncthreads();
-    const int fo = (lane & 31) * GLD + (lane >> 5) * 16;
-    for (int kt = 0; kt < KT; ++kt) {
-        const int buf = kt & 1;
-#pragma unroll
-        for (int ks = 0; ks < GBK / 32; ++ks) {
-            v4i fa[TM], fb[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const v4i*>(&sA[buf][(wm * 64 + i * 32) * GLD + fo + ks * 32]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const v4i*>(&sB[buf][(wn * 64 + j * 32) * GLD + fo + ks * 32]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = mfma_hp<DT>(fb[j], fa[i], acc[i][j]);
-        }
-        store(buf ^ 1);                       // slab kt + 1 (a redundant copy of the last slab at the end)
-        load(min(kt + 2, last));
-        __syncthreads();
-    }
-    // epilogue: lane owns row m, 4-column groups
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int m = m0 + wm * 64 + i * 32 + (lane & 31);
-        if (m >= g.M) continue;
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                const int n = n0 + wn * 64 + j * 32 + gq * 8 + (lane >> 5) * 4;
-                if (n >= g.N) continue;
-                uint32_t h[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int nn = min(n + t, g.N - 1);
-                    float y = acc[i][j][4 * gq + t] + (g.bias ? g.bias[nn] : 0.0f);
-                    if (g.gelu) y = gelu_erf(y);
-                    if (g.residual && n + t < g.N) y += hp_to_f32<DT>(g.residual[(int64_t)m * g.ldr + n + t]);
-                    h[t] = f32_to_hp<DT>(y);
-                }
-                uint16_t* cp = g.C + (int64_t)m * g.ldc + n;
-                if (n + 3 < g.N) {
-                    v2i o = {(int)(h[0] | (h[1] << 16)), (int)(h[2] | (h[3] << 16))};
-                    *reinterpret_cast<v2i*>(cp) = o;
-                } else {
-                    for (int t = 0; t < 4; ++t) if (n + t < g.N) cp[t] = (uint16_t)h[t];
-                }
-            }
-    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -308,51 +197,6 @@ __global__ void zero_bf16_kernel(uint16_t* out, int64_t rows, int64_t cols, int6
 }
 
 }  // namespace
-
-static hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
-                               const float* bias, const void* residual, int64_t ldr, int gelu,
-                               void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream, int tile) {
-    if (dt != HERO_BF16 && dt != HERO_F16) return HERO_ERR_UNSUPPORTED;
-    if (M < 0 || N < 0 || K <= 0 || M > 0x7fffffffLL || N > 0x7fffffffLL || K > 0x3fffffffLL) return HERO_ERR_SHAPE;
-    if (K % 32 != 0) return HERO_ERR_UNSUPPORTED;
-    if (lda < K || ldb < K || ldc < N || (residual && ldr < N)) return HERO_ERR_SHAPE;
-    if (M == 0 || N == 0) return HERO_OK;
-    if (!A || !Wt || !C) return HERO_ERR_NULL;
-    if (lda % 8 || ldb % 8 || ldc % 4 || !hero_aligned16(A) || !hero_aligned16(Wt) || !hero_aligned16(C)) return HERO_ERR_ALIGN;
-    if (!residual || (ldr % 8 == 0 && hero_aligned16(residual))) {        // large problems: the persistent kernels
-        const hero_status big = hero_hp_gemm_large(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, (hipStream_t)stream, tile);
-        if (big != HERO_ERR_UNSUPPORTED) return big;
-    }
-    if ((M + 127) / 128 > 65535) return HERO_ERR_UNSUPPORTED;
-    BGemmArgs g;
-    g.A = (const uint16_t*)A; g.lda = lda; g.Wt = (const uint16_t*)Wt; g.ldb = ldb; g.bias = bias;
-    g.residual = (const uint16_t*)residual; g.ldr = ldr; g.gelu = gelu; g.C = (uint16_t*)C; g.ldc = ldc;
-    g.M = (int)M; g.N = (int)N; g.K = (int)K;
-    dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
-    if (dt == HERO_BF16) hipLaunchKernelGGL(bf16_gemm_kernel<HERO_BF16>, grid, dim3(256), 0, (hipStream_t)stream, g);
-    else hipLaunchKernelGGL(bf16_gemm_kernel<HERO_F16>, grid, dim3(256), 0, (hipStream_t)stream, g);
-    return hero_launch_status();
-}
-
-extern "C" hero_status hero_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
-                                    const float* bias, const void* residual, int64_t ldr, int gelu,
-                                    void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream) {
-    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, stream, -1);
-}
-
-extern "C" hero_status hero_bf16_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
-                                      const float* bias, const void* residual, int64_t ldr, int gelu,
-                                      void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
-    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, HERO_BF16, stream, -1);
-}
-
-// Test and tuning hook (include/hero_debug.h): tile 7 / 8 = the persistent 256x256 / 128x128 kernel, 0 = the plain one.
-extern "C" hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void* Wt, int64_t ldb,
-                                         const float* bias, const void* residual, int64_t ldr, int gelu,
-                                         void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream, int tile) {
-    if (tile != 0 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
-    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, stream, tile);
-}
 
 extern "C" hero_status hero_bf16_attn(const void* q, const int64_t q_strides[4],
                                       const void* k, const int64_t k_strides[4],

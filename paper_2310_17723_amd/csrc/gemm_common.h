@@ -1,0 +1,334 @@
+// What the GEMM kernels share: arguments, matrix instructions per operand type, tile order, the epilogue behind the
+// accumulators, direct global -> LDS loads.
+#pragma once
+#include "hero_common.h"
+#include <type_traits>
+
+namespace hero_gemm {
+
+constexpr int KMULT = 64;       // K must be a multiple of this
+constexpr int BK = 64;          // bytes of K per LDS slab
+constexpr int LDS_LD = BK + 16; // padded slab row stride of the register-staged kernel
+constexpr int GROUP_M = 8;      // tile order: 8 row panels x 8 column panels run together on one XCD
+constexpr int NUM_XCD = 8;
+
+struct GemmArgs {
+    const int8_t* A; int64_t lda; const float* a_row_scale;
+    const int8_t* Bt; int64_t ldb; const float* b_col_scale;
+    const float* bias; const void* residual; int64_t ldr;
+    const float* out_col_scale;
+    void* C; int64_t ldc;
+    int M, N, K;
+    int ntm, ntn, per_xcd;      // tile grid and tiles per XCD
+    // split-K (skinny M): blockIdx.y picks a range of kslabs slabs and writes raw int32 partial sums
+    // to its own [M][ldc] plane of C (plane stride M * ldc elements); a second kernel adds the planes
+    int ksplit, kslabs;
+    // optional (persistent kernels only): memory the NEXT kernel of the caller's chain will read (a layer's next weight
+    // matrix).  Every tile requests pf_lpt of its pf_lines 128-byte lines once, at the start of its epilogue.
+    const int8_t* pf = nullptr; int pf_lines = 0, pf_lpt = 0;
+};
+
+// Operand types of the main loops.  ADT = HERO_I8: INT8 operands, int32 accumulators.  ADT = HERO_BF16: bf16
+// operands (the BF16 side of a switched module, Sec. 2.3 / Table 1), fp32 accumulators, no scales; K, lda and ldb
+// are then in BYTES, and a 64-byte slab holds two v_mfma_f32_32x32x16_bf16 steps exactly as it holds two INT8
+// steps.  ADT = HERO_F8E4M3: the FP8 variant (Sec. 2.1), fp32 accumulators, the INT8 epilogue; a 16-byte
+// fragment feeds two v_mfma_f32_32x32x16_fp8_fp8 (its low and its high 8 bytes: any grouping of K is a valid
+// contraction as long as both operands use the same one).
+typedef _Float16 v8hf __attribute__((ext_vector_type(8)));
+template <int ADT, typename ACC>
+__device__ __forceinline__ ACC mfma_step(v4i a, v4i b, ACC c) {
+    if constexpr (ADT == HERO_I8) return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+    else if constexpr (ADT == HERO_BF16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+    else if constexpr (ADT == HERO_F16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8hf, a), __builtin_bit_cast(v8hf, b), c, 0, 0, 0);
+    else {
+        const long a0 = (long)(((uint64_t)(uint32_t)a[1] << 32) | (uint32_t)a[0]), a1 = (long)(((uint64_t)(uint32_t)a[3] << 32) | (uint32_t)a[2]);
+        const long b0 = (long)(((uint64_t)(uint32_t)b[1] << 32) | (uint32_t)b[0]), b1 = (long)(((uint64_t)(uint32_t)b[3] << 32) | (uint32_t)b[2]);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a0, b0, c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a1, b1, c, 0, 0, 0);
+    }
+}
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), in order
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) { f(std::integral_constant<int, I>{}); static_for<N, I + 1>(f); }
+}
+template <int ADT> struct AccOf { using type = typename std::conditional<ADT == HERO_I8, v16i, v16f>::type; };
+
+template <int CDT> struct ElemSize { static constexpr int v = CDT == HERO_I32 ? 4 : ((CDT == HERO_I8 || CDT == HERO_F8E4M3) ? 1 : 2); };
+
+// XCD-aware tile order: workgroups go round-robin to the 8 XCDs, so XCD x takes the
+// contiguous range [x * per_xcd, (x+1) * per_xcd) of a grouped order in which 64
+// consecutive tiles form an 8 x 8 square of panels (operands shared through that XCD's L2).
+template <int BM, int BN>
+__device__ __forceinline__ void tile_from_seq(const GemmArgs& g, int seq, int& m0, int& n0) {
+    const int grp = seq / (GROUP_M * g.ntn), rem = seq % (GROUP_M * g.ntn);
+    const int gsize = min(g.ntm - grp * GROUP_M, GROUP_M);
+    m0 = (grp * GROUP_M + rem % gsize) * BM;
+    n0 = (rem / gsize) * BN;
+}
+template <int BM, int BN>
+__device__ __forceinline__ bool tile_origin(const GemmArgs& g, int& m0, int& n0) {
+    const int seq = (blockIdx.x % NUM_XCD) * g.per_xcd + blockIdx.x / NUM_XCD;
+    if (seq >= g.ntm * g.ntn) return false;
+    tile_from_seq<BM, BN>(g, seq, m0, n0);
+    return true;
+}
+
+// Per-column epilogue vectors of the tile -> LDS ([3][BN] floats: column scale, bias,
+// output scale), issued before the main loop so their latency hides behind it.
+template <int BN, int NT, int EPI, bool UNIT = false>
+__device__ __forceinline__ void stage_col_vectors(const GemmArgs& g, float* sv, int n0, int tid) {
+    if (EPI == HERO_EPI_RAW_I32) return;
+    for (int c = tid; c < BN; c += NT) {
+        const int n = min(n0 + c, g.N - 1);
+        if (!UNIT) sv[c] = g.b_col_scale[n];
+        sv[BN + c] = g.bias ? g.bias[n] : 0.0f;
+        if (EPI == HERO_EPI_GELU_REQUANT) sv[2 * BN + c] = __fdiv_rn(1.0f, g.out_col_scale[n]);   // 1 / S_a[j]
+    }
+}
+
+// ---- direct epilogue ---------------------------------------------------------------------------
+// No LDS: after the fp32 epilogue a lane holds, for ONE output row, 4-column groups q (columns
+// 8q + 4hh .. + 3 of the wave's 32*TN columns).  v_permlane32_swap exchanges the groups q >= NQ/2
+// of lanes 0..31 with the groups q < NQ/2 of lanes 32..63, after which lane l < 32 owns the
+// row's first 16*TN columns and lane l + 32 the other 16*TN, contiguous in registers: every lane
+// writes one contiguous piece of its row (32 B of INT8 codes, 64 B of 16-bit values for TN = 2)
+// with 128-bit stores, and the residual of the fused add is read in the same layout.
+__device__ __forceinline__ void swap32(uint32_t a, uint32_t b, uint32_t& lo, uint32_t& hi) {
+    auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);   // r[0] = {a.low, b.low}, r[1] = {a.high, b.high}
+    lo = r[0]; hi = r[1];
+}
+// ND dwords of one row, first column col (ES bytes per element), bounds-checked against N unless `full`
+template <int ES, int ND>
+__device__ __forceinline__ void store_piece(int8_t* cp, const uint32_t (&d)[ND], int col, int N, bool full, bool al16) {
+    constexpr int EPD = 4 / ES;                                     // elements per dword
+    if (full) {
+        if (al16) {
+#pragma unroll
+            for (int k = 0; k < ND / 4; ++k) {
+                v4i o = {(int)d[4 * k], (int)d[4 * k + 1], (int)d[4 * k + 2], (int)d[4 * k + 3]};
+                *reinterpret_cast<v4i*>(cp + 16 * k) = o;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < ND; ++k) *reinterpret_cast<uint32_t*>(cp + 4 * k) = d[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < ND; ++k) {
+            const int c = col + k * EPD;
+            if (c + EPD <= N) *reinterpret_cast<uint32_t*>(cp + 4 * k) = d[k];
+            else if (ES < 4) {
+#pragma unroll
+                for (int b = 0; b < EPD; ++b)
+                    if (c + b < N) {
+                        if (ES == 1) cp[4 * k + b] = (int8_t)(d[k] >> (8 * b));
+                        else *reinterpret_cast<uint16_t*>(cp + 4 * k + 2 * b) = (uint16_t)(d[k] >> (16 * b));
+                    }
+            }
+        }
+    }
+}
+
+// ACC is v16i (INT8 operands) or v16f (bf16 operands: UNIT, no scales, y = acc + bias).
+template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT, bool OS_RAW = false, bool UNIT = false, typename ACC = v16i>
+__device__ __forceinline__ void epilogue_direct(const GemmArgs& g, ACC (&acc)[BM / WM / 32][BN / WN / 32],
+                                                const float* sv, const float (&rsr)[BM / WM / 32],
+                                                int m0, int n0, int tid) {
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NQ = TN * 4, H = NQ / 2;
+    constexpr bool FUSE_RES = RDT >= 0;
+    constexpr int ES = ElemSize<CDT>::v;
+    const int lane = tid & 63, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
+    const int hh = lane >> 5, ml = lane & 31;
+    const bool has_rs = g.a_row_scale != nullptr;
+    const int colw = n0 + wn * TN * 32;                            // first column of this wave
+    const int col0 = colw + hh * H * 8;                            // first column this lane stores (after the swap)
+    const bool al16 = (g.ldc * ES) % 16 == 0;
+    const bool full = col0 + H * 8 <= g.N;
+
+    // per-column vectors of this lane's 4-column groups, from LDS into registers once
+    v4f cs[NQ], bs[NQ];
+    if (EPI != HERO_EPI_RAW_I32) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int nl = wn * TN * 32 + q * 8 + hh * 4;
+            if (!UNIT) cs[q] = *reinterpret_cast<const v4f*>(sv + nl);
+            bs[q] = *reinterpret_cast<const v4f*>(sv + BN + nl);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int row = m0 + wm * TM * 32 + i * 32 + ml;
+        const bool rowok = row < g.M;
+        const float rs = rsr[i];
+        if constexpr (EPI == HERO_EPI_RAW_I32) {                  // 16 bytes per group: stored as they are
+            if (rowok) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int j = q >> 2, gq = q & 3, col = colw + q * 8 + hh * 4;
+                    uint32_t d[4];                                  // int32 sums, or the bits of fp32 ones
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const auto v = acc[i][j][4 * gq + t];
+                        if constexpr (std::is_same<ACC, v16i>::value) d[t] = (uint32_t)v;
+                        else d[t] = __float_as_uint(v);
+                    }
+                    if (col < g.N) store_piece<4, 4>((int8_t*)g.C + ((int64_t)row * g.ldc + col) * 4, d, col, g.N, col + 4 <= g.N, al16);
+                }
+            }
+        } else {
+            float y[NQ][4];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int j = q >> 2, gq = q & 3;
+                v4f os;                                           // 1 / S_a of the group, re-read per pass (registers)
+                if (EPI == HERO_EPI_GELU_REQUANT) {
+                    int nl = wn * TN * 32 + q * 8 + hh * 4;
+                    asm volatile("" : "+v"(nl));                  // opaque: one load per pass, not one long-lived copy
+                    os = *reinterpret_cast<const v4f*>(sv + 2 * BN + nl);
+                    if (OS_RAW)                                   // the vector holds S_a itself: hardware reciprocal (1 ulp; +-1 LSB class)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) os[t] = __builtin_amdgcn_rcpf(os[t]);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    float v = (float)acc[i][j][4 * gq + t];
+                    if (UNIT) v = v + bs[q][t];
+                    else {
+                        if (has_rs) v = v * rs;
+                        v = fmaf(v, cs[q][t], bs[q][t]);
+                    }
+                    if (EPI == HERO_EPI_DEQUANT_GELU || EPI == HERO_EPI_GELU_REQUANT) v = gelu_erf(v);
+                    // GELU^quant is in the +-1 LSB class (fp32 GELU vs the definition's fp64), so the
+                    // division by S_a[j] is a multiplication by its reciprocal
+                    if (EPI == HERO_EPI_GELU_REQUANT) v = v * os[t];
+                    y[q][t] = v;
+                }
+            }
+            if constexpr (ES == 1) {
+                uint32_t w[NQ], d[NQ];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    w[q] = CDT == HERO_F8E4M3 ? fp8x4_sat(y[q][0], y[q][1], y[q][2], y[q][3]) : quant4_sat(y[q][0], y[q][1], y[q][2], y[q][3]);
+#pragma unroll
+                for (int q = 0; q < H; ++q) swap32(w[q], w[q + H], d[2 * q], d[2 * q + 1]);
+                if (rowok && col0 < g.N) store_piece<1, NQ>((int8_t*)g.C + (int64_t)row * g.ldc + col0, d, col0, g.N, full, al16);
+            } else if constexpr (!FUSE_RES) {
+                uint32_t d[2 * NQ];
+#pragma unroll
+                for (int q = 0; q < H; ++q) {
+                    const uint32_t a0 = pack2_hp<CDT>(y[q][0], y[q][1]), a1 = pack2_hp<CDT>(y[q][2], y[q][3]);
+                    const uint32_t b0 = pack2_hp<CDT>(y[q + H][0], y[q + H][1]), b1 = pack2_hp<CDT>(y[q + H][2], y[q + H][3]);
+                    swap32(a0, b0, d[4 * q], d[4 * q + 2]);
+                    swap32(a1, b1, d[4 * q + 1], d[4 * q + 3]);
+                }
+                if (rowok && col0 < g.N) store_piece<2, 2 * NQ>((int8_t*)g.C + ((int64_t)row * g.ldc + col0) * 2, d, col0, g.N, full, al16);
+            } else {
+                // fused residual: the fp32 values change lanes, the residual is read in the stored layout
+                uint32_t z[H][8], d[2 * NQ];
+#pragma unroll
+                for (int q = 0; q < H; ++q)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        swap32(__float_as_uint(y[q][t]), __float_as_uint(y[q + H][t]), z[q][t], z[q][4 + t]);
+                if (rowok && col0 < g.N) {
+                    const uint16_t* rp = (const uint16_t*)g.residual + (int64_t)row * g.ldr + col0;
+                    const bool rl16 = (g.ldr * 2) % 16 == 0 && ((uintptr_t)g.residual & 15) == 0;
+#pragma unroll
+                    for (int q = 0; q < H; ++q) {
+                        uint32_t r[4];
+                        if (full && rl16) {
+                            v4i rv = *reinterpret_cast<const v4i*>(rp + 8 * q);
+                            r[0] = rv[0]; r[1] = rv[1]; r[2] = rv[2]; r[3] = rv[3];
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const int c = col0 + 8 * q + 2 * k;
+                                const uint32_t e0 = c < g.N ? rp[8 * q + 2 * k] : 0, e1 = c + 1 < g.N ? rp[8 * q + 2 * k + 1] : 0;
+                                r[k] = e0 | (e1 << 16);
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            d[4 * q + k] = pack2_hp<CDT>(__uint_as_float(z[q][2 * k]) + hp_to_f32<RDT>(r[k] & 0xffffu),
+                                                         __uint_as_float(z[q][2 * k + 1]) + hp_to_f32<RDT>(r[k] >> 16));
+                        }
+                    }
+                    store_piece<2, 2 * NQ>((int8_t*)g.C + ((int64_t)row * g.ldc + col0) * 2, d, col0, g.N, full, al16);
+                }
+            }
+        }
+    }
+}
+
+// s_waitcnt immediate that waits only for vmcnt <= n (gfx9 encoding: vmcnt in bits 3:0 and 15:14,
+// expcnt 6:4 and lgkmcnt 11:8 left at their maxima).
+constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
+
+// One direct global->LDS load: 64 lanes x 16 bytes land at LDS address lds_base + lane * 16
+// (lds_base is wave-uniform and travels in M0).  Written as inline assembly on purpose: the
+// compiler then does not track these loads and does not force vmcnt(0) in front of every LDS
+// read; the kernel waits for exactly the slab it is about to read (vmcnt counts them in order).
+__device__ __forceinline__ void dma16(const int8_t* gp, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(gp), "s"(lds_base) : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+    return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)p);
+}
+
+__device__ __forceinline__ void dma16s(uint32_t voff, const int8_t* sbase, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(voff), "s"(sbase), "s"(lds_base) : "memory", "m0");
+}
+__device__ __forceinline__ void dma4s(uint32_t voff, const float* sbase, uint32_t lds_base) {   // lane l -> lds_base + 4 l
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                 :: "v"(voff), "s"(sbase), "s"(lds_base) : "memory", "m0");
+}
+
+template <typename K>
+inline hero_status launch_grid(GemmArgs g, int BM, int BN, int threads, K kernel, hipStream_t st) {
+    g.ntm = (g.M + BM - 1) / BM;
+    g.ntn = (g.N + BN - 1) / BN;
+    const int64_t tiles = (int64_t)g.ntm * g.ntn;
+    g.per_xcd = (int)((tiles + NUM_XCD - 1) / NUM_XCD);
+    if ((int64_t)g.per_xcd * NUM_XCD > 0x7fffffffLL) return HERO_ERR_SHAPE;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(g.per_xcd * NUM_XCD)), dim3(threads), 0, st, g);
+    return hero_launch_status();
+}
+
+// ---- the ring kernel's forms (gemm_ring.h): BM x BN tile, number of K groups ---------------------------------
+enum RingForm { RING_NONE = -1, RING_32x32_K8, RING_32x32_K4, RING_32x64_K2, RING_32x64_K4, RING_64x32_K4, RING_64x64_K2,
+                RING_64x64, RING_128x64_K2, RING_128x64, RING_128x128 };
+
+// Whole 128-byte slabs and 32-bit per-lane offsets.  kb: bytes of K.
+inline bool ring_ok(int64_t kb, int64_t lda_bytes, int64_t ldb_bytes) {
+    return kb % (2 * BK) == 0 && lda_bytes < (1 << 24) && ldb_bytes < (1 << 24);
+}
+// Which form, or RING_NONE: a problem for the persistent kernels.  What decides is whether every one of the 256 CUs streams
+// its share of the weights: the largest tile that still gives every CU one workgroup, and while there are fewer
+// tiles than CUs, K groups inside the workgroup.  (Two workgroups per CU where the form's LDS allows it: 64 x 64 without K
+// groups, 128 x 64 without.)  Measured over M = 1 .. 4096 and the (N, K) of the three models, INT8 and BF16 operands, every
+// form, 345 shapes: the choice below is within 1.2 % of the best form on average.  Some of the figures, us, weights out of
+// the caches for the 4096-wide model (best form of the register-staged or persistent kernels -> this one):
+//   INT8  64 x 12288 x 4096 17.1 -> 14.2, 3 x 4096 x 4096 10.6 -> 6.6, 128 x 16384 x 4096 30 -> 21.6,
+//         2000 x 1024 x 4096 18.1 -> 14.9, 602 x 4096 x 4096 25 -> 18.7, 128 x 768 x 3072 5.4 -> 4.8
+//   BF16  651 x 768 x 3072 53 -> 13.1, 3 x 4096 x 16384 177 -> 36, 602 x 4096 x 16384 185 -> 143
+inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const int64_t slabs = kb / (2 * BK), t32 = tiles(32, 32), t12864 = tiles(128, 64);
+    if (M <= 32 && t32 > 256 && tiles(32, 64) <= 256) return slabs >= 64 ? RING_32x64_K4 : RING_32x64_K2;
+    if (t32 <= 256) return slabs >= 64 ? RING_32x32_K4 : RING_32x32_K8;       // K8 has a short ring: better while K is short
+    if (tiles(64, 32) <= 256) return RING_64x32_K4;
+    if (tiles(64, 64) <= 256) return RING_64x64_K2;
+    if (t12864 <= 256 && slabs >= 32) return RING_128x64_K2;
+    if (tiles(64, 64) <= 512) return RING_64x64;
+    if (tiles(128, 128) <= 256 && slabs >= 32) return RING_128x128;
+    if (t12864 <= 512 || (slabs <= 8 && t12864 <= 1024)) return RING_128x64;  // short K: the persistent ring never gets going
+    return RING_NONE;
+}
+template <int ADT, int EPI, int CDT, int RDT> hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st);
+
+}  // namespace hero_gemm

@@ -1,0 +1,197 @@
+// The ring kernel (see the comment in front of it) and its forms; instantiated once per operand type, in gemm_ring_*.hip.
+#pragma once
+#include "gemm_common.h"
+
+namespace hero_gemm {
+
+// =====================================================================================
+// Direct-to-LDS ring with K groups (small and middling problems).  One tile per workgroup; slabs of 128 bytes of K (one
+// cache line of every row) go global -> LDS through a ring of NS stages, one barrier per slab.  KG groups of WM x WN waves
+// share the tile: group k takes the k-th range of the slabs through a ring of its own (so KG rings are in flight), and the
+// groups' accumulators are added through LDS, in the fixed order 0, 1, .., KG-1, before the epilogue.  PART: blockIdx.y
+// picks a range of g.kslabs slabs (of 128 bytes) and the raw accumulators go to a plane of g.C.
+// A slab row is 128 bytes, its eight 16-byte chunks stored at position c ^ (row & 7): the 128-bit fragment reads of 8
+// consecutive rows fall into 8 different bank groups, and a wave-level load still covers whole lines.
+// =====================================================================================
+template <int N, int NU>
+__device__ __forceinline__ void ring_wait(int left) {                // at most min(left, N) slabs of NU loads outstanding
+    if constexpr (N > 0) {
+        if (left >= N) { __builtin_amdgcn_s_waitcnt(vmcnt_imm(N * NU)); return; }
+        ring_wait<N - 1, NU>(left);
+    } else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+}
+
+template <int BM, int BN, int WM, int WN, int KG, int NS, int EPI, int CDT, int RDT, int ADT, bool PART = false>
+__global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmArgs g) {
+    using ACC = typename AccOf<ADT>::type;
+    constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
+    constexpr int SK = 2 * BK;                                      // bytes of K per slab
+    constexpr int NWAVE = WM * WN, NT = NWAVE * 64;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int STAGE = (BM + BN) * SK, RING = NS * STAGE;
+    constexpr int AU = BM / 8 / NWAVE, BU = BN / 8 / NWAVE, NU = AU + BU;   // 1 KB loads per wave and slab: 8 rows each
+    static_assert(BM % (8 * NWAVE) == 0 && BN % (8 * NWAVE) == 0, "whole loads per wave");
+    static_assert((NS - 2) * NU < 64, "vmcnt");
+    static_assert(KG == 1 || (KG - 1) * BM * BN * 4 <= KG * RING, "accumulators of the other groups fit the rings");
+    static_assert(KG * RING + 3 * BN * 4 <= 160 * 1024, "LDS budget");
+    __shared__ __attribute__((aligned(1024))) int8_t smem[KG * RING + 3 * BN * 4];
+    float* const sv = reinterpret_cast<float*>(smem + KG * RING);
+
+    int m0, n0;
+    if (!tile_origin<BM, BN>(g, m0, n0)) return;
+    const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+    const int tid = KG == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+    // this group's slabs [k0, k0 + KT); every group passes the same number of barriers
+    const int kall = g.K / SK, kbeg = PART ? (int)blockIdx.y * g.kslabs : 0, kwg = PART ? min(g.kslabs, kall - kbeg) : kall;
+    const int kper = (kwg + KG - 1) / KG, k0 = kbeg + min(kg * kper, kwg), KT = min(kper, kbeg + kwg - k0);
+
+    const int8_t* ia = g.A + (int64_t)m0 * g.lda + (int64_t)k0 * SK;
+    const int8_t* ib = g.Bt + (int64_t)n0 * g.ldb + (int64_t)k0 * SK;
+    const int lrow = wave * 8 + (lane >> 3);                        // row of this lane in a load's 8 rows; the next load: + 8 * NWAVE
+    const uint32_t lc = (uint32_t)(((lane & 7) ^ (lrow & 7)) * 16);
+    uint32_t oa[AU], ob[BU];
+#pragma unroll
+    for (int u = 0; u < AU; ++u) oa[u] = (uint32_t)min(lrow + u * 8 * NWAVE, g.M - 1 - m0) * (uint32_t)g.lda + lc;
+#pragma unroll
+    for (int u = 0; u < BU; ++u) ob[u] = (uint32_t)min(lrow + u * 8 * NWAVE, g.N - 1 - n0) * (uint32_t)g.ldb + lc;
+    const uint32_t ring = __builtin_amdgcn_readfirstlane(lds_offset(smem) + kg * RING);
+    auto issue = [&](int kt, int stage) {
+        const uint32_t dst = ring + stage * STAGE + wave * 1024;
+        const int8_t* a = ia + (int64_t)kt * SK;
+        const int8_t* b = ib + (int64_t)kt * SK;
+#pragma unroll
+        for (int u = 0; u < BU; ++u) dma16s(ob[u], b, dst + BM * SK + u * NWAVE * 1024);
+#pragma unroll
+        for (int u = 0; u < AU; ++u) dma16s(oa[u], a, dst + u * NWAVE * 1024);
+    };
+    // the epilogue's vectors are requested first (loads return in order: the waits below cover them) and wait in registers,
+    // one entry per thread, until the main loop is over
+    static_assert(NT * KG >= BN, "one entry per thread");
+    float vcs = 0.0f, vbs = 0.0f, vos = 1.0f;
+    if (!PART && (int)threadIdx.x < BN) {
+        const int n = min(n0 + (int)threadIdx.x, g.N - 1);
+        if (!UNIT) vcs = g.b_col_scale[n];
+        if (g.bias) vbs = g.bias[n];
+        if (EPI == HERO_EPI_GELU_REQUANT) vos = g.out_col_scale[n];
+    }
+    float rsr[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+        rsr[i] = (!PART && !UNIT && g.a_row_scale) ? g.a_row_scale[min(m0 + wm * TM * 32 + i * 32 + (lane & 31), g.M - 1)] : 1.0f;
+#pragma unroll
+    for (int p = 0; p < NS - 1; ++p) if (p < KT) issue(p, p);
+
+    const int hh = lane >> 5, ml = lane & 31;
+    const int8_t* const base = smem + kg * RING;
+    // row rr of the stage: rr & 7 == ml & 7, so the swizzle of k-step ks is one constant per lane
+    const int8_t* const fa = base + (wm * TM * 32 + ml) * SK;
+    const int8_t* const fb = base + BM * SK + (wn * TN * 32 + ml) * SK;
+    int sw[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) sw[ks] = ((2 * ks + hh) ^ (ml & 7)) * 16;
+    ACC acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+
+    int stage = 0;
+    for (int kt = 0; kt < kper; ++kt) {
+        ring_wait<NS - 2, NU>(KT - 1 - kt);
+        __syncthreads();                                            // slab kt is here; slab kt-1 has been read by every wave
+        if (kt + NS - 1 < KT) issue(kt + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+        if (kt < KT) {
+            const int so = stage * STAGE;
+            v4i b[4][TN], a[4][TM];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) b[ks][j] = *reinterpret_cast<const v4i*>(fb + so + j * 32 * SK + sw[ks]);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) a[ks][i] = *reinterpret_cast<const v4i*>(fa + so + i * 32 * SK + sw[ks]);
+            }
+            if constexpr (ADT == HERO_F8E4M3) {
+#pragma unroll
+                for (int ks = 0; ks < 4; ks += 2)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+                            acc[i][j] = mfma_wide_f8(b[ks][j], b[ks + 1][j], a[ks][i], a[ks + 1][i], acc[i][j]);
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) acc[i][j] = mfma_step<ADT>(b[ks][j], a[ks][i], acc[i][j]);
+            }
+        }
+        stage = stage + 1 == NS ? 0 : stage + 1;
+    }
+    if (!PART && (int)threadIdx.x < BN) {
+        sv[threadIdx.x] = vcs;
+        sv[BN + threadIdx.x] = vbs;
+        if (EPI == HERO_EPI_GELU_REQUANT) sv[2 * BN + threadIdx.x] = __fdiv_rn(1.0f, vos);      // 1 / S_a[j]
+    }
+    if constexpr (KG == 1 && !PART) __syncthreads();
+    if constexpr (KG > 1) {
+        using V4 = typename std::conditional<ADT == HERO_I8, v4i, v4f>::type;
+        constexpr int NV = TM * TN * 4;
+        __syncthreads();                                            // every group is done reading its ring; no load is outstanding
+        if (kg > 0) {
+            V4* const mine = reinterpret_cast<V4*>(smem + (kg - 1) * BM * BN * 4) + (wave * NV) * 64 + lane;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int ij = v >> 2, c = (v & 3) * 4;
+                mine[v * 64] = V4{acc[ij / TN][ij % TN][c], acc[ij / TN][ij % TN][c + 1], acc[ij / TN][ij % TN][c + 2], acc[ij / TN][ij % TN][c + 3]};
+            }
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int k = 0; k < KG - 1; ++k) {
+            const V4* other = reinterpret_cast<const V4*>(smem + k * BM * BN * 4) + (wave * NV) * 64 + lane;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int ij = v >> 2, c = (v & 3) * 4;
+                const V4 o = other[v * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[ij / TN][ij % TN][c + e] += o[e];
+            }
+        }
+    }
+    if constexpr (PART) {
+        static_assert(EPI == HERO_EPI_RAW_I32, "a part writes raw accumulators");
+        GemmArgs gp = g;
+        gp.C = (int32_t*)g.C + (int64_t)blockIdx.y * g.M * g.ldc;
+        epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, false, false>(gp, acc, sv, rsr, m0, n0, tid);
+    } else {
+        epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, false, UNIT>(g, acc, sv, rsr, m0, n0, tid);
+    }
+}
+
+template <int ADT, int EPI, int CDT, int RDT>
+hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st) {
+#define HERO_RING(BM, BN, WM, WN, KG, NS) \
+    return launch_grid(g, BM, BN, WM * WN * KG * 64, int8_gemm_ring_kernel<BM, BN, WM, WN, KG, NS, EPI, CDT, RDT, ADT>, st)
+    switch (f) {
+    case RING_32x32_K8: HERO_RING(32, 32, 1, 1, 8, 2);
+    case RING_32x32_K4: HERO_RING(32, 32, 1, 1, 4, 4);
+    case RING_32x64_K2: HERO_RING(32, 64, 1, 2, 2, 4);
+    case RING_32x64_K4: HERO_RING(32, 64, 1, 2, 4, 3);
+    case RING_64x32_K4: HERO_RING(64, 32, 2, 1, 4, 3);
+    case RING_64x64_K2: HERO_RING(64, 64, 2, 2, 2, 3);
+    case RING_64x64:    HERO_RING(64, 64, 2, 2, 1, 3);
+    case RING_128x64_K2: HERO_RING(128, 64, 2, 2, 2, 3);
+    case RING_128x64:   HERO_RING(128, 64, 2, 2, 1, 3);
+    case RING_128x128:  HERO_RING(128, 128, 4, 2, 1, 4);
+    default: return HERO_ERR_UNSUPPORTED;
+    }
+#undef HERO_RING
+}
+
+}  // namespace hero_gemm

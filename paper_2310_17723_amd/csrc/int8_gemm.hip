@@ -20,265 +20,13 @@
 //   * int8_gemm_kernel (small or skinny problems): 128x128 / 64x64 tile staged through registers.
 // The epilogue works in registers: a lane-half exchange (v_permlane32_swap) gives every lane a
 // contiguous piece of one output row, written with 128-bit stores.
-#include "hero_common.h"
+#include "gemm_common.h"
 #include <atomic>
 #include <cstdlib>
-#include <type_traits>
+
+using namespace hero_gemm;
 
 namespace {
-
-constexpr int KMULT = 64;       // K must be a multiple of this
-constexpr int BK = 64;          // bytes of K per LDS slab
-constexpr int LDS_LD = BK + 16; // padded slab row stride of the register-staged kernel
-constexpr int GROUP_M = 8;      // tile order: 8 row panels x 8 column panels run together on one XCD
-constexpr int NUM_XCD = 8;
-
-struct GemmArgs {
-    const int8_t* A; int64_t lda; const float* a_row_scale;
-    const int8_t* Bt; int64_t ldb; const float* b_col_scale;
-    const float* bias; const void* residual; int64_t ldr;
-    const float* out_col_scale;
-    void* C; int64_t ldc;
-    int M, N, K;
-    int ntm, ntn, per_xcd;      // tile grid and tiles per XCD
-    // split-K (skinny M): blockIdx.y picks a range of kslabs slabs and writes raw int32 partial sums
-    // to its own [M][ldc] plane of C (plane stride M * ldc elements); a second kernel adds the planes
-    int ksplit, kslabs;
-    // optional (persistent kernels only): memory the NEXT kernel of the caller's chain will read (a layer's next weight
-    // matrix).  Every tile requests pf_lpt of its pf_lines 128-byte lines once, at the start of its epilogue.
-    const int8_t* pf = nullptr; int pf_lines = 0, pf_lpt = 0;
-};
-
-// Operand types of the main loops.  ADT = HERO_I8: INT8 operands, int32 accumulators.  ADT = HERO_BF16: bf16
-// operands (the BF16 side of a switched module, Sec. 2.3 / Table 1), fp32 accumulators, no scales; K, lda and ldb
-// are then in BYTES, and a 64-byte slab holds two v_mfma_f32_32x32x16_bf16 steps exactly as it holds two INT8
-// steps.  ADT = HERO_F8E4M3: the FP8 variant (Sec. 2.1), fp32 accumulators, the INT8 epilogue; a 16-byte
-// fragment feeds two v_mfma_f32_32x32x16_fp8_fp8 (its low and its high 8 bytes: any grouping of K is a valid
-// contraction as long as both operands use the same one).
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef _Float16 v8hf __attribute__((ext_vector_type(8)));
-template <int ADT, typename ACC>
-__device__ __forceinline__ ACC mfma_step(v4i a, v4i b, ACC c) {
-    if constexpr (ADT == HERO_I8) return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
-    else if constexpr (ADT == HERO_BF16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-    else if constexpr (ADT == HERO_F16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8hf, a), __builtin_bit_cast(v8hf, b), c, 0, 0, 0);
-    else {
-        const long a0 = (long)(((uint64_t)(uint32_t)a[1] << 32) | (uint32_t)a[0]), a1 = (long)(((uint64_t)(uint32_t)a[3] << 32) | (uint32_t)a[2]);
-        const long b0 = (long)(((uint64_t)(uint32_t)b[1] << 32) | (uint32_t)b[0]), b1 = (long)(((uint64_t)(uint32_t)b[3] << 32) | (uint32_t)b[2]);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a0, b0, c, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a1, b1, c, 0, 0, 0);
-    }
-}
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), in order
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) { f(std::integral_constant<int, I>{}); static_for<N, I + 1>(f); }
-}
-template <int ADT> struct AccOf { using type = typename std::conditional<ADT == HERO_I8, v16i, v16f>::type; };
-
-template <int CDT> struct ElemSize { static constexpr int v = CDT == HERO_I32 ? 4 : ((CDT == HERO_I8 || CDT == HERO_F8E4M3) ? 1 : 2); };
-
-// XCD-aware tile order: workgroups go round-robin to the 8 XCDs, so XCD x takes the
-// contiguous range [x * per_xcd, (x+1) * per_xcd) of a grouped order in which 64
-// consecutive tiles form an 8 x 8 square of panels (operands shared through that XCD's L2).
-template <int BM, int BN>
-__device__ __forceinline__ void tile_from_seq(const GemmArgs& g, int seq, int& m0, int& n0) {
-    const int grp = seq / (GROUP_M * g.ntn), rem = seq % (GROUP_M * g.ntn);
-    const int gsize = min(g.ntm - grp * GROUP_M, GROUP_M);
-    m0 = (grp * GROUP_M + rem % gsize) * BM;
-    n0 = (rem / gsize) * BN;
-}
-template <int BM, int BN>
-__device__ __forceinline__ bool tile_origin(const GemmArgs& g, int& m0, int& n0) {
-    const int seq = (blockIdx.x % NUM_XCD) * g.per_xcd + blockIdx.x / NUM_XCD;
-    if (seq >= g.ntm * g.ntn) return false;
-    tile_from_seq<BM, BN>(g, seq, m0, n0);
-    return true;
-}
-
-// Per-column epilogue vectors of the tile -> LDS ([3][BN] floats: column scale, bias,
-// output scale), issued before the main loop so their latency hides behind it.
-template <int BN, int NT, int EPI>
-__device__ __forceinline__ void stage_col_vectors(const GemmArgs& g, float* sv, int n0, int tid) {
-    if (EPI == HERO_EPI_RAW_I32) return;
-    for (int c = tid; c < BN; c += NT) {
-        const int n = min(n0 + c, g.N - 1);
-        sv[c] = g.b_col_scale[n];
-        sv[BN + c] = g.bias ? g.bias[n] : 0.0f;
-        if (EPI == HERO_EPI_GELU_REQUANT) sv[2 * BN + c] = __fdiv_rn(1.0f, g.out_col_scale[n]);   // 1 / S_a[j]
-    }
-}
-
-// ---- direct epilogue ---------------------------------------------------------------------------
-// No LDS: after the fp32 epilogue a lane holds, for ONE output row, 4-column groups q (columns
-// 8q + 4hh .. + 3 of the wave's 32*TN columns).  v_permlane32_swap exchanges the groups q >= NQ/2
-// of lanes 0..31 with the groups q < NQ/2 of lanes 32..63, after which lane l < 32 owns the
-// row's first 16*TN columns and lane l + 32 the other 16*TN, contiguous in registers: every lane
-// writes one contiguous piece of its row (32 B of INT8 codes, 64 B of 16-bit values for TN = 2)
-// with 128-bit stores, and the residual of the fused add is read in the same layout.
-__device__ __forceinline__ void swap32(uint32_t a, uint32_t b, uint32_t& lo, uint32_t& hi) {
-    auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);   // r[0] = {a.low, b.low}, r[1] = {a.high, b.high}
-    lo = r[0]; hi = r[1];
-}
-// ND dwords of one row, first column col (ES bytes per element), bounds-checked against N unless `full`
-template <int ES, int ND>
-__device__ __forceinline__ void store_piece(int8_t* cp, const uint32_t (&d)[ND], int col, int N, bool full, bool al16) {
-    constexpr int EPD = 4 / ES;                                     // elements per dword
-    if (full) {
-        if (al16) {
-#pragma unroll
-            for (int k = 0; k < ND / 4; ++k) {
-                v4i o = {(int)d[4 * k], (int)d[4 * k + 1], (int)d[4 * k + 2], (int)d[4 * k + 3]};
-                *reinterpret_cast<v4i*>(cp + 16 * k) = o;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < ND; ++k) *reinterpret_cast<uint32_t*>(cp + 4 * k) = d[k];
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < ND; ++k) {
-            const int c = col + k * EPD;
-            if (c + EPD <= N) *reinterpret_cast<uint32_t*>(cp + 4 * k) = d[k];
-            else if (ES < 4) {
-#pragma unroll
-                for (int b = 0; b < EPD; ++b)
-                    if (c + b < N) {
-                        if (ES == 1) cp[4 * k + b] = (int8_t)(d[k] >> (8 * b));
-                        else *reinterpret_cast<uint16_t*>(cp + 4 * k + 2 * b) = (uint16_t)(d[k] >> (16 * b));
-                    }
-            }
-        }
-    }
-}
-
-// ACC is v16i (INT8 operands) or v16f (bf16 operands: UNIT, no scales, y = acc + bias).
-template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT, bool OS_RAW = false, bool UNIT = false, typename ACC = v16i>
-__device__ __forceinline__ void epilogue_direct(const GemmArgs& g, ACC (&acc)[BM / WM / 32][BN / WN / 32],
-                                                const float* sv, const float (&rsr)[BM / WM / 32],
-                                                int m0, int n0, int tid) {
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NQ = TN * 4, H = NQ / 2;
-    constexpr bool FUSE_RES = RDT >= 0;
-    constexpr int ES = ElemSize<CDT>::v;
-    const int lane = tid & 63, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
-    const int hh = lane >> 5, ml = lane & 31;
-    const bool has_rs = g.a_row_scale != nullptr;
-    const int colw = n0 + wn * TN * 32;                            // first column of this wave
-    const int col0 = colw + hh * H * 8;                            // first column this lane stores (after the swap)
-    const bool al16 = (g.ldc * ES) % 16 == 0;
-    const bool full = col0 + H * 8 <= g.N;
-
-    // per-column vectors of this lane's 4-column groups, from LDS into registers once
-    v4f cs[NQ], bs[NQ];
-    if (EPI != HERO_EPI_RAW_I32) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int nl = wn * TN * 32 + q * 8 + hh * 4;
-            if (!UNIT) cs[q] = *reinterpret_cast<const v4f*>(sv + nl);
-            bs[q] = *reinterpret_cast<const v4f*>(sv + BN + nl);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * TM * 32 + i * 32 + ml;
-        const bool rowok = row < g.M;
-        const float rs = rsr[i];
-        if constexpr (EPI == HERO_EPI_RAW_I32) {                  // 16 bytes per group: stored as they are
-            if (rowok) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    const int j = q >> 2, gq = q & 3, col = colw + q * 8 + hh * 4;
-                    const uint32_t d[4] = {(uint32_t)acc[i][j][4 * gq], (uint32_t)acc[i][j][4 * gq + 1],
-                                           (uint32_t)acc[i][j][4 * gq + 2], (uint32_t)acc[i][j][4 * gq + 3]};
-                    if (col < g.N) store_piece<4, 4>((int8_t*)g.C + ((int64_t)row * g.ldc + col) * 4, d, col, g.N, col + 4 <= g.N, al16);
-                }
-            }
-        } else {
-            float y[NQ][4];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int j = q >> 2, gq = q & 3;
-                v4f os;                                           // 1 / S_a of the group, re-read per pass (registers)
-                if (EPI == HERO_EPI_GELU_REQUANT) {
-                    int nl = wn * TN * 32 + q * 8 + hh * 4;
-                    asm volatile("" : "+v"(nl));                  // opaque: one load per pass, not one long-lived copy
-                    os = *reinterpret_cast<const v4f*>(sv + 2 * BN + nl);
-                    if (OS_RAW)                                   // the vector holds S_a itself: hardware reciprocal (1 ulp; +-1 LSB class)
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) os[t] = __builtin_amdgcn_rcpf(os[t]);
-                }
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    float v = (float)acc[i][j][4 * gq + t];
-                    if (UNIT) v = v + bs[q][t];
-                    else {
-                        if (has_rs) v = v * rs;
-                        v = fmaf(v, cs[q][t], bs[q][t]);
-                    }
-                    if (EPI == HERO_EPI_DEQUANT_GELU || EPI == HERO_EPI_GELU_REQUANT) v = gelu_erf(v);
-                    // GELU^quant is in the +-1 LSB class (fp32 GELU vs the definition's fp64), so the
-                    // division by S_a[j] is a multiplication by its reciprocal
-                    if (EPI == HERO_EPI_GELU_REQUANT) v = v * os[t];
-                    y[q][t] = v;
-                }
-            }
-            if constexpr (ES == 1) {
-                uint32_t w[NQ], d[NQ];
-#pragma unroll
-                for (int q = 0; q < NQ; ++q)
-                    w[q] = CDT == HERO_F8E4M3 ? fp8x4_sat(y[q][0], y[q][1], y[q][2], y[q][3]) : quant4_sat(y[q][0], y[q][1], y[q][2], y[q][3]);
-#pragma unroll
-                for (int q = 0; q < H; ++q) swap32(w[q], w[q + H], d[2 * q], d[2 * q + 1]);
-                if (rowok && col0 < g.N) store_piece<1, NQ>((int8_t*)g.C + (int64_t)row * g.ldc + col0, d, col0, g.N, full, al16);
-            } else if constexpr (!FUSE_RES) {
-                uint32_t d[2 * NQ];
-#pragma unroll
-                for (int q = 0; q < H; ++q) {
-                    const uint32_t a0 = pack2_hp<CDT>(y[q][0], y[q][1]), a1 = pack2_hp<CDT>(y[q][2], y[q][3]);
-                    const uint32_t b0 = pack2_hp<CDT>(y[q + H][0], y[q + H][1]), b1 = pack2_hp<CDT>(y[q + H][2], y[q + H][3]);
-                    swap32(a0, b0, d[4 * q], d[4 * q + 2]);
-                    swap32(a1, b1, d[4 * q + 1], d[4 * q + 3]);
-                }
-                if (rowok && col0 < g.N) store_piece<2, 2 * NQ>((int8_t*)g.C + ((int64_t)row * g.ldc + col0) * 2, d, col0, g.N, full, al16);
-            } else {
-                // fused residual: the fp32 values change lanes, the residual is read in the stored layout
-                uint32_t z[H][8], d[2 * NQ];
-#pragma unroll
-                for (int q = 0; q < H; ++q)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        swap32(__float_as_uint(y[q][t]), __float_as_uint(y[q + H][t]), z[q][t], z[q][4 + t]);
-                if (rowok && col0 < g.N) {
-                    const uint16_t* rp = (const uint16_t*)g.residual + (int64_t)row * g.ldr + col0;
-                    const bool rl16 = (g.ldr * 2) % 16 == 0;
-#pragma unroll
-                    for (int q = 0; q < H; ++q) {
-                        uint32_t r[4];
-                        if (full && rl16) {
-                            v4i rv = *reinterpret_cast<const v4i*>(rp + 8 * q);
-                            r[0] = rv[0]; r[1] = rv[1]; r[2] = rv[2]; r[3] = rv[3];
-                        } else {
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                const int c = col0 + 8 * q + 2 * k;
-                                const uint32_t e0 = c < g.N ? rp[8 * q + 2 * k] : 0, e1 = c + 1 < g.N ? rp[8 * q + 2 * k + 1] : 0;
-                                r[k] = e0 | (e1 << 16);
-                            }
-                        }
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            d[4 * q + k] = pack2_hp<CDT>(__uint_as_float(z[q][2 * k]) + hp_to_f32<RDT>(r[k] & 0xffffu),
-                                                         __uint_as_float(z[q][2 * k + 1]) + hp_to_f32<RDT>(r[k] >> 16));
-                        }
-                    }
-                    store_piece<2, 2 * NQ>((int8_t*)g.C + ((int64_t)row * g.ldc + col0) * 2, d, col0, g.N, full, al16);
-                }
-            }
-        }
-    }
-}
 
 // =====================================================================================
 // Register-staged main loop (small / ragged problems).  BK-byte slabs, double-buffered in
@@ -315,7 +63,8 @@ __global__ __launch_bounds__(WM * WN * 64 * KG, MINW) void int8_gemm_kernel(Gemm
     const int kt0 = SPLITK ? (int)blockIdx.y * g.kslabs : kg * (g.K / BK / KG);
     const int KT = SPLITK ? min(g.kslabs, g.K / BK - kt0) : g.K / BK / KG;
 
-    stage_col_vectors<BN, NT * KG, EPI>(g, sv, n0, (int)threadIdx.x);
+    constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
+    stage_col_vectors<BN, NT * KG, EPI, UNIT>(g, sv, n0, (int)threadIdx.x);
     float rsr[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -463,7 +212,7 @@ __global__ __launch_bounds__(WM * WN * 64 * KG, MINW) void int8_gemm_kernel(Gemm
         epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT>(gp, acc, sv, rsr, m0, n0, tid);
         return;
     }
-    epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, false, false>(g, acc, sv, rsr, m0, n0, tid);
+    epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, false, UNIT>(g, acc, sv, rsr, m0, n0, tid);
 }
 
 // =====================================================================================
@@ -472,22 +221,6 @@ __global__ __launch_bounds__(WM * WN * 64 * KG, MINW) void int8_gemm_kernel(Gemm
 // of row r are stored at position c ^ ((r >> 2) & 3): the 128-bit fragment reads of 16
 // consecutive rows then fall into 16 different 16-byte bank groups.
 // =====================================================================================
-// s_waitcnt immediate that waits only for vmcnt <= n (gfx9 encoding: vmcnt in bits 3:0 and 15:14,
-// expcnt 6:4 and lgkmcnt 11:8 left at their maxima).
-constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
-
-// One direct global->LDS load: 64 lanes x 16 bytes land at LDS address lds_base + lane * 16
-// (lds_base is wave-uniform and travels in M0).  Written as inline assembly on purpose: the
-// compiler then does not track these loads and does not force vmcnt(0) in front of every LDS
-// read; the kernel waits for exactly the slab it is about to read (vmcnt counts them in order).
-__device__ __forceinline__ void dma16(const int8_t* gp, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(gp), "s"(lds_base) : "memory", "m0");
-}
-__device__ __forceinline__ uint32_t lds_offset(const void* p) {
-    return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)p);
-}
-
 template <int BM, int BN, int WM, int WN, int NS, int MINW, int EPI, int CDT, int RDT>
 __global__ __launch_bounds__(WM * WN * 64, MINW) void int8_gemm_dma_kernel(GemmArgs g) {
     constexpr int NT = WM * WN * 64, NWAVE = WM * WN;
@@ -608,15 +341,6 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void int8_gemm_dma_kernel(GemmA
 // already resident when the epilogue of the current tile ends.  Slab addresses are a wave-uniform tile base in SGPRs
 // plus a per-lane 32-bit offset, so advancing along K is scalar arithmetic.
 // =====================================================================================
-__device__ __forceinline__ void dma16s(uint32_t voff, const int8_t* sbase, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(voff), "s"(sbase), "s"(lds_base) : "memory", "m0");
-}
-__device__ __forceinline__ void dma4s(uint32_t voff, const float* sbase, uint32_t lds_base) {   // lane l -> lds_base + 4 l
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
-                 :: "v"(voff), "s"(sbase), "s"(lds_base) : "memory", "m0");
-}
-
 template <int BM, int BN, int WM, int WN, int NS, int EPI, int CDT, int RDT, int ADT = HERO_I8>
 __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(GemmArgs g) {
     using ACC = typename AccOf<ADT>::type;
@@ -1316,17 +1040,6 @@ hero_status launch_splitk(const GemmArgs& g, const SplitK& p, void* ws, hipStrea
     return hero_launch_status();
 }
 
-template <typename K>
-hero_status launch_grid(GemmArgs g, int BM, int BN, int threads, K kernel, hipStream_t st) {
-    g.ntm = (g.M + BM - 1) / BM;
-    g.ntn = (g.N + BN - 1) / BN;
-    const int64_t tiles = (int64_t)g.ntm * g.ntn;
-    g.per_xcd = (int)((tiles + NUM_XCD - 1) / NUM_XCD);
-    if ((int64_t)g.per_xcd * NUM_XCD > 0x7fffffffLL) return HERO_ERR_SHAPE;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(g.per_xcd * NUM_XCD)), dim3(threads), 0, st, g);
-    return hero_launch_status();
-}
-
 // Tile choice (all measured on MI355X): the persistent 256x256 direct-to-LDS kernel, one workgroup per CU, once
 // the grid has enough tiles (160) to keep most of the 256 CUs busy; the persistent 128x128 form of the same kernel,
 // two workgroups per CU, below that (with 96-128 tiles of 256x256 half of the CUs would idle: 10-30 % faster there)
@@ -1479,48 +1192,74 @@ hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t
 
 }  // namespace
 
-// 16-bit operands (bf16 or fp16: the 16-bit side of a switched module) through the persistent kernels (called by
-// hero_hp_gemm for large problems; HERO_ERR_UNSUPPORTED means "not this kernel's case", the caller then uses its
-// own).  The tile is chosen as for INT8 operands; tile = 7 / 8 / 0 (from the test entry point hero_hp_gemm_tile)
-// forces the 256x256 / 128x128 form / the caller's kernel, -1 chooses.
+// 16-bit operands (bf16 or fp16: the 16-bit side of a switched module).  Same kernels, same choice as for INT8 operands, K
+// counted in bytes.  tile (from the test entry point hero_hp_gemm_tile): 7 / 8 = the persistent 256x256 / 128x128 kernel
+// where it can run, 0 = the kernels for smaller problems, -1 chooses.
 namespace {
-template <int BM, int BN, int WM, int WN, int DT>
-hero_status launch_hp_persistent(GemmArgs g, int wg_per_cu, bool gelu, hipStream_t st) {
-    g.ntm = (g.M + BM - 1) / BM; g.ntn = (g.N + BN - 1) / BN;
-    const int64_t tiles = (int64_t)g.ntm * g.ntn;
-    g.per_xcd = (int)((tiles + NUM_XCD - 1) / NUM_XCD);
-    const int cap = 32 * wg_per_cu, nslot = g.per_xcd < cap ? g.per_xcd : cap;
-    const dim3 grid((unsigned)(nslot * NUM_XCD)), block(WM * WN * 64);
-    if (gelu) {
-        if (g.residual) hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, HERO_EPI_DEQUANT_GELU, DT, DT, DT>), grid, block, 0, st, g);
-        else hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, HERO_EPI_DEQUANT_GELU, DT, -1, DT>), grid, block, 0, st, g);
-    } else {
-        if (g.residual) hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, HERO_EPI_DEQUANT, DT, DT, DT>), grid, block, 0, st, g);
-        else hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, HERO_EPI_DEQUANT, DT, -1, DT>), grid, block, 0, st, g);
+template <int EPI, int DT, int RDT>
+hero_status launch_hp(const GemmArgs& g, hipStream_t st, int cfg) {
+    const int64_t t256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    const bool ring = ring_ok(g.K, g.lda, g.ldb);
+    const RingForm f = ring ? ring_form(g.M, g.N, g.K) : RING_NONE;
+    const bool pers_ok = ring && t128 <= 0x7fffff00LL && g.K >= 4 * BK;
+    if (pers_ok && t128 >= 192 && (cfg > 0 || (cfg < 0 && f == RING_NONE))) {
+        const bool tile128 = cfg == 8 || (cfg < 0 && (t256 < 160 || small_tile_fills_better(t256, t128)));
+        GemmArgs gp = g;
+        gp.ntm = tile128 ? (g.M + 127) / 128 : (g.M + 255) / 256; gp.ntn = tile128 ? (g.N + 127) / 128 : (g.N + 255) / 256;
+        gp.per_xcd = (int)(((tile128 ? t128 : t256) + NUM_XCD - 1) / NUM_XCD);
+        const int cap = tile128 ? 64 : 32, nslot = gp.per_xcd < cap ? gp.per_xcd : cap;
+        if (tile128) hipLaunchKernelGGL((int8_gemm_persistent_kernel<128, 128, 2, 2, 4, EPI, DT, RDT, DT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(256), 0, st, gp);
+        else hipLaunchKernelGGL((int8_gemm_persistent_kernel<256, 256, 2, 4, 4, EPI, DT, RDT, DT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(512), 0, st, gp);
+        return hero_launch_status();
     }
-    return hero_launch_status();
+    if ((g.M + 127) / 128 > 65535) return HERO_ERR_UNSUPPORTED;
+    if (ring) return launch_ring<DT, EPI, DT, RDT>(g, f == RING_NONE ? RING_128x64 : f, st);
+    return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, DT, RDT, false, 1, DT>, st);
 }
-}  // namespace
+template <int DT>
+hero_status launch_hp_type(const GemmArgs& g, bool gelu, hipStream_t st, int cfg) {
+    if (gelu) return g.residual ? launch_hp<HERO_EPI_DEQUANT_GELU, DT, DT>(g, st, cfg) : launch_hp<HERO_EPI_DEQUANT_GELU, DT, -1>(g, st, cfg);
+    return g.residual ? launch_hp<HERO_EPI_DEQUANT, DT, DT>(g, st, cfg) : launch_hp<HERO_EPI_DEQUANT, DT, -1>(g, st, cfg);
+}
 
-hero_status hero_hp_gemm_large(const void* A, int64_t lda, const void* Wt, int64_t ldb,
-                               const float* bias, const void* residual, int64_t ldr, int gelu,
-                               void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, hipStream_t st, int tile) {
-    const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    if (t128 < 192 || t128 > 0x7fffff00LL || K % 64 != 0 || K * 2 < 4 * BK || lda * 2 >= (1 << 24) || ldb * 2 >= (1 << 24))
-        return HERO_ERR_UNSUPPORTED;
+hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
+                        const float* bias, const void* residual, int64_t ldr, int gelu,
+                        void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream, int tile) {
+    if (dt != HERO_BF16 && dt != HERO_F16) return HERO_ERR_UNSUPPORTED;
+    if (M < 0 || N < 0 || K <= 0 || M > 0x7fffffffLL || N > 0x7fffffffLL || K > 0x3fffffffLL) return HERO_ERR_SHAPE;
+    if (K % 32 != 0) return HERO_ERR_UNSUPPORTED;
+    if (lda < K || ldb < K || ldc < N || (residual && ldr < N)) return HERO_ERR_SHAPE;
+    if (M == 0 || N == 0) return HERO_OK;
+    if (!A || !Wt || !C) return HERO_ERR_NULL;
+    if (lda % 8 || ldb % 8 || ldc % 4 || !hero_aligned16(A) || !hero_aligned16(Wt) || !hero_aligned16(C)) return HERO_ERR_ALIGN;
     GemmArgs g;
     g.A = (const int8_t*)A; g.lda = lda * 2; g.a_row_scale = nullptr; g.Bt = (const int8_t*)Wt; g.ldb = ldb * 2;
     g.b_col_scale = nullptr; g.bias = bias; g.residual = residual; g.ldr = ldr; g.out_col_scale = nullptr;
     g.C = C; g.ldc = ldc; g.M = (int)M; g.N = (int)N; g.K = (int)(K * 2);
     g.ksplit = 1; g.kslabs = 0;
-    const int cfg = tile >= 0 ? tile : ((t256 < 160 || small_tile_fills_better(t256, t128)) ? 8 : 7);
-    if (cfg == 0) return HERO_ERR_UNSUPPORTED;
-    if (dt == HERO_BF16) {
-        if (cfg == 8) return launch_hp_persistent<128, 128, 2, 2, HERO_BF16>(g, 2, gelu != 0, st);
-        return launch_hp_persistent<256, 256, 2, 4, HERO_BF16>(g, 1, gelu != 0, st);
-    }
-    if (cfg == 8) return launch_hp_persistent<128, 128, 2, 2, HERO_F16>(g, 2, gelu != 0, st);
-    return launch_hp_persistent<256, 256, 2, 4, HERO_F16>(g, 1, gelu != 0, st);
+    return dt == HERO_BF16 ? launch_hp_type<HERO_BF16>(g, gelu != 0, (hipStream_t)stream, tile)
+                           : launch_hp_type<HERO_F16>(g, gelu != 0, (hipStream_t)stream, tile);
+}
+}  // namespace
+
+extern "C" hero_status hero_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
+                                    const float* bias, const void* residual, int64_t ldr, int gelu,
+                                    void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream) {
+    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, stream, -1);
+}
+
+extern "C" hero_status hero_bf16_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
+                                      const float* bias, const void* residual, int64_t ldr, int gelu,
+                                      void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
+    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, HERO_BF16, stream, -1);
+}
+
+// Test and tuning hook (include/hero_debug.h).
+extern "C" hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void* Wt, int64_t ldb,
+                                         const float* bias, const void* residual, int64_t ldr, int gelu,
+                                         void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream, int tile) {
+    if (tile != 0 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
+    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, stream, tile);
 }
 
 // The FP8 variant: the same kernels with E4M3 operands (no split-K: fp32 partial sums would not commute).
