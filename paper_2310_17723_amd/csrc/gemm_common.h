@@ -330,5 +330,7 @@ inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
     return RING_NONE;
 }
 template <int ADT, int EPI, int CDT, int RDT> hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st);
+// g.ksplit ranges of g.kslabs slabs, raw accumulators into planes of g.C; the two forms of the K split
+template <int ADT> hero_status launch_ring_part(GemmArgs g, RingForm f, hipStream_t st);
 
 }  // namespace hero_gemm

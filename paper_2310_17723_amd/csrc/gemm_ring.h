@@ -68,8 +68,9 @@ __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmA
     // the epilogue's vectors are requested first (loads return in order: the waits below cover them) and wait in registers,
     // one entry per thread, until the main loop is over
     static_assert(NT * KG >= BN, "one entry per thread");
+    constexpr bool VECS = !PART && EPI != HERO_EPI_RAW_I32;         // raw sums: the caller may have no vectors at all
     float vcs = 0.0f, vbs = 0.0f, vos = 1.0f;
-    if (!PART && (int)threadIdx.x < BN) {
+    if (VECS && (int)threadIdx.x < BN) {
         const int n = min(n0 + (int)threadIdx.x, g.N - 1);
         if (!UNIT) vcs = g.b_col_scale[n];
         if (g.bias) vbs = g.bias[n];
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmA
     float rsr[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
-        rsr[i] = (!PART && !UNIT && g.a_row_scale) ? g.a_row_scale[min(m0 + wm * TM * 32 + i * 32 + (lane & 31), g.M - 1)] : 1.0f;
+        rsr[i] = (VECS && !UNIT && g.a_row_scale) ? g.a_row_scale[min(m0 + wm * TM * 32 + i * 32 + (lane & 31), g.M - 1)] : 1.0f;
 #pragma unroll
     for (int p = 0; p < NS - 1; ++p) if (p < KT) issue(p, p);
 
@@ -132,12 +133,12 @@ __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmA
         }
         stage = stage + 1 == NS ? 0 : stage + 1;
     }
-    if (!PART && (int)threadIdx.x < BN) {
+    if (VECS && (int)threadIdx.x < BN) {
         sv[threadIdx.x] = vcs;
         sv[BN + threadIdx.x] = vbs;
         if (EPI == HERO_EPI_GELU_REQUANT) sv[2 * BN + threadIdx.x] = __fdiv_rn(1.0f, vos);      // 1 / S_a[j]
     }
-    if constexpr (KG == 1 && !PART) __syncthreads();
+    if constexpr (KG == 1 && VECS) __syncthreads();
     if constexpr (KG > 1) {
         using V4 = typename std::conditional<ADT == HERO_I8, v4i, v4f>::type;
         constexpr int NV = TM * TN * 4;
@@ -192,6 +193,19 @@ hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st) {
     default: return HERO_ERR_UNSUPPORTED;
     }
 #undef HERO_RING
+}
+
+template <int ADT>
+hero_status launch_ring_part(GemmArgs g, RingForm f, hipStream_t st) {
+    const int BM = f == RING_64x64_K2 ? 64 : 128;
+    g.ntm = (g.M + BM - 1) / BM;
+    g.ntn = (g.N + 63) / 64;
+    g.per_xcd = (int)(((int64_t)g.ntm * g.ntn + NUM_XCD - 1) / NUM_XCD);
+    const dim3 grid((unsigned)(g.per_xcd * NUM_XCD), (unsigned)g.ksplit);
+    if (f == RING_64x64_K2) hipLaunchKernelGGL((int8_gemm_ring_kernel<64, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>), grid, dim3(512), 0, st, g);
+    else if (f == RING_128x64_K2) hipLaunchKernelGGL((int8_gemm_ring_kernel<128, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>), grid, dim3(512), 0, st, g);
+    else return HERO_ERR_UNSUPPORTED;
+    return hero_launch_status();
 }
 
 }  // namespace hero_gemm

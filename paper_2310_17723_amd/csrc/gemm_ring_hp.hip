@@ -3,6 +3,7 @@
 
 namespace hero_gemm {
 #define HERO_RING_HP(DT) \
+    template hero_status launch_ring_part<DT>(GemmArgs, RingForm, hipStream_t); \
     template hero_status launch_ring<DT, HERO_EPI_DEQUANT, DT, -1>(const GemmArgs&, RingForm, hipStream_t); \
     template hero_status launch_ring<DT, HERO_EPI_DEQUANT, DT, DT>(const GemmArgs&, RingForm, hipStream_t); \
     template hero_status launch_ring<DT, HERO_EPI_DEQUANT_GELU, DT, -1>(const GemmArgs&, RingForm, hipStream_t); \

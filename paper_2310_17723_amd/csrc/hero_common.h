@@ -40,8 +40,15 @@ hero_status hero_fp8_gemm_prefetching(const void* A, int64_t lda, const float* a
                                       const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,
                                       hero_epilogue epi, const float* out_col_scale,
                                       void* C, hero_dtype c_dt, int64_t ldc,
-                                      int64_t M, int64_t N, int64_t K, void* stream,
+                                      int64_t M, int64_t N, int64_t K,
+                                      void* workspace, size_t workspace_bytes, void* stream,
                                       const void* prefetch, size_t prefetch_bytes);
+
+// the 16-bit product with scratch for the K split of a skinny problem
+hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t ldb,
+                            const float* bias, const void* residual, int64_t ldr, int gelu,
+                            void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt,
+                            void* workspace, size_t workspace_bytes, void* stream);
 
 // ---- 16-bit float storage (round to nearest even) -------------------------------------
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }

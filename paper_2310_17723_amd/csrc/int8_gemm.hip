@@ -32,39 +32,29 @@ namespace {
 // Register-staged main loop (small / ragged problems).  BK-byte slabs, double-buffered in
 // LDS with an 80-byte padded row stride, PD slabs in flight in registers.
 // =====================================================================================
-// KG > 1: KG groups of WM x WN waves share the tile and split K among themselves (every group has its own
-// slab buffers and runs the same number of iterations, so the barriers stay workgroup-wide); the groups'
-// accumulators are added through LDS before the epilogue.  For small problems with a long K: the number of
-// workgroups is fixed by M and N, more waves per workgroup shorten the K loop.
-template <int BM, int BN, int WM, int WN, int PD, int MINW, int EPI, int CDT, int RDT, bool SPLITK = false, int KG = 1, int ADT = HERO_I8>
-__global__ __launch_bounds__(WM * WN * 64 * KG, MINW) void int8_gemm_kernel(GemmArgs g) {
+template <int BM, int BN, int WM, int WN, int PD, int MINW, int EPI, int CDT, int RDT, int ADT = HERO_I8>
+__global__ __launch_bounds__(WM * WN * 64, MINW) void int8_gemm_kernel(GemmArgs g) {
     using ACC = typename AccOf<ADT>::type;
-    static_assert(ADT == HERO_I8 || !SPLITK, "split K over workgroups: integer partial sums only");
-    constexpr int NT = WM * WN * 64;                          // threads of one K group
+    constexpr int NT = WM * WN * 64;
     constexpr int CPR = BK / 16;                              // 16-byte chunks per slab row
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int A_UNITS = BM * CPR / NT, B_UNITS = BN * CPR / NT;
     static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/threads mismatch");
     static_assert(PD % 2 == 0, "prefetch distance must be even (LDS buffer parity is compile-time)");
     constexpr int POOL = 2 * (BM + BN) * LDS_LD;
-    static_assert(KG == 1 || (!SPLITK && BM * BN * 4 <= POOL), "K groups: one tile of accumulators must fit a group's slab buffers");
-    __shared__ __attribute__((aligned(16))) int8_t smem[KG * POOL + 3 * BN * 4];
-    const int kg = KG == 1 ? 0 : (int)threadIdx.x / NT;       // K group of this wave
-    int8_t* const sA0 = smem + kg * POOL;                     // [2][BM * LDS_LD]
+    __shared__ __attribute__((aligned(16))) int8_t smem[POOL + 3 * BN * 4];
+    int8_t* const sA0 = smem;                                 // [2][BM * LDS_LD]
     int8_t* const sB0 = sA0 + 2 * BM * LDS_LD;                // [2][BN * LDS_LD]
-    float* const sv = reinterpret_cast<float*>(smem + KG * POOL);
+    float* const sv = reinterpret_cast<float*>(smem + POOL);
 
-    const int tid = KG == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     int m0, n0;
     if (!tile_origin<BM, BN>(g, m0, n0)) return;
-    // this group's slabs: all of K, the blockIdx.y-th range of kslabs slabs (never empty), or the kg-th
-    // of KG equal ranges (the launch requires K / BK to be a multiple of KG)
-    const int kt0 = SPLITK ? (int)blockIdx.y * g.kslabs : kg * (g.K / BK / KG);
-    const int KT = SPLITK ? min(g.kslabs, g.K / BK - kt0) : g.K / BK / KG;
+    const int KT = g.K / BK;
 
     constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
-    stage_col_vectors<BN, NT * KG, EPI, UNIT>(g, sv, n0, (int)threadIdx.x);
+    stage_col_vectors<BN, NT, EPI, UNIT>(g, sv, n0, tid);
     float rsr[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -77,12 +67,12 @@ __global__ __launch_bounds__(WM * WN * 64 * KG, MINW) void int8_gemm_kernel(Gemm
 #pragma unroll
     for (int u = 0; u < A_UNITS; ++u) {
         int idx = tid + u * NT, row = idx / CPR, ch = idx % CPR;
-        pa[u] = g.A + (int64_t)min(m0 + row, g.M - 1) * g.lda + ch * 16 + (int64_t)kt0 * BK;   // clamp: ragged M
+        pa[u] = g.A + (int64_t)min(m0 + row, g.M - 1) * g.lda + ch * 16;   // clamp: ragged M
     }
 #pragma unroll
     for (int u = 0; u < B_UNITS; ++u) {
         int idx = tid + u * NT, row = idx / CPR, ch = idx % CPR;
-        pb[u] = g.Bt + (int64_t)min(n0 + row, g.N - 1) * g.ldb + ch * 16 + (int64_t)kt0 * BK;
+        pb[u] = g.Bt + (int64_t)min(n0 + row, g.N - 1) * g.ldb + ch * 16;
     }
     const int lds_unit0 = (tid / CPR) * LDS_LD + (tid % CPR) * 16;                // + u * (NT / CPR) * LDS_LD
     v4i ra[PD][A_UNITS], rb[PD][B_UNITS];
@@ -177,41 +167,6 @@ __global__ __launch_bounds__(WM * WN * 64 * KG, MINW) void int8_gemm_kernel(Gemm
     };
     for (; kt + PD <= KT; kt += PD) trip(std::true_type{});
     if (kt < KT) trip(std::false_type{});
-    if constexpr (KG > 1) {
-        // groups 1 .. KG-1 hand their accumulators to group 0 (register-major, lane-minor: no bank conflicts);
-        // the loop's last barrier has released every group's slab buffers.  Integer sums are exact in any order;
-        // the fp32 sums of the FP8 variant are added in the fixed order group 0, 1, .., KG-1.
-        using V4 = typename std::conditional<ADT == HERO_I8, v4i, v4f>::type;
-        constexpr int NV = TM * TN * 4;
-        V4* const mine = reinterpret_cast<V4*>(smem + kg * POOL) + (wave * NV) * 64 + lane;
-        if (kg > 0) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const int ij = v >> 2, c = (v & 3) * 4;
-                mine[v * 64] = V4{acc[ij / TN][ij % TN][c], acc[ij / TN][ij % TN][c + 1], acc[ij / TN][ij % TN][c + 2], acc[ij / TN][ij % TN][c + 3]};
-            }
-        }
-        __syncthreads();
-        if (kg > 0) return;
-#pragma unroll
-        for (int k = 1; k < KG; ++k) {
-            const V4* other = reinterpret_cast<const V4*>(smem + k * POOL) + (wave * NV) * 64 + lane;
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const int ij = v >> 2, c = (v & 3) * 4;
-                const V4 o = other[v * 64];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[ij / TN][ij % TN][c + e] += o[e];
-            }
-        }
-    }
-    if constexpr (SPLITK && ADT == HERO_I8) {
-        static_assert(EPI == HERO_EPI_RAW_I32, "split-K writes raw partial sums");
-        GemmArgs gp = g;
-        gp.C = (int32_t*)g.C + (int64_t)blockIdx.y * g.M * g.ldc;
-        epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT>(gp, acc, sv, rsr, m0, n0, tid);
-        return;
-    }
     epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, false, UNIT>(g, acc, sv, rsr, m0, n0, tid);
 }
 
@@ -933,29 +888,26 @@ __global__ __launch_bounds__(512, 2) void int8_gemm_ovl_kernel(GemmArgs g) {
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));                      // the redundant tail loads
 }
 
-// Split-K for skinny M with a long K (M <= 128, K >= 8192, at most 128 tiles: the weights are streamed once and
-// too few tiles exist to do that from every CU).  Pass 1: the register-staged kernel with a second grid dimension over K ranges writes raw int32
-// partial sums, one [M][ldp] plane per range, into the caller's scratch.  Pass 2 (splitk_reduce_kernel) adds
-// the planes and runs the epilogue.  Integer sums commute and the epilogue arithmetic is the same, in the
-// same order, as in the one-pass kernels, so the results are identical; the kernel boundary is the only
-// synchronisation (device-wide fences inside one kernel measured 4x slower than no split at all).
-struct SplitK { int BM, BN, ksplit, kslabs; int64_t ldp; size_t bytes; };
-inline SplitK splitk_plan(int64_t M, int64_t N, int64_t K) {
-    SplitK p = {0, 0, 1, 0, 0, 0};
+// Split-K for skinny M with a long K (M <= 128, 64 slabs of 128 bytes or more): the weights are streamed once, and too few
+// tiles exist to do that from every CU.  Pass 1: the ring kernel with a second grid dimension over K ranges writes raw
+// partial sums, one [M][ldp] plane per range, into the caller's scratch, as many ranges as give every CU one
+// workgroup.  Pass 2 (splitk_reduce_kernel) adds the planes and runs the epilogue; the arithmetic is the same, in the same
+// order, as in the one-pass kernels.  The kernel boundary is the only synchronisation (device-wide fences inside one
+// kernel measured 4x slower than no split at all).  Measured with cold weights, one pass -> split: INT8 64 x 4096 x 16384
+// 23.6 -> 19.7 us, 3 rows 19.7 -> 17.6, 100 rows 26.3 -> 24.1; BF16 64 rows 44.4 -> 35.6, 3 rows 36.2 -> 30.5; with
+// K = 4096 the second launch costs more than the split gives.
+// The scratch is sized for `ksplit` ranges (two 64 x 64 or 128 x 128 tiles per CU), an upper bound of what is used.
+struct SplitK { int ksplit; int64_t ldp; size_t bytes; };
+inline SplitK splitk_plan(int64_t M, int64_t N, int64_t K) {            // K in bytes
+    SplitK p = {1, 0, 0};
     if (M <= 0 || N <= 0 || M > 128 || K % BK != 0) return p;
-    p.BM = p.BN = M <= 64 ? 64 : 128;
-    const int64_t tiles = ((M + p.BM - 1) / p.BM) * ((N + p.BN - 1) / p.BN), kt = K / BK;
-    // Measured: two launches pay only for a long K over few tiles (64 x 4096 x 16384: 20 us against 31 in one pass);
-    // with K = 4096 the one-pass kernels (four K groups per workgroup up to 128 tiles, plain 64 x 64 tiles beyond)
-    // are 20-35 % faster than the split (64 x 12288 x 4096: 15.4 against 20.1 us), and small weights are
-    // launch-bound anyway.
-    if (tiles > 128 || kt < 128 || N * K < (4 << 20)) return p;
-    int64_t want = (512 + tiles - 1) / tiles;                         // about two workgroups per CU
+    const int64_t b = M <= 64 ? 64 : 128, tiles = (N + b - 1) / b, kt = K / BK;
+    if (tiles > 128 || kt < 128 || N * K < (4 << 20)) return p;         // small weights are launch-bound anyway
+    int64_t want = (512 + tiles - 1) / tiles;
     if (want > 16) want = 16;
     int64_t kslabs = (kt + want - 1) / want;
     if (kslabs < 4) kslabs = 4;
-    p.kslabs = (int)kslabs;
-    p.ksplit = (int)((kt + kslabs - 1) / kslabs);                     // every range non-empty
+    p.ksplit = (int)((kt + kslabs - 1) / kslabs);
     if (p.ksplit <= 1) { p.ksplit = 1; return p; }
     p.ldp = (N + 3) & ~(int64_t)3;
     p.bytes = (size_t)p.ksplit * M * p.ldp * 4;
@@ -963,16 +915,24 @@ inline SplitK splitk_plan(int64_t M, int64_t N, int64_t K) {
 }
 
 // Pass 2 of split-K: one thread per 4 consecutive columns of a row.
-template <int EPI, int CDT, int RDT>
+// Integer sums are exact in any order; fp32 partial sums (E4M3 and 16-bit operands) are added in the fixed order of the
+// ranges, so a result does not vary from run to run.
+template <int EPI, int CDT, int RDT, int ADT>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const int32_t* part, int64_t ldp) {
+    constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;
+    using V4 = typename std::conditional<ADT == HERO_I8, v4i, v4f>::type;
     constexpr int ES = ElemSize<CDT>::v;
     const int nq = (g.N + 3) / 4;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (int64_t)g.M * nq) return;
     const int m = (int)(idx / nq), n = (int)(idx % nq) * 4;
-    v4i a = {0, 0, 0, 0};
-    for (int ks = 0; ks < g.ksplit; ++ks)
-        a += *reinterpret_cast<const v4i*>(part + ((int64_t)ks * g.M + m) * ldp + n);
+    V4 a = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int ks = 0; ks < g.ksplit; ++ks) {
+        const V4 p = *reinterpret_cast<const V4*>(part + ((int64_t)ks * g.M + m) * ldp + n);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] += p[t];
+    }
     const int nv = min(4, g.N - n);                                    // valid columns
     uint32_t e[4];                                                     // outputs as element bit patterns
     if constexpr (EPI == HERO_EPI_RAW_I32) {
@@ -985,15 +945,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const in
         for (int t = 0; t < 4; ++t) {
             const int nn = min(n + t, g.N - 1);
             float v = (float)a[t];
-            if (g.a_row_scale) v = v * rs;
-            v = fmaf(v, g.b_col_scale[nn], g.bias ? g.bias[nn] : 0.0f);
+            if (UNIT) v = v + (g.bias ? g.bias[nn] : 0.0f);
+            else {
+                if (g.a_row_scale) v = v * rs;
+                v = fmaf(v, g.b_col_scale[nn], g.bias ? g.bias[nn] : 0.0f);
+            }
             if (EPI == HERO_EPI_DEQUANT_GELU || EPI == HERO_EPI_GELU_REQUANT) v = gelu_erf(v);
             if (EPI == HERO_EPI_GELU_REQUANT) v = v * __fdiv_rn(1.0f, g.out_col_scale[nn]);
             if (RDT >= 0 && t < nv) v += hp_to_f32<RDT>(((const uint16_t*)g.residual)[(int64_t)m * g.ldr + n + t]);
             y[t] = v;
         }
         if constexpr (ES == 1) {
-            const uint32_t w = quant4_sat(y[0], y[1], y[2], y[3]);
+            const uint32_t w = CDT == HERO_F8E4M3 ? fp8x4_sat(y[0], y[1], y[2], y[3]) : quant4_sat(y[0], y[1], y[2], y[3]);
 #pragma unroll
             for (int t = 0; t < 4; ++t) e[t] = (w >> (8 * t)) & 0xffu;
         } else {
@@ -1015,29 +978,29 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const in
     }
 }
 
-template <int EPI, int CDT, int RDT>
-hero_status launch_splitk(const GemmArgs& g, const SplitK& p, void* ws, hipStream_t st) {
+// Runs the split where it is one (true: *status is the outcome).
+template <int EPI, int CDT, int RDT, int ADT>
+bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, hero_status* status) {
+    if (!ws || !ring_ok(g.K, g.lda, g.ldb)) return false;
+    const SplitK p = splitk_plan(g.M, g.N, g.K);
+    if (p.ksplit <= 1 || ws_bytes < p.bytes) return false;
+    const RingForm f = g.M <= 64 ? RING_64x64_K2 : RING_128x64_K2;      // both: 64 columns, one workgroup per CU
+    const int slabs = g.K / (2 * BK), ntn = (g.N + 63) / 64, want = min(256 / ntn, p.ksplit);
+    if (want < 2) return false;
     GemmArgs g1 = g;                                                   // pass 1: raw partial planes in the scratch
     g1.a_row_scale = nullptr; g1.b_col_scale = nullptr; g1.bias = nullptr; g1.residual = nullptr; g1.out_col_scale = nullptr;
     g1.C = ws; g1.ldc = p.ldp;
-    g1.ntm = (g.M + p.BM - 1) / p.BM;
-    g1.ntn = (g.N + p.BN - 1) / p.BN;
-    const int64_t tiles = (int64_t)g1.ntm * g1.ntn;
-    g1.per_xcd = (int)((tiles + NUM_XCD - 1) / NUM_XCD);
-    g1.ksplit = p.ksplit; g1.kslabs = p.kslabs;
-    const dim3 grid((unsigned)(g1.per_xcd * NUM_XCD), (unsigned)p.ksplit);
-    // (measured on 64 x 4096 x 16384 with cold weights: 8 slabs in flight are 3 % slower than 4; 26 us with the
-    // reduction pass, 2.6 TB/s)
-    if (p.BM == 64) hipLaunchKernelGGL((int8_gemm_kernel<64, 64, 2, 2, 4, 2, HERO_EPI_RAW_I32, HERO_I32, -1, true>), grid, dim3(256), 0, st, g1);
-    else hipLaunchKernelGGL((int8_gemm_kernel<128, 128, 2, 2, 2, 2, HERO_EPI_RAW_I32, HERO_I32, -1, true>), grid, dim3(256), 0, st, g1);
-    hero_status s1 = hero_launch_status();
-    if (s1 != HERO_OK) return s1;
+    g1.kslabs = (slabs + want - 1) / want;
+    g1.ksplit = (slabs + g1.kslabs - 1) / g1.kslabs;                   // every range non-empty
+    *status = launch_ring_part<ADT>(g1, f, st);
+    if (*status != HERO_OK) return true;
     GemmArgs g2 = g;                                                   // pass 2: sum of the planes + epilogue
-    g2.ksplit = p.ksplit; g2.kslabs = p.kslabs;
+    g2.ksplit = g1.ksplit;
     const int64_t threads = (int64_t)g.M * ((g.N + 3) / 4);
-    hipLaunchKernelGGL((splitk_reduce_kernel<EPI, CDT, RDT>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
+    hipLaunchKernelGGL((splitk_reduce_kernel<EPI, CDT, RDT, ADT>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
                        g2, (const int32_t*)ws, p.ldp);
-    return hero_launch_status();
+    *status = hero_launch_status();
+    return true;
 }
 
 // Tile choice (all measured on MI355X): the persistent 256x256 direct-to-LDS kernel, one workgroup per CU, once
@@ -1112,10 +1075,10 @@ inline bool small_tile_fills_better(int64_t t256, int64_t t128) {
 template <int EPI, int CDT, int RDT>
 hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
     int cfg = tile;
-    if (cfg < 0 && ws) {                                               // skinny M with a workspace: split K
-        const SplitK p = splitk_plan(g.M, g.N, g.K);
-        if (p.ksplit > 1 && ws_bytes >= p.bytes) return launch_splitk<EPI, CDT, RDT>(g, p, ws, st);
-    }
+    hero_status split;
+    if (cfg < 0 && launch_splitk<EPI, CDT, RDT, HERO_I8>(g, ws, ws_bytes, st, &split)) return split;
+    const bool ring = ring_ok(g.K, g.lda, g.ldb);
+    const RingForm form = ring ? ring_form(g.M, g.N, g.K) : RING_NONE;
     // persistent kernels: K long enough that the slab ring never runs more than one tile ahead, whole pairs of
     // slabs, 32-bit per-lane offsets (256 rows of lda / ldb bytes)
     const bool pers_ok = g.K >= 4 * BK && g.K % (2 * BK) == 0 && g.lda < (1 << 24) && g.ldb < (1 << 24);
@@ -1123,7 +1086,8 @@ hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t
     const bool ovl_ok = pers_ok && g.K >= 16 * BK && RDT < 0;
     if (cfg < 0) {
         const int64_t t256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-        if (t256 >= 160) cfg = !pers_ok ? 1 : (small_tile_fills_better(t256, t128) ? 8 : 7);
+        if (form != RING_NONE) cfg = 2;
+        else if (t256 >= 160) cfg = !pers_ok ? 1 : (small_tile_fills_better(t256, t128) ? 8 : 7);
         else if (g.M <= 64 || t128 < 192) cfg = 2;
         else cfg = pers_ok ? 8 : 0;
     } else if (cfg == 9 && !ovl_ok) {
@@ -1144,47 +1108,8 @@ hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t
     if (cfg == 7) return launch_persistent<256, 256, 2, 4, EPI, CDT, RDT>(g, 1, st);
     if (cfg == 8) return launch_persistent<128, 128, 2, 2, EPI, CDT, RDT>(g, 2, st);
     if (cfg == 1) return launch_grid(g, 256, 256, 512, int8_gemm_dma_kernel<256, 256, 2, 4, 4, 2, EPI, CDT, RDT>, st);
-    if (cfg == 2) {                             // small or skinny problems: 64x64 tiles
-        // few tiles and a long K: 4 groups of waves per workgroup split K (K / 64 must divide evenly);
-        // measured: 8-10 % at 128 tiles or fewer, a loss with more tiles or with 2 groups
-        const int64_t t64 = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
-        const int kt = g.K / BK;
-        // One row of tiles (M <= 64: a decode step) streams the weight matrix once and is bound by how many of its
-        // bytes are in flight.  Measured inside a layer, i.e. with weights that are NOT in the Infinity Cache (timed
-        // alone and back to back the same kernels look 30 % faster than they are): up to 128 tiles, 64 x 32 tiles
-        // with 8 slabs in flight in registers (64 x 4096 x 4096: 13.1 us against 16.6 for the four-K-group form);
-        // beyond, two K groups per workgroup with 4 slabs each (64 x 12288 x 4096: 17.5 against 23.3 us for the
-        // plain 64 x 64 tile; 64 x 16384 x 4096: 18.8-21.0 against 26.5-27.0; 8 or 16 slabs in flight, four K
-        // groups or 64 x 32 tiles are all slower there).  More bytes in flight do not help beyond that: a form of
-        // this kernel with two producer waves that kept seven 16 KB stages (112 KB per workgroup) on their way
-        // straight into an LDS ring was correct and no faster (64 x 16384 x 4096: 23.4 us; with 64 workgroups, 64 x
-        // 4096 x 16384: 51 us = 21 GB/s per compute unit).  A compute unit pulls about 21-23 GB/s from HBM whatever
-        // it has outstanding (the decode attention reaches 5.9 TB/s with all 256 of them streaming), so what counts
-        // is that every unit streams its 1/256 of the weights: 64-column tiles do that for N = 16384 and leave a
-        // quarter of the chip idle for N = 12288.  Narrower strips do not fix that either: every workgroup also reads
-        // all of the M x K activations (from the L2, but through the same per-unit path), so 16-column strips (tried
-        // with 32-wide tiles whose upper half repeats the last owned column) move four times the activation bytes per
-        // weight byte: 64 x 4096 x 4096 11.8 us (13.0 with 32 columns), 64 x 12288 x 4096 29-38 us (17.5),
-        // 64 x 4096 x 16384 without a split 35-40 us (28 with the split and its reduction pass).
-        if (g.M <= 64 && kt >= 32) {
-            if (t64 <= 128) return launch_grid(g, 64, 32, 128, int8_gemm_kernel<64, 32, 2, 1, 8, 2, EPI, CDT, RDT>, st);
-            if (kt % 2 == 0) return launch_grid(g, 64, 64, 512, int8_gemm_kernel<64, 64, 2, 2, 4, 1, EPI, CDT, RDT, false, 2>, st);
-        }
-        // Small problems (a BERT-base layer: 128 tokens) are bound by how many compute units stream the weights at
-        // all, so the tiles shrink with the problem.  Measured as the layer runs them (weights in the caches): up to 32
-        // tiles of 64 x 64, 32 x 32 tiles with four K groups (128 x 768 x 3072: 5.5 us against 8.4 for 64 x 64 with
-        // four groups) or, with a short K, two (128 x 768 x 768: 3.9 against 4.4); up to 128 tiles, 64 x 32 tiles with
-        // two K groups (128 x 2304 x 768: 4.2 against 4.6; 128 x 3072 x 768 + GELU^quant: 4.7 against 5.1;
-        // 512 x 1024 x 4096: 8.6 against 10.2); beyond, plain 64 x 64 tiles (512 x 3072 x 1024: 7.2, every smaller
-        // tile slower).
-        if (t64 <= 32 && kt >= 32 && kt % 4 == 0)
-            return launch_grid(g, 32, 32, 256, int8_gemm_kernel<32, 32, 1, 1, 4, 1, EPI, CDT, RDT, false, 4>, st);
-        if (t64 <= 32 && kt % 2 == 0)
-            return launch_grid(g, 32, 32, 128, int8_gemm_kernel<32, 32, 1, 1, 8, 2, EPI, CDT, RDT, false, 2>, st);
-        if (t64 <= 128 && kt % 2 == 0)
-            return launch_grid(g, 64, 32, 256, int8_gemm_kernel<64, 32, 2, 1, 4, 2, EPI, CDT, RDT, false, 2>, st);
-        if (t64 <= 128 && kt >= 32 && kt % 4 == 0)
-            return launch_grid(g, 64, 64, 1024, int8_gemm_kernel<64, 64, 2, 2, 2, 1, EPI, CDT, RDT, false, 4>, st);
+    if (cfg == 2) {                             // small or skinny problems
+        if (ring) return launch_ring<HERO_I8, EPI, CDT, RDT>(g, form == RING_NONE ? RING_128x64 : form, st);
         return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, CDT, RDT>, st);
     }
     return launch_grid(g, 128, 128, 256, int8_gemm_kernel<128, 128, 2, 2, 2, 2, EPI, CDT, RDT>, st);
@@ -1197,7 +1122,9 @@ hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t
 // where it can run, 0 = the kernels for smaller problems, -1 chooses.
 namespace {
 template <int EPI, int DT, int RDT>
-hero_status launch_hp(const GemmArgs& g, hipStream_t st, int cfg) {
+hero_status launch_hp(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int cfg) {
+    hero_status split;
+    if (cfg < 0 && launch_splitk<EPI, DT, RDT, DT>(g, ws, ws_bytes, st, &split)) return split;
     const int64_t t256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
     const bool ring = ring_ok(g.K, g.lda, g.ldb);
     const RingForm f = ring ? ring_form(g.M, g.N, g.K) : RING_NONE;
@@ -1214,17 +1141,17 @@ hero_status launch_hp(const GemmArgs& g, hipStream_t st, int cfg) {
     }
     if ((g.M + 127) / 128 > 65535) return HERO_ERR_UNSUPPORTED;
     if (ring) return launch_ring<DT, EPI, DT, RDT>(g, f == RING_NONE ? RING_128x64 : f, st);
-    return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, DT, RDT, false, 1, DT>, st);
+    return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, DT, RDT, DT>, st);
 }
 template <int DT>
-hero_status launch_hp_type(const GemmArgs& g, bool gelu, hipStream_t st, int cfg) {
-    if (gelu) return g.residual ? launch_hp<HERO_EPI_DEQUANT_GELU, DT, DT>(g, st, cfg) : launch_hp<HERO_EPI_DEQUANT_GELU, DT, -1>(g, st, cfg);
-    return g.residual ? launch_hp<HERO_EPI_DEQUANT, DT, DT>(g, st, cfg) : launch_hp<HERO_EPI_DEQUANT, DT, -1>(g, st, cfg);
+hero_status launch_hp_type(const GemmArgs& g, bool gelu, void* ws, size_t wsb, hipStream_t st, int cfg) {
+    if (gelu) return g.residual ? launch_hp<HERO_EPI_DEQUANT_GELU, DT, DT>(g, ws, wsb, st, cfg) : launch_hp<HERO_EPI_DEQUANT_GELU, DT, -1>(g, ws, wsb, st, cfg);
+    return g.residual ? launch_hp<HERO_EPI_DEQUANT, DT, DT>(g, ws, wsb, st, cfg) : launch_hp<HERO_EPI_DEQUANT, DT, -1>(g, ws, wsb, st, cfg);
 }
 
 hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
                         const float* bias, const void* residual, int64_t ldr, int gelu,
-                        void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream, int tile) {
+                        void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* ws, size_t ws_bytes, void* stream, int tile) {
     if (dt != HERO_BF16 && dt != HERO_F16) return HERO_ERR_UNSUPPORTED;
     if (M < 0 || N < 0 || K <= 0 || M > 0x7fffffffLL || N > 0x7fffffffLL || K > 0x3fffffffLL) return HERO_ERR_SHAPE;
     if (K % 32 != 0) return HERO_ERR_UNSUPPORTED;
@@ -1237,21 +1164,29 @@ hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
     g.b_col_scale = nullptr; g.bias = bias; g.residual = residual; g.ldr = ldr; g.out_col_scale = nullptr;
     g.C = C; g.ldc = ldc; g.M = (int)M; g.N = (int)N; g.K = (int)(K * 2);
     g.ksplit = 1; g.kslabs = 0;
-    return dt == HERO_BF16 ? launch_hp_type<HERO_BF16>(g, gelu != 0, (hipStream_t)stream, tile)
-                           : launch_hp_type<HERO_F16>(g, gelu != 0, (hipStream_t)stream, tile);
+    return dt == HERO_BF16 ? launch_hp_type<HERO_BF16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile)
+                           : launch_hp_type<HERO_F16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile);
 }
 }  // namespace
+
+// hero_hp_gemm with scratch for the K split (hero_layer_fwd).  Not part of the C ABI.
+hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t ldb,
+                            const float* bias, const void* residual, int64_t ldr, int gelu,
+                            void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt,
+                            void* workspace, size_t workspace_bytes, void* stream) {
+    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, workspace, workspace_bytes, stream, -1);
+}
 
 extern "C" hero_status hero_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
                                     const float* bias, const void* residual, int64_t ldr, int gelu,
                                     void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream) {
-    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, stream, -1);
+    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, nullptr, 0, stream, -1);
 }
 
 extern "C" hero_status hero_bf16_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
                                       const float* bias, const void* residual, int64_t ldr, int gelu,
                                       void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, void* stream) {
-    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, HERO_BF16, stream, -1);
+    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, HERO_BF16, nullptr, 0, stream, -1);
 }
 
 // Test and tuning hook (include/hero_debug.h).
@@ -1259,17 +1194,19 @@ extern "C" hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void*
                                          const float* bias, const void* residual, int64_t ldr, int gelu,
                                          void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream, int tile) {
     if (tile != 0 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
-    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, stream, tile);
+    return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, nullptr, 0, stream, tile);
 }
 
-// The FP8 variant: the same kernels with E4M3 operands (no split-K: fp32 partial sums would not commute).
+// The FP8 variant: the same kernels and the same choice with E4M3 operands.
 template <int EPI, int CDT, int RDT>
-hero_status launch_epi_fp8(GemmArgs g, hipStream_t st, int cfg) {
+hero_status launch_epi_fp8(GemmArgs g, void* ws, size_t ws_bytes, hipStream_t st, int cfg) {
+    hero_status split;
+    if (cfg < 0 && launch_splitk<EPI, CDT, RDT, HERO_F8E4M3>(g, ws, ws_bytes, st, &split)) return split;
     const int64_t t256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const bool pers_ok = t128 <= 0x7fffff00LL && g.K >= 4 * BK && g.K % (2 * BK) == 0 && g.lda < (1 << 24) && g.ldb < (1 << 24);
+    const bool ring = ring_ok(g.K, g.lda, g.ldb), pers_ok = ring && t128 <= 0x7fffff00LL && g.K >= 4 * BK;
+    const RingForm form = ring ? ring_form(g.M, g.N, g.K) : RING_NONE;
     // cfg: -1 = chosen here; 0 / 7 / 8 forced by the test entry point hero_fp8_gemm_tile
-    const bool small = g.M <= 64 || t128 < 192;
-    if (pers_ok && (cfg == 7 || cfg == 8 || (cfg < 0 && !small))) {
+    if (pers_ok && (cfg == 7 || cfg == 8 || (cfg < 0 && form == RING_NONE))) {
         const bool tile128 = cfg == 8 || (cfg < 0 && (t256 < 160 || small_tile_fills_better(t256, t128)));
         g.ntm = tile128 ? (g.M + 127) / 128 : (g.M + 255) / 256; g.ntn = tile128 ? (g.N + 127) / 128 : (g.N + 255) / 256;
         g.per_xcd = (int)(((tile128 ? t128 : t256) + NUM_XCD - 1) / NUM_XCD);
@@ -1279,19 +1216,8 @@ hero_status launch_epi_fp8(GemmArgs g, hipStream_t st, int cfg) {
         else hipLaunchKernelGGL((int8_gemm_persistent_kernel<256, 256, 2, 4, 4, EPI, CDT, RDT, HERO_F8E4M3>), dim3((unsigned)(nslot * NUM_XCD)), dim3(512), 0, st, g);
         return hero_launch_status();
     }
-    if (small && cfg != 0) {
-        // few tiles and a long K: four groups of waves per workgroup split K, as for INT8 operands
-        const int64_t t64 = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
-        const int kt = g.K / BK;
-        if (g.M <= 64 && kt >= 32) {                          // one row of tiles: the forms chosen for INT8 operands (cold weights)
-            if (t64 <= 128 && kt < 128) return launch_grid(g, 64, 32, 128, int8_gemm_kernel<64, 32, 2, 1, 8, 2, EPI, CDT, RDT, false, 1, HERO_F8E4M3>, st);
-            if (t64 > 128 && kt % 2 == 0) return launch_grid(g, 64, 64, 512, int8_gemm_kernel<64, 64, 2, 2, 4, 1, EPI, CDT, RDT, false, 2, HERO_F8E4M3>, st);
-        }
-        if (t64 <= 128 && kt >= 32 && kt % 4 == 0)
-            return launch_grid(g, 64, 64, 1024, int8_gemm_kernel<64, 64, 2, 2, 2, 1, EPI, CDT, RDT, false, 4, HERO_F8E4M3>, st);
-        return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, CDT, RDT, false, 1, HERO_F8E4M3>, st);
-    }
-    return launch_grid(g, 128, 128, 256, int8_gemm_kernel<128, 128, 2, 2, 2, 2, EPI, CDT, RDT, false, 1, HERO_F8E4M3>, st);
+    if (ring && cfg != 0) return launch_ring<HERO_F8E4M3, EPI, CDT, RDT>(g, form == RING_NONE ? RING_128x64 : form, st);
+    return launch_grid(g, 128, 128, 256, int8_gemm_kernel<128, 128, 2, 2, 2, 2, EPI, CDT, RDT, HERO_F8E4M3>, st);
 }
 
 static hero_status run_fp8_gemm(const void* A, int64_t lda, const float* a_row_scale,
@@ -1299,7 +1225,7 @@ static hero_status run_fp8_gemm(const void* A, int64_t lda, const float* a_row_s
                                 const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,
                                 hero_epilogue epi, const float* out_col_scale,
                                 void* C, hero_dtype c_dt, int64_t ldc,
-                                int64_t M, int64_t N, int64_t K, void* stream, int tile,
+                                int64_t M, int64_t N, int64_t K, void* workspace, size_t workspace_bytes, void* stream, int tile,
                                 const void* prefetch = nullptr, size_t prefetch_bytes = 0) {
     if (M < 0 || N < 0 || K <= 0) return HERO_ERR_SHAPE;
     if (M > 0x7fffffffLL || N > 0x7fffffffLL || K > 0x7fffffffLL) return HERO_ERR_SHAPE;
@@ -1329,17 +1255,17 @@ static hero_status run_fp8_gemm(const void* A, int64_t lda, const float* a_row_s
     set_prefetch(g, prefetch, prefetch_bytes);
     hipStream_t st = (hipStream_t)stream;
     switch (epi) {
-    case HERO_EPI_REQUANT: return launch_epi_fp8<HERO_EPI_REQUANT, HERO_F8E4M3, -1>(g, st, tile);
-    case HERO_EPI_GELU_REQUANT: return launch_epi_fp8<HERO_EPI_GELU_REQUANT, HERO_F8E4M3, -1>(g, st, tile);
+    case HERO_EPI_REQUANT: return launch_epi_fp8<HERO_EPI_REQUANT, HERO_F8E4M3, -1>(g, workspace, workspace_bytes, st, tile);
+    case HERO_EPI_GELU_REQUANT: return launch_epi_fp8<HERO_EPI_GELU_REQUANT, HERO_F8E4M3, -1>(g, workspace, workspace_bytes, st, tile);
     case HERO_EPI_DEQUANT_GELU:
-        return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT_GELU, HERO_BF16, -1>(g, st, tile)
-                                 : launch_epi_fp8<HERO_EPI_DEQUANT_GELU, HERO_F16, -1>(g, st, tile);
+        return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT_GELU, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
+                                 : launch_epi_fp8<HERO_EPI_DEQUANT_GELU, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
     default:
         if (!residual)
-            return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT, HERO_BF16, -1>(g, st, tile)
-                                     : launch_epi_fp8<HERO_EPI_DEQUANT, HERO_F16, -1>(g, st, tile);
-        return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16>(g, st, tile)
-                                 : launch_epi_fp8<HERO_EPI_DEQUANT, HERO_F16, HERO_F16>(g, st, tile);
+            return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
+                                     : launch_epi_fp8<HERO_EPI_DEQUANT, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
+        return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16>(g, workspace, workspace_bytes, st, tile)
+                                 : launch_epi_fp8<HERO_EPI_DEQUANT, HERO_F16, HERO_F16>(g, workspace, workspace_bytes, st, tile);
     }
 }
 
@@ -1449,10 +1375,11 @@ hero_status hero_fp8_gemm_prefetching(const void* A, int64_t lda, const float* a
                                       const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,
                                       hero_epilogue epi, const float* out_col_scale,
                                       void* C, hero_dtype c_dt, int64_t ldc,
-                                      int64_t M, int64_t N, int64_t K, void* stream,
+                                      int64_t M, int64_t N, int64_t K,
+                                      void* workspace, size_t workspace_bytes, void* stream,
                                       const void* prefetch, size_t prefetch_bytes) {
     return run_fp8_gemm(A, lda, a_row_scale, Bt, ldb, b_col_scale, bias, residual, res_dt, ldr, epi, out_col_scale,
-                        C, c_dt, ldc, M, N, K, stream, -1, prefetch, prefetch_bytes);
+                        C, c_dt, ldc, M, N, K, workspace, workspace_bytes, stream, -1, prefetch, prefetch_bytes);
 }
 
 extern "C" hero_status hero_int8_gemm_ws(const int8_t* A, int64_t lda, const float* a_row_scale,
@@ -1473,7 +1400,7 @@ extern "C" hero_status hero_fp8_gemm(const void* A, int64_t lda, const float* a_
                                      void* C, hero_dtype c_dt, int64_t ldc,
                                      int64_t M, int64_t N, int64_t K, void* stream) {
     return run_fp8_gemm(A, lda, a_row_scale, Bt, ldb, b_col_scale, bias, residual, res_dt, ldr, epi, out_col_scale,
-                        C, c_dt, ldc, M, N, K, stream, -1);
+                        C, c_dt, ldc, M, N, K, nullptr, 0, stream, -1);
 }
 
 // Test and tuning hooks (include/hero_debug.h): the same calls with the kernel choice forced.
@@ -1496,7 +1423,7 @@ extern "C" hero_status hero_fp8_gemm_tile(const void* A, int64_t lda, const floa
                                           int64_t M, int64_t N, int64_t K, void* stream, int tile) {
     if (tile != 0 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
     return run_fp8_gemm(A, lda, a_row_scale, Bt, ldb, b_col_scale, bias, residual, res_dt, ldr, epi, out_col_scale,
-                        C, c_dt, ldc, M, N, K, stream, tile);
+                        C, c_dt, ldc, M, N, K, nullptr, 0, stream, tile);
 }
 
 // ---- hero_int8_gemm_static: the split-K scratch lives in the library ---------------------------------------

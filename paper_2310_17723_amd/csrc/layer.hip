@@ -40,15 +40,14 @@ Workspace plan(const hero_layer_desc* d, int64_t T) {
     w.mid_hp = take(!(d->mode_mask & HERO_M_FC1) ? (size_t)T * d->d * 2 : 0);          // 16-bit X_mid for a 16-bit FC1
     w.a = take((size_t)T * d->f * e_a);
     w.x2 = take(pre ? 0 : (size_t)T * d->d * e_a);
-    // split-K scratch of the skinny (decode) GEMMs: the largest of the four shapes, shared (stream order);
-    // none in the FP8 variant (fp32 partial sums would not commute)
+    // split-K scratch of the skinny (decode) GEMMs: the largest of the four shapes (K in bytes of its operands),
+    // shared (stream order)
     size_t g = 0;
-    if (!(d->mode_mask & HERO_M_FP8)) {
-        g = hero_int8_gemm_workspace_bytes(T, 3 * (int64_t)d->d, d->d);
-        g = std::max(g, hero_int8_gemm_workspace_bytes(T, d->d, d->d));
-        g = std::max(g, hero_int8_gemm_workspace_bytes(T, d->f, d->d));
-        g = std::max(g, hero_int8_gemm_workspace_bytes(T, d->d, d->f));
-    }
+    auto split = [&](int64_t N, int64_t K, uint32_t bit) { g = std::max(g, hero_int8_gemm_workspace_bytes(T, N, (d->mode_mask & bit) ? K : 2 * K)); };
+    split(3 * (int64_t)d->d, d->d, HERO_M_QKV);
+    split(d->d, d->d, HERO_M_ATTN_OUT);
+    split(d->f, d->d, HERO_M_FC1);
+    split(d->d, d->f, HERO_M_FC2);
     w.gemm_ws_bytes = g;
     w.gemm_ws = take(g);
     w.total = off;
@@ -178,7 +177,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
             HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln1_g, w->ln1_b, desc->eps,
                                        T, d, xin_q, xin_s, nullptr, HERO_BF16, stream));
         HERO_TRY(hero_fp8_gemm_prefetching(xin_q, d, xin_s, w->w_qkv, d, w->w_qkv_s, w->b_qkv, nullptr, HERO_BF16, 0,
-                                           HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d, T, 3 * d, d, stream, w->w_o, (size_t)(d * d)));
+                                           HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d, T, 3 * d, d, gws, ws.gemm_ws_bytes, stream, w->w_o, (size_t)(d * d)));
         const int64_t qs[4] = {S * 3 * d, 3 * d, Dh, 1};
         const int8_t* qp = (const int8_t*)qkv;
         const int8_t *kp = qp + d, *vp = qp + 2 * d;
@@ -196,25 +195,25 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                w->attn_out_scale, 0, (hero_mask)desc->mask, io->kv_len, attn, F8, d, stream));
         if (!pre) {
             HERO_TRY(hero_fp8_gemm_prefetching(attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, nullptr, HERO_BF16, 0,
-                                               HERO_EPI_REQUANT, nullptr, xo, F8, d, T, d, d, stream, w->w_1, (size_t)(f * d)));
+                                               HERO_EPI_REQUANT, nullptr, xo, F8, d, T, d, d, gws, ws.gemm_ws_bytes, stream, w->w_1, (size_t)(f * d)));
             HERO_TRY(hero_ln_quant_fp8(xin_q, F8, xin_s, xo, F8, w->S_o, w->ln1_g, w->ln1_b, desc->eps, T, d,
                                        mid_q, mid_s, nullptr, HERO_BF16, stream));
         } else {
             HERO_TRY(hero_fp8_gemm_prefetching(attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, io->h, HERO_BF16, d,
-                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, d, stream, w->w_1, (size_t)(f * d)));
+                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, d, gws, ws.gemm_ws_bytes, stream, w->w_1, (size_t)(f * d)));
             HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
                                        T, d, mid_q, mid_s, nullptr, HERO_BF16, stream));
         }
         HERO_TRY(hero_fp8_gemm_prefetching(mid_q, d, mid_s, w->w_1, d, w->w_1_s, w->b_1, nullptr, HERO_BF16, 0,
-                                           HERO_EPI_GELU_REQUANT, w->S_a, act, F8, f, T, f, d, stream, w->w_2, (size_t)(d * f)));
+                                           HERO_EPI_GELU_REQUANT, w->S_a, act, F8, f, T, f, d, gws, ws.gemm_ws_bytes, stream, w->w_2, (size_t)(d * f)));
         if (!pre) {
             HERO_TRY(hero_fp8_gemm_prefetching(act, f, nullptr, w->w_2, f, w->w_2_s, w->b_2, nullptr, HERO_BF16, 0,
-                                               HERO_EPI_REQUANT, nullptr, x2, F8, d, T, d, f, stream, io->next_read, io->next_read_bytes));
+                                               HERO_EPI_REQUANT, nullptr, x2, F8, d, T, d, f, gws, ws.gemm_ws_bytes, stream, io->next_read, io->next_read_bytes));
             HERO_TRY(hero_ln_quant_fp8(mid_q, F8, mid_s, x2, F8, w->S_x2, w->ln2_g, w->ln2_b, desc->eps, T, d,
                                        io->out_q, io->out_scale, nullptr, HERO_BF16, stream));
         } else {
             HERO_TRY(hero_fp8_gemm_prefetching(act, f, nullptr, w->w_2, f, w->w_2_s, w->b_2, io->h, HERO_BF16, d,
-                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, f, stream, io->next_read, io->next_read_bytes));
+                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, f, gws, ws.gemm_ws_bytes, stream, io->next_read, io->next_read_bytes));
         }
         return HERO_OK;
     }
@@ -230,7 +229,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                             qkv, attn_i8 ? HERO_I8 : HP, 3 * d, T, 3 * d, d, gws, ws.gemm_ws_bytes, stream,
                                             o_i8 ? w->w_o : nullptr, (size_t)(d * d)));
     else
-        HERO_TRY(hero_hp_gemm(xin_hp, d, w->w_qkv_hp, d, w->b_qkv, nullptr, 0, 0, qkv, 3 * d, T, 3 * d, d, HP, stream));
+        HERO_TRY(hero_hp_gemm_ws(xin_hp, d, w->w_qkv_hp, d, w->b_qkv, nullptr, 0, 0, qkv, 3 * d, T, 3 * d, d, HP, gws, ws.gemm_ws_bytes, stream));
     // (3) attention
     const int64_t qs[4] = {S * 3 * d, 3 * d, Dh, 1};
     if (attn_i8) {
@@ -264,7 +263,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                                 HERO_EPI_REQUANT, nullptr, xo, HERO_I8, d, T, d, d, gws, ws.gemm_ws_bytes, stream,
                                                 fc1_i8 ? w->w_1 : nullptr, (size_t)(f * d)));
         else
-            HERO_TRY(hero_hp_gemm(attn, d, w->w_o_bf16, d, w->b_o, nullptr, 0, 0, xo, d, T, d, d, HP, stream));
+            HERO_TRY(hero_hp_gemm_ws(attn, d, w->w_o_bf16, d, w->b_o, nullptr, 0, 0, xo, d, T, d, d, HP, gws, ws.gemm_ws_bytes, stream));
         HERO_TRY(hero_ln_quant(x1, x1_dt, q_i8 ? xin_s : nullptr, xo, o_i8 ? HERO_I8 : HP, o_i8 ? w->S_o : nullptr,
                                w->ln1_g, w->ln1_b, desc->eps, T, d, mid_q, mid_s, fc1_i8 ? nullptr : mid_hp, HP, stream));
     } else {
@@ -273,7 +272,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                                 HERO_EPI_DEQUANT, nullptr, io->h, HP, d, T, d, d, gws, ws.gemm_ws_bytes, stream,
                                                 fc1_i8 ? w->w_1 : nullptr, (size_t)(f * d)));
         else
-            HERO_TRY(hero_hp_gemm(attn, d, w->w_o_bf16, d, w->b_o, io->h, d, 0, io->h, d, T, d, d, HP, stream));
+            HERO_TRY(hero_hp_gemm_ws(attn, d, w->w_o_bf16, d, w->b_o, io->h, d, 0, io->h, d, T, d, d, HP, gws, ws.gemm_ws_bytes, stream));
         HERO_TRY(hero_ln_quant(io->h, HP, nullptr, nullptr, HERO_I8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
                                T, d, mid_q, mid_s, fc1_i8 ? nullptr : mid_hp, HP, stream));
     }
@@ -284,7 +283,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                             act, fc2_i8 ? HERO_I8 : HP, f, T, f, d, gws, ws.gemm_ws_bytes, stream,
                                             fc2_i8 ? w->w_2 : nullptr, (size_t)(d * f)));
     else
-        HERO_TRY(hero_hp_gemm(mid_hp, d, w->w_1_hp, d, w->b_1, nullptr, 0, 1, act, f, T, f, d, HP, stream));
+        HERO_TRY(hero_hp_gemm_ws(mid_hp, d, w->w_1_hp, d, w->b_1, nullptr, 0, 1, act, f, T, f, d, HP, gws, ws.gemm_ws_bytes, stream));
     // (6) FC2 and the closing LN^quant (POST_LN) or residual add (PRE_LN)
     if (!pre) {
         if (fc2_i8)
@@ -292,7 +291,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                                 HERO_EPI_REQUANT, nullptr, x2, HERO_I8, d, T, d, f, gws, ws.gemm_ws_bytes, stream,
                                                 io->next_read, io->next_read_bytes));
         else
-            HERO_TRY(hero_hp_gemm(act, f, w->w_2_bf16, f, w->b_2, nullptr, 0, 0, x2, d, T, d, f, HP, stream));
+            HERO_TRY(hero_hp_gemm_ws(act, f, w->w_2_bf16, f, w->b_2, nullptr, 0, 0, x2, d, T, d, f, HP, gws, ws.gemm_ws_bytes, stream));
         HERO_TRY(hero_ln_quant(fc1_i8 ? (const void*)mid_q : (const void*)mid_hp, fc1_i8 ? HERO_I8 : HP, fc1_i8 ? mid_s : nullptr,
                                x2, fc2_i8 ? HERO_I8 : HP, fc2_i8 ? w->S_x2 : nullptr, w->ln2_g, w->ln2_b, desc->eps, T, d,
                                io->out_q, io->out_scale, io->out_hp, HP, stream));
@@ -302,7 +301,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                                 HERO_EPI_DEQUANT, nullptr, io->h, HP, d, T, d, f, gws, ws.gemm_ws_bytes, stream,
                                                 io->next_read, io->next_read_bytes));
         else
-            HERO_TRY(hero_hp_gemm(act, f, w->w_2_bf16, f, w->b_2, io->h, d, 0, io->h, d, T, d, f, HP, stream));
+            HERO_TRY(hero_hp_gemm_ws(act, f, w->w_2_bf16, f, w->b_2, io->h, d, 0, io->h, d, T, d, f, HP, gws, ws.gemm_ws_bytes, stream));
     }
     return HERO_OK;
 }

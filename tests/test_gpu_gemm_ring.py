@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import paper_2310_17723_amd as pkg
+from paper_2310_17723_amd import binding as HB, prep
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +54,77 @@ def test_hp_gemm_forms(M, N, kb, dt, gelu, res):
         ref = ref + r.double()
     ulp = 2.0 ** -8 if dt == torch.bfloat16 else 2.0 ** -11        # half a unit in the last place
     assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * ulp + 2.0 ** -25).all())
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_int8_gemm_forms(M, N, K):
+    """Integer sums are exact in any order: the raw product, and one rounding behind the pinned epilogue."""
+    hero = pkg.load()
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a = _strided(torch.randint(-127, 128, (M, K), device="cuda", generator=g, dtype=torch.int8), 16)
+    w = torch.randint(-127, 128, (N, K), device="cuda", generator=g, dtype=torch.int8)
+    acc = (a.double() @ w.double().t()).to(torch.int32)
+    assert torch.equal(hero.hero_int8_gemm(a, w), acc)
+    rs, cs = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) / (90 * K ** 0.5)
+    bias = torch.randn(N, device="cuda", generator=g)
+    res = torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16)
+    x = acc.float() * rs[:, None]                                    # one fp32 product, then one fused multiply-add
+    y = (x.double() * cs.double() + bias.double()).float()
+    got = hero.hero_int8_gemm(a, w, rs, cs, bias, residual=res, epi=HB.EPI_DEQUANT, out_dtype=torch.bfloat16)
+    # (the double sum is rounded twice, the fused instruction once: they part at most at a tie, one code in some millions)
+    assert float((got != (y + res.float()).to(torch.bfloat16)).float().mean()) <= 1e-6
+    got = hero.hero_int8_gemm(a, w, rs, cs * 40, bias * 40, epi=HB.EPI_REQUANT, out_dtype=torch.int8)
+    y = (x.double() * (cs * 40).double() + (bias * 40).double()).float()
+    assert int((got.int() - y.round().clamp(-127, 127).int()).abs().max()) <= 1
+    assert float((got.int() != y.round().clamp(-127, 127).int()).float().mean()) <= 1e-6
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_fp8_gemm_forms(M, N, K):
+    hero = pkg.load()
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a = (torch.randn((M, K), device="cuda", generator=g) * 60).clamp(-448, 448).to(torch.float8_e4m3fn)
+    w = (torch.randn((N, K), device="cuda", generator=g) * 60).clamp(-448, 448).to(torch.float8_e4m3fn)
+    rs, cs = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) / (3600 * K ** 0.5)
+    bias = torch.randn(N, device="cuda", generator=g)
+    y = hero.hero_fp8_gemm(a, w, rs, cs, bias, epi=HB.EPI_DEQUANT, out_dtype=torch.bfloat16)
+    s = rs.double()[:, None] * cs.double()
+    ref = (a.double() @ w.double().t()) * s + bias.double()
+    # fp32 sums in any order: (K + 4) * 2^-24 of the sum of the magnitudes; then one rounding to bf16
+    bound = (K + 4) * 2.0 ** -24 * ((a.double().abs() @ w.double().abs().t()) * s + bias.double().abs())
+    assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * 2.0 ** -8).all())
+
+
+@pytest.mark.parametrize("B", [1, 5, 64, 100])
+@pytest.mark.parametrize("fmt", ["fp8", "bf16"])
+def test_layer_split_k(B, fmt):
+    """One token per sequence through a layer whose FC2 is long enough for the K split (E4M3 codes, or 16 bits), against the
+    same layer run one sequence block at a time through a scratch that is dirty: the same bits."""
+    hero = pkg.load()
+    d, H, Dh, f = 1024, 8, 128, 8192
+    mode = HB.MODE_M3 | HB.M_FP8 if fmt == "fp8" else HB.MODE_M2
+    g = torch.Generator(device="cuda").manual_seed(B)
+    p = {k: torch.randn(s, device="cuda", generator=g) * 0.03 for k, s in
+         {"w_qkv": (d, 3 * d), "b_qkv": (3 * d,), "w_o": (d, d), "b_o": (d,), "w_1": (d, f), "b_1": (f,), "w_2": (f, d), "b_2": (d,)}.items()}
+    for k in ("ln1", "ln2"):
+        p[k + "_g"], p[k + "_b"] = 1 + 0.1 * torch.randn(d, device="cuda", generator=g), torch.zeros(d, device="cuda")
+    x = torch.randn((2 * 64, d), device="cuda", generator=g).double()
+    sc, _ = prep.calibrate(p, x, HB.ARCH_PRE_LN, H, Dh, 1e-5, HB.MASK_CAUSAL, 2, 64, hero=hero, fp8=fmt == "fp8")
+    t, qk, ps = prep.prepare(p, sc, HB.ARCH_PRE_LN, d, Dh, mode & ~HB.M_FP8, hero=hero, fp8=fmt == "fp8")
+    W, desc = hero.layer_weights(t, qk, ps), hero.layer_desc(HB.ARCH_PRE_LN, d, H, Dh, f, 1e-5, HB.MASK_CAUSAL, mode)
+    h0 = torch.randn((B, d), device="cuda", generator=g).to(torch.bfloat16)
+
+    def run(h, poison):
+        n = h.shape[0]
+        ws = torch.full((hero.hero_layer_workspace_bytes(desc, n, 1),), poison, dtype=torch.uint8, device="cuda")
+        kc = torch.zeros((n, H, 4, Dh), dtype=torch.float8_e4m3fn if fmt == "fp8" else torch.int8, device="cuda")
+        vc, out = torch.zeros_like(kc), h.clone()
+        hero.hero_layer_fwd(desc, W, n, 1, ws, h=out, kv_len=torch.ones(n, dtype=torch.int32, device="cuda"), k_cache=kc, v_cache=vc)
+        return out
+    one = run(h0, 0xFF)
+    assert bool(torch.isfinite(one.float()).all())
+    assert torch.equal(one, run(h0, 0x00))
+    # every row on its own is in the same class (another form may serve it: the fp32 sums are ordered otherwise)
+    rows = torch.cat([run(h0[b:b + 1], 0xFF) for b in range(0, B, max(1, B // 3))]).float()
+    sel = one[0:B:max(1, B // 3)].float()
+    assert float((rows - sel).norm() / sel.norm()) <= 1e-2
