@@ -50,6 +50,12 @@ hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t 
                             void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt,
                             void* workspace, size_t workspace_bytes, void* stream);
 
+// one decode step's attention, the new K / V rows appended to the cache by the same kernel (int8_attn.hip)
+hero_status hero_attn_decode_append(const int8_t* q, const int64_t q_strides[4], const int8_t* kn, const int8_t* vn, int64_t nstride,
+                                    int8_t* kc, int8_t* vc, const int64_t c_strides[4], int64_t B, int64_t H, int64_t Smax, int64_t Dh,
+                                    float qk_scale, float p_scale, const float* out_col_scale, int out_scale_is_scalar, hero_mask mask,
+                                    const int32_t* kv_len, void* out, hero_dtype out_dt, int64_t ldo, bool fp8, void* stream);
+
 // ---- 16-bit float storage (round to nearest even) -------------------------------------
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));

@@ -41,6 +41,9 @@ struct AttnArgs {
     const float* out_col_scale; int scale_is_scalar;
     int mask; const int32_t* kv_len;
     void* out; int64_t ldo;
+    // decode inside a layer: this call's key / value rows [B][H * DH] (row stride nstride), not yet in the cache; the kernel
+    // writes them at position kv_len[b] - 1 (kc / vc: the cache, writable) and attends to them.  NULL: nothing to append
+    const int8_t* kn; const int8_t* vn; int64_t nstride; int8_t* kc; int8_t* vc;
 };
 
 // FMT = HERO_F8E4M3: the same flow with E4M3 codes (Sec. 2.1): q, k, v are E4M3 bytes, the scores and the PV sums
@@ -532,33 +535,50 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
 
 // ------------------------------------------------------------------------------------------
 // Decode (one query per sequence): HBM-bound on the K and V cache, so no matrix cores; K and
-// V are each read exactly once.  One block per (batch, head); 8 lanes share a key (16 bytes of
-// the row each, so a wave-level load covers 8 whole rows = 1 KB of consecutive cache).
+// V are each read exactly once.  One block per (batch, head); Dh / 16 lanes share a key (16 bytes of
+// the row each, so a wave-level load covers whole rows = 1 KB of consecutive cache).
 //   phase 1: integer scores q.k (v_dot4) for every key -> LDS
 //   phase 2: row max / sum in the log2 domain (block reduction), codes 0..255 -> LDS
 //   phase 3: acc[e] = sum_k P[k] * v[k][e] in int32, reduced over the key groups through LDS
+// What bounds the stream is the bytes in flight: UNR loads per lane, NT lanes.  With many blocks, 256 threads (several
+// blocks per CU, their phases overlap: 64 x 32 heads x 2049 keys 189 us, 5.7 TB/s); with at most one block per CU,
+// 1024 threads, i.e. four times the bytes in flight per block (the rule and its figures: attn_entry).  The first V loads
+// are out during the softmax.
+// In a layer, the block also appends this call's K / V row to its cache: no other block reads that row, and the two
+// 4-5 us launches of a step that copied it are gone.
 // ------------------------------------------------------------------------------------------
 constexpr int DEC_MAX_KEYS = 16384;
 
 // FMT = HERO_F8E4M3: E4M3 operands: the bytes are decoded two at a time (v_cvt_pk_f32_fp8), scores and PV sums are
 // fp32, the probability code is e4m3(min(p / S_p, 448)) and its decoded value is what PV multiplies.
-template <int DH, int ODT, int FMT = HERO_I8>
-__global__ __launch_bounds__(256) void int8_attn_decode_kernel(AttnArgs a) {
+template <int DH, int ODT, int FMT, int NT>
+__global__ __launch_bounds__(NT) void int8_attn_decode_kernel(AttnArgs a) {
     constexpr bool F8 = FMT == HERO_F8E4M3;
     using ST = typename std::conditional<F8, float, int>::type;      // score / accumulator element
     constexpr int LPK = DH / 16;                 // lanes per key
-    constexpr int KPI = 256 / LPK;               // keys per block iteration
+    constexpr int KPI = NT / LPK;                // keys per block iteration
+    constexpr int NW = NT / 64;
     extern __shared__ __attribute__((aligned(16))) int smem_dec[];
     ST* sc = reinterpret_cast<ST*>(smem_dec);                      // [len] scores, later codes (F8: their decoded values)
-    __shared__ float red[8];
-    __shared__ ST racc[KPI][DH + 4];
+    __shared__ float red[2 * NW];
+    __shared__ ST racc[NW][DH + 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.y, h = blockIdx.x;
-    const int len = a.kv_len ? min(max(a.kv_len[b], 0), a.Skv) : a.Skv;     // one query: it sees every valid key
+    const int kvl = a.kv_len ? a.kv_len[b] : a.Skv;
+    const int len = min(max(kvl, 0), a.Skv);     // one query: it sees every valid key
     const int sub = tid % LPK, kg = tid / LPK;
     const int8_t* kbase = a.k + (int64_t)b * a.ks[0] + (int64_t)h * a.ks[2] + sub * 16;
     const int8_t* vbase = a.v + (int64_t)b * a.vs[0] + (int64_t)h * a.vs[2] + sub * 16;
     const v4i qv = *reinterpret_cast<const v4i*>(a.q + (int64_t)b * a.qs[0] + (int64_t)h * a.qs[2] + sub * 16);
+    // the appended row: position len - 1, kept in the registers of every key group (group 0 uses it)
+    const bool app = a.kn && kvl >= 1 && kvl <= a.Skv;               // block-uniform
+    const int hist = app ? len - 1 : len;                            // keys that are read from the cache
+    v4i kn = {0, 0, 0, 0}, vn = {0, 0, 0, 0};
+    if (app) {
+        const int64_t src = (int64_t)b * a.nstride + (int64_t)h * DH + sub * 16;
+        kn = *reinterpret_cast<const v4i*>(a.kn + src);
+        vn = *reinterpret_cast<const v4i*>(a.vn + src);
+    }
     // 16 E4M3 bytes -> 16 floats
     auto decode16 = [](const v4i& w, float (&f)[16]) {
 #pragma unroll
@@ -589,26 +609,38 @@ __global__ __launch_bounds__(256) void int8_attn_decode_kernel(AttnArgs a) {
         return d;
     };
     // the stream is bound by the bytes in flight: UNR unconditional loads per lane are issued before the first is
-    // used (whole groups of UNR * KPI keys), the ragged rest goes one guarded load at a time
+    // used (whole groups of UNR * KPI keys), the ragged rest goes in one round of UNR clamped loads
     constexpr int UNR = 8;
-    int k0 = 0;
-    for (; k0 + UNR * KPI <= len; k0 += UNR * KPI) {
+    auto take = [&](int key, ST d) {
+        if (sub == 0 && key < hist) { sc[key] = d; lmax = max(lmax, d); }
+    };
+    for (int k0 = 0; k0 < hist; k0 += UNR * KPI) {
         v4i kv[UNR];
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) kv[u] = *reinterpret_cast<const v4i*>(kbase + (int64_t)(k0 + u * KPI + kg) * a.ks[1]);
+        for (int u = 0; u < UNR; ++u) kv[u] = *reinterpret_cast<const v4i*>(kbase + (int64_t)min(k0 + u * KPI + kg, hist - 1) * a.ks[1]);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const ST d = score(kv[u]);
-            if (sub == 0) { sc[k0 + u * KPI + kg] = d; lmax = max(lmax, d); }
+            if (k0 + u * KPI >= hist) break;                          // block-uniform
+            take(k0 + u * KPI + kg, score(kv[u]));
         }
     }
-    for (; k0 < len; k0 += KPI) {
-        const int key = k0 + kg;
-        v4i kv = {0, 0, 0, 0};
-        if (key < len) kv = *reinterpret_cast<const v4i*>(kbase + (int64_t)key * a.ks[1]);
-        const ST d = score(kv);
-        if (sub == 0 && key < len) { sc[key] = d; lmax = max(lmax, d); }
+    if (app) {
+        const ST d = score(kn);
+        if (tid == 0) sc[hist] = d;
+        lmax = max(lmax, d);
+        if (kg == 0) {
+            const int64_t dst = (int64_t)hist * a.ks[1], vst = (int64_t)hist * a.vs[1];
+            *reinterpret_cast<v4i*>(a.kc + (kbase - a.k) + dst) = kn;
+            *reinterpret_cast<v4i*>(a.vc + (vbase - a.v) + vst) = vn;
+        }
     }
+    // the first V loads are in flight during the softmax
+    v4i vv[UNR];
+    auto load_v = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) vv[u] = *reinterpret_cast<const v4i*>(vbase + (int64_t)min(k0 + u * KPI + kg, hist - 1) * a.vs[1]);
+    };
+    if (hist > 0) load_v(0);
     // block max
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lmax = max(lmax, __shfl_xor(lmax, o));
@@ -616,18 +648,29 @@ __global__ __launch_bounds__(256) void int8_attn_decode_kernel(AttnArgs a) {
     __syncthreads();
     const float c2 = a.qk_scale * 1.44269504088896340736f;
     float m2;
-    if constexpr (F8) m2 = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) * c2;
-    else m2 = (float)max(max(__float_as_int(red[0]), __float_as_int(red[1])), max(__float_as_int(red[2]), __float_as_int(red[3]))) * c2;
+    if constexpr (F8) {
+        float m = red[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, red[w]);
+        m2 = m * c2;
+    } else {
+        int m = __float_as_int(red[0]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = max(m, __float_as_int(red[w]));
+        m2 = (float)m * c2;
+    }
     // ---- phase 2: sum, then codes --------------------------------------------------------------
     float lsum = 0.0f;
-    for (int k = tid; k < len; k += 256) lsum += __builtin_amdgcn_exp2f(fmaf((float)sc[k], c2, -m2));
+    for (int k = tid; k < len; k += NT) lsum += __builtin_amdgcn_exp2f(fmaf((float)sc[k], c2, -m2));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o);
-    if (lane == 0) red[4 + wave] = lsum;
+    if (lane == 0) red[NW + wave] = lsum;
     __syncthreads();
-    const float l = red[4] + red[5] + red[6] + red[7];
+    float l = red[NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) l += red[NW + w];
     const float off = l > 0.0f ? -m2 - __log2f(l * a.p_scale) : -INFINITY;
-    for (int k = tid; k < len; k += 256) {
+    for (int k = tid; k < len; k += NT) {
         const float e = __builtin_amdgcn_exp2f(fmaf((float)sc[k], c2, off));
         if constexpr (F8) sc[k] = __builtin_amdgcn_cvt_f32_fp8(__builtin_amdgcn_cvt_pk_fp8_f32(fminf(e, 448.0f), 0.0f, 0, false), 0);
         else sc[k] = (int)__builtin_amdgcn_cvt_pk_u8_f32(e, 0, 0u);
@@ -637,35 +680,41 @@ __global__ __launch_bounds__(256) void int8_attn_decode_kernel(AttnArgs a) {
     ST acc[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0;
-    auto pv = [&](const v4i& vv, const ST p) {
+    auto pv = [&](const v4i& w, const ST p) {
         if constexpr (F8) {
             float vf[16];
-            decode16(vv, vf);
+            decode16(w, vf);
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[e] = fmaf(p, vf[e], acc[e]);
         } else {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[e] += p * (int)(int8_t)(vv[e >> 2] >> (8 * (e & 3)));
+            for (int e = 0; e < 16; ++e) acc[e] += p * (int)(int8_t)(w[e >> 2] >> (8 * (e & 3)));
         }
     };
-    k0 = 0;
-    for (; k0 + UNR * KPI <= len; k0 += UNR * KPI) {
-        v4i vv[UNR];
+    for (int k0 = 0; k0 < hist; k0 += UNR * KPI) {
+        if (k0 > 0) load_v(k0);
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) vv[u] = *reinterpret_cast<const v4i*>(vbase + (int64_t)(k0 + u * KPI + kg) * a.vs[1]);
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) pv(vv[u], sc[k0 + u * KPI + kg]);
+        for (int u = 0; u < UNR; ++u) {
+            const int key = k0 + u * KPI + kg;
+            if (k0 + u * KPI >= hist) break;                          // block-uniform
+            pv(vv[u], key < hist ? sc[key] : (ST)0);
+        }
     }
-    for (; k0 < len; k0 += KPI) {
-        const int key = k0 + kg;
-        if (key < len) pv(*reinterpret_cast<const v4i*>(vbase + (int64_t)key * a.vs[1]), sc[key]);
-    }
+    if (app && kg == 0) pv(vn, sc[hist]);
+    // sum over the key groups: across a wave's lanes first, then through LDS in the fixed order of the waves
 #pragma unroll
-    for (int e = 0; e < 16; ++e) racc[kg][sub * 16 + e] = acc[e];
+    for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int o = LPK; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
+    if (lane < LPK) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) racc[wave][sub * 16 + e] = acc[e];
+    }
     __syncthreads();
     if (tid < DH) {
         ST tot = 0;
-        for (int g = 0; g < KPI; ++g) tot += racc[g][tid];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) tot += racc[w][tid];
         const float scl = a.scale_is_scalar ? a.out_col_scale[0] : a.out_col_scale[h * DH + tid];
         const float y = (float)tot * scl;
         const int64_t oidx = (int64_t)b * a.ldo + (int64_t)h * DH + tid;
@@ -683,14 +732,14 @@ __global__ void zero_rows_kernel(int8_t* out, int64_t bytes) {
 // The decode kernel keeps one score per key in dynamic LDS; beyond 32 KB a kernel must be told once (per device) how
 // much it may ask for.  The attribute is raised to the kernel's maximum the first time a launch needs more than the
 // default, not on every call.
-template <int DH, int ODT, int FMT>
+template <int DH, int ODT, int FMT, int NT>
 bool decode_lds_ready(size_t lds) {
     static std::atomic<bool> raised[64];
     if (lds <= 32768) return true;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
     if (raised[dev].load(std::memory_order_acquire)) return true;
-    if (hipFuncSetAttribute((const void*)int8_attn_decode_kernel<DH, ODT, FMT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void*)int8_attn_decode_kernel<DH, ODT, FMT, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             DEC_MAX_KEYS * (int)sizeof(int)) != hipSuccess) return false;
     raised[dev].store(true, std::memory_order_release);
     return true;
@@ -716,7 +765,8 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
                        float qk_scale, const float* qk_scale_h, bool online, bool fp8,
                        float p_scale, const float* out_col_scale, int out_scale_is_scalar,
                        hero_mask mask, const int32_t* kv_len,
-                       void* out, hero_dtype out_dt, int64_t ldo, void* stream) {
+                       void* out, hero_dtype out_dt, int64_t ldo, void* stream,
+                       const int8_t* kn = nullptr, const int8_t* vn = nullptr, int64_t nstride = 0) {
     if (B < 0 || H < 0 || Sq < 0 || Skv < 0) return HERO_ERR_SHAPE;
     if (Dh != 64 && Dh != 128) return HERO_ERR_UNSUPPORTED;
     const hero_dtype dt8 = fp8 ? HERO_F8E4M3 : HERO_I8;                  // the 8-bit output format is the operands'
@@ -745,6 +795,7 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     a.B = (int)B; a.H = (int)H; a.Sq = (int)Sq; a.Skv = (int)Skv;
     a.qk_scale = qk_scale; a.qk_scale_h = qk_scale_h; a.p_scale = p_scale; a.out_col_scale = out_col_scale; a.scale_is_scalar = out_scale_is_scalar;
     a.mask = (int)mask; a.kv_len = kv_len; a.out = out; a.ldo = ldo;
+    a.kn = kn; a.vn = vn; a.nstride = nstride; a.kc = const_cast<int8_t*>(k); a.vc = const_cast<int8_t*>(v);
     a.use_buf = Skv > 0 && k_strides[1] >= 0 && v_strides[1] >= 0 &&
                 (Skv + BKV) * k_strides[1] + Dh < (1LL << 31) && (Skv + BKV) * v_strides[1] + Dh < (1LL << 31);
     hipStream_t st = (hipStream_t)stream;
@@ -757,11 +808,15 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     }
     if (online) return Dh == 64 ? launch<64, true>(a, out_dt, st) : launch<128, true>(a, out_dt, st);
     if (Sq == 1 && Skv <= DEC_MAX_KEYS) {          // decode: the cache-streaming kernel
-        dim3 grid((unsigned)H, (unsigned)B), block(256);
+        // One block per CU or fewer: wide blocks (96 blocks x 1150 keys 23.4 -> 15.5 us; 224 x 550: 11.6).  From two blocks
+        // on a CU narrow ones are ahead (288 x 530: 14.9 us against 19.0 wide; 768 x 830 E4M3: 33 against 35 with 512 threads).
+        const int nt = B * H <= 256 ? 1024 : 256;
+        dim3 grid((unsigned)H, (unsigned)B), block(nt);
         const size_t lds = (size_t)Skv * sizeof(int);
-#define HERO_DEC(DH_, ODT_, FMT_) do { \
-            if (!decode_lds_ready<DH_, ODT_, FMT_>(lds)) return HERO_ERR_LAUNCH; \
-            hipLaunchKernelGGL((int8_attn_decode_kernel<DH_, ODT_, FMT_>), grid, block, lds, st, a); } while (0)
+#define HERO_DEC_NT(DH_, ODT_, FMT_, NT_) do { \
+            if (!decode_lds_ready<DH_, ODT_, FMT_, NT_>(lds)) return HERO_ERR_LAUNCH; \
+            hipLaunchKernelGGL((int8_attn_decode_kernel<DH_, ODT_, FMT_, NT_>), grid, block, lds, st, a); } while (0)
+#define HERO_DEC(DH_, ODT_, FMT_) do { if (nt == 1024) HERO_DEC_NT(DH_, ODT_, FMT_, 1024); else HERO_DEC_NT(DH_, ODT_, FMT_, 256); } while (0)
 #define HERO_DEC_DT(DH_, FMT_) do { \
             if (out_dt == HERO_BF16) HERO_DEC(DH_, HERO_BF16, FMT_); else if (out_dt == HERO_F16) HERO_DEC(DH_, HERO_F16, FMT_); \
             else HERO_DEC(DH_, FMT_, FMT_); } while (0)
@@ -769,6 +824,7 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
         else { if (Dh == 64) HERO_DEC_DT(64, HERO_I8); else HERO_DEC_DT(128, HERO_I8); }
 #undef HERO_DEC_DT
 #undef HERO_DEC
+#undef HERO_DEC_NT
         return hero_launch_status();
     }
     if (fp8) return Dh == 64 ? launch<64, false, HERO_F8E4M3>(a, out_dt, st) : launch<128, false, HERO_F8E4M3>(a, out_dt, st);
@@ -776,6 +832,18 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
 }
 
 }  // namespace
+
+// One decode step of a layer: hero_int8_attn / hero_fp8_attn over the cache, with this call's K / V rows (row stride nstride)
+// written to their place in it by the same kernel.  HERO_ERR_UNSUPPORTED: not a case of that kernel (the caller appends and
+// attends in two launches).  Not part of the C ABI.
+hero_status hero_attn_decode_append(const int8_t* q, const int64_t q_strides[4], const int8_t* kn, const int8_t* vn, int64_t nstride,
+                                    int8_t* kc, int8_t* vc, const int64_t c_strides[4], int64_t B, int64_t H, int64_t Smax, int64_t Dh,
+                                    float qk_scale, float p_scale, const float* out_col_scale, int out_scale_is_scalar, hero_mask mask,
+                                    const int32_t* kv_len, void* out, hero_dtype out_dt, int64_t ldo, bool fp8, void* stream) {
+    if (Smax <= 0 || Smax > DEC_MAX_KEYS) return HERO_ERR_UNSUPPORTED;
+    return attn_entry(q, q_strides, kc, c_strides, vc, c_strides, B, H, 1, Smax, Dh, qk_scale, nullptr, false, fp8, p_scale,
+                      out_col_scale, out_scale_is_scalar, mask, kv_len, out, out_dt, ldo, stream, kn, vn, nstride);
+}
 
 extern "C" hero_status hero_int8_attn(const int8_t* q, const int64_t q_strides[4],
                                       const int8_t* k, const int64_t k_strides[4],

@@ -170,6 +170,36 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     hipStream_t st = (hipStream_t)stream;
     void* gws = ws.gemm_ws_bytes ? (void*)(base + ws.gemm_ws) : nullptr;   // split-K scratch of the skinny GEMMs
 
+    // 8-bit attention over this call's keys or, with a cache, over the cache, to which they are appended first: in one kernel
+    // for a decode step (no block reads another's row), by a copy of the bytes (codes of either format) otherwise
+    const int64_t qs[4] = {S * 3 * d, 3 * d, Dh, 1};
+    auto attend8 = [&](bool fp8) -> hero_status {
+        const int8_t* qp = (const int8_t*)qkv;
+        const int8_t *kp = qp + d, *vp = qp + 2 * d;
+        const int64_t* ks = qs;
+        const int64_t cs[4] = {H * io->Smax * Dh, Dh, io->Smax * Dh, 1};
+        const hero_dtype out_dt = fp8 ? HERO_F8E4M3 : (o_i8 ? HERO_I8 : HP);
+        const int scalar = fp8 || o_i8 ? 0 : 1;
+        int64_t Skv = S;
+        if (cache) {
+            if (S == 1) {
+                const hero_status s1 = hero_attn_decode_append(qp, qs, kp, vp, 3 * d, io->k_cache, io->v_cache, cs, B, H, io->Smax, Dh,
+                                                               w->qk_scale, w->p_scale, w->attn_out_scale, scalar, (hero_mask)desc->mask,
+                                                               io->kv_len, attn, out_dt, d, fp8, stream);
+                if (s1 != HERO_ERR_UNSUPPORTED) return s1;
+            }
+            const int64_t n = T * (d / 16);
+            hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                               qp, io->k_cache, io->v_cache, io->kv_len, (int)B, (int)S, (int)H, (int)Dh, io->Smax);
+            HERO_TRY(hero_launch_status());
+            kp = io->k_cache; vp = io->v_cache; Skv = io->Smax; ks = cs;
+        }
+        if (fp8) return hero_fp8_attn(qp, qs, kp, ks, vp, ks, B, H, S, Skv, Dh, w->qk_scale, w->p_scale, w->attn_out_scale, scalar,
+                                      (hero_mask)desc->mask, io->kv_len, attn, out_dt, d, stream);
+        return hero_int8_attn(qp, qs, kp, ks, vp, ks, B, H, S, Skv, Dh, w->qk_scale, w->p_scale, w->attn_out_scale, scalar,
+                              (hero_mask)desc->mask, io->kv_len, attn, out_dt, d, stream);
+    };
+
     // ---- the FP8 variant (Sec. 2.1): the same chain with E4M3 codes in every 8-bit buffer
     if (mode & HERO_M_FP8) {
         const hero_dtype F8 = HERO_F8E4M3;
@@ -178,21 +208,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                        T, d, xin_q, xin_s, nullptr, HERO_BF16, stream));
         HERO_TRY(hero_fp8_gemm_prefetching(xin_q, d, xin_s, w->w_qkv, d, w->w_qkv_s, w->b_qkv, nullptr, HERO_BF16, 0,
                                            HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d, T, 3 * d, d, gws, ws.gemm_ws_bytes, stream, w->w_o, (size_t)(d * d)));
-        const int64_t qs[4] = {S * 3 * d, 3 * d, Dh, 1};
-        const int8_t* qp = (const int8_t*)qkv;
-        const int8_t *kp = qp + d, *vp = qp + 2 * d;
-        int64_t ks[4] = {qs[0], qs[1], qs[2], qs[3]};
-        int64_t Skv = S;
-        if (cache) {                                              // the cache holds E4M3 (SQ) codes: a byte copy
-            const int64_t n = T * (d / 16);
-            hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                               qp, io->k_cache, io->v_cache, io->kv_len, (int)B, (int)S, (int)H, (int)Dh, io->Smax);
-            HERO_TRY(hero_launch_status());
-            kp = io->k_cache; vp = io->v_cache; Skv = io->Smax;
-            ks[0] = H * io->Smax * Dh; ks[1] = Dh; ks[2] = io->Smax * Dh; ks[3] = 1;
-        }
-        HERO_TRY(hero_fp8_attn(qp, qs, kp, ks, vp, ks, B, H, S, Skv, Dh, w->qk_scale, w->p_scale,
-                               w->attn_out_scale, 0, (hero_mask)desc->mask, io->kv_len, attn, F8, d, stream));
+        HERO_TRY(attend8(true));
         if (!pre) {
             HERO_TRY(hero_fp8_gemm_prefetching(attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, nullptr, HERO_BF16, 0,
                                                HERO_EPI_REQUANT, nullptr, xo, F8, d, T, d, d, gws, ws.gemm_ws_bytes, stream, w->w_1, (size_t)(f * d)));
@@ -231,23 +247,8 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     else
         HERO_TRY(hero_hp_gemm_ws(xin_hp, d, w->w_qkv_hp, d, w->b_qkv, nullptr, 0, 0, qkv, 3 * d, T, 3 * d, d, HP, gws, ws.gemm_ws_bytes, stream));
     // (3) attention
-    const int64_t qs[4] = {S * 3 * d, 3 * d, Dh, 1};
     if (attn_i8) {
-        const int8_t* qp = (const int8_t*)qkv;
-        const int8_t *kp = qp + d, *vp = qp + 2 * d;
-        int64_t ks[4] = {qs[0], qs[1], qs[2], qs[3]};
-        int64_t Skv = S;
-        if (cache) {
-            const int64_t n = T * (d / 16);
-            hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                               qp, io->k_cache, io->v_cache, io->kv_len, (int)B, (int)S, (int)H, (int)Dh, io->Smax);
-            HERO_TRY(hero_launch_status());
-            kp = io->k_cache; vp = io->v_cache; Skv = io->Smax;
-            ks[0] = H * io->Smax * Dh; ks[1] = Dh; ks[2] = io->Smax * Dh; ks[3] = 1;
-        }
-        HERO_TRY(hero_int8_attn(qp, qs, kp, ks, vp, ks, B, H, S, Skv, Dh, w->qk_scale, w->p_scale,
-                                w->attn_out_scale, o_i8 ? 0 : 1, (hero_mask)desc->mask, io->kv_len,
-                                attn, o_i8 ? HERO_I8 : HP, d, stream));
+        HERO_TRY(attend8(false));
     } else {
         const uint16_t* qp = (const uint16_t*)qkv;
         HERO_TRY(hero_hp_attn(qp, qs, qp + d, qs, qp + 2 * d, qs, B, H, S, S, Dh, w->qk_scale,
