@@ -97,6 +97,16 @@ __device__ __forceinline__ void store_hp(const float (&v)[EPL], uint16_t* dst) {
     }
 }
 
+// four codes behind a LayerNorm.  E4M3: of the true quotient, |y / s| <= 448 (1 + 2^-23) clamped to the format's range;
+// INT8: |v * inv_sc| <= 127 (1 + 2^-22), so v * inv_sc + 128 rounds into 1 .. 255
+__device__ __forceinline__ uint32_t codes4(const float* v, float sc, float inv_sc, bool f8) {
+    if (f8) return fp8x4_sat(__fdiv_rn(v[0], sc), __fdiv_rn(v[1], sc), __fdiv_rn(v[2], sc), __fdiv_rn(v[3], sc));
+    uint32_t w = 0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(v[t], inv_sc, 128.0f), t, w);
+    return w ^ 0x80808080u;
+}
+
 constexpr int ln_max_waves(int nch) { return nch <= 2 ? 16 : (nch == 4 ? 8 : 4); }   // per workgroup: the row must fit the registers
 
 // XDT: HERO_I8 / HERO_BF16 / HERO_F16.  RDT: -1 (no second addend) / HERO_I8 / HERO_BF16 / HERO_F16.
@@ -372,6 +382,114 @@ __global__ __launch_bounds__(64 * ln_max_waves(NCH)) void ln_quant_kernel(LnArgs
     }
 }
 
+// ---- wide rows of 16-bit values: one WORKGROUP per row -------------------------------------------------------
+// A row of 4096 values is eight chunks per lane of the kernel above: 80 registers, four waves per CU, every row a serial
+// chain of eight loads, and a launch of a few rows (a decode step) is one wave's latency.  Here the 256 threads of a
+// workgroup share a row (NC chunks of 8 elements per thread), gamma and beta stay in registers, the next row is in flight
+// while the current one is worked on, and the three reductions meet through LDS (one barrier each).
+// Bound: HBM for many rows, the launch for few (figures: launch_r).
+template <int XDT, int NC>
+__global__ __launch_bounds__(256) void ln_quant_row_kernel(LnArgs a) {
+    constexpr int NW = 4;
+    __shared__ float red[3][2][NW];
+    const int D = a.D, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint16_t* const xp = (const uint16_t*)a.x;
+    v4i rx[NC];
+    auto fetch = [&](int64_t row) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int j0 = (c * 256 + tid) * 8;
+            if (j0 < D) rx[c] = *reinterpret_cast<const v4i*>(xp + row * (int64_t)D + j0);
+        }
+    };
+    int64_t row = blockIdx.x;
+    fetch(row);
+    v4f g[NC][2], b[NC][2];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int j0 = (c * 256 + tid) * 8;
+#pragma unroll
+        for (int e4 = 0; e4 < 2; ++e4) {
+            g[c][e4] = b[c][e4] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            if (j0 < D) {
+                g[c][e4] = *reinterpret_cast<const v4f*>(a.gamma + j0 + 4 * e4);
+                if (a.beta) b[c][e4] = *reinterpret_cast<const v4f*>(a.beta + j0 + 4 * e4);
+            }
+        }
+    }
+    // held from here on (otherwise the compiler fetches them again for every row)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e4 = 0; e4 < 2; ++e4) { asm volatile("" : "+v"(g[c][e4])); asm volatile("" : "+v"(b[c][e4])); }
+    const float inv_d = 1.0f / (float)D;
+    // (the buffers alternate with the row: a wave may be one row ahead of the others' reads, never two)
+    for (int par = 0;; par ^= 1) {
+        float v[NC][8];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const bool in = (c * 256 + tid) * 8 < D;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[c][e] = in ? hp_to_f32<XDT>(((uint32_t)rx[c][e >> 1] >> (16 * (e & 1))) & 0xffffu) : 0.0f;
+        }
+        const int64_t next = row + gridDim.x;
+        if (next < a.M) fetch(next);
+        float s = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += v[c][e];
+        s = wave_reduce<false>(s);
+        if (lane == 0) red[0][par][wave] = s;
+        __syncthreads();
+        const float mean = (red[0][par][0] + red[0][par][1] + red[0][par][2] + red[0][par][3]) * inv_d;
+        float q = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const float mean_c = (c * 256 + tid) * 8 < D ? mean : 0.0f;       // padding stays out of the squared deviations
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                v[c][e] -= mean_c;
+                q = fmaf(v[c][e], v[c][e], q);
+            }
+        }
+        q = wave_reduce<false>(q);
+        if (lane == 0) red[1][par][wave] = q;
+        __syncthreads();
+        const float var = (red[1][par][0] + red[1][par][1] + red[1][par][2] + red[1][par][3]) * inv_d;
+        const float rstd = __builtin_amdgcn_rsqf(var + a.eps);
+        float amax = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                v[c][e] = fmaf(v[c][e] * rstd, g[c][e >> 2][e & 3], b[c][e >> 2][e & 3]);             // (padded columns have gamma = beta = 0)
+                amax = fmaxf(amax, fabsf(v[c][e]));
+            }
+        amax = wave_reduce<true>(amax);
+        if (lane == 0) red[2][par][wave] = amax;
+        __syncthreads();
+        amax = fmaxf(fmaxf(red[2][par][0], red[2][par][1]), fmaxf(red[2][par][2], red[2][par][3]));
+        const float sc = amax == 0.0f ? 1.0f : __fdiv_rn(amax, a.y_fp8 ? 448.0f : 127.0f);
+        const float inv_sc = __builtin_amdgcn_rcpf(sc);
+        if (tid == 0) a.y_scale[row] = sc;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int j0 = (c * 256 + tid) * 8;
+            if (j0 >= D) continue;
+            const int64_t off = row * (int64_t)D + j0;
+            uint32_t pk[2];
+#pragma unroll
+            for (int e4 = 0; e4 < 2; ++e4) pk[e4] = codes4(v[c] + 4 * e4, sc, inv_sc, a.y_fp8);
+            *reinterpret_cast<v2i*>(a.y_q + off) = v2i{(int)pk[0], (int)pk[1]};
+            if (a.hp_dt == HERO_BF16) store_hp<HERO_BF16, 8>(v[c], (uint16_t*)a.y_hp + off);
+            else if (a.hp_dt == HERO_F16) store_hp<HERO_F16, 8>(v[c], (uint16_t*)a.y_hp + off);
+        }
+        row = next;
+        if (row >= a.M) break;
+    }
+}
+
 template <int XDT, int RDT, int NCH, bool GATHER = false>
 hero_status launch_nch(const LnArgs& a, hipStream_t st) {
     constexpr int CH = (XDT == HERO_I8 ? 16 : 8) * HERO_WAVE;
@@ -404,12 +522,24 @@ hero_status launch_nch(const LnArgs& a, hipStream_t st) {
     return hero_launch_status();
 }
 
+constexpr int64_t LN_ROW_BLOCKS = 256 * 6;
+
 template <int XDT, int RDT>
 hero_status launch_r(const LnArgs& a, hipStream_t st) {
     constexpr int CH = (XDT == HERO_I8 ? 16 : 8) * HERO_WAVE;
     const int nch = (a.D + CH - 1) / CH;
     if (nch <= 1) return launch_nch<XDT, RDT, 1>(a, st);
     if (nch <= 2) return launch_nch<XDT, RDT, 2>(a, st);
+    if constexpr (XDT != HERO_I8 && RDT < 0) {
+        if (a.gamma && hero_aligned16(a.gamma) && hero_aligned16(a.beta)) {   // 16-bit rows of more than 1024 values (the residual stream): a workgroup per row
+            // (measured, D = 4096 bf16, us, before -> now: 3 rows 7.0 -> 4.1, 64 rows 8.0 -> 4.8, 602 rows 8.7 -> 5.8,
+            // 16384 rows 56 -> 40 = 5 TB/s)
+            const unsigned blocks = (unsigned)(a.M < LN_ROW_BLOCKS ? a.M : LN_ROW_BLOCKS);
+            if (nch <= 4) hipLaunchKernelGGL((ln_quant_row_kernel<XDT, 1>), dim3(blocks), dim3(256), 0, st, a);
+            else hipLaunchKernelGGL((ln_quant_row_kernel<XDT, 2>), dim3(blocks), dim3(256), 0, st, a);
+            return hero_launch_status();
+        }
+    }
     if (nch <= 4) return launch_nch<XDT, RDT, 4>(a, st);
     if (nch <= 8) return launch_nch<XDT, RDT, 8>(a, st);
     return HERO_ERR_UNSUPPORTED;
