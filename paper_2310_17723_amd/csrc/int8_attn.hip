@@ -534,6 +534,231 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
 }
 
 // ------------------------------------------------------------------------------------------
+// Few query blocks (a short sentence, a prompt chunk of few users): the kernel above runs as one serial chain of two
+// passes over the keys per block of 128 queries, on as many CUs as there are blocks.  Here a block owns 32 queries and its
+// NW waves split the KEYS: wave w takes the 32-key steps w, w + NW, .., with K fragments straight from memory, V transposed
+// through LDS of its own and no barrier inside a pass.  The waves' row maxima and sums meet in LDS between the passes, their
+// PV sums (exact integers; E4M3: fp32, added in the order of the waves) at the end.  Four times the K / V reads from the
+// L2 for a quarter of the chain; bound by latency.  Same codes by the same formulas as above; the offset of the unsigned codes is
+// removed by a second matrix instruction as in the online variant, so o = -sum code * v.
+// ------------------------------------------------------------------------------------------
+template <int DH, int ODT, int FMT, int NW>
+__global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
+    constexpr bool F8 = FMT == HERO_F8E4M3;
+    using SACC = typename std::conditional<F8, v16f, v16i>::type;
+    using ST = typename std::conditional<F8, float, int>::type;
+    using V4 = typename std::conditional<F8, v4f, v4i>::type;
+    constexpr int SQ = 32, SK = 32, VLD = SK + 16, DS = DH / 32, VU = (SK / 4) * (DH / 4) / 64, TLD = 36;
+    __shared__ __attribute__((aligned(16))) int8_t pool[NW * DH * VLD > NW * SQ * TLD * 4 ? NW * DH * VLD : NW * SQ * TLD * 4];
+    __shared__ float sm[NW][SQ], sl[NW][SQ];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hh = lane >> 5, ql = lane & 31;
+    constexpr int HG = DH >= 128 ? 1 : 128 / DH;                 // block order: as above, per 32 queries
+    const int nqb = (a.Sq + SQ - 1) / SQ;
+    const int slot = blockIdx.x / 8, grp = (slot / (HG * nqb)) * 8 + (blockIdx.x % 8), within = slot % (HG * nqb);
+    const int bh = grp * HG + within / nqb;
+    if (bh >= a.B * a.H) return;
+    const int b = bh / a.H, h = bh % a.H, q0 = (within % nqb) * SQ;
+    const int len = a.kv_len ? min(max(a.kv_len[b], 0), a.Skv) : a.Skv;
+    const int shift = len - a.Sq, qi = q0 + ql;
+    int nvis = len, kmax = len;
+    if (a.mask == HERO_MASK_CAUSAL) {
+        nvis = min(len, qi + shift + 1);
+        kmax = min(len, min(q0 + SQ, a.Sq) + shift);
+    }
+    nvis = max(nvis, 0);
+    const int qlim = (a.mask == HERO_MASK_PADDING && a.Sq == a.Skv) ? len : a.Sq;      // padded positions ask nothing
+    const int nsteps = q0 >= qlim ? 0 : (max(kmax, 0) + SK - 1) / SK;                  // block-uniform
+    v4i qf[DS];
+    {
+        const int8_t* qp = a.q + (int64_t)b * a.qs[0] + (int64_t)min(qi, a.Sq - 1) * a.qs[1] + (int64_t)h * a.qs[2];
+#pragma unroll
+        for (int d = 0; d < DS; ++d) qf[d] = *reinterpret_cast<const v4i*>(qp + d * 32 + hh * 16);
+    }
+    const int8_t* const kbase = a.k + (int64_t)b * a.ks[0] + (int64_t)h * a.ks[2] + hh * 16;
+    const int8_t* const vbase = a.v + (int64_t)b * a.vs[0] + (int64_t)h * a.vs[2];
+    int8_t* const sv = pool + wave * DH * VLD;
+    v4i k0[DS], k1[DS];                                          // two steps in flight in pass 1
+    int rv[VU][4];
+    auto load_k = [&](v4i (&kf)[DS], int step) {                                // lane: key row ql of the step, its 16-byte pieces of half hh
+        const int8_t* p = kbase + (int64_t)min(step * SK + ql, a.Skv - 1) * a.ks[1];
+#pragma unroll
+        for (int d = 0; d < DS; ++d) kf[d] = *reinterpret_cast<const v4i*>(p + d * 32);
+    };
+    // V unit: 4 keys x 4 channels; eight consecutive lanes read 32 contiguous bytes of one key row
+    auto load_v = [&](int step) {
+#pragma unroll
+        for (int u = 0; u < VU; ++u) {
+            const int kg = (lane >> 3) & 7, cg = (lane & 7) + 8 * u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                rv[u][i] = *reinterpret_cast<const int*>(vbase + (int64_t)min(step * SK + kg * 4 + i, a.Skv - 1) * a.vs[1] + cg * 4);
+        }
+    };
+    auto store_v = [&]() {
+#pragma unroll
+        for (int u = 0; u < VU; ++u) {
+            const int kg = (lane >> 3) & 7, cg = (lane & 7) + 8 * u;
+            const uint32_t d0 = rv[u][0], d1 = rv[u][1], d2 = rv[u][2], d3 = rv[u][3];
+            const uint32_t lo01 = __builtin_amdgcn_perm(d1, d0, 0x05010400u), hi01 = __builtin_amdgcn_perm(d1, d0, 0x07030602u);
+            const uint32_t lo23 = __builtin_amdgcn_perm(d3, d2, 0x05010400u), hi23 = __builtin_amdgcn_perm(d3, d2, 0x07030602u);
+            const uint32_t t[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                                   __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+            const int pos = (kg & 1) * 16 + (kg >> 1) * 4;       // the key order of the PV fragment (see the kernel above)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) *reinterpret_cast<uint32_t*>(&sv[(cg * 4 + j) * VLD + pos]) = t[j];
+        }
+    };
+    auto scores = [&](const v4i (&kf)[DS]) {
+        SACC acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0;
+        if constexpr (F8) {
+#pragma unroll
+            for (int d = 0; d < DS; d += 2) acc = mfma_wide_f8(kf[d], kf[d + 1], qf[d], qf[d + 1], acc);
+        } else {
+#pragma unroll
+            for (int d = 0; d < DS; ++d) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[d], qf[d], acc, 0, 0, 0);
+        }
+        return acc;
+    };
+    const float c2 = a.qk_scale * 1.44269504088896340736f;
+    constexpr int MASKED = -0x40000000;
+    constexpr float FMASKED = -3.0e38f;
+
+    int nvis_min = nvis;                                         // the first step with a key hidden from some query
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) nvis_min = min(nvis_min, __shfl_xor(nvis_min, o));
+
+    // ---- pass 1: this wave's row maxima and sums
+    float m2 = -INFINITY, l = 0.0f;
+    auto stats = [&](v4i (&kf)[DS], int step) {
+        SACC acc = scores(kf);
+        if (step + 2 * NW < nsteps) load_k(kf, step + 2 * NW);
+        if ((step + 1) * SK > nvis_min) {
+            const int lim = nvis - (step * SK + hh * 4);         // key visible iff 8g + t < lim
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if constexpr (F8) acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : FMASKED;
+                else acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : MASKED;
+            }
+        }
+        auto smax = acc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) smax = max(smax, acc[r]);
+        smax = max(smax, __shfl_xor(smax, 32));
+        if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {
+            const float mn = fmaxf(m2, (float)smax * c2);
+            float sum = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf((float)acc[r], c2, -mn));
+            l = fmaf(l, __builtin_amdgcn_exp2f(m2 - mn), sum);
+            m2 = mn;
+        }
+    };
+    if (wave < nsteps) load_k(k0, wave);
+    if (wave + NW < nsteps) load_k(k1, wave + NW);
+    for (int step = wave; step < nsteps; step += 2 * NW) {
+        stats(k0, step);
+        if (step + NW < nsteps) stats(k1, step + NW);
+    }
+    if (wave < nsteps) { load_k(k0, wave); load_v(wave); }       // in flight while the waves meet
+    l += __shfl_xor(l, 32);
+    if (hh == 0) { sm[wave][ql] = m2; sl[wave][ql] = l; }
+    __syncthreads();
+    float M = sm[0][ql];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, sm[w][ql]);
+    float L = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { const float lw = sl[w][ql]; if (lw > 0.0f) L = fmaf(lw, __builtin_amdgcn_exp2f(sm[w][ql] - M), L); }
+    const float off = L > 0.0f ? -M - __log2f(L * a.p_scale) : -INFINITY;
+
+    // ---- pass 2: codes and PV
+    SACC o[DS];
+#pragma unroll
+    for (int c = 0; c < DS; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[c][r] = 0;
+    const v4i cm127 = {(int)0x81818181u, (int)0x81818181u, (int)0x81818181u, (int)0x81818181u}, zero = {0, 0, 0, 0};
+    for (int step = wave; step < nsteps; step += NW) {
+        store_v();
+        const SACC acc = scores(k0);
+        if (step + NW < nsteps) { load_k(k0, step + NW); load_v(step + NW); }
+        v4i pf;
+        auto codes = [&](auto EDGE) {
+            const int lim = nvis - (step * SK + hh * 4);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float e[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    e[t] = __builtin_amdgcn_exp2f(fmaf((float)acc[4 * g + t], c2, off));
+                    if constexpr (decltype(EDGE)::value) e[t] = (g * 8 + t) < lim ? e[t] : 0.0f;
+                }
+                if constexpr (F8) {
+                    const int w = __builtin_amdgcn_cvt_pk_fp8_f32(fminf(e[0], 448.0f), fminf(e[1], 448.0f), 0, false);
+                    pf[g] = __builtin_amdgcn_cvt_pk_fp8_f32(fminf(e[2], 448.0f), fminf(e[3], 448.0f), w, true);
+                } else {
+                    uint32_t w = 0;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) w = __builtin_amdgcn_cvt_pk_u8_f32(e[t], t, w);
+                    pf[g] = (int)(w ^ 0x7f7f7f7fu);              // 127 - code as signed bytes
+                }
+            }
+        };
+        if ((step + 1) * SK > nvis_min) codes(std::true_type{}); else codes(std::false_type{});
+        // the wave reads what its own lanes wrote: LDS operations of one wave keep their order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int c = 0; c < DS; ++c) {
+            const v4i vf = *reinterpret_cast<const v4i*>(&sv[(c * 32 + ql) * VLD + hh * 16]);
+            if constexpr (F8) o[c] = mfma_wide_f8(vf, zero, pf, zero, o[c]);
+            else {
+                o[c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf, o[c], 0, 0, 0);
+                o[c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, cm127, o[c], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    // ---- the waves' sums, 32 channels at a time: [wave][query][channel] in LDS, 4 channels of a query per thread
+    ST* const tile = reinterpret_cast<ST*>(pool);
+#pragma unroll
+    for (int c = 0; c < DS; ++c) {
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<V4*>(tile + (wave * SQ + ql) * TLD + g * 8 + hh * 4) = V4{o[c][4 * g], o[c][4 * g + 1], o[c][4 * g + 2], o[c][4 * g + 3]};
+        __syncthreads();
+        if (tid < SQ * 8) {
+            const int q = tid >> 3, e0 = c * 32 + (tid & 7) * 4;
+            V4 tot = {0, 0, 0, 0};
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const V4 p = *reinterpret_cast<const V4*>(tile + (w * SQ + q) * TLD + (tid & 7) * 4);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) tot[t] += p[t];
+            }
+            if (q0 + q < a.Sq) {
+                float y[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float sc = a.scale_is_scalar ? a.out_col_scale[0] : a.out_col_scale[h * DH + e0 + t];
+                    y[t] = (F8 ? (float)tot[t] : (float)(-tot[t])) * sc;
+                    if (q0 + q >= qlim) y[t] = 0.0f;             // padded query: zeros
+                }
+                const int64_t oi = ((int64_t)b * a.Sq + q0 + q) * a.ldo + (int64_t)h * DH + e0;
+                if (ODT == HERO_I8) *reinterpret_cast<uint32_t*>((int8_t*)a.out + oi) = quant4_sat(y[0], y[1], y[2], y[3]);
+                else if (ODT == HERO_F8E4M3) *reinterpret_cast<uint32_t*>((int8_t*)a.out + oi) = fp8x4_sat(y[0], y[1], y[2], y[3]);
+                else *reinterpret_cast<v2i*>((uint16_t*)a.out + oi) = v2i{(int)pack2_hp<ODT>(y[0], y[1]), (int)pack2_hp<ODT>(y[2], y[3])};
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // Decode (one query per sequence): HBM-bound on the K and V cache, so no matrix cores; K and
 // V are each read exactly once.  One block per (batch, head); Dh / 16 lanes share a key (16 bytes of
 // the row each, so a wave-level load covers whole rows = 1 KB of consecutive cache).
@@ -757,6 +982,18 @@ hero_status launch(const AttnArgs& a, hero_dtype out_dt, hipStream_t st) {
     return hero_launch_status();
 }
 
+template <int DH, int FMT, int NW>
+hero_status launch_split(const AttnArgs& a, hero_dtype out_dt, hipStream_t st) {
+    constexpr int HG = DH >= 128 ? 1 : 128 / DH;
+    const int64_t nqb = (a.Sq + 31) / 32, hgroups = ((int64_t)a.B * a.H + HG - 1) / HG, rounds = (hgroups + 7) / 8;
+    if (rounds * 8 * HG * nqb > 0x7fffffffLL) return HERO_ERR_SHAPE;
+    dim3 grid((unsigned)(rounds * 8 * HG * nqb)), block(64 * NW);
+    if (out_dt == HERO_BF16) hipLaunchKernelGGL((int8_attn_split_kernel<DH, HERO_BF16, FMT, NW>), grid, block, 0, st, a);
+    else if (out_dt == HERO_F16) hipLaunchKernelGGL((int8_attn_split_kernel<DH, HERO_F16, FMT, NW>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((int8_attn_split_kernel<DH, FMT, FMT, NW>), grid, block, 0, st, a);
+    return hero_launch_status();
+}
+
 // argument checks and dispatch shared by the two entry points (online: the single-sweep variant)
 hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
                        const int8_t* k, const int64_t k_strides[4],
@@ -826,6 +1063,14 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
 #undef HERO_DEC
 #undef HERO_DEC_NT
         return hero_launch_status();
+    }
+    // At most one 128-query block per CU, or a single 32-query piece: the keys are split over the waves.  Measured, us, 128-query
+    // kernel -> split: 1 x 12 heads x 128 8.8 -> 5.3, 2 x 16 x 512 18.5 -> 10.8, 2 x 32 x 301 behind 900 keys 47.6 -> 37.2,
+    // 8 x 32 x 8 behind 2000 keys 78.7 -> 31.0, 256 blocks of 1 x 32 x 1024 causal 43 -> 37; beyond (512 blocks of 8 x 16 x 512)
+    // 23.5 -> 26.0: there the chip is full and reading K / V four times as often costs more than the shorter chain gives.
+    if (B * H * ((Sq + BQ - 1) / BQ) <= 256 || Sq <= 32) {
+        if (fp8) return Dh == 64 ? launch_split<64, HERO_F8E4M3, 4>(a, out_dt, st) : launch_split<128, HERO_F8E4M3, 4>(a, out_dt, st);
+        return Dh == 64 ? launch_split<64, HERO_I8, 4>(a, out_dt, st) : launch_split<128, HERO_I8, 4>(a, out_dt, st);
     }
     if (fp8) return Dh == 64 ? launch<64, false, HERO_F8E4M3>(a, out_dt, st) : launch<128, false, HERO_F8E4M3>(a, out_dt, st);
     return Dh == 64 ? launch<64>(a, out_dt, st) : launch<128>(a, out_dt, st);
