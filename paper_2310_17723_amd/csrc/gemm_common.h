@@ -313,15 +313,16 @@ inline bool ring_ok(int64_t kb, int64_t lda_bytes, int64_t ldb_bytes) {
 // groups, 128 x 64 without.)  Measured over M = 1 .. 4096 and the (N, K) of the three models, INT8 and BF16 operands, every
 // form, 345 shapes: the choice below is within 1.2 % of the best form on average.  Some of the figures, us, weights out of
 // the caches for the 4096-wide model (best form of the register-staged or persistent kernels -> this one):
-//   INT8  64 x 12288 x 4096 17.1 -> 14.2, 3 x 4096 x 4096 10.6 -> 6.6, 128 x 16384 x 4096 30 -> 21.6,
-//         2000 x 1024 x 4096 18.1 -> 14.9, 602 x 4096 x 4096 25 -> 18.7, 128 x 768 x 3072 5.4 -> 4.8
-//   BF16  651 x 768 x 3072 53 -> 13.1, 3 x 4096 x 16384 177 -> 36, 602 x 4096 x 16384 185 -> 143
+//   INT8  64 x 12288 x 4096 17.1 -> 14.4, 3 x 4096 x 4096 10.6 -> 5.7, 128 x 16384 x 4096 30 -> 21.6,
+//         2000 x 1024 x 4096 18.1 -> 14.3, 602 x 4096 x 4096 25 -> 20.2, 128 x 768 x 3072 5.4 -> 4.9
+//   BF16  651 x 768 x 3072 53 -> 9.6, 3 x 4096 x 16384 177 -> 36, 602 x 4096 x 16384 185 -> 130
 inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const int64_t slabs = kb / (2 * BK), t32 = tiles(32, 32), t12864 = tiles(128, 64);
     if (M <= 32 && t32 > 256 && tiles(32, 64) <= 256) return slabs >= 64 ? RING_32x64_K4 : RING_32x64_K2;
-    if (t32 <= 256) return slabs >= 64 ? RING_32x32_K4 : RING_32x32_K8;       // K8 has a short ring: better while K is short
+    if (t32 <= 256) return slabs >= 32 ? RING_32x32_K4 : RING_32x32_K8;       // K8 has a short ring: better while K is short
     if (tiles(64, 32) <= 256) return RING_64x32_K4;
+    if (tiles(32, 64) <= 256) return RING_32x64_K4;                           // (651 x 768: 252 of these, 264 of the others)
     if (tiles(64, 64) <= 256) return RING_64x64_K2;
     if (t12864 <= 256 && slabs >= 32) return RING_128x64_K2;
     if (tiles(64, 64) <= 512) return RING_64x64;

@@ -17,7 +17,8 @@ SHAPES = [
     (31, 12284, 2176),       # 32x64, two groups, 17 slabs
     (32, 12300, 8192),       # 32x64, four groups
     (65, 2308, 640),         # 64x32
-    (129, 3076, 768),        # 64x64, two groups
+    (651, 764, 3072),        # 32x64, four groups, many row tiles
+    (129, 4612, 768),        # 64x64, two groups
     (100, 12292, 4224),      # 128x64, two groups, 33 slabs
     (641, 2052, 384),        # 64x64
     (300, 10244, 4096),      # 128x128
