@@ -301,7 +301,7 @@ inline hero_status launch_grid(GemmArgs g, int BM, int BN, int threads, K kernel
 
 // ---- the ring kernel's forms (gemm_ring.h): BM x BN tile, number of K groups ---------------------------------
 enum RingForm { RING_NONE = -1, RING_32x32_K8, RING_32x32_K4, RING_32x64_K2, RING_32x64_K4, RING_64x32_K4, RING_64x64_K2,
-                RING_64x64, RING_128x64_K2, RING_128x64, RING_128x128 };
+                RING_64x64, RING_128x64_K2, RING_128x64, RING_128x128, RING_128x256 /* K split only */ };
 
 // Whole 128-byte slabs and 32-bit per-lane offsets.  kb: bytes of K.
 inline bool ring_ok(int64_t kb, int64_t lda_bytes, int64_t ldb_bytes) {
@@ -331,7 +331,7 @@ inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
     return RING_NONE;
 }
 template <int ADT, int EPI, int CDT, int RDT> hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st);
-// g.ksplit ranges of g.kslabs slabs, raw accumulators into planes of g.C; the two forms of the K split
+// g.ksplit ranges of g.kslabs slabs, raw accumulators into planes of g.C; the forms of the K split
 template <int ADT> hero_status launch_ring_part(GemmArgs g, RingForm f, hipStream_t st);
 
 }  // namespace hero_gemm

@@ -206,15 +206,18 @@ hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st) {
 
 template <int ADT>
 hero_status launch_ring_part(GemmArgs g, RingForm f, hipStream_t st) {
-    const int BM = f == RING_64x64_K2 ? 64 : 128;
-    g.ntm = (g.M + BM - 1) / BM;
-    g.ntn = (g.N + 63) / 64;
-    g.per_xcd = (int)(((int64_t)g.ntm * g.ntn + NUM_XCD - 1) / NUM_XCD);
-    const dim3 grid((unsigned)(g.per_xcd * NUM_XCD), (unsigned)g.ksplit);
-    if (f == RING_64x64_K2) hipLaunchKernelGGL((int8_gemm_ring_kernel<64, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>), grid, dim3(512), 0, st, g);
-    else if (f == RING_128x64_K2) hipLaunchKernelGGL((int8_gemm_ring_kernel<128, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>), grid, dim3(512), 0, st, g);
-    else return HERO_ERR_UNSUPPORTED;
-    return hero_launch_status();
+    auto go = [&](int BM, int BN, int threads, auto kernel) -> hero_status {
+        g.ntm = (g.M + BM - 1) / BM;
+        g.ntn = (g.N + BN - 1) / BN;
+        g.per_xcd = (int)(((int64_t)g.ntm * g.ntn + NUM_XCD - 1) / NUM_XCD);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(g.per_xcd * NUM_XCD), (unsigned)g.ksplit), dim3(threads), 0, st, g);
+        return hero_launch_status();
+    };
+    if (f == RING_64x64_K2) return go(64, 64, 512, int8_gemm_ring_kernel<64, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>);
+    if (f == RING_128x64_K2) return go(128, 64, 512, int8_gemm_ring_kernel<128, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>);
+    if constexpr (ADT == HERO_BF16 || ADT == HERO_F16)
+        if (f == RING_128x256) return go(128, 256, 256, int8_gemm_ring_kernel<128, 256, 2, 2, 1, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>);
+    return HERO_ERR_UNSUPPORTED;
 }
 
 }  // namespace hero_gemm

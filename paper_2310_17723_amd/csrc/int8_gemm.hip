@@ -914,6 +914,21 @@ inline SplitK splitk_plan(int64_t M, int64_t N, int64_t K) {            // K in 
     return p;
 }
 
+// A middling 16-bit product with a very long K (FC2 of a prompt chunk, 256 slabs or more): one round of 128 x 128 tiles leaves
+// a part of the CUs without work, and their 32 x 64 wave tiles are bound by LDS reads.  Tiles of 128 x 256 (64 x 128 per wave:
+// 0.56 of the LDS bytes per multiply-add) times as many K ranges as fill the 256 CUs, at least three.  Measured, BF16,
+// N = 4096, K = 16384, best form in one pass -> split: M = 150 67 -> 52 us, 300 83 -> 69, 512 94 -> 87, 602 131 -> 108; with
+// half the slabs (INT8 codes) the planes cost what the split gives (300 rows 44.7 -> 43.3, 400 47 -> 51).
+inline SplitK mid_split_plan(int64_t M, int64_t N, int64_t kb) {
+    SplitK p = {1, 0, 0};
+    const int64_t tiles = ((M + 127) / 128) * ((N + 255) / 256);
+    if (M <= 128 || kb % (2 * BK) != 0 || kb < 256 * 2 * BK || tiles <= 0 || tiles * 3 > 256) return p;
+    p.ksplit = (int)(256 / tiles < 8 ? 256 / tiles : 8);
+    p.ldp = (N + 3) & ~(int64_t)3;
+    p.bytes = (size_t)p.ksplit * M * p.ldp * 4;
+    return p;
+}
+
 // Pass 2 of split-K: one thread per 4 consecutive columns of a row.
 // Integer sums are exact in any order; fp32 partial sums (E4M3 and 16-bit operands) are added in the fixed order of the
 // ranges, so a result does not vary from run to run.
@@ -982,10 +997,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const in
 template <int EPI, int CDT, int RDT, int ADT>
 bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, hero_status* status) {
     if (!ws || !ring_ok(g.K, g.lda, g.ldb)) return false;
-    const SplitK p = splitk_plan(g.M, g.N, g.K);
+    constexpr bool HP = ADT == HERO_BF16 || ADT == HERO_F16;
+    const bool mid = HP && g.M > 128;
+    const SplitK p = mid ? mid_split_plan(g.M, g.N, g.K) : splitk_plan(g.M, g.N, g.K);
     if (p.ksplit <= 1 || ws_bytes < p.bytes) return false;
-    const RingForm f = g.M <= 64 ? RING_64x64_K2 : RING_128x64_K2;      // both: 64 columns, one workgroup per CU
-    const int slabs = g.K / (2 * BK), ntn = (g.N + 63) / 64, want = min(256 / ntn, p.ksplit);
+    const RingForm f = mid ? RING_128x256 : (g.M <= 64 ? RING_64x64_K2 : RING_128x64_K2);   // skinny: 64 columns, one workgroup per CU
+    const int slabs = g.K / (2 * BK), ntn = (g.N + 63) / 64, want = mid ? p.ksplit : min(256 / ntn, p.ksplit);
     if (want < 2) return false;
     GemmArgs g1 = g;                                                   // pass 1: raw partial planes in the scratch
     g1.a_row_scale = nullptr; g1.b_col_scale = nullptr; g1.bias = nullptr; g1.residual = nullptr; g1.out_col_scale = nullptr;
@@ -1168,6 +1185,11 @@ hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
                            : launch_hp_type<HERO_F16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile);
 }
 }  // namespace
+
+size_t hero_hp_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    const size_t a = splitk_plan(M, N, 2 * K).bytes, b = mid_split_plan(M, N, 2 * K).bytes;
+    return a > b ? a : b;
+}
 
 // hero_hp_gemm with scratch for the K split (hero_layer_fwd).  Not part of the C ABI.
 hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t ldb,

@@ -40,10 +40,11 @@ Workspace plan(const hero_layer_desc* d, int64_t T) {
     w.mid_hp = take(!(d->mode_mask & HERO_M_FC1) ? (size_t)T * d->d * 2 : 0);          // 16-bit X_mid for a 16-bit FC1
     w.a = take((size_t)T * d->f * e_a);
     w.x2 = take(pre ? 0 : (size_t)T * d->d * e_a);
-    // split-K scratch of the skinny (decode) GEMMs: the largest of the four shapes (K in bytes of its operands),
-    // shared (stream order)
+    // split-K scratch of the skinny (decode) and long-K GEMMs: the largest of the four shapes, shared (stream order)
     size_t g = 0;
-    auto split = [&](int64_t N, int64_t K, uint32_t bit) { g = std::max(g, hero_int8_gemm_workspace_bytes(T, N, (d->mode_mask & bit) ? K : 2 * K)); };
+    auto split = [&](int64_t N, int64_t K, uint32_t bit) {
+        g = std::max(g, (d->mode_mask & bit) ? hero_int8_gemm_workspace_bytes(T, N, K) : hero_hp_gemm_workspace_bytes(T, N, K));
+    };
     split(3 * (int64_t)d->d, d->d, HERO_M_QKV);
     split(d->d, d->d, HERO_M_ATTN_OUT);
     split(d->f, d->d, HERO_M_FC1);

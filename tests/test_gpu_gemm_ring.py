@@ -96,13 +96,13 @@ def test_fp8_gemm_forms(M, N, K):
     assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * 2.0 ** -8).all())
 
 
-@pytest.mark.parametrize("B", [1, 5, 64, 100])
-@pytest.mark.parametrize("fmt", ["fp8", "bf16"])
-def test_layer_split_k(B, fmt):
-    """One token per sequence through a layer whose FC2 is long enough for the K split (E4M3 codes, or 16 bits), against the
-    same layer run one sequence block at a time through a scratch that is dirty: the same bits."""
+@pytest.mark.parametrize("B,fmt,f", [(b, t, 8192) for b in (1, 5, 64, 100) for t in ("fp8", "bf16")] +
+                         [(129, "bf16", 16384 + 64), (300, "bf16", 16384), (700, "bf16", 16384)])
+def test_layer_split_k(B, fmt, f):
+    """One token per sequence through a layer whose FC2 is long enough for the K split (E4M3 codes, or 16 bits: skinny, and
+    middling with 128 x 256 tiles), through a scratch that is dirty, against the same again and against single rows."""
     hero = pkg.load()
-    d, H, Dh, f = 1024, 8, 128, 8192
+    d, H, Dh = 1024, 8, 128
     mode = HB.MODE_M3 | HB.M_FP8 if fmt == "fp8" else HB.MODE_M2
     g = torch.Generator(device="cuda").manual_seed(B)
     p = {k: torch.randn(s, device="cuda", generator=g) * 0.03 for k, s in
