@@ -44,3 +44,33 @@ def test_split_against_block(Dh, fp8, mask, Sq, Skv):
         assert float((x - y).abs().max()) <= 2.0 ** -3 * float(x.abs().max())
     else:
         assert int((a.int() - b.int()).abs().max()) <= 1
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("mask", [HB.MASK_NONE, HB.MASK_PADDING, HB.MASK_CAUSAL])
+@pytest.mark.parametrize("Sq,Skv", [(1, 1), (20, 77), (33, 33), (129, 129), (97, 261), (513, 513)])
+def test_16_bit_split_against_block(Dh, dt, mask, Sq, Skv):
+    """The 16-bit attention likewise, and both against 64 bits: the probabilities are rounded to 16 bits before PV (relative
+    2^-9 for bf16, 2^-12 for fp16), the output once more."""
+    lens = [Skv, Skv - 1 if Sq < Skv or mask == HB.MASK_PADDING else Skv, max(1, Skv // 2) if Sq == Skv and mask != HB.MASK_CAUSAL else Skv]
+    hero, B, H = pkg.load(), 3, 3
+    g = torch.Generator(device="cuda").manual_seed(Sq + Skv)
+    q, k, v = (torch.randn((B, s, H, Dh), device="cuda", generator=g).to(dt) for s in (Sq, Skv, Skv))
+    kv = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    scale = 2.0 / Dh ** 0.5
+    call = lambda r: hero.hero_hp_attn(*(t.repeat(r, 1, 1, 1) for t in (q, k, v)), scale, mask=mask, kv_len=kv.repeat(r))
+    outs = [call(1)]
+    if Sq > 32:
+        outs.append(call(256 // (B * H * ((Sq + 127) // 128)) + 1)[:B * Sq])
+    a = torch.einsum("bihd,bjhd->bhij", q.double().cpu(), k.double().cpu()) * scale
+    i, j, n = torch.arange(Sq)[:, None], torch.arange(Skv)[None, :], kv.cpu()[:, None, None]
+    vis = (j < n) & ((j <= i + n - Sq) if mask == HB.MASK_CAUSAL else torch.ones_like(n, dtype=torch.bool))
+    if mask == HB.MASK_PADDING and Sq == Skv:
+        vis = vis & (i < n)
+    p = torch.softmax(a.masked_fill(~vis[:, None], -1e300), 3) * vis[:, None]
+    ref = torch.einsum("bhij,bjhd->bihd", p, v.double().cpu()).reshape(B * Sq, H * Dh)
+    mag = torch.einsum("bhij,bjhd->bihd", p, v.double().cpu().abs()).reshape(B * Sq, H * Dh)
+    eps = 2.0 ** -8 if dt == torch.bfloat16 else 2.0 ** -11
+    for o in outs:
+        assert bool(((o.double().cpu() - ref).abs() <= 2 * eps * mag + eps * ref.abs() + 1e-6).all())
