@@ -15,7 +15,7 @@ extern "C" {
 #endif
 
 /* GeMM^quant (Sec. 2.1, 2.2.2, 2.2.3) with the kernel forced.  tile: 0 = 128x128 tile staged through registers,
- * 1 = 256x256 direct-to-LDS, one tile per workgroup, 2 = 64x64 (small and skinny problems), 7 = 256x256
+ * 1 = 256x256 direct-to-LDS, one tile per workgroup, 2 = small and middling problems, 7 = 256x256
  * persistent, 8 = 128x128 persistent (two workgroups per CU), 9 = 256x128 persistent with the epilogue of a tile
  * inside the main loop of the next one (K >= 1024, no fused residual).  Never splits K. */
 hero_status hero_int8_gemm_tile(const int8_t* A, int64_t lda, const float* a_row_scale,
@@ -25,7 +25,7 @@ hero_status hero_int8_gemm_tile(const int8_t* A, int64_t lda, const float* a_row
                                 void* C, hero_dtype c_dt, int64_t ldc,
                                 int64_t M, int64_t N, int64_t K, void* stream, int tile);
 
-/* The FP8 variant (Sec. 2.1).  tile: 0 = register-staged kernels, 7 / 8 = persistent 256x256 / 128x128. */
+/* The FP8 variant (Sec. 2.1).  tile: 0 = 128x128 staged through registers, 7 / 8 = persistent 256x256 / 128x128. */
 hero_status hero_fp8_gemm_tile(const void* A, int64_t lda, const float* a_row_scale,
                                const void* Bt, int64_t ldb, const float* b_col_scale,
                                const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,

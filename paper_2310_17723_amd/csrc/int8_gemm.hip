@@ -9,7 +9,7 @@
 // lane l holds, for ONE output row m = l % 32, the columns n = 8g + 4(l/32) + t (register
 // 4g + t): the per-row scale is one register and a lane owns 4 consecutive columns.
 //
-// Three main loops share one epilogue:
+// Four main loops share one epilogue (gemm_common.h):
 //   * int8_gemm_persistent_kernel (large problems): 256x256 block tile, 8 waves of 128x64,
 //     slabs of 64 bytes of K copied global -> LDS directly (global_load_lds_dwordx4) through
 //     a ring of 4 stages; one workgroup per CU walks its tiles and the ring runs through the
@@ -17,7 +17,8 @@
 //     serves the sizes at which the large tile would leave CUs idle; per tile area it needs
 //     twice the L2 -> LDS traffic and is 10-15 % slower once every CU has work.
 //   * int8_gemm_dma_kernel: the same tile, one tile per workgroup (short K, huge strides).
-//   * int8_gemm_kernel (small or skinny problems): 128x128 / 64x64 tile staged through registers.
+//   * int8_gemm_ring_kernel (gemm_ring.h; small and middling problems): 32x32 .. 128x128 tiles, 128-byte slabs, K groups.
+//   * int8_gemm_kernel (K that is no whole slab): 128x128 / 64x64 tile staged through registers.
 // The epilogue works in registers: a lane-half exchange (v_permlane32_swap) gives every lane a
 // contiguous piece of one output row, written with 128-bit stores.
 #include "gemm_common.h"
@@ -1025,12 +1026,11 @@ bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st,
 // two workgroups per CU, below that (with 96-128 tiles of 256x256 half of the CUs would idle: 10-30 % faster there)
 // and where the last round of 256x256 tiles would be so empty that the small tile fills the chip better
 // (small_tile_fills_better below; per full round the small tile is 10-15 % slower, it needs twice the L2 -> LDS
-// traffic); 64x64 register-staged tiles, or smaller ones, while
-// fewer than 192 tiles of 128x128 exist (small problems are latency-bound: more, shorter workgroups).  The
+// traffic); the ring kernel where ring_form (gemm_common.h) has a form: everything smaller, and a short K.  The
 // persistent kernels need K >= 256, K % 128 == 0 and 32-bit per-lane offsets; otherwise the one-tile-per-workgroup
-// 256x256 kernel or the register-staged 128x128 one take their place.
+// 256x256 kernel or the register-staged ones take their place.
 // The test hook hero_int8_gemm_tile forces a form: 0 = 128x128 register-staged, 1 = 256x256 one tile per workgroup,
-// 2 = 64x64 (and its skinny relatives), 7 = 256x256 persistent, 8 = 128x128 persistent.
+// 2 = the ring kernel's forms, 7 = 256x256 persistent, 8 = 128x128 persistent.
 // the prefetch hint's share per tile: at most one request per lane
 inline void share_prefetch(GemmArgs& g, int64_t tiles, int lanes) {
     if (g.pf_lines <= 0) return;
@@ -1076,7 +1076,7 @@ hero_status launch_ovl(const GemmArgs& g, hipStream_t st) {
 }
 
 // tile: -1 = chosen from the problem size (the product path); 0 = 128x128 register-staged, 1 = 256x256 one tile per
-// workgroup, 2 = 64x64, 7 = 256x256 persistent, 8 = 128x128 persistent, 9 = 256x128 persistent with the overlapped
+// workgroup, 2 = the ring kernel, 7 = 256x256 persistent, 8 = 128x128 persistent, 9 = 256x128 persistent with the overlapped
 // epilogue (forced by the test entry point hero_int8_gemm_tile only; a forced kernel that cannot run the shape falls
 // back to its one-tile-per-workgroup relative).
 // 256 x 256 tiles, one workgroup per CU, or 128 x 128 tiles, two per CU?  Per full round the small tile is 10-15 % slower
