@@ -59,6 +59,7 @@ SYMBOLS = {
     "hero_int8_gemm_tile": (i32, [vp, i64, vp, vp, i64, vp, vp, vp, i32, i64, i32, vp, vp, i32, i64, i64, i64, i64, vp, i32]),
     "hero_fp8_gemm_tile": (i32, [vp, i64, vp, vp, i64, vp, vp, vp, i32, i64, i32, vp, vp, i32, i64, i64, i64, i64, vp, i32]),
     "hero_hp_gemm_tile": (i32, [vp, i64, vp, i64, vp, vp, i64, i32, vp, i64, i64, i64, i64, i32, vp, i32]),
+    "hero_gemm_kernel": (i32, [i32, i32, i64, i64, i64, i64, i64]),
     "hero_hp_gemm": (i32, [vp, i64, vp, i64, vp, vp, i64, i32, vp, i64, i64, i64, i64, i32, vp]),
     "hero_hp_attn": (i32, [vp, C.POINTER(i64), vp, C.POINTER(i64), vp, C.POINTER(i64), i64, i64, i64, i64, i64,
                            f32, i32, vp, vp, i64, i32, vp]),
@@ -223,6 +224,10 @@ class Hero:
         st = self.lib.hero_fp8_gemm(*args) if tile is None else self.lib.hero_fp8_gemm_tile(*args, int(tile))
         self._check(st)
         return C_out
+
+    def hero_gemm_kernel(self, dtype, M, N, K, lda=None, ldb=None, gelu=False) -> int:
+        """The kernel a product of this size runs (include/hero_debug.h); launches nothing."""
+        return int(self.lib.hero_gemm_kernel(_DT[dtype], int(gelu), M, N, K, lda or K, ldb or K))
 
     def hero_int8_gemm_workspace_bytes(self, M, N, K) -> int:
         return int(self.lib.hero_int8_gemm_workspace_bytes(M, N, K))

@@ -35,7 +35,7 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def build_lib(verbose: bool = True, jobs: int = 8) -> str:
+def build_lib(verbose: bool = True, jobs: int = 16) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)

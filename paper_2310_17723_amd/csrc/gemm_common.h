@@ -303,10 +303,8 @@ inline hero_status launch_grid(GemmArgs g, int BM, int BN, int threads, K kernel
 enum RingForm { RING_NONE = -1, RING_32x32_K8, RING_32x32_K4, RING_32x64_K2, RING_32x64_K4, RING_64x32_K4, RING_64x64_K2,
                 RING_64x64, RING_128x64_K2, RING_128x64, RING_128x128, RING_128x256 /* K split only */ };
 
-// Whole 128-byte slabs and 32-bit per-lane offsets.  kb: bytes of K.
-inline bool ring_ok(int64_t kb, int64_t lda_bytes, int64_t ldb_bytes) {
-    return kb % (2 * BK) == 0 && lda_bytes < (1 << 24) && ldb_bytes < (1 << 24);
-}
+// 32-bit per-lane offsets (256 rows of lda / ldb bytes)
+inline bool ring_ok(int64_t lda_bytes, int64_t ldb_bytes) { return lda_bytes < (1 << 24) && ldb_bytes < (1 << 24); }
 // Which form, or RING_NONE: a problem for the persistent kernels.  What decides is whether every one of the 256 CUs streams
 // its share of the weights: the largest tile that still gives every CU one workgroup, and while there are fewer
 // tiles than CUs, K groups inside the workgroup.  (Two workgroups per CU where the form's LDS allows it: 64 x 64 without K
@@ -318,7 +316,7 @@ inline bool ring_ok(int64_t kb, int64_t lda_bytes, int64_t ldb_bytes) {
 //   BF16  651 x 768 x 3072 53 -> 9.6, 3 x 4096 x 16384 177 -> 36, 602 x 4096 x 16384 185 -> 130
 inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    const int64_t slabs = kb / (2 * BK), t32 = tiles(32, 32), t12864 = tiles(128, 64);
+    const int64_t slabs = (kb + 2 * BK - 1) / (2 * BK), t32 = tiles(32, 32), t12864 = tiles(128, 64);
     if (M <= 32 && t32 > 256 && tiles(32, 64) <= 256) return slabs >= 64 ? RING_32x64_K4 : RING_32x64_K2;
     if (t32 <= 256) return slabs >= 32 ? RING_32x32_K4 : RING_32x32_K8;       // K8 has a short ring: better while K is short
     if (tiles(64, 32) <= 256) return RING_64x32_K4;
@@ -330,8 +328,16 @@ inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
     if (t12864 <= 512 || (slabs <= 8 && t12864 <= 1024)) return RING_128x64;  // short K: the persistent ring never gets going
     return RING_NONE;
 }
-template <int ADT, int EPI, int CDT, int RDT> hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st);
+template <int ADT, int EPI, int CDT, int RDT, bool HALF> hero_status launch_ring_slabs(const GemmArgs& g, RingForm f, hipStream_t st);
+template <int ADT, int EPI, int CDT, int RDT>
+hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st) {
+    return g.K % (2 * BK) != 0 ? launch_ring_slabs<ADT, EPI, CDT, RDT, true>(g, f, st) : launch_ring_slabs<ADT, EPI, CDT, RDT, false>(g, f, st);
+}
 // g.ksplit ranges of g.kslabs slabs, raw accumulators into planes of g.C; the forms of the K split
-template <int ADT> hero_status launch_ring_part(GemmArgs g, RingForm f, hipStream_t st);
+template <int ADT, bool HALF> hero_status launch_ring_part_slabs(GemmArgs g, RingForm f, hipStream_t st);
+template <int ADT>
+hero_status launch_ring_part(const GemmArgs& g, RingForm f, hipStream_t st) {
+    return g.K % (2 * BK) != 0 ? launch_ring_part_slabs<ADT, true>(g, f, st) : launch_ring_part_slabs<ADT, false>(g, f, st);
+}
 
 }  // namespace hero_gemm

@@ -21,7 +21,7 @@ __device__ __forceinline__ void ring_wait(int left) {                // at most 
     } else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 }
 
-template <int BM, int BN, int WM, int WN, int KG, int NS, int EPI, int CDT, int RDT, int ADT, bool PART = false>
+template <int BM, int BN, int WM, int WN, int KG, int NS, int EPI, int CDT, int RDT, int ADT, bool PART, bool HALF>
 __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmArgs g) {
     using ACC = typename AccOf<ADT>::type;
     constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
@@ -43,11 +43,17 @@ __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmA
     const int tid = KG == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
     // this group's slabs [k0, k0 + KT); every group passes the same number of barriers
-    const int kall = g.K / SK, kbeg = PART ? (int)blockIdx.y * g.kslabs : 0, kwg = PART ? min(g.kslabs, kall - kbeg) : kall;
+    const int kall = HALF ? g.K / SK + 1 : g.K / SK, kbeg = PART ? (int)blockIdx.y * g.kslabs : 0, kwg = PART ? min(g.kslabs, kall - kbeg) : kall;
     const int kper = (kwg + KG - 1) / KG, k0 = kbeg + min(kg * kper, kwg), KT = min(kper, kbeg + kwg - k0);
 
-    const int8_t* ia = g.A + (int64_t)m0 * g.lda + (int64_t)k0 * SK;
-    const int8_t* ib = g.Bt + (int64_t)n0 * g.ldb + (int64_t)k0 * SK;
+    // HALF: K is an odd number of 64-byte pieces and ends in half a slab.  The group that owns it takes it FIRST, its lanes of the
+    // upper half repeating the lower one (the memory behind a row's end is not the kernel's to read), and leaves out the matrix
+    // instructions of that half.  A kernel of its own: tests for it in the other one cost 2-5 % of a small product.  Measured with
+    // cold weights, us, register-staged tile -> here: INT8 1 x 4096 x 4160 20.5 -> 8, 64 x 4096 x 16448 with the K split 72 -> 24,
+    // E4M3 64 x 4096 x 16448 100 -> 27, BF16 1000 x 4096 x 8256 bytes 92 -> 46.
+    const int half = HALF && KT > 0 && k0 + KT == kall ? 1 : 0;
+    const int8_t* ia = g.A + (int64_t)m0 * g.lda + (int64_t)(k0 - half) * SK;        // slab kt of this group: + kt * SK
+    const int8_t* ib = g.Bt + (int64_t)n0 * g.ldb + (int64_t)(k0 - half) * SK;
     const int lrow = wave * 8 + (lane >> 3);                        // row of this lane in a load's 8 rows; the next load: + 8 * NWAVE
     const uint32_t lc = (uint32_t)(((lane & 7) ^ (lrow & 7)) * 16);
     uint32_t oa[AU], ob[BU];
@@ -80,8 +86,14 @@ __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmA
 #pragma unroll
     for (int i = 0; i < TM; ++i)
         rsr[i] = (VECS && !UNIT && g.a_row_scale) ? g.a_row_scale[min(m0 + wm * TM * 32 + i * 32 + (lane & 31), g.M - 1)] : 1.0f;
+    if (HALF && half) {
 #pragma unroll
-    for (int p = 0; p < NS; ++p) if (p < KT) issue(p, p);
+        for (int u = 0; u < BU; ++u) dma16s(ob[u] - (lc & (uint32_t)BK), ib + (int64_t)KT * SK, ring + wave * 1024 + BM * SK + u * NWAVE * 1024);
+#pragma unroll
+        for (int u = 0; u < AU; ++u) dma16s(oa[u] - (lc & (uint32_t)BK), ia + (int64_t)KT * SK, ring + wave * 1024 + u * NWAVE * 1024);
+    }
+#pragma unroll
+    for (int p = 0; p < NS; ++p) if (p >= half && p < KT) issue(p, p);
 
     const int hh = lane >> 5, ml = lane & 31;
     const int8_t* const base = smem + kg * RING;
@@ -139,7 +151,7 @@ __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmA
         __syncthreads();                                            // ... and everybody's; slab kt has been read by every wave
         if (kt + 1 < KT) read(next, 0, f0);
         if (kt + NS < KT) issue(kt + NS, stage);
-        if (kt < KT) multiply(f1);
+        if (kt < KT && kt >= half) multiply(f1);
         stage = next;
     }
     if (VECS && (int)threadIdx.x < BN) {
@@ -184,10 +196,10 @@ __global__ __launch_bounds__(WM * WN * 64 * KG) void int8_gemm_ring_kernel(GemmA
     }
 }
 
-template <int ADT, int EPI, int CDT, int RDT>
-hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st) {
+template <int ADT, int EPI, int CDT, int RDT, bool HALF>
+hero_status launch_ring_slabs(const GemmArgs& g, RingForm f, hipStream_t st) {
 #define HERO_RING(BM, BN, WM, WN, KG, NS) \
-    return launch_grid(g, BM, BN, WM * WN * KG * 64, int8_gemm_ring_kernel<BM, BN, WM, WN, KG, NS, EPI, CDT, RDT, ADT>, st)
+    return launch_grid(g, BM, BN, WM * WN * KG * 64, int8_gemm_ring_kernel<BM, BN, WM, WN, KG, NS, EPI, CDT, RDT, ADT, false, HALF>, st)
     switch (f) {
     case RING_32x32_K8: HERO_RING(32, 32, 1, 1, 8, 2);
     case RING_32x32_K4: HERO_RING(32, 32, 1, 1, 4, 4);
@@ -204,8 +216,8 @@ hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st) {
 #undef HERO_RING
 }
 
-template <int ADT>
-hero_status launch_ring_part(GemmArgs g, RingForm f, hipStream_t st) {
+template <int ADT, bool HALF>
+hero_status launch_ring_part_slabs(GemmArgs g, RingForm f, hipStream_t st) {
     auto go = [&](int BM, int BN, int threads, auto kernel) -> hero_status {
         g.ntm = (g.M + BM - 1) / BM;
         g.ntn = (g.N + BN - 1) / BN;
@@ -213,11 +225,29 @@ hero_status launch_ring_part(GemmArgs g, RingForm f, hipStream_t st) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(g.per_xcd * NUM_XCD), (unsigned)g.ksplit), dim3(threads), 0, st, g);
         return hero_launch_status();
     };
-    if (f == RING_64x64_K2) return go(64, 64, 512, int8_gemm_ring_kernel<64, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>);
-    if (f == RING_128x64_K2) return go(128, 64, 512, int8_gemm_ring_kernel<128, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>);
+    if (f == RING_64x64_K2) return go(64, 64, 512, int8_gemm_ring_kernel<64, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true, HALF>);
+    if (f == RING_128x64_K2) return go(128, 64, 512, int8_gemm_ring_kernel<128, 64, 2, 2, 2, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true, HALF>);
     if constexpr (ADT == HERO_BF16 || ADT == HERO_F16)
-        if (f == RING_128x256) return go(128, 256, 256, int8_gemm_ring_kernel<128, 256, 2, 2, 1, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>);
+        if (f == RING_128x256) return go(128, 256, 256, int8_gemm_ring_kernel<128, 256, 2, 2, 1, 3, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true, HALF>);
     return HERO_ERR_UNSUPPORTED;
 }
+
+// what gemm_ring_*.hip (K of whole slabs) and gemm_ring_*_half.hip instantiate for their operand type
+#define HERO_RING_8BIT(ADT, CDT8, HALF) \
+    template hero_status launch_ring_part_slabs<ADT, HALF>(GemmArgs, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_REQUANT, CDT8, -1, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_GELU_REQUANT, CDT8, -1, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_DEQUANT, HERO_BF16, -1, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_DEQUANT, HERO_F16, -1, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_DEQUANT, HERO_F16, HERO_F16, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_DEQUANT_GELU, HERO_BF16, -1, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<ADT, HERO_EPI_DEQUANT_GELU, HERO_F16, -1, HALF>(const GemmArgs&, RingForm, hipStream_t);
+#define HERO_RING_16BIT(DT, HALF) \
+    template hero_status launch_ring_part_slabs<DT, HALF>(GemmArgs, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<DT, HERO_EPI_DEQUANT, DT, -1, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<DT, HERO_EPI_DEQUANT, DT, DT, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<DT, HERO_EPI_DEQUANT_GELU, DT, -1, HALF>(const GemmArgs&, RingForm, hipStream_t); \
+    template hero_status launch_ring_slabs<DT, HERO_EPI_DEQUANT_GELU, DT, DT, HALF>(const GemmArgs&, RingForm, hipStream_t);
 
 }  // namespace hero_gemm

@@ -2,13 +2,5 @@
 #include "gemm_ring.h"
 
 namespace hero_gemm {
-template hero_status launch_ring_part<HERO_F8E4M3>(GemmArgs, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_REQUANT, HERO_F8E4M3, -1>(const GemmArgs&, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_GELU_REQUANT, HERO_F8E4M3, -1>(const GemmArgs&, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_BF16, -1>(const GemmArgs&, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_F16, -1>(const GemmArgs&, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16>(const GemmArgs&, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_F16, HERO_F16>(const GemmArgs&, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_DEQUANT_GELU, HERO_BF16, -1>(const GemmArgs&, RingForm, hipStream_t);
-template hero_status launch_ring<HERO_F8E4M3, HERO_EPI_DEQUANT_GELU, HERO_F16, -1>(const GemmArgs&, RingForm, hipStream_t);
+HERO_RING_8BIT(HERO_F8E4M3, HERO_F8E4M3, false)
 }  // namespace hero_gemm

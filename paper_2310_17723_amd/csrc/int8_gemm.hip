@@ -18,7 +18,8 @@
 //     twice the L2 -> LDS traffic and is 10-15 % slower once every CU has work.
 //   * int8_gemm_dma_kernel: the same tile, one tile per workgroup (short K, huge strides).
 //   * int8_gemm_ring_kernel (gemm_ring.h; small and middling problems): 32x32 .. 128x128 tiles, 128-byte slabs, K groups.
-//   * int8_gemm_kernel (K that is no whole slab): 128x128 / 64x64 tile staged through registers.
+//   * int8_gemm_kernel (rows too far apart for 32-bit offsets; a short K that ends in half a slab, over many rows): 128x128 /
+//     64x64 tile staged through registers.
 // The epilogue works in registers: a lane-half exchange (v_permlane32_swap) gives every lane a
 // contiguous piece of one output row, written with 128-bit stores.
 #include "gemm_common.h"
@@ -553,7 +554,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
 // load stream that is latency-bound), so the two kernels end within 2 % of each other (99 / 101 us with
 // GELU^quant) when both are timed alone with operands that stay in the memory-side cache.  Inside a layer the
 // weights come from HBM, and there the deeper ring decides: this kernel is the tile choice's pick for a GELU epilogue
-// with K < 2048 (the numbers are beside the rule in launch_epi); the test entry point reaches it as tile code 9.
+// with K < 2048 (the numbers are beside the rule in choose()); the test entry point reaches it as tile code 9.
 // =====================================================================================
 // wait for vmcnt <= N and for every LDS access of this wave, then the workgroup barrier.  Inline assembly: the
 // kernel below has global stores inside its main loop, and a __syncthreads() there would make the compiler
@@ -923,7 +924,7 @@ inline SplitK splitk_plan(int64_t M, int64_t N, int64_t K) {            // K in 
 inline SplitK mid_split_plan(int64_t M, int64_t N, int64_t kb) {
     SplitK p = {1, 0, 0};
     const int64_t tiles = ((M + 127) / 128) * ((N + 255) / 256);
-    if (M <= 128 || kb % (2 * BK) != 0 || kb < 256 * 2 * BK || tiles <= 0 || tiles * 3 > 256) return p;
+    if (M <= 128 || kb < 256 * 2 * BK || tiles <= 0 || tiles * 3 > 256) return p;
     p.ksplit = (int)(256 / tiles < 8 ? 256 / tiles : 8);
     p.ldp = (N + 3) & ~(int64_t)3;
     p.bytes = (size_t)p.ksplit * M * p.ldp * 4;
@@ -997,13 +998,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const in
 // Runs the split where it is one (true: *status is the outcome).
 template <int EPI, int CDT, int RDT, int ADT>
 bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, hero_status* status) {
-    if (!ws || !ring_ok(g.K, g.lda, g.ldb)) return false;
+    if (!ws || !ring_ok(g.lda, g.ldb)) return false;
     constexpr bool HP = ADT == HERO_BF16 || ADT == HERO_F16;
     const bool mid = HP && g.M > 128;
     const SplitK p = mid ? mid_split_plan(g.M, g.N, g.K) : splitk_plan(g.M, g.N, g.K);
     if (p.ksplit <= 1 || ws_bytes < p.bytes) return false;
     const RingForm f = mid ? RING_128x256 : (g.M <= 64 ? RING_64x64_K2 : RING_128x64_K2);   // skinny: 64 columns, one workgroup per CU
-    const int slabs = g.K / (2 * BK), ntn = (g.N + 63) / 64, want = mid ? p.ksplit : min(256 / ntn, p.ksplit);
+    const int slabs = (g.K + 2 * BK - 1) / (2 * BK), ntn = (g.N + 63) / 64, want = mid ? p.ksplit : min(256 / ntn, p.ksplit);
     if (want < 2) return false;
     GemmArgs g1 = g;                                                   // pass 1: raw partial planes in the scratch
     g1.a_row_scale = nullptr; g1.b_col_scale = nullptr; g1.bias = nullptr; g1.residual = nullptr; g1.out_col_scale = nullptr;
@@ -1021,16 +1022,12 @@ bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st,
     return true;
 }
 
-// Tile choice (all measured on MI355X): the persistent 256x256 direct-to-LDS kernel, one workgroup per CU, once
-// the grid has enough tiles (160) to keep most of the 256 CUs busy; the persistent 128x128 form of the same kernel,
+// Tile choice (all measured on MI355X; choose() below): the persistent 256x256 direct-to-LDS kernel, one workgroup per CU,
+// once the grid has enough tiles (160) to keep most of the 256 CUs busy; the persistent 128x128 form of the same kernel,
 // two workgroups per CU, below that (with 96-128 tiles of 256x256 half of the CUs would idle: 10-30 % faster there)
 // and where the last round of 256x256 tiles would be so empty that the small tile fills the chip better
 // (small_tile_fills_better below; per full round the small tile is 10-15 % slower, it needs twice the L2 -> LDS
-// traffic); the ring kernel where ring_form (gemm_common.h) has a form: everything smaller, and a short K.  The
-// persistent kernels need K >= 256, K % 128 == 0 and 32-bit per-lane offsets; otherwise the one-tile-per-workgroup
-// 256x256 kernel or the register-staged ones take their place.
-// The test hook hero_int8_gemm_tile forces a form: 0 = 128x128 register-staged, 1 = 256x256 one tile per workgroup,
-// 2 = the ring kernel's forms, 7 = 256x256 persistent, 8 = 128x128 persistent.
+// traffic); the ring kernel where ring_form (gemm_common.h) has a form: everything smaller, and a short K.
 // the prefetch hint's share per tile: at most one request per lane
 inline void share_prefetch(GemmArgs& g, int64_t tiles, int lanes) {
     if (g.pf_lines <= 0) return;
@@ -1047,7 +1044,7 @@ inline void set_prefetch(GemmArgs& g, const void* prefetch, size_t prefetch_byte
     }
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT>
+template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT, int ADT>
 hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) {
     GemmArgs gp = g;
     gp.ntm = (g.M + BM - 1) / BM; gp.ntn = (g.N + BN - 1) / BN;
@@ -1057,7 +1054,7 @@ hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) 
     share_prefetch(gp, tiles, WM * WN * 64);
     const int cap = 32 * wg_per_cu;                                   // 32 CUs per XCD
     const int nslot = gp.per_xcd < cap ? gp.per_xcd : cap;
-    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, EPI, CDT, RDT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
+    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
     return hero_launch_status();
 }
 
@@ -1075,10 +1072,6 @@ hero_status launch_ovl(const GemmArgs& g, hipStream_t st) {
     return hero_launch_status();
 }
 
-// tile: -1 = chosen from the problem size (the product path); 0 = 128x128 register-staged, 1 = 256x256 one tile per
-// workgroup, 2 = the ring kernel, 7 = 256x256 persistent, 8 = 128x128 persistent, 9 = 256x128 persistent with the overlapped
-// epilogue (forced by the test entry point hero_int8_gemm_tile only; a forced kernel that cannot run the shape falls
-// back to its one-tile-per-workgroup relative).
 // 256 x 256 tiles, one workgroup per CU, or 128 x 128 tiles, two per CU?  Per full round the small tile is 10-15 % slower
 // (twice the L2 -> LDS traffic), but the large one wastes what its last round leaves empty: 384 tiles on 256 CUs are
 // one and a half rounds (8192 x 3072 x 1024, 16-bit output: 47.3 us against 42.0 with the small tile), 512 tiles are
@@ -1089,81 +1082,85 @@ inline bool small_tile_fills_better(int64_t t256, int64_t t128) {
     return e128 > e256;
 }
 
-template <int EPI, int CDT, int RDT>
-hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
-    int cfg = tile;
-    hero_status split;
-    if (cfg < 0 && launch_splitk<EPI, CDT, RDT, HERO_I8>(g, ws, ws_bytes, st, &split)) return split;
-    const bool ring = ring_ok(g.K, g.lda, g.ldb);
-    const RingForm form = ring ? ring_form(g.M, g.N, g.K) : RING_NONE;
-    // persistent kernels: K long enough that the slab ring never runs more than one tile ahead, whole pairs of
-    // slabs, 32-bit per-lane offsets (256 rows of lda / ldb bytes)
-    const bool pers_ok = g.K >= 4 * BK && g.K % (2 * BK) == 0 && g.lda < (1 << 24) && g.ldb < (1 << 24);
+// What runs a product.  The codes of the kernels are those of the test hooks (include/hero_debug.h).
+enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_PERS256 = 7, K_PERS128 = 8, K_OVL = 9 };
+struct Choice { Kernel kernel; RingForm form; };
+
+// kb, lda, ldb in bytes; gelu: the epilogue has a GELU; res: a fused residual.  tile: -1 chooses, otherwise the code a test hook
+// forces (a forced kernel that cannot run the shape gives way to its closest relative).
+inline Choice choose(hero_dtype adt, bool gelu, bool res, int64_t M, int64_t N, int64_t kb, int64_t lda, int64_t ldb, int tile = -1) {
+    const bool i8 = adt == HERO_I8, ring = ring_ok(lda, ldb);
+    const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    // persistent kernels: K long enough that the slab ring never runs more than one tile ahead, whole pairs of slabs, 32-bit
+    // per-lane offsets
+    const bool pers_ok = ring && kb >= 4 * BK && kb % (2 * BK) == 0 && t128 <= 0x7fffff00LL;
     // the overlapped-epilogue kernel: its epilogue is spread over the first 16 slabs of the next tile; no fused residual
-    const bool ovl_ok = pers_ok && g.K >= 16 * BK && RDT < 0;
-    if (cfg < 0) {
-        const int64_t t256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-        if (form != RING_NONE) cfg = 2;
-        else if (t256 >= 160) cfg = !pers_ok ? 1 : (small_tile_fills_better(t256, t128) ? 8 : 7);
-        else if (g.M <= 64 || t128 < 192) cfg = 2;
-        else cfg = pers_ok ? 8 : 0;
-    } else if (cfg == 9 && !ovl_ok) {
-        cfg = pers_ok ? 7 : 1;
-    } else if ((cfg == 7 || cfg == 8) && !pers_ok) {
-        cfg = cfg == 7 ? 1 : 0;
+    const bool ovl_ok = i8 && pers_ok && kb >= 16 * BK && !res;
+    const RingForm form = ring ? ring_form(M, N, kb) : RING_NONE;
+    const Choice small = {ring ? K_RING : (M <= 64 || t128 < 192 ? K_REG64 : K_REG128), form == RING_NONE ? RING_128x64 : form};
+    if (tile >= 0) {
+        if (tile == K_OVL && ovl_ok) return {K_OVL, RING_NONE};
+        if (tile == K_PERS256 || tile == K_PERS128 || tile == K_OVL) {
+            if (pers_ok && (adt == HERO_I8 || adt == HERO_F8E4M3 || t128 >= 192)) return {tile == K_PERS128 ? K_PERS128 : K_PERS256, RING_NONE};
+            if (i8) return {tile == K_PERS128 ? K_REG128 : K_DMA256, RING_NONE};
+            return small;
+        }
+        if (tile == K_RING || (tile == 0 && (adt == HERO_BF16 || adt == HERO_F16))) return small;
+        return {tile == K_DMA256 ? K_DMA256 : K_REG128, RING_NONE};
     }
-    // A GELU epilogue behind a short K goes to the overlapped-epilogue kernel: timed alone with resident operands it
-    // is 3 % behind the 256 x 256 tile (95 against 92.5 us at 16384 x 4096 x 1024), but in a layer the weights come
-    // from HBM and its six slabs of lookahead lose 4 us to that where the other loses 13 (rotating operands: 99.5
-    // against 105.2 us; the 24-layer BERT-large stack 7.95 -> 7.75 ms).  From K = 4096 on its slower main loop
-    // costs more than the hidden epilogue saves (GPT prefill, FC1 16384 x 16384 x 4096: +11 %).
-    // Forcing each of the layer's other GEMMs (QKV, attention-output, FC2) to this kernel or to the 128 x 128 tiles
-    // inside the stack made every one of them slower (7.46 -> 7.50-7.67 ms per 24 layers).
+    if (form != RING_NONE) return small;
+    if (pers_ok) {
+        if (t256 < 160 || small_tile_fills_better(t256, t128)) return {K_PERS128, RING_NONE};
+        // A GELU epilogue behind a short K goes to the overlapped-epilogue kernel: timed alone with resident operands it
+        // is 3 % behind the 256 x 256 tile (95 against 92.5 us at 16384 x 4096 x 1024), but in a layer the weights come
+        // from HBM and its six slabs of lookahead lose 4 us to that where the other loses 13 (rotating operands: 99.5
+        // against 105.2 us; the 24-layer BERT-large stack 7.95 -> 7.75 ms).  From K = 4096 on its slower main loop
+        // costs more than the hidden epilogue saves (GPT prefill, FC1 16384 x 16384 x 4096: +11 %).
+        // Forcing each of the layer's other GEMMs (QKV, attention-output, FC2) to this kernel or to the 128 x 128 tiles
+        // inside the stack made every one of them slower (7.46 -> 7.50-7.67 ms per 24 layers).
+        return {gelu && ovl_ok && kb < 2048 ? K_OVL : K_PERS256, RING_NONE};
+    }
+    // K that ends in half a slab: the one-tile-per-workgroup 256 x 256 kernel (INT8) once its grid fills the chip, else 128 x 128
+    // tiles, through the ring from 32 slabs on.  us, ring / registers: 2048 x 4096 x 4160 INT8 52.1 / 54.8, E4M3 51.0 / 55.7,
+    // x 8256 bytes of BF16 90.4 / 99.7, but 2048 x 4096 x 2112 INT8 32.6 / 31.1, 8192 x 1024 x 1056 BF16 28.5 / 26.8.
+    if (i8 && t256 >= 160) return {K_DMA256, RING_NONE};
+    if (ring && kb >= 32 * 2 * BK) return {K_RING, RING_128x128};
+    return {M <= 64 || t128 < 192 ? K_REG64 : K_REG128, RING_NONE};
+}
+
+template <int ADT, int EPI, int CDT, int RDT>
+hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
+    switch (c.kernel) {
+    case K_OVL: if constexpr (ADT == HERO_I8 && RDT < 0) return launch_ovl<EPI, CDT>(g, st); else return HERO_ERR_UNSUPPORTED;
+    case K_PERS256: return launch_persistent<256, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
+    case K_PERS128: return launch_persistent<128, 128, 2, 2, EPI, CDT, RDT, ADT>(g, 2, st);
+    case K_DMA256:
+        if constexpr (ADT == HERO_I8) return launch_grid(g, 256, 256, 512, int8_gemm_dma_kernel<256, 256, 2, 4, 4, 2, EPI, CDT, RDT>, st);
+        else return HERO_ERR_UNSUPPORTED;
+    case K_RING: return launch_ring<ADT, EPI, CDT, RDT>(g, c.form, st);
+    case K_REG64: return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, CDT, RDT, ADT>, st);
+    default: return launch_grid(g, 128, 128, 256, int8_gemm_kernel<128, 128, 2, 2, 2, 2, EPI, CDT, RDT, ADT>, st);
+    }
+}
+
+template <int ADT, int EPI, int CDT, int RDT>
+hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
+    hero_status split;
+    if (tile < 0 && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
     constexpr bool GELU_EPI = EPI == HERO_EPI_GELU_REQUANT || EPI == HERO_EPI_DEQUANT_GELU;
-    if (GELU_EPI && tile < 0 && cfg == 7 && ovl_ok && g.K < 2048) cfg = 9;
-    if constexpr (RDT < 0) { if (cfg == 9) return launch_ovl<EPI, CDT>(g, st); }
-    if (cfg == 7) return launch_persistent<256, 256, 2, 4, EPI, CDT, RDT>(g, 1, st);
-    if (cfg == 8) return launch_persistent<128, 128, 2, 2, EPI, CDT, RDT>(g, 2, st);
-    if (cfg == 1) return launch_grid(g, 256, 256, 512, int8_gemm_dma_kernel<256, 256, 2, 4, 4, 2, EPI, CDT, RDT>, st);
-    if (cfg == 2) {                             // small or skinny problems
-        if (ring) return launch_ring<HERO_I8, EPI, CDT, RDT>(g, form == RING_NONE ? RING_128x64 : form, st);
-        return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, CDT, RDT>, st);
-    }
-    return launch_grid(g, 128, 128, 256, int8_gemm_kernel<128, 128, 2, 2, 2, 2, EPI, CDT, RDT>, st);
+    const Choice c = choose((hero_dtype)ADT, GELU_EPI, RDT >= 0, g.M, g.N, g.K, g.lda, g.ldb, tile);
+    return launch_choice<ADT, EPI, CDT, RDT>(g, c, st);
 }
 
 }  // namespace
 
 // 16-bit operands (bf16 or fp16: the 16-bit side of a switched module).  Same kernels, same choice as for INT8 operands, K
-// counted in bytes.  tile (from the test entry point hero_hp_gemm_tile): 7 / 8 = the persistent 256x256 / 128x128 kernel
-// where it can run, 0 = the kernels for smaller problems, -1 chooses.
+// counted in bytes.
 namespace {
-template <int EPI, int DT, int RDT>
-hero_status launch_hp(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int cfg) {
-    hero_status split;
-    if (cfg < 0 && launch_splitk<EPI, DT, RDT, DT>(g, ws, ws_bytes, st, &split)) return split;
-    const int64_t t256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const bool ring = ring_ok(g.K, g.lda, g.ldb);
-    const RingForm f = ring ? ring_form(g.M, g.N, g.K) : RING_NONE;
-    const bool pers_ok = ring && t128 <= 0x7fffff00LL && g.K >= 4 * BK;
-    if (pers_ok && t128 >= 192 && (cfg > 0 || (cfg < 0 && f == RING_NONE))) {
-        const bool tile128 = cfg == 8 || (cfg < 0 && (t256 < 160 || small_tile_fills_better(t256, t128)));
-        GemmArgs gp = g;
-        gp.ntm = tile128 ? (g.M + 127) / 128 : (g.M + 255) / 256; gp.ntn = tile128 ? (g.N + 127) / 128 : (g.N + 255) / 256;
-        gp.per_xcd = (int)(((tile128 ? t128 : t256) + NUM_XCD - 1) / NUM_XCD);
-        const int cap = tile128 ? 64 : 32, nslot = gp.per_xcd < cap ? gp.per_xcd : cap;
-        if (tile128) hipLaunchKernelGGL((int8_gemm_persistent_kernel<128, 128, 2, 2, 4, EPI, DT, RDT, DT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(256), 0, st, gp);
-        else hipLaunchKernelGGL((int8_gemm_persistent_kernel<256, 256, 2, 4, 4, EPI, DT, RDT, DT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(512), 0, st, gp);
-        return hero_launch_status();
-    }
-    if ((g.M + 127) / 128 > 65535) return HERO_ERR_UNSUPPORTED;
-    if (ring) return launch_ring<DT, EPI, DT, RDT>(g, f == RING_NONE ? RING_128x64 : f, st);
-    return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, DT, RDT, DT>, st);
-}
 template <int DT>
-hero_status launch_hp_type(const GemmArgs& g, bool gelu, void* ws, size_t wsb, hipStream_t st, int cfg) {
-    if (gelu) return g.residual ? launch_hp<HERO_EPI_DEQUANT_GELU, DT, DT>(g, ws, wsb, st, cfg) : launch_hp<HERO_EPI_DEQUANT_GELU, DT, -1>(g, ws, wsb, st, cfg);
-    return g.residual ? launch_hp<HERO_EPI_DEQUANT, DT, DT>(g, ws, wsb, st, cfg) : launch_hp<HERO_EPI_DEQUANT, DT, -1>(g, ws, wsb, st, cfg);
+hero_status launch_hp(const GemmArgs& g, bool gelu, void* ws, size_t wsb, hipStream_t st, int tile) {
+    if (gelu) return g.residual ? launch_epi<DT, HERO_EPI_DEQUANT_GELU, DT, DT>(g, ws, wsb, st, tile) : launch_epi<DT, HERO_EPI_DEQUANT_GELU, DT, -1>(g, ws, wsb, st, tile);
+    return g.residual ? launch_epi<DT, HERO_EPI_DEQUANT, DT, DT>(g, ws, wsb, st, tile) : launch_epi<DT, HERO_EPI_DEQUANT, DT, -1>(g, ws, wsb, st, tile);
 }
 
 hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
@@ -1181,8 +1178,13 @@ hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
     g.b_col_scale = nullptr; g.bias = bias; g.residual = residual; g.ldr = ldr; g.out_col_scale = nullptr;
     g.C = C; g.ldc = ldc; g.M = (int)M; g.N = (int)N; g.K = (int)(K * 2);
     g.ksplit = 1; g.kslabs = 0;
-    return dt == HERO_BF16 ? launch_hp_type<HERO_BF16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile)
-                           : launch_hp_type<HERO_F16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile);
+    // more than 2^23 rows: the persistent kernels only (INT8 operands end there altogether)
+    if (M > 65535 * 128LL) {
+        const Kernel k = choose(dt, gelu != 0, residual != nullptr, M, N, g.K, g.lda, g.ldb, tile).kernel;
+        if (k != K_PERS256 && k != K_PERS128) return HERO_ERR_UNSUPPORTED;
+    }
+    return dt == HERO_BF16 ? launch_hp<HERO_BF16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile)
+                           : launch_hp<HERO_F16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile);
 }
 }  // namespace
 
@@ -1219,29 +1221,14 @@ extern "C" hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void*
     return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, nullptr, 0, stream, tile);
 }
 
-// The FP8 variant: the same kernels and the same choice with E4M3 operands.
-template <int EPI, int CDT, int RDT>
-hero_status launch_epi_fp8(GemmArgs g, void* ws, size_t ws_bytes, hipStream_t st, int cfg) {
-    hero_status split;
-    if (cfg < 0 && launch_splitk<EPI, CDT, RDT, HERO_F8E4M3>(g, ws, ws_bytes, st, &split)) return split;
-    const int64_t t256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const bool ring = ring_ok(g.K, g.lda, g.ldb), pers_ok = ring && t128 <= 0x7fffff00LL && g.K >= 4 * BK;
-    const RingForm form = ring ? ring_form(g.M, g.N, g.K) : RING_NONE;
-    // cfg: -1 = chosen here; 0 / 7 / 8 forced by the test entry point hero_fp8_gemm_tile
-    if (pers_ok && (cfg == 7 || cfg == 8 || (cfg < 0 && form == RING_NONE))) {
-        const bool tile128 = cfg == 8 || (cfg < 0 && (t256 < 160 || small_tile_fills_better(t256, t128)));
-        g.ntm = tile128 ? (g.M + 127) / 128 : (g.M + 255) / 256; g.ntn = tile128 ? (g.N + 127) / 128 : (g.N + 255) / 256;
-        g.per_xcd = (int)(((tile128 ? t128 : t256) + NUM_XCD - 1) / NUM_XCD);
-        const int cap = tile128 ? 64 : 32, nslot = g.per_xcd < cap ? g.per_xcd : cap;
-        share_prefetch(g, tile128 ? t128 : t256, tile128 ? 256 : 512);
-        if (tile128) hipLaunchKernelGGL((int8_gemm_persistent_kernel<128, 128, 2, 2, 4, EPI, CDT, RDT, HERO_F8E4M3>), dim3((unsigned)(nslot * NUM_XCD)), dim3(256), 0, st, g);
-        else hipLaunchKernelGGL((int8_gemm_persistent_kernel<256, 256, 2, 4, 4, EPI, CDT, RDT, HERO_F8E4M3>), dim3((unsigned)(nslot * NUM_XCD)), dim3(512), 0, st, g);
-        return hero_launch_status();
-    }
-    if (ring && cfg != 0) return launch_ring<HERO_F8E4M3, EPI, CDT, RDT>(g, form == RING_NONE ? RING_128x64 : form, st);
-    return launch_grid(g, 128, 128, 256, int8_gemm_kernel<128, 128, 2, 2, 2, 2, EPI, CDT, RDT, HERO_F8E4M3>, st);
+// Test hook (include/hero_debug.h): what the product entry points run without scratch.
+extern "C" int hero_gemm_kernel(hero_dtype dt, int gelu, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+    const int64_t es = dt == HERO_BF16 || dt == HERO_F16 ? 2 : 1;
+    const Choice c = choose(dt, gelu != 0, false, M, N, K * es, lda * es, ldb * es);
+    return c.kernel == K_RING ? 16 + (int)c.form : (int)c.kernel;
 }
 
+// The FP8 variant: the same kernels and the same choice with E4M3 operands.
 static hero_status run_fp8_gemm(const void* A, int64_t lda, const float* a_row_scale,
                                 const void* Bt, int64_t ldb, const float* b_col_scale,
                                 const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,
@@ -1277,17 +1264,17 @@ static hero_status run_fp8_gemm(const void* A, int64_t lda, const float* a_row_s
     set_prefetch(g, prefetch, prefetch_bytes);
     hipStream_t st = (hipStream_t)stream;
     switch (epi) {
-    case HERO_EPI_REQUANT: return launch_epi_fp8<HERO_EPI_REQUANT, HERO_F8E4M3, -1>(g, workspace, workspace_bytes, st, tile);
-    case HERO_EPI_GELU_REQUANT: return launch_epi_fp8<HERO_EPI_GELU_REQUANT, HERO_F8E4M3, -1>(g, workspace, workspace_bytes, st, tile);
+    case HERO_EPI_REQUANT: return launch_epi<HERO_F8E4M3, HERO_EPI_REQUANT, HERO_F8E4M3, -1>(g, workspace, workspace_bytes, st, tile);
+    case HERO_EPI_GELU_REQUANT: return launch_epi<HERO_F8E4M3, HERO_EPI_GELU_REQUANT, HERO_F8E4M3, -1>(g, workspace, workspace_bytes, st, tile);
     case HERO_EPI_DEQUANT_GELU:
-        return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT_GELU, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
-                                 : launch_epi_fp8<HERO_EPI_DEQUANT_GELU, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
+        return c_dt == HERO_BF16 ? launch_epi<HERO_F8E4M3, HERO_EPI_DEQUANT_GELU, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
+                                 : launch_epi<HERO_F8E4M3, HERO_EPI_DEQUANT_GELU, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
     default:
         if (!residual)
-            return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
-                                     : launch_epi_fp8<HERO_EPI_DEQUANT, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
-        return c_dt == HERO_BF16 ? launch_epi_fp8<HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16>(g, workspace, workspace_bytes, st, tile)
-                                 : launch_epi_fp8<HERO_EPI_DEQUANT, HERO_F16, HERO_F16>(g, workspace, workspace_bytes, st, tile);
+            return c_dt == HERO_BF16 ? launch_epi<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
+                                     : launch_epi<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
+        return c_dt == HERO_BF16 ? launch_epi<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16>(g, workspace, workspace_bytes, st, tile)
+                                 : launch_epi<HERO_F8E4M3, HERO_EPI_DEQUANT, HERO_F16, HERO_F16>(g, workspace, workspace_bytes, st, tile);
     }
 }
 
@@ -1362,18 +1349,18 @@ static hero_status run_int8_gemm(const int8_t* A, int64_t lda, const float* a_ro
     set_prefetch(g, prefetch, prefetch_bytes);
     hipStream_t st = (hipStream_t)stream;
     switch (epi) {
-    case HERO_EPI_RAW_I32: return launch_epi<HERO_EPI_RAW_I32, HERO_I32, -1>(g, workspace, workspace_bytes, st, tile);
-    case HERO_EPI_REQUANT: return launch_epi<HERO_EPI_REQUANT, HERO_I8, -1>(g, workspace, workspace_bytes, st, tile);
-    case HERO_EPI_GELU_REQUANT: return launch_epi<HERO_EPI_GELU_REQUANT, HERO_I8, -1>(g, workspace, workspace_bytes, st, tile);
+    case HERO_EPI_RAW_I32: return launch_epi<HERO_I8, HERO_EPI_RAW_I32, HERO_I32, -1>(g, workspace, workspace_bytes, st, tile);
+    case HERO_EPI_REQUANT: return launch_epi<HERO_I8, HERO_EPI_REQUANT, HERO_I8, -1>(g, workspace, workspace_bytes, st, tile);
+    case HERO_EPI_GELU_REQUANT: return launch_epi<HERO_I8, HERO_EPI_GELU_REQUANT, HERO_I8, -1>(g, workspace, workspace_bytes, st, tile);
     case HERO_EPI_DEQUANT_GELU:
-        return c_dt == HERO_BF16 ? launch_epi<HERO_EPI_DEQUANT_GELU, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
-                                 : launch_epi<HERO_EPI_DEQUANT_GELU, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
+        return c_dt == HERO_BF16 ? launch_epi<HERO_I8, HERO_EPI_DEQUANT_GELU, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
+                                 : launch_epi<HERO_I8, HERO_EPI_DEQUANT_GELU, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
     case HERO_EPI_DEQUANT:
         if (!residual)
-            return c_dt == HERO_BF16 ? launch_epi<HERO_EPI_DEQUANT, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
-                                     : launch_epi<HERO_EPI_DEQUANT, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
-        if (c_dt == HERO_BF16) return launch_epi<HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16>(g, workspace, workspace_bytes, st, tile);
-        return launch_epi<HERO_EPI_DEQUANT, HERO_F16, HERO_F16>(g, workspace, workspace_bytes, st, tile);
+            return c_dt == HERO_BF16 ? launch_epi<HERO_I8, HERO_EPI_DEQUANT, HERO_BF16, -1>(g, workspace, workspace_bytes, st, tile)
+                                     : launch_epi<HERO_I8, HERO_EPI_DEQUANT, HERO_F16, -1>(g, workspace, workspace_bytes, st, tile);
+        if (c_dt == HERO_BF16) return launch_epi<HERO_I8, HERO_EPI_DEQUANT, HERO_BF16, HERO_BF16>(g, workspace, workspace_bytes, st, tile);
+        return launch_epi<HERO_I8, HERO_EPI_DEQUANT, HERO_F16, HERO_F16>(g, workspace, workspace_bytes, st, tile);
     default: return HERO_ERR_UNSUPPORTED;
     }
 }

@@ -1,0 +1,29 @@
+"""Which kernel a product runs, asked of the library's own rule (include/hero_debug.h); nothing is launched."""
+import pytest
+import torch
+
+import paper_2310_17723_amd as pkg
+
+FORMS = ["32x32/8", "32x32/4", "32x64/2", "32x64/4", "64x32/4", "64x64/2", "64x64", "128x64/2", "128x64", "128x128"]
+DTYPES = [torch.int8, torch.float8_e4m3fn, torch.bfloat16, torch.float16]
+
+
+def kernel(dt, M, N, kb, **kw):
+    k = pkg.load().hero_gemm_kernel(dt, M, N, kb // dt.itemsize, **kw)
+    return FORMS[k - 16] if k >= 16 else k
+
+
+@pytest.mark.parametrize("dt", DTYPES)
+def test_half_slab_keeps_the_ring(dt):
+    """A K of an odd number of 64-byte pieces runs what the next whole slab would: the direct-to-LDS ring, not the kernel that
+    stages through registers (measured 1.7 to 3.5 times as long for few rows)."""
+    for N, K in ((768, 768), (1024, 1024), (4096, 2048), (4096, 4096), (12288, 4096), (4096, 16384)):
+        for M in (1, 16, 64, 100, 256, 512, 1000):
+            whole = kernel(dt, M, N, K + 128)
+            if isinstance(whole, str):
+                assert kernel(dt, M, N, K + 64) == whole, (M, N, K)
+    assert kernel(dt, 2048, 4096, 4160) == "128x128"            # no form for a whole slab either: 128 x 128 tiles
+    assert kernel(dt, 2048, 4096, 2112) == 0                    # .. through registers while K is short
+    assert kernel(dt, 4096, 4096, 2112) == (1 if dt == torch.int8 else 0)
+    # rows too far apart for 32-bit offsets: registers, the small tile for few rows
+    assert kernel(dt, 64, 4096, 4096, lda=1 << 24) == 3 and kernel(dt, 4096, 4096, 1024, lda=1 << 24) in (0, 1)

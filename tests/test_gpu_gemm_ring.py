@@ -24,6 +24,19 @@ SHAPES = [
     (300, 10244, 4096),      # 128x128
     (1025, 2300, 1024),      # 128x64
     (65, 260, 192),          # K is one and a half slabs
+    # K that ends in half a slab, in every form
+    (1, 32, 64),             # 32x32, half a slab for eight groups
+    (33, 100, 832),          # 32x32, eight groups
+    (7, 4000, 8256),         # 32x32, four groups
+    (31, 12284, 2112),       # 32x64, two groups
+    (32, 12300, 8256),       # 32x64, four groups
+    (100, 4092, 4160),       # 64x32, four groups
+    (129, 4612, 832),        # 64x64, two groups
+    (100, 12292, 4160),      # 128x64, two groups
+    (641, 2052, 320),        # 64x64
+    (1025, 2300, 960),       # 128x64
+    (1100, 4100, 4160),      # 128x128, more tiles than a round
+    (1500, 4100, 1088),      # (the register-staged kernel: K too short for that)
 ]
 
 
@@ -94,6 +107,18 @@ def test_fp8_gemm_forms(M, N, K):
     # fp32 sums in any order: (K + 4) * 2^-24 of the sum of the magnitudes; then one rounding to bf16
     bound = (K + 4) * 2.0 ** -24 * ((a.double().abs() @ w.double().abs().t()) * s + bias.double().abs())
     assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * 2.0 ** -8).all())
+
+
+@pytest.mark.parametrize("M", [1, 33, 64, 100])
+def test_int8_split_half_slab(M):
+    """The K split of a skinny product whose K ends in half a slab: raw sums exact, through a scratch that is dirty."""
+    hero, N, K = pkg.load(), 1028, 8192 + 64
+    g = torch.Generator(device="cuda").manual_seed(M)
+    a = _strided(torch.randint(-127, 128, (M, K), device="cuda", generator=g, dtype=torch.int8), 16)
+    w = torch.randint(-127, 128, (N, K), device="cuda", generator=g, dtype=torch.int8)
+    ws = torch.full((hero.hero_int8_gemm_workspace_bytes(M, N, K),), 0xA5, dtype=torch.uint8, device="cuda")
+    assert ws.numel() > 0
+    assert torch.equal(hero.hero_int8_gemm(a, w, workspace=ws), (a.double() @ w.double().t()).to(torch.int32))
 
 
 @pytest.mark.parametrize("B,fmt,f", [(b, t, 8192) for b in (1, 5, 64, 100) for t in ("fp8", "bf16")] +
