@@ -893,27 +893,27 @@ __global__ __launch_bounds__(512, 2) void int8_gemm_ovl_kernel(GemmArgs g) {
 // Split-K for skinny M with a long K (M <= 128, 64 slabs of 128 bytes or more): the weights are streamed once, and too few
 // tiles exist to do that from every CU.  Pass 1: the ring kernel with a second grid dimension over K ranges writes raw
 // partial sums, one [M][ldp] plane per range, into the caller's scratch, as many ranges as give every CU one
-// workgroup.  Pass 2 (splitk_reduce_kernel) adds the planes and runs the epilogue; the arithmetic is the same, in the same
-// order, as in the one-pass kernels.  The kernel boundary is the only synchronisation (device-wide fences inside one
+// workgroup of 64 columns.  Pass 2 (splitk_reduce_kernel) adds the planes and runs the epilogue: its arithmetic is the one-pass
+// kernels', in the same order; INT8 sums are exact, fp32 ones (E4M3, 16 bits) are added in the fixed order of the ranges.
+// The kernel boundary is the only synchronisation (device-wide fences inside one
 // kernel measured 4x slower than no split at all).  Measured with cold weights, one pass -> split: INT8 64 x 4096 x 16384
 // 23.6 -> 19.7 us, 3 rows 19.7 -> 17.6, 100 rows 26.3 -> 24.1; BF16 64 rows 44.4 -> 35.6, 3 rows 36.2 -> 30.5; with
 // K = 4096 the second launch costs more than the split gives.
-// The scratch is sized for `ksplit` ranges (two 64 x 64 or 128 x 128 tiles per CU), an upper bound of what is used.
-struct SplitK { int ksplit; int64_t ldp; size_t bytes; };
-inline SplitK splitk_plan(int64_t M, int64_t N, int64_t K) {            // K in bytes
-    SplitK p = {1, 0, 0};
-    if (M <= 0 || N <= 0 || M > 128 || K % BK != 0) return p;
-    const int64_t b = M <= 64 ? 64 : 128, tiles = (N + b - 1) / b, kt = K / BK;
-    if (tiles > 128 || kt < 128 || N * K < (4 << 20)) return p;         // small weights are launch-bound anyway
-    int64_t want = (512 + tiles - 1) / tiles;
-    if (want > 16) want = 16;
-    int64_t kslabs = (kt + want - 1) / want;
-    if (kslabs < 4) kslabs = 4;
-    p.ksplit = (int)((kt + kslabs - 1) / kslabs);
-    if (p.ksplit <= 1) { p.ksplit = 1; return p; }
+struct SplitK { int ksplit, kslabs; int64_t ldp; size_t bytes; };      // ranges, 128-byte slabs of each, the planes' stride and size
+inline SplitK split_ranges(int64_t M, int64_t N, int64_t kb, int64_t want) {
+    const int64_t slabs = (kb + 2 * BK - 1) / (2 * BK), kslabs = (slabs + want - 1) / want;
+    SplitK p;
+    p.kslabs = (int)kslabs;
+    p.ksplit = (int)((slabs + kslabs - 1) / kslabs);                   // every range non-empty
     p.ldp = (N + 3) & ~(int64_t)3;
     p.bytes = (size_t)p.ksplit * M * p.ldp * 4;
     return p;
+}
+inline SplitK splitk_plan(int64_t M, int64_t N, int64_t kb) {           // kb: bytes of K
+    const int64_t b = M <= 64 ? 64 : 128, tiles = (N + b - 1) / b, want = 256 / ((N + 63) / 64 > 0 ? (N + 63) / 64 : 1);
+    if (M <= 0 || N <= 0 || M > 128 || kb % BK != 0 || tiles > 128 || kb < 128 * BK || N * kb < (4 << 20) /* launch-bound anyway */ || want < 2)
+        return SplitK{1, 0, 0, 0};
+    return split_ranges(M, N, kb, want < 16 ? want : 16);
 }
 
 // A middling 16-bit product with a very long K (FC2 of a prompt chunk, 256 slabs or more): one round of 128 x 128 tiles leaves
@@ -922,14 +922,11 @@ inline SplitK splitk_plan(int64_t M, int64_t N, int64_t K) {            // K in 
 // N = 4096, K = 16384, best form in one pass -> split: M = 150 67 -> 52 us, 300 83 -> 69, 512 94 -> 87, 602 131 -> 108; with
 // half the slabs (INT8 codes) the planes cost what the split gives (300 rows 44.7 -> 43.3, 400 47 -> 51).
 inline SplitK mid_split_plan(int64_t M, int64_t N, int64_t kb) {
-    SplitK p = {1, 0, 0};
     const int64_t tiles = ((M + 127) / 128) * ((N + 255) / 256);
-    if (M <= 128 || kb < 256 * 2 * BK || tiles <= 0 || tiles * 3 > 256) return p;
-    p.ksplit = (int)(256 / tiles < 8 ? 256 / tiles : 8);
-    p.ldp = (N + 3) & ~(int64_t)3;
-    p.bytes = (size_t)p.ksplit * M * p.ldp * 4;
-    return p;
+    if (M <= 128 || kb < 256 * 2 * BK || tiles <= 0 || tiles * 3 > 256) return SplitK{1, 0, 0, 0};
+    return split_ranges(M, N, kb, 256 / tiles < 8 ? 256 / tiles : 8);
 }
+inline SplitK hp_split_plan(int64_t M, int64_t N, int64_t kb) { return M <= 128 ? splitk_plan(M, N, kb) : mid_split_plan(M, N, kb); }
 
 // Pass 2 of split-K: one thread per 4 consecutive columns of a row.
 // Integer sums are exact in any order; fp32 partial sums (E4M3 and 16-bit operands) are added in the fixed order of the
@@ -999,22 +996,17 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const in
 template <int EPI, int CDT, int RDT, int ADT>
 bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, hero_status* status) {
     if (!ws || !ring_ok(g.lda, g.ldb)) return false;
-    constexpr bool HP = ADT == HERO_BF16 || ADT == HERO_F16;
-    const bool mid = HP && g.M > 128;
-    const SplitK p = mid ? mid_split_plan(g.M, g.N, g.K) : splitk_plan(g.M, g.N, g.K);
+    const SplitK p = ADT == HERO_BF16 || ADT == HERO_F16 ? hp_split_plan(g.M, g.N, g.K) : splitk_plan(g.M, g.N, g.K);
     if (p.ksplit <= 1 || ws_bytes < p.bytes) return false;
-    const RingForm f = mid ? RING_128x256 : (g.M <= 64 ? RING_64x64_K2 : RING_128x64_K2);   // skinny: 64 columns, one workgroup per CU
-    const int slabs = (g.K + 2 * BK - 1) / (2 * BK), ntn = (g.N + 63) / 64, want = mid ? p.ksplit : min(256 / ntn, p.ksplit);
-    if (want < 2) return false;
+    const RingForm f = g.M > 128 ? RING_128x256 : (g.M <= 64 ? RING_64x64_K2 : RING_128x64_K2);     // skinny: 64 columns, one workgroup per CU
     GemmArgs g1 = g;                                                   // pass 1: raw partial planes in the scratch
     g1.a_row_scale = nullptr; g1.b_col_scale = nullptr; g1.bias = nullptr; g1.residual = nullptr; g1.out_col_scale = nullptr;
     g1.C = ws; g1.ldc = p.ldp;
-    g1.kslabs = (slabs + want - 1) / want;
-    g1.ksplit = (slabs + g1.kslabs - 1) / g1.kslabs;                   // every range non-empty
+    g1.kslabs = p.kslabs; g1.ksplit = p.ksplit;
     *status = launch_ring_part<ADT>(g1, f, st);
     if (*status != HERO_OK) return true;
     GemmArgs g2 = g;                                                   // pass 2: sum of the planes + epilogue
-    g2.ksplit = g1.ksplit;
+    g2.ksplit = p.ksplit;
     const int64_t threads = (int64_t)g.M * ((g.N + 3) / 4);
     hipLaunchKernelGGL((splitk_reduce_kernel<EPI, CDT, RDT, ADT>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
                        g2, (const int32_t*)ws, p.ldp);
@@ -1188,10 +1180,7 @@ hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
 }
 }  // namespace
 
-size_t hero_hp_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    const size_t a = splitk_plan(M, N, 2 * K).bytes, b = mid_split_plan(M, N, 2 * K).bytes;
-    return a > b ? a : b;
-}
+size_t hero_hp_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) { return hp_split_plan(M, N, 2 * K).bytes; }
 
 // hero_hp_gemm with scratch for the K split (hero_layer_fwd).  Not part of the C ABI.
 hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t ldb,
@@ -1278,8 +1267,16 @@ static hero_status run_fp8_gemm(const void* A, int64_t lda, const float* a_row_s
     }
 }
 
+size_t hero_fp8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) { return splitk_plan(M, N, K).bytes; }
+
+// The size callers have always been asked for, and by which hero_int8_gemm_static refuses: two tiles of 64 x 64 (M > 64: 128 x
+// 128) per CU, at most 16 ranges.  An upper bound of the plan's own; 0 where the plan does not split.
 extern "C" size_t hero_int8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    return splitk_plan(M, N, K).bytes;
+    const SplitK p = splitk_plan(M, N, K);
+    if (p.ksplit <= 1) return 0;
+    const int64_t b = M <= 64 ? 64 : 128, tiles = (N + b - 1) / b, kt = K / BK, want = (512 + tiles - 1) / tiles;
+    const int64_t kslabs = (kt + (want < 16 ? want : 16) - 1) / (want < 16 ? want : 16);
+    return (size_t)((kt + kslabs - 1) / kslabs) * M * p.ldp * 4;
 }
 
 extern "C" hero_status hero_int8_gemm(const int8_t* A, int64_t lda, const float* a_row_scale,
@@ -1469,7 +1466,7 @@ extern "C" hero_status hero_int8_gemm_static(const int8_t* A, int64_t lda, const
     const hero_status cs = check_gemm_args(A, lda, Bt, ldb, b_col_scale, residual, res_dt, ldr, epi, out_col_scale,
                                            C, c_dt, ldc, M, N, K, &noop);
     if (cs != HERO_OK || noop) return cs;
-    const size_t need = splitk_plan(M, N, K).bytes;
+    const size_t need = hero_int8_gemm_workspace_bytes(M, N, K);
     if (need > (size_t)HERO_STATIC_SCRATCH_BYTES) return HERO_ERR_WORKSPACE;   // beyond the built-in scratch
     void* ws = nullptr;
     if (need) {

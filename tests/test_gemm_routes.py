@@ -27,3 +27,13 @@ def test_half_slab_keeps_the_ring(dt):
     assert kernel(dt, 4096, 4096, 2112) == (1 if dt == torch.int8 else 0)
     # rows too far apart for 32-bit offsets: registers, the small tile for few rows
     assert kernel(dt, 64, 4096, 4096, lda=1 << 24) == 3 and kernel(dt, 4096, 4096, 1024, lda=1 << 24) in (0, 1)
+
+
+def test_split_scratch_is_asked_for_where_k_splits():
+    """hero_int8_gemm_workspace_bytes: 0 for a shape that runs in one pass (so that the entry point with the built-in scratch
+    takes it, whatever its size), a size for one that splits, K of whole slabs or not."""
+    need = pkg.load().hero_int8_gemm_workspace_bytes
+    for M, N, K in ((128, 16384, 8192), (65, 8256, 16384), (100, 12288, 8192), (64, 16384, 8192), (129, 4096, 16384), (64, 4096, 4096)):
+        assert need(M, N, K) == 0, (M, N, K)
+    for M, N, K in ((1, 512, 8192), (64, 4096, 16384), (64, 8192, 8192), (128, 8192, 8192), (100, 2304, 8192), (33, 4096, 8256)):
+        assert need(M, N, K) >= 2 * M * N * 4, (M, N, K)

@@ -65,3 +65,15 @@ def test_static_scratch_gemm_refuses_what_does_not_fit(hero):
         hero.hero_int8_gemm(c["A"], c["Bt"], a_row_scale=c["a_row_scale"], b_col_scale=c["b_col_scale"], bias=c["bias"],
                             epi=HB.EPI_REQUANT, out_dtype=torch.int8, static_scratch=True)
     assert e.value.status == 5
+
+
+@pytest.mark.parametrize("M,N,K", [(128, 16384, 8192), (65, 8260, 8256)])
+def test_static_scratch_gemm_runs_what_does_not_split(hero, M, N, K):
+    """Too many column tiles for the K split: no scratch is needed, and none is missed."""
+    assert hero.hero_int8_gemm_workspace_bytes(M, N, K) == 0
+    g = torch.Generator(device="cuda").manual_seed(M)
+    a = torch.randint(-127, 128, (M, K), device="cuda", generator=g, dtype=torch.int8)
+    w = torch.randint(-127, 128, (N, K), device="cuda", generator=g, dtype=torch.int8)
+    got = hero.hero_int8_gemm(a, w, static_scratch=True)
+    assert torch.equal(got[:, ::37], (a.double() @ w[::37].double().t()).to(torch.int32))
+    assert torch.equal(got, hero.hero_int8_gemm(a, w))
