@@ -371,13 +371,16 @@ typedef struct {
     const void* next_read; size_t next_read_bytes;
 } hero_layer_io;
 
-/* Bytes of scratch hero_layer_fwd needs for T = B*S rows of this layer. */
+/* Bytes of scratch hero_layer_fwd can use for T = B*S rows of this layer.  Part of it is scratch for the K split of the GEMMs,
+ * which only some sizes have, so a smaller T may ask for more than a larger one.  Where E4M3 or 16-bit modules are what asks
+ * for that part, a workspace without it is accepted and they run in one pass (their fp32 sums are then ordered otherwise);
+ * INT8 modules insist on theirs (T <= 128 rows, K >= 8192). */
 size_t hero_layer_workspace_bytes(const hero_layer_desc* desc, int64_t B, int64_t S);
 
 /* One W8A8 layer: enqueues LN^quant, the four GeMM^quant, the attention and (POST_LN) the
  * closing LN^quant on `stream`, with no host synchronisation.  Paper: Sec. 2.2.2, 2.2.3,
- * Sec. 2.3 Table 1.  `workspace` is device scratch of at least
- * hero_layer_workspace_bytes() bytes, 256-byte aligned, owned by the caller; its contents
+ * Sec. 2.3 Table 1.  `workspace` is device scratch of
+ * hero_layer_workspace_bytes() bytes (see there for what may be missing), 256-byte aligned, owned by the caller; its contents
  * are undefined afterwards.  Supported mode masks: see mode_mask above. */
 hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_layer_weights* w, const hero_layer_io* io,
                            void* workspace, size_t workspace_bytes, void* stream);

@@ -18,7 +18,7 @@ namespace {
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Workspace {
-    size_t xin_q, xin_s, xin_hp, qkv, attn, xo, mid_q, mid_s, mid_hp, a, x2, gemm_ws, gemm_ws_bytes, total;
+    size_t xin_q, xin_s, xin_hp, qkv, attn, xo, mid_q, mid_s, mid_hp, a, x2, gemm_ws, required, total;
 };
 
 Workspace plan(const hero_layer_desc* d, int64_t T) {
@@ -40,18 +40,21 @@ Workspace plan(const hero_layer_desc* d, int64_t T) {
     w.mid_hp = take(!(d->mode_mask & HERO_M_FC1) ? (size_t)T * d->d * 2 : 0);          // 16-bit X_mid for a 16-bit FC1
     w.a = take((size_t)T * d->f * e_a);
     w.x2 = take(pre ? 0 : (size_t)T * d->d * e_a);
-    // split-K scratch of the skinny (decode) and long-K GEMMs: the largest of the four shapes, shared (stream order)
-    size_t g = 0;
-    auto split = [&](int64_t N, int64_t K, uint32_t bit) {
-        g = std::max(g, (d->mode_mask & bit) ? hero_int8_gemm_workspace_bytes(T, N, K) : hero_hp_gemm_workspace_bytes(T, N, K));
-    };
-    split(3 * (int64_t)d->d, d->d, HERO_M_QKV);
-    split(d->d, d->d, HERO_M_ATTN_OUT);
-    split(d->f, d->d, HERO_M_FC1);
-    split(d->d, d->f, HERO_M_FC2);
-    w.gemm_ws_bytes = g;
-    w.gemm_ws = take(g);
-    w.total = off;
+    // split-K scratch of the skinny (decode) and long-K GEMMs, shared (stream order): the largest of the four shapes.  A call is
+    // refused only without INT8's; what E4M3 or 16-bit linears can use beyond that is taken if it is there, and they run in one
+    // pass otherwise.  (It exists for bands of T only: a workspace sized for a larger T may not have it.)
+    const int64_t D = d->d, F = d->f, nk[4][2] = {{3 * D, D}, {D, D}, {F, D}, {D, F}};
+    const uint32_t bit[4] = {HERO_M_QKV, HERO_M_ATTN_OUT, HERO_M_FC1, HERO_M_FC2};
+    const bool fp8 = (d->mode_mask & HERO_M_FP8) != 0;
+    size_t i8 = 0, any = 0;
+    for (int l = 0; l < 4; ++l) {
+        if (!fp8) i8 = std::max(i8, hero_int8_gemm_workspace_bytes(T, nk[l][0], nk[l][1]));
+        if (fp8) any = std::max(any, hero_fp8_gemm_workspace_bytes(T, nk[l][0], nk[l][1]));
+        else if (!(d->mode_mask & bit[l])) any = std::max(any, hero_hp_gemm_workspace_bytes(T, nk[l][0], nk[l][1]));
+    }
+    w.gemm_ws = off;
+    w.required = off + align256(i8);
+    w.total = off + align256(std::max(i8, any));
     return w;
 }
 
@@ -120,7 +123,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     if (B < 0 || S < 0) return HERO_ERR_SHAPE;
     if (T == 0) return HERO_OK;
     const Workspace ws = plan(desc, T);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < ws.total) return HERO_ERR_WORKSPACE;
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < ws.required) return HERO_ERR_WORKSPACE;
     const bool pre = desc->arch == HERO_ARCH_PRE_LN;
     const uint32_t mode = desc->mode_mask;
     const bool q_i8 = mode & HERO_M_QKV, attn_i8 = mode & HERO_M_ATTN, o_i8 = mode & HERO_M_ATTN_OUT;
@@ -169,7 +172,8 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     void* act = base + ws.a;
     void* x2 = base + ws.x2;
     hipStream_t st = (hipStream_t)stream;
-    void* gws = ws.gemm_ws_bytes ? (void*)(base + ws.gemm_ws) : nullptr;   // split-K scratch of the skinny GEMMs
+    const size_t gws_bytes = workspace_bytes - ws.gemm_ws;               // split-K scratch: a GEMM that finds too little does not split
+    void* gws = gws_bytes ? (void*)(base + ws.gemm_ws) : nullptr;
 
     // 8-bit attention over this call's keys or, with a cache, over the cache, to which they are appended first: in one kernel
     // for a decode step (no block reads another's row), by a copy of the bytes (codes of either format) otherwise
@@ -208,29 +212,29 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
             HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln1_g, w->ln1_b, desc->eps,
                                        T, d, xin_q, xin_s, nullptr, HERO_BF16, stream));
         HERO_TRY(hero_fp8_gemm_prefetching(xin_q, d, xin_s, w->w_qkv, d, w->w_qkv_s, w->b_qkv, nullptr, HERO_BF16, 0,
-                                           HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d, T, 3 * d, d, gws, ws.gemm_ws_bytes, stream, w->w_o, (size_t)(d * d)));
+                                           HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d, T, 3 * d, d, gws, gws_bytes, stream, w->w_o, (size_t)(d * d)));
         HERO_TRY(attend8(true));
         if (!pre) {
             HERO_TRY(hero_fp8_gemm_prefetching(attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, nullptr, HERO_BF16, 0,
-                                               HERO_EPI_REQUANT, nullptr, xo, F8, d, T, d, d, gws, ws.gemm_ws_bytes, stream, w->w_1, (size_t)(f * d)));
+                                               HERO_EPI_REQUANT, nullptr, xo, F8, d, T, d, d, gws, gws_bytes, stream, w->w_1, (size_t)(f * d)));
             HERO_TRY(hero_ln_quant_fp8(xin_q, F8, xin_s, xo, F8, w->S_o, w->ln1_g, w->ln1_b, desc->eps, T, d,
                                        mid_q, mid_s, nullptr, HERO_BF16, stream));
         } else {
             HERO_TRY(hero_fp8_gemm_prefetching(attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, io->h, HERO_BF16, d,
-                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, d, gws, ws.gemm_ws_bytes, stream, w->w_1, (size_t)(f * d)));
+                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, d, gws, gws_bytes, stream, w->w_1, (size_t)(f * d)));
             HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
                                        T, d, mid_q, mid_s, nullptr, HERO_BF16, stream));
         }
         HERO_TRY(hero_fp8_gemm_prefetching(mid_q, d, mid_s, w->w_1, d, w->w_1_s, w->b_1, nullptr, HERO_BF16, 0,
-                                           HERO_EPI_GELU_REQUANT, w->S_a, act, F8, f, T, f, d, gws, ws.gemm_ws_bytes, stream, w->w_2, (size_t)(d * f)));
+                                           HERO_EPI_GELU_REQUANT, w->S_a, act, F8, f, T, f, d, gws, gws_bytes, stream, w->w_2, (size_t)(d * f)));
         if (!pre) {
             HERO_TRY(hero_fp8_gemm_prefetching(act, f, nullptr, w->w_2, f, w->w_2_s, w->b_2, nullptr, HERO_BF16, 0,
-                                               HERO_EPI_REQUANT, nullptr, x2, F8, d, T, d, f, gws, ws.gemm_ws_bytes, stream, io->next_read, io->next_read_bytes));
+                                               HERO_EPI_REQUANT, nullptr, x2, F8, d, T, d, f, gws, gws_bytes, stream, io->next_read, io->next_read_bytes));
             HERO_TRY(hero_ln_quant_fp8(mid_q, F8, mid_s, x2, F8, w->S_x2, w->ln2_g, w->ln2_b, desc->eps, T, d,
                                        io->out_q, io->out_scale, nullptr, HERO_BF16, stream));
         } else {
             HERO_TRY(hero_fp8_gemm_prefetching(act, f, nullptr, w->w_2, f, w->w_2_s, w->b_2, io->h, HERO_BF16, d,
-                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, f, gws, ws.gemm_ws_bytes, stream, io->next_read, io->next_read_bytes));
+                                               HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, f, gws, gws_bytes, stream, io->next_read, io->next_read_bytes));
         }
         return HERO_OK;
     }
@@ -243,10 +247,10 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     if (q_i8)
         HERO_TRY(hero_int8_gemm_prefetching(xin_q, d, xin_s, w->w_qkv, d, w->w_qkv_s, w->b_qkv, nullptr, HP, 0,
                                             attn_i8 ? HERO_EPI_REQUANT : HERO_EPI_DEQUANT, nullptr,
-                                            qkv, attn_i8 ? HERO_I8 : HP, 3 * d, T, 3 * d, d, gws, ws.gemm_ws_bytes, stream,
+                                            qkv, attn_i8 ? HERO_I8 : HP, 3 * d, T, 3 * d, d, gws, gws_bytes, stream,
                                             o_i8 ? w->w_o : nullptr, (size_t)(d * d)));
     else
-        HERO_TRY(hero_hp_gemm_ws(xin_hp, d, w->w_qkv_hp, d, w->b_qkv, nullptr, 0, 0, qkv, 3 * d, T, 3 * d, d, HP, gws, ws.gemm_ws_bytes, stream));
+        HERO_TRY(hero_hp_gemm_ws(xin_hp, d, w->w_qkv_hp, d, w->b_qkv, nullptr, 0, 0, qkv, 3 * d, T, 3 * d, d, HP, gws, gws_bytes, stream));
     // (3) attention
     if (attn_i8) {
         HERO_TRY(attend8(false));
@@ -262,19 +266,19 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     if (!pre) {
         if (o_i8)
             HERO_TRY(hero_int8_gemm_prefetching((const int8_t*)attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, nullptr, HP, 0,
-                                                HERO_EPI_REQUANT, nullptr, xo, HERO_I8, d, T, d, d, gws, ws.gemm_ws_bytes, stream,
+                                                HERO_EPI_REQUANT, nullptr, xo, HERO_I8, d, T, d, d, gws, gws_bytes, stream,
                                                 fc1_i8 ? w->w_1 : nullptr, (size_t)(f * d)));
         else
-            HERO_TRY(hero_hp_gemm_ws(attn, d, w->w_o_bf16, d, w->b_o, nullptr, 0, 0, xo, d, T, d, d, HP, gws, ws.gemm_ws_bytes, stream));
+            HERO_TRY(hero_hp_gemm_ws(attn, d, w->w_o_bf16, d, w->b_o, nullptr, 0, 0, xo, d, T, d, d, HP, gws, gws_bytes, stream));
         HERO_TRY(hero_ln_quant(x1, x1_dt, q_i8 ? xin_s : nullptr, xo, o_i8 ? HERO_I8 : HP, o_i8 ? w->S_o : nullptr,
                                w->ln1_g, w->ln1_b, desc->eps, T, d, mid_q, mid_s, fc1_i8 ? nullptr : mid_hp, HP, stream));
     } else {
         if (o_i8)
             HERO_TRY(hero_int8_gemm_prefetching((const int8_t*)attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, io->h, HP, d,
-                                                HERO_EPI_DEQUANT, nullptr, io->h, HP, d, T, d, d, gws, ws.gemm_ws_bytes, stream,
+                                                HERO_EPI_DEQUANT, nullptr, io->h, HP, d, T, d, d, gws, gws_bytes, stream,
                                                 fc1_i8 ? w->w_1 : nullptr, (size_t)(f * d)));
         else
-            HERO_TRY(hero_hp_gemm_ws(attn, d, w->w_o_bf16, d, w->b_o, io->h, d, 0, io->h, d, T, d, d, HP, gws, ws.gemm_ws_bytes, stream));
+            HERO_TRY(hero_hp_gemm_ws(attn, d, w->w_o_bf16, d, w->b_o, io->h, d, 0, io->h, d, T, d, d, HP, gws, gws_bytes, stream));
         HERO_TRY(hero_ln_quant(io->h, HP, nullptr, nullptr, HERO_I8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
                                T, d, mid_q, mid_s, fc1_i8 ? nullptr : mid_hp, HP, stream));
     }
@@ -282,28 +286,28 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     if (fc1_i8)
         HERO_TRY(hero_int8_gemm_prefetching(mid_q, d, mid_s, w->w_1, d, w->w_1_s, w->b_1, nullptr, HP, 0,
                                             fc2_i8 ? HERO_EPI_GELU_REQUANT : HERO_EPI_DEQUANT_GELU, w->S_a,
-                                            act, fc2_i8 ? HERO_I8 : HP, f, T, f, d, gws, ws.gemm_ws_bytes, stream,
+                                            act, fc2_i8 ? HERO_I8 : HP, f, T, f, d, gws, gws_bytes, stream,
                                             fc2_i8 ? w->w_2 : nullptr, (size_t)(d * f)));
     else
-        HERO_TRY(hero_hp_gemm_ws(mid_hp, d, w->w_1_hp, d, w->b_1, nullptr, 0, 1, act, f, T, f, d, HP, gws, ws.gemm_ws_bytes, stream));
+        HERO_TRY(hero_hp_gemm_ws(mid_hp, d, w->w_1_hp, d, w->b_1, nullptr, 0, 1, act, f, T, f, d, HP, gws, gws_bytes, stream));
     // (6) FC2 and the closing LN^quant (POST_LN) or residual add (PRE_LN)
     if (!pre) {
         if (fc2_i8)
             HERO_TRY(hero_int8_gemm_prefetching((const int8_t*)act, f, nullptr, w->w_2, f, w->w_2_s, w->b_2, nullptr, HP, 0,
-                                                HERO_EPI_REQUANT, nullptr, x2, HERO_I8, d, T, d, f, gws, ws.gemm_ws_bytes, stream,
+                                                HERO_EPI_REQUANT, nullptr, x2, HERO_I8, d, T, d, f, gws, gws_bytes, stream,
                                                 io->next_read, io->next_read_bytes));
         else
-            HERO_TRY(hero_hp_gemm_ws(act, f, w->w_2_bf16, f, w->b_2, nullptr, 0, 0, x2, d, T, d, f, HP, gws, ws.gemm_ws_bytes, stream));
+            HERO_TRY(hero_hp_gemm_ws(act, f, w->w_2_bf16, f, w->b_2, nullptr, 0, 0, x2, d, T, d, f, HP, gws, gws_bytes, stream));
         HERO_TRY(hero_ln_quant(fc1_i8 ? (const void*)mid_q : (const void*)mid_hp, fc1_i8 ? HERO_I8 : HP, fc1_i8 ? mid_s : nullptr,
                                x2, fc2_i8 ? HERO_I8 : HP, fc2_i8 ? w->S_x2 : nullptr, w->ln2_g, w->ln2_b, desc->eps, T, d,
                                io->out_q, io->out_scale, io->out_hp, HP, stream));
     } else {
         if (fc2_i8)
             HERO_TRY(hero_int8_gemm_prefetching((const int8_t*)act, f, nullptr, w->w_2, f, w->w_2_s, w->b_2, io->h, HP, d,
-                                                HERO_EPI_DEQUANT, nullptr, io->h, HP, d, T, d, f, gws, ws.gemm_ws_bytes, stream,
+                                                HERO_EPI_DEQUANT, nullptr, io->h, HP, d, T, d, f, gws, gws_bytes, stream,
                                                 io->next_read, io->next_read_bytes));
         else
-            HERO_TRY(hero_hp_gemm_ws(act, f, w->w_2_bf16, f, w->b_2, io->h, d, 0, io->h, d, T, d, f, HP, gws, ws.gemm_ws_bytes, stream));
+            HERO_TRY(hero_hp_gemm_ws(act, f, w->w_2_bf16, f, w->b_2, io->h, d, 0, io->h, d, T, d, f, HP, gws, gws_bytes, stream));
     }
     return HERO_OK;
 }
