@@ -225,9 +225,9 @@ class Hero:
         self._check(st)
         return C_out
 
-    def hero_gemm_kernel(self, dtype, M, N, K, lda=None, ldb=None, gelu=False) -> int:
+    def hero_gemm_kernel(self, dtype, M, N, K, lda=None, ldb=None, epi=EPI_DEQUANT) -> int:
         """The kernel a product of this size runs (include/hero_debug.h); launches nothing."""
-        return int(self.lib.hero_gemm_kernel(_DT[dtype], int(gelu), M, N, K, lda or K, ldb or K))
+        return int(self.lib.hero_gemm_kernel(_DT[dtype], int(epi), M, N, K, lda or K, ldb or K))
 
     def hero_int8_gemm_workspace_bytes(self, M, N, K) -> int:
         return int(self.lib.hero_int8_gemm_workspace_bytes(M, N, K))

@@ -24,7 +24,8 @@ struct GemmArgs {
     // to its own [M][ldc] plane of C (plane stride M * ldc elements); a second kernel adds the planes
     int ksplit, kslabs;
     // optional (persistent kernels only): memory the NEXT kernel of the caller's chain will read (a layer's next weight
-    // matrix).  Every tile requests pf_lpt of its pf_lines 128-byte lines once, at the start of its epilogue.
+    // matrix).  Every tile requests pf_lpt of its pf_lines 128-byte lines once, at the start of its epilogue.  (The ring kernel
+    // does not: requests behind its first slabs changed 24 layers of BERT-large at 1500 .. 6000 tokens by +-0.3 %, -1.4 % at most.)
     const int8_t* pf = nullptr; int pf_lines = 0, pf_lpt = 0;
 };
 
@@ -314,7 +315,7 @@ inline bool ring_ok(int64_t lda_bytes, int64_t ldb_bytes) { return lda_bytes < (
 //   INT8  64 x 12288 x 4096 17.1 -> 14.4, 3 x 4096 x 4096 10.6 -> 5.7, 128 x 16384 x 4096 30 -> 21.6,
 //         2000 x 1024 x 4096 18.1 -> 14.3, 602 x 4096 x 4096 25 -> 20.2, 128 x 768 x 3072 5.4 -> 4.9
 //   BF16  651 x 768 x 3072 53 -> 9.6, 3 x 4096 x 16384 177 -> 36, 602 x 4096 x 16384 185 -> 130
-inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
+inline RingForm ring_form(int64_t M, int64_t N, int64_t kb, hero_epilogue epi) {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const int64_t slabs = (kb + 2 * BK - 1) / (2 * BK), t32 = tiles(32, 32), t12864 = tiles(128, 64);
     if (M <= 32 && t32 > 256 && tiles(32, 64) <= 256) return slabs >= 64 ? RING_32x64_K4 : RING_32x64_K2;
@@ -324,8 +325,14 @@ inline RingForm ring_form(int64_t M, int64_t N, int64_t kb) {
     if (tiles(64, 64) <= 256) return RING_64x64_K2;
     if (t12864 <= 256 && slabs >= 32) return RING_128x64_K2;
     if (tiles(64, 64) <= 512) return RING_64x64;
-    if (tiles(128, 128) <= 256 && slabs >= 32) return RING_128x128;
-    if (t12864 <= 512 || (slabs <= 8 && t12864 <= 1024)) return RING_128x64;  // short K: the persistent ring never gets going
+    // Two rounds or more.  A tile of 64 columns writes half a 128-byte line of an 8-bit result, and GELU leaves the matrix cores
+    // idle between two tiles of a workgroup, so only 16-bit and raw results without GELU go on, while K is short (the persistent
+    // ring never gets going).  us, 128 x 64 ring / persistent: REQUANT 8192 x 1024 x 1024 19.0 / 15.1, 6000 x 768 x 768 12.0 /
+    // 10.1, GELU^quant 2048 x 4096 x 1024 20.0 / 18.2; DEQUANT 8192 x 1024 x 1024 15.7 / 16.5, 2048 x 3072 x 1024 13.2 / 15.0.
+    // (the last full round of an 8-bit result: REQUANT 4096 x 1024 x 1024 128 x 64 11.1, 128 x 128 9.3)
+    const bool gelu = epi == HERO_EPI_DEQUANT_GELU || epi == HERO_EPI_GELU_REQUANT;
+    if (tiles(128, 128) <= 256 && (slabs >= 32 || (epi == HERO_EPI_REQUANT && t12864 > 448))) return RING_128x128;
+    if (t12864 <= 512 || (epi != HERO_EPI_REQUANT && !gelu && slabs <= 8 && t12864 <= 1024)) return RING_128x64;
     return RING_NONE;
 }
 template <int ADT, int EPI, int CDT, int RDT, bool HALF> hero_status launch_ring_slabs(const GemmArgs& g, RingForm f, hipStream_t st);

@@ -1078,9 +1078,9 @@ inline bool small_tile_fills_better(int64_t t256, int64_t t128) {
 enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_PERS256 = 7, K_PERS128 = 8, K_OVL = 9 };
 struct Choice { Kernel kernel; RingForm form; };
 
-// kb, lda, ldb in bytes; gelu: the epilogue has a GELU; res: a fused residual.  tile: -1 chooses, otherwise the code a test hook
+// kb, lda, ldb in bytes; res: a fused residual.  tile: -1 chooses, otherwise the code a test hook
 // forces (a forced kernel that cannot run the shape gives way to its closest relative).
-inline Choice choose(hero_dtype adt, bool gelu, bool res, int64_t M, int64_t N, int64_t kb, int64_t lda, int64_t ldb, int tile = -1) {
+inline Choice choose(hero_dtype adt, hero_epilogue epi, bool res, int64_t M, int64_t N, int64_t kb, int64_t lda, int64_t ldb, int tile = -1) {
     const bool i8 = adt == HERO_I8, ring = ring_ok(lda, ldb);
     const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
     // persistent kernels: K long enough that the slab ring never runs more than one tile ahead, whole pairs of slabs, 32-bit
@@ -1088,7 +1088,7 @@ inline Choice choose(hero_dtype adt, bool gelu, bool res, int64_t M, int64_t N, 
     const bool pers_ok = ring && kb >= 4 * BK && kb % (2 * BK) == 0 && t128 <= 0x7fffff00LL;
     // the overlapped-epilogue kernel: its epilogue is spread over the first 16 slabs of the next tile; no fused residual
     const bool ovl_ok = i8 && pers_ok && kb >= 16 * BK && !res;
-    const RingForm form = ring ? ring_form(M, N, kb) : RING_NONE;
+    const RingForm form = ring ? ring_form(M, N, kb, epi) : RING_NONE;
     const Choice small = {ring ? K_RING : (M <= 64 || t128 < 192 ? K_REG64 : K_REG128), form == RING_NONE ? RING_128x64 : form};
     if (tile >= 0) {
         if (tile == K_OVL && ovl_ok) return {K_OVL, RING_NONE};
@@ -1110,6 +1110,7 @@ inline Choice choose(hero_dtype adt, bool gelu, bool res, int64_t M, int64_t N, 
         // costs more than the hidden epilogue saves (GPT prefill, FC1 16384 x 16384 x 4096: +11 %).
         // Forcing each of the layer's other GEMMs (QKV, attention-output, FC2) to this kernel or to the 128 x 128 tiles
         // inside the stack made every one of them slower (7.46 -> 7.50-7.67 ms per 24 layers).
+        const bool gelu = epi == HERO_EPI_DEQUANT_GELU || epi == HERO_EPI_GELU_REQUANT;
         return {gelu && ovl_ok && kb < 2048 ? K_OVL : K_PERS256, RING_NONE};
     }
     // K that ends in half a slab: the one-tile-per-workgroup 256 x 256 kernel (INT8) once its grid fills the chip, else 128 x 128
@@ -1139,8 +1140,7 @@ template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
     hero_status split;
     if (tile < 0 && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
-    constexpr bool GELU_EPI = EPI == HERO_EPI_GELU_REQUANT || EPI == HERO_EPI_DEQUANT_GELU;
-    const Choice c = choose((hero_dtype)ADT, GELU_EPI, RDT >= 0, g.M, g.N, g.K, g.lda, g.ldb, tile);
+    const Choice c = choose((hero_dtype)ADT, (hero_epilogue)EPI, RDT >= 0, g.M, g.N, g.K, g.lda, g.ldb, tile);
     return launch_choice<ADT, EPI, CDT, RDT>(g, c, st);
 }
 
@@ -1172,7 +1172,7 @@ hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
     g.ksplit = 1; g.kslabs = 0;
     // more than 2^23 rows: the persistent kernels only (INT8 operands end there altogether)
     if (M > 65535 * 128LL) {
-        const Kernel k = choose(dt, gelu != 0, residual != nullptr, M, N, g.K, g.lda, g.ldb, tile).kernel;
+        const Kernel k = choose(dt, gelu ? HERO_EPI_DEQUANT_GELU : HERO_EPI_DEQUANT, residual != nullptr, M, N, g.K, g.lda, g.ldb, tile).kernel;
         if (k != K_PERS256 && k != K_PERS128) return HERO_ERR_UNSUPPORTED;
     }
     return dt == HERO_BF16 ? launch_hp<HERO_BF16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile)
@@ -1211,9 +1211,9 @@ extern "C" hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void*
 }
 
 // Test hook (include/hero_debug.h): what the product entry points run without scratch.
-extern "C" int hero_gemm_kernel(hero_dtype dt, int gelu, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+extern "C" int hero_gemm_kernel(hero_dtype dt, hero_epilogue epi, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
     const int64_t es = dt == HERO_BF16 || dt == HERO_F16 ? 2 : 1;
-    const Choice c = choose(dt, gelu != 0, false, M, N, K * es, lda * es, ldb * es);
+    const Choice c = choose(dt, epi, false, M, N, K * es, lda * es, ldb * es);
     return c.kernel == K_RING ? 16 + (int)c.form : (int)c.kernel;
 }
 
