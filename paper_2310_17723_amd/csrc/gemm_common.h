@@ -325,6 +325,10 @@ inline RingForm ring_form(int64_t M, int64_t N, int64_t kb, hero_epilogue epi) {
     if (tiles(64, 64) <= 256) return RING_64x64_K2;
     if (t12864 <= 256 && slabs >= 32) return RING_128x64_K2;
     if (tiles(64, 64) <= 512) return RING_64x64;
+    // Few rows and more columns than that (a vocabulary's logits): the weights are all there is to stream, and tall tiles stream
+    // them through fewer waves.  us, cold weights, persistent 256 x 256 / this: INT8 1 x 50304 x 4096 57 / 44, 64 rows 58 / 54, BF16
+    // 16 rows 108 / 83; 64 x 64 / 32 x 64 with two K groups: 1 x 36864 x 4096 38 / 33, 1 x 50304 x 768 11.9 / 15.7.
+    if (M <= 64) return M <= 32 && slabs >= 32 ? (slabs >= 64 ? RING_32x64_K4 : RING_32x64_K2) : RING_64x64;
     // Two rounds or more.  A tile of 64 columns writes half a 128-byte line of an 8-bit result, and GELU leaves the matrix cores
     // idle between two tiles of a workgroup, so only 16-bit and raw results without GELU go on, while K is short (the persistent
     // ring never gets going).  us, 128 x 64 ring / persistent: REQUANT 8192 x 1024 x 1024 19.0 / 15.1, 6000 x 768 x 768 12.0 /

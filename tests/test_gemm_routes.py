@@ -52,3 +52,12 @@ def test_narrow_tiles_are_not_for_two_rounds_of_8_bit_results(dt):
         assert kernel(dt, M, N, K, epi=HB.EPI_GELU_REQUANT) in PERSISTENT, (M, N, K)
     assert kernel(dt, 4096, 1024, 1024, epi=HB.EPI_REQUANT) == "128x128"
     assert kernel(dt, 3000, 1024, 1024, epi=HB.EPI_REQUANT) == "128x64"
+
+
+@pytest.mark.parametrize("dt", DTYPES)
+def test_few_rows_of_many_columns_keep_small_tiles(dt):
+    """A product of at most 64 rows never runs tiles of 128 or 256 rows, however many columns it has."""
+    for N in (33000, 36864, 50304, 131072):
+        for kb in (1024, 4096, 8192):
+            assert kernel(dt, 1, N, kb) == {1024: "64x64", 4096: "32x64/2", 8192: "32x64/4"}[kb]
+            assert kernel(dt, 33, N, kb) == kernel(dt, 64, N, kb) == "64x64"

@@ -24,6 +24,9 @@ SHAPES = [
     (300, 10244, 4096),      # 128x128
     (1025, 2300, 1024),      # 128x64
     (65, 260, 192),          # K is one and a half slabs
+    # few rows of many columns
+    (3, 36868, 4096),        # 32x64, two groups, more tiles than a round
+    (64, 33004, 1024),       # 64x64
     # K that ends in half a slab, in every form
     (1, 32, 64),             # 32x32, half a slab for eight groups
     (33, 100, 832),          # 32x32, eight groups
