@@ -766,13 +766,35 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
 //   phase 2: row max / sum in the log2 domain (block reduction), codes 0..255 -> LDS
 //   phase 3: acc[e] = sum_k P[k] * v[k][e] in int32, reduced over the key groups through LDS
 // What bounds the stream is the bytes in flight: UNR loads per lane, NT lanes.  With many blocks, 256 threads (several
-// blocks per CU, their phases overlap: 64 x 32 heads x 2049 keys 189 us, 5.7 TB/s); with at most one block per CU,
-// 1024 threads, i.e. four times the bytes in flight per block (the rule and its figures: attn_entry).  The first V loads
-// are out during the softmax.
+// blocks per CU, their phases overlap: 64 x 32 heads x 2049 keys 189 us, 5.7 TB/s); with at most one block per CU, 512 threads
+// and the first V loads out during the softmax (the rule and its figures: attn_entry).  A short cache is bound by the chain
+// of reductions: those go through data-parallel moves, not LDS.
 // In a layer, the block also appends this call's K / V row to its cache: no other block reads that row, and the two
 // 4-5 us launches of a step that copied it are gone.
 // ------------------------------------------------------------------------------------------
 constexpr int DEC_MAX_KEYS = 16384;
+
+// The value of lane ^ O (O a power of two), where every lane that agrees in the lower bits of log2 O already holds the same in
+// the bits above (a butterfly from the top down, or from the bottom up for O <= 2): data-parallel moves, no trip through LDS.
+template <int O, typename T>
+__device__ __forceinline__ T lane_xor(T x) {
+    const uint32_t b = __builtin_bit_cast(uint32_t, x);
+    if constexpr (O == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+        return __builtin_bit_cast(T, (threadIdx.x & 32) ? r[0] : r[1]);
+    } else if constexpr (O == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+        return __builtin_bit_cast(T, (threadIdx.x & 16) ? r[0] : r[1]);
+    } else {
+        constexpr int ctrl = O == 8 ? 0x128 : (O == 4 ? 0x124 : (O == 2 ? 0x4E : 0xB1));      // row_ror:8, row_ror:4, quad_perm
+        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, (int)b, ctrl, 0xF, 0xF, true));
+    }
+}
+template <typename T, typename F>
+__device__ __forceinline__ T wave_butterfly(T x, F op) {                 // 32 down to 1: every lane ends with the wave's value
+    x = op(x, lane_xor<32>(x)); x = op(x, lane_xor<16>(x)); x = op(x, lane_xor<8>(x));
+    x = op(x, lane_xor<4>(x)); x = op(x, lane_xor<2>(x)); return op(x, lane_xor<1>(x));
+}
 
 // FMT = HERO_F8E4M3: E4M3 operands: the bytes are decoded two at a time (v_cvt_pk_f32_fp8), scores and PV sums are
 // fp32, the probability code is e4m3(min(p / S_p, 448)) and its decoded value is what PV multiplies.
@@ -785,8 +807,9 @@ __global__ __launch_bounds__(NT) void int8_attn_decode_kernel(AttnArgs a) {
     constexpr int NW = NT / 64;
     extern __shared__ __attribute__((aligned(16))) int smem_dec[];
     ST* sc = reinterpret_cast<ST*>(smem_dec);                      // [len] scores, later codes (F8: their decoded values)
+    using V4 = typename std::conditional<F8, v4f, v4i>::type;
     __shared__ float red[2 * NW];
-    __shared__ ST racc[NW][DH + 4];
+    __shared__ __attribute__((aligned(16))) ST racc[NW][DH + 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.y, h = blockIdx.x;
     const int kvl = a.kv_len ? a.kv_len[b] : a.Skv;
@@ -829,26 +852,43 @@ __global__ __launch_bounds__(NT) void int8_attn_decode_kernel(AttnArgs a) {
 #pragma unroll
             for (int w = 0; w < 4; ++w) d = __builtin_amdgcn_sdot4(kv[w], qv[w], d, false);
         }
-#pragma unroll
-        for (int o = 1; o < LPK; o <<= 1) d += __shfl_xor(d, o);
+        d += lane_xor<1>(d);
+        d += lane_xor<2>(d);
+        if constexpr (LPK == 8)                                           // the other quad of the eight lanes (both are uniform by now)
+            d += __builtin_bit_cast(ST, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, d), 0x141, 0xF, 0xF, true));     // row_half_mirror
         return d;
     };
-    // the stream is bound by the bytes in flight: UNR unconditional loads per lane are issued before the first is
-    // used (whole groups of UNR * KPI keys), the ragged rest goes in one round of UNR clamped loads
-    constexpr int UNR = 8;
+    // the stream is bound by the bytes in flight: UNR loads per lane are issued before the first is used.  Unit u of a round is
+    // KPI keys, KPW of them this wave's; in the last, partial round a wave leaves out the units in which it has no key (all but
+    // a few of them where the cache is short)
+    constexpr int UNR = 8, KPW = 64 / LPK, ROUND = UNR * KPI;
+    const int full = hist / ROUND * ROUND;
+    const int rest = (max(hist - full - __builtin_amdgcn_readfirstlane(wave) * KPW, 0) + KPI - 1) / KPI;      // units of this wave
+    auto load_full = [&](v4i (&r)[UNR], const int8_t* base, int64_t stride, int k0) {
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) r[u] = *reinterpret_cast<const v4i*>(base + (int64_t)(k0 + u * KPI + kg) * stride);
+    };
+    auto load_rest = [&](v4i (&r)[UNR], const int8_t* base, int64_t stride) {
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+            if (u < rest) r[u] = *reinterpret_cast<const v4i*>(base + (int64_t)min(full + u * KPI + kg, hist - 1) * stride);
+    };
     auto take = [&](int key, ST d) {
         if (sub == 0 && key < hist) { sc[key] = d; lmax = max(lmax, d); }
     };
-    for (int k0 = 0; k0 < hist; k0 += UNR * KPI) {
-        v4i kv[UNR];
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) kv[u] = *reinterpret_cast<const v4i*>(kbase + (int64_t)min(k0 + u * KPI + kg, hist - 1) * a.ks[1]);
+    v4i kv[UNR];
+    for (int k0 = 0; k0 < full; k0 += ROUND) {
+        load_full(kv, kbase, a.ks[1], k0);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            if (k0 + u * KPI >= hist) break;                          // block-uniform
-            take(k0 + u * KPI + kg, score(kv[u]));
+            const ST d = score(kv[u]);
+            if (sub == 0) sc[k0 + u * KPI + kg] = d;
+            lmax = max(lmax, d);
         }
     }
+    load_rest(kv, kbase, a.ks[1]);
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) if (u < rest) take(full + u * KPI + kg, score(kv[u]));
     if (app) {
         const ST d = score(kn);
         if (tid == 0) sc[hist] = d;
@@ -859,16 +899,12 @@ __global__ __launch_bounds__(NT) void int8_attn_decode_kernel(AttnArgs a) {
             *reinterpret_cast<v4i*>(a.vc + (vbase - a.v) + vst) = vn;
         }
     }
-    // the first V loads are in flight during the softmax
+    // one block per CU: the first V loads are in flight during the softmax (several overlap anyway, and need the registers)
+    constexpr bool EARLY_V = NT > 256;
     v4i vv[UNR];
-    auto load_v = [&](int k0) {
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) vv[u] = *reinterpret_cast<const v4i*>(vbase + (int64_t)min(k0 + u * KPI + kg, hist - 1) * a.vs[1]);
-    };
-    if (hist > 0) load_v(0);
+    if (!EARLY_V) {} else if (full > 0) load_full(vv, vbase, a.vs[1], 0); else load_rest(vv, vbase, a.vs[1]);
     // block max
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lmax = max(lmax, __shfl_xor(lmax, o));
+    lmax = wave_butterfly(lmax, [](ST x, ST y) { return max(x, y); });
     if (lane == 0) red[wave] = F8 ? (float)lmax : __int_as_float((int)lmax);
     __syncthreads();
     const float c2 = a.qk_scale * 1.44269504088896340736f;
@@ -887,8 +923,7 @@ __global__ __launch_bounds__(NT) void int8_attn_decode_kernel(AttnArgs a) {
     // ---- phase 2: sum, then codes --------------------------------------------------------------
     float lsum = 0.0f;
     for (int k = tid; k < len; k += NT) lsum += __builtin_amdgcn_exp2f(fmaf((float)sc[k], c2, -m2));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o);
+    lsum = wave_butterfly(lsum, [](float x, float y) { return x + y; });
     if (lane == 0) red[NW + wave] = lsum;
     __syncthreads();
     float l = red[NW];
@@ -916,24 +951,40 @@ __global__ __launch_bounds__(NT) void int8_attn_decode_kernel(AttnArgs a) {
             for (int e = 0; e < 16; ++e) acc[e] += p * (int)(int8_t)(w[e >> 2] >> (8 * (e & 3)));
         }
     };
-    for (int k0 = 0; k0 < hist; k0 += UNR * KPI) {
-        if (k0 > 0) load_v(k0);
+    for (int k0 = 0; k0 < full; k0 += ROUND) {
+        if (!EARLY_V || k0 > 0) load_full(vv, vbase, a.vs[1], k0);
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int key = k0 + u * KPI + kg;
-            if (k0 + u * KPI >= hist) break;                          // block-uniform
-            pv(vv[u], key < hist ? sc[key] : (ST)0);
-        }
+        for (int u = 0; u < UNR; ++u) pv(vv[u], sc[k0 + u * KPI + kg]);
+    }
+    if (!EARLY_V || full > 0) load_rest(vv, vbase, a.vs[1]);
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+        const int key = full + u * KPI + kg;
+        if (u < rest) pv(vv[u], key < hist ? sc[key] : (ST)0);
     }
     if (app && kg == 0) pv(vn, sc[hist]);
-    // sum over the key groups: across a wave's lanes first, then through LDS in the fixed order of the waves
+    // sum over the key groups: across a wave's lanes first, then through LDS in the fixed order of the waves.  The halves and the
+    // rows of 16 lanes exchange elements while they add (v_permlane32_swap, v_permlane16_swap), so a lane of row r is left with
+    // the elements 8 (r / 2) + 4 (r % 2) + 0 .. 3 of its 16, for the key groups of its row, which rotations add.  (Sixteen
+    // butterflies through LDS cost a block of 1024 threads 2 us.)
+    auto bits = [](ST x) { return __builtin_bit_cast(uint32_t, x); };
+    auto val = [](uint32_t x) { return __builtin_bit_cast(ST, x); };
+    ST half[8], quad[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
+    for (int e = 0; e < 8; ++e) {
+        const auto r = __builtin_amdgcn_permlane32_swap(bits(acc[e]), bits(acc[e + 8]), false, false);
+        half[e] = val(r[0]) + val(r[1]);
+    }
 #pragma unroll
-        for (int o = LPK; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
-    if (lane < LPK) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) racc[wave][sub * 16 + e] = acc[e];
+    for (int e = 0; e < 4; ++e) {
+        const auto r = __builtin_amdgcn_permlane16_swap(bits(half[e]), bits(half[e + 4]), false, false);
+        quad[e] = val(r[0]) + val(r[1]);
+        quad[e] += val((uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits(quad[e]), 0x128, 0xF, 0xF, true));              // row_ror:8
+        if (LPK == 4) quad[e] += val((uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits(quad[e]), 0x124, 0xF, 0xF, true));  // row_ror:4
+    }
+    if ((lane & 15) < LPK) {
+        const int row = lane >> 4;
+        *reinterpret_cast<V4*>(&racc[wave][sub * 16 + 8 * (row >> 1) + 4 * (row & 1)]) = V4{quad[0], quad[1], quad[2], quad[3]};
     }
     __syncthreads();
     if (tid < DH) {
@@ -1045,15 +1096,16 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     }
     if (online) return Dh == 64 ? launch<64, true>(a, out_dt, st) : launch<128, true>(a, out_dt, st);
     if (Sq == 1 && Skv <= DEC_MAX_KEYS) {          // decode: the cache-streaming kernel
-        // One block per CU or fewer: wide blocks (96 blocks x 1150 keys 23.4 -> 15.5 us; 224 x 550: 11.6).  From two blocks
-        // on a CU narrow ones are ahead (288 x 530: 14.9 us against 19.0 wide; 768 x 830 E4M3: 33 against 35 with 512 threads).
-        const int nt = B * H <= 256 ? 1024 : 256;
+        // One block per CU or fewer: 512 threads.  Measured, us, 256 / 512 / 1024 threads: 96 blocks (Dh 128) x 1 key 3.3 / 3.5 /
+        // 4.1, x 128 4.6 / 4.5 / 4.8, x 512 8.1 / 6.9 / 7.0, x 2048 23.6 / 18.6 / 19.1; 256 blocks x 1000 16.5 / 14.5 / 16.6.  From two
+        // blocks on a CU narrow ones are ahead: 288 x 1000 18.9 / 20.3 / 23.6, 768 x 1 3.8 / 5.5 / 9.6.
+        const int nt = B * H <= 256 ? 512 : 256;
         dim3 grid((unsigned)H, (unsigned)B), block(nt);
         const size_t lds = (size_t)Skv * sizeof(int);
 #define HERO_DEC_NT(DH_, ODT_, FMT_, NT_) do { \
             if (!decode_lds_ready<DH_, ODT_, FMT_, NT_>(lds)) return HERO_ERR_LAUNCH; \
             hipLaunchKernelGGL((int8_attn_decode_kernel<DH_, ODT_, FMT_, NT_>), grid, block, lds, st, a); } while (0)
-#define HERO_DEC(DH_, ODT_, FMT_) do { if (nt == 1024) HERO_DEC_NT(DH_, ODT_, FMT_, 1024); else HERO_DEC_NT(DH_, ODT_, FMT_, 256); } while (0)
+#define HERO_DEC(DH_, ODT_, FMT_) do { if (nt == 512) HERO_DEC_NT(DH_, ODT_, FMT_, 512); else HERO_DEC_NT(DH_, ODT_, FMT_, 256); } while (0)
 #define HERO_DEC_DT(DH_, FMT_) do { \
             if (out_dt == HERO_BF16) HERO_DEC(DH_, HERO_BF16, FMT_); else if (out_dt == HERO_F16) HERO_DEC(DH_, HERO_F16, FMT_); \
             else HERO_DEC(DH_, FMT_, FMT_); } while (0)

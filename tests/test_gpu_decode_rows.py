@@ -53,6 +53,48 @@ def test_append_in_attention(H, Dh, fmt, B):
     assert bool(torch.isfinite(h.float()).all())
 
 
+# cache lengths around the rounds and units of both block widths (a unit is 32 .. 128 keys, a round eight of them)
+LENGTHS = [0, 1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300, 511, 512, 513, 600, 1023, 1024, 1025, 1100]
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_decode_attention_lengths(Dh, fp8):
+    """One query per sequence against 64 bits, every length, from wide blocks (72 of them) and from narrow ones (the same again
+    until there are more than 256)."""
+    hero, B, H, cap = pkg.load(), len(LENGTHS), 3, 1100
+    g = torch.Generator(device="cuda").manual_seed(Dh)
+    dt = torch.float8_e4m3fn if fp8 else torch.int8
+    draw = lambda S: (torch.randn((B, S, H, Dh), device="cuda", generator=g) * 30).clamp(-127, 127).to(dt)
+    q, k, v = draw(1), draw(cap), draw(cap)
+    kv = torch.tensor(LENGTHS, dtype=torch.int32, device="cuda")
+    qk, ps = 0.08 / Dh ** 0.5 / 30, 1 / 448 if fp8 else 1 / 255
+    one = torch.ones(1, device="cuda")
+    fn = hero.hero_fp8_attn if fp8 else hero.hero_int8_attn
+    call = lambda r: fn(*(t.repeat(r, 1, 1, 1) for t in (q, k, v)), qk, ps, one, out_scale_is_scalar=True, kv_len=kv.repeat(r),
+                        out_dtype=torch.float16).reshape(r, B, H, Dh).double()
+    a = (q.double() * k.double()).sum(3).transpose(1, 2) * qk                       # [B, H, cap]
+    hidden = torch.arange(cap, device="cuda")[None, None, :] >= kv[:, None, None]
+    p = torch.softmax(a.masked_fill(hidden, -1e300), 2) * (kv > 0)[:, None, None] / ps
+    if fp8:
+        step = 2.0 ** (torch.floor(torch.log2(p.clamp(min=2.0 ** -6))) - 3)
+        p = ((p / step).round() * step).clamp(max=448)
+    else:
+        p = p.round()
+    p = p.masked_fill(hidden, 0.0)
+    ref = (p[..., None] * v.double().transpose(1, 2)).sum(2)                        # [B, H, Dh]
+    # a probability code parts where it lies within fp32 rounding (6e-5 of a step) of a tie: about one in 2e4, by one step of at
+    # most 1 (E4M3: 1 / 8 of its value), so a few of a row's keys move its outputs by some 1e2; then one rounding to fp16
+    near = 3 * 127 * (p.amax(2, keepdim=True) / 8 if fp8 else torch.ones_like(p[..., :1]))
+    for o in (call(1), call(4)):
+        assert bool((o == o[:1]).all())
+        d = (o[0] - ref).abs()
+        assert bool((d <= near + ref.abs() * 2.0 ** -11 + 2.0 ** -14).all())
+        close = d <= ref.abs() * 2.0 ** -10 + (1e-5 * p.sum(2, keepdim=True) * 448 if fp8 else 0.0) + 2.0 ** -14
+        assert float((~close).any(2).float().mean()) <= 0.1                           # rows with any parted code
+        assert bool((o[0, 0] == 0).all())
+
+
 @pytest.mark.parametrize("D", [1040, 2048, 2064, 4096])
 @pytest.mark.parametrize("M", [1, 3, 1537, 4000])
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
