@@ -1119,8 +1119,10 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     // At most one 128-query block per CU, or a single 32-query piece: the keys are split over the waves.  Measured, us, 128-query
     // kernel -> split: 1 x 12 heads x 128 8.8 -> 5.3, 2 x 16 x 512 18.5 -> 10.8, 2 x 32 x 301 behind 900 keys 47.6 -> 37.2,
     // 8 x 32 x 8 behind 2000 keys 78.7 -> 31.0, 256 blocks of 1 x 32 x 1024 causal 43 -> 37; beyond (512 blocks of 8 x 16 x 512)
-    // 23.5 -> 26.0: there the chip is full and reading K / V four times as often costs more than the shorter chain gives.
-    if (B * H * ((Sq + BQ - 1) / BQ) <= 256 || Sq <= 32) {
+    // 23.5 -> 26.0: there the chip is full and reading K / V four times as often costs more than the shorter chain gives.  With
+    // Dh = 128 a CU holds fewer of its blocks, and it is full from three pieces of 32 queries on: 2 x 32 x 301 (640 pieces) above,
+    // but 8 x 32 x 128 (1024) 12.3 -> 14.1, E4M3 4 x 32 x 200 (896) 13.9 -> 14.8.
+    if ((B * H * ((Sq + BQ - 1) / BQ) <= 256 && (Dh == 64 || B * H * ((Sq + 31) / 32) <= 768)) || Sq <= 32) {
         if (fp8) return Dh == 64 ? launch_split<64, HERO_F8E4M3, 4>(a, out_dt, st) : launch_split<128, HERO_F8E4M3, 4>(a, out_dt, st);
         return Dh == 64 ? launch_split<64, HERO_I8, 4>(a, out_dt, st) : launch_split<128, HERO_I8, 4>(a, out_dt, st);
     }
