@@ -531,9 +531,11 @@ hero_status launch_r(const LnArgs& a, hipStream_t st) {
     if (nch <= 1) return launch_nch<XDT, RDT, 1>(a, st);
     if (nch <= 2) return launch_nch<XDT, RDT, 2>(a, st);
     if constexpr (XDT != HERO_I8 && RDT < 0) {
-        if (a.gamma && hero_aligned16(a.gamma) && hero_aligned16(a.beta)) {   // 16-bit rows of more than 1024 values (the residual stream): a workgroup per row
-            // (measured, D = 4096 bf16, us, before -> now: 3 rows 7.0 -> 4.1, 64 rows 8.0 -> 4.8, 602 rows 8.7 -> 5.8,
-            // 16384 rows 56 -> 40 = 5 TB/s)
+        // 16-bit rows of more than 1024 values (the residual stream): a workgroup per row.  Rows of up to 2048 values give
+        // each of its threads one chunk at most between three barriers: many of them stay with a wave per row.
+        // (measured, bf16, us, wave -> workgroup: D = 4096, 3 rows 6.4 -> 3.2, 64 rows 6.8 -> 3.5, 602 rows 7.2 -> 4.6, 16384 rows 51 -> 35
+        // = 5.8 TB/s; D = 2048, 64 rows 4.5 -> 3.1, 1500 rows 5.2 -> 4.8, 4096 rows 7.5 -> 8.0, 16384 rows 19.8 -> 22.0)
+        if ((nch > 4 || a.M <= 2048) && a.gamma && hero_aligned16(a.gamma) && hero_aligned16(a.beta)) {
             const unsigned blocks = (unsigned)(a.M < LN_ROW_BLOCKS ? a.M : LN_ROW_BLOCKS);
             if (nch <= 4) hipLaunchKernelGGL((ln_quant_row_kernel<XDT, 1>), dim3(blocks), dim3(256), 0, st, a);
             else hipLaunchKernelGGL((ln_quant_row_kernel<XDT, 2>), dim3(blocks), dim3(256), 0, st, a);
