@@ -61,3 +61,11 @@ def test_few_rows_of_many_columns_keep_small_tiles(dt):
         for kb in (1024, 4096, 8192):
             assert kernel(dt, 1, N, kb) == {1024: "64x64", 4096: "32x64/2", 8192: "32x64/4"}[kb]
             assert kernel(dt, 33, N, kb) == kernel(dt, 64, N, kb) == "64x64"
+
+
+def test_ring_test_shapes_reach_every_form():
+    """The shapes of the ring kernel's GPU tests select every form, with whole slabs and with half a one, for every type."""
+    from test_gpu_gemm_ring import SHAPES
+    for dt in DTYPES:
+        for half in (0, 64):
+            assert set(FORMS) <= {kernel(dt, M, N, kb) for M, N, kb in SHAPES if kb % 128 == half}

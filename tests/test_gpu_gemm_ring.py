@@ -1,6 +1,6 @@
 """The direct-to-LDS ring GEMM (small and middling problems): every form of its rule at the edges of its tiles, against the
 same product in 64 bits.  Shapes: one row / one column past a tile, ragged N, K of one slab, K that the K groups share
-unevenly (empty groups among them), K that is no whole slab (the register-staged kernel)."""
+unevenly (empty groups among them), K that ends in half a slab.  test_gemm_routes.py checks that they reach every form."""
 import pytest
 import torch
 
@@ -16,14 +16,17 @@ SHAPES = [
     (7, 4000, 8192 + 128),   # 32x32, four groups, 65 slabs
     (31, 12284, 2176),       # 32x64, two groups, 17 slabs
     (32, 12300, 8192),       # 32x64, four groups
-    (65, 2308, 640),         # 64x32
+    (65, 2308, 640),         # 32x32, five slabs over eight groups, three row tiles
+    (65, 3076, 640),         # 64x32, four groups
+    (100, 4092, 4224),       # 64x32, four groups, 33 slabs
+    (127, 3000, 128),        # 64x32, one slab for four groups
     (651, 764, 3072),        # 32x64, four groups, many row tiles
     (129, 4612, 768),        # 64x64, two groups
     (100, 12292, 4224),      # 128x64, two groups, 33 slabs
     (641, 2052, 384),        # 64x64
     (300, 10244, 4096),      # 128x128
     (1025, 2300, 1024),      # 128x64
-    (65, 260, 192),          # K is one and a half slabs
+    (65, 260, 192),          # 32x32, one and a half slabs
     # few rows of many columns
     (3, 36868, 4096),        # 32x64, two groups, more tiles than a round
     (64, 33004, 1024),       # 64x64

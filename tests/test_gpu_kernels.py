@@ -445,9 +445,8 @@ def test_gemm_skinny_split_k_workspace(hero, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(64, 4096, 4096), (37, 1000, 2048), (64, 12288, 4096), (5, 8264, 2176), (64, 8200, 2112), (1, 16384, 4096)])
 def test_gemm_skinny_one_pass_forms(hero, M, N, K):
-    """One row of tiles (M <= 64, a decode step) without a scratch: 64 x 32 tiles with eight slabs in flight up to
-    128 tiles of 64 x 64, two K groups per workgroup beyond (the last shape has an odd slab count and takes the plain
-    tile).  Every epilogue in its class: raw / REQUANT / DEQUANT (+ residual, in place) bit-exact, GELU^quant +-1."""
+    """One row of tiles (M <= 64, a decode step) without a scratch: the ring kernel's forms for few rows (one shape has an odd
+    number of 64-byte pieces of K).  Every epilogue in its class: raw / REQUANT / DEQUANT (+ residual, in place) bit-exact, GELU^quant +-1."""
     c = synth.gemm_case(900 + M + N % 97, M, K, N)
     A, Bt, rs, cs, bias = c["A"], c["Bt"], c["a_row_scale"], c["b_col_scale"], c["bias"]
     dA, dB = dev(A), dev(Bt)
@@ -673,7 +672,7 @@ def test_fp8_gemm_matches_oracle(hero, M, N, K, tile):
     (the oracle carries the exact sum), the INT8 path's epilogue.  16-bit outputs within 2e-2, E4M3 outputs equal
     up to an adjacent code on <= 0.5 %.  The large shapes run the persistent kernels with ragged edges: by
     default the 256 x 256 one (182 tiles) and the 128 x 128 one (110 tiles of 256 x 256), then each the other one.
-    The last shape (few tiles, K = 2304) runs the workgroup with four K groups: fp32 partial sums added through LDS."""
+    The last shape (few tiles, K = 2304) runs a form with K groups: fp32 partial sums added through LDS."""
     tile = None if tile is None else int(tile)
     g = synth.rng(1300 + M)
     X = (g.standard_normal((M, K)) * g.uniform(0.5, 4, (M, 1))).astype(np.float32)
@@ -760,6 +759,40 @@ def test_fp8_attn_matches_oracle(hero, B, Sq, Skv, H, Dh, mask):
         gotb = hero.hero_fp8_attn(dev(q), dev(k), dev(v), qk_scale, sp, dev(sc), out_scale_is_scalar=True,
                                   mask=mask, kv_len=dev(kv_len), out_dtype=tdt)
         assert_fp8_attn_values(cvt(to_np(gotb)), cvt(refb), "16-bit output", flip_bound=D / cs[None, :] * sc[0])
+
+
+def _repeated(reps, *arrays):
+    return [None if a is None else dev(np.concatenate([a] * reps)) for a in arrays]
+
+
+@pytest.mark.parametrize("mask", [O.MASK_NONE, O.MASK_PADDING, O.MASK_CAUSAL])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("B,Sq,Skv,H,Dh", ATTN_SHAPES)
+def test_block_attn_matches_oracle(hero, B, Sq, Skv, H, Dh, fp8, mask):
+    """The shapes above are few query blocks, whose keys are split over a block's waves.  The same sequences repeated until there
+    are more 128-query blocks than CUs run the 128-query kernel: every repeat alike, and the oracle's codes."""
+    reps = 256 // (B * H * ((Sq + 127) // 128)) + 1
+    kv_len = None
+    if mask == O.MASK_PADDING:
+        kv_len = np.int32([Skv - 3, 0][:B]) if B == 2 else np.int32([Skv // 2 + 1])
+    if mask == O.MASK_CAUSAL and Sq != Skv:
+        kv_len = np.int32([Skv, Skv - 50][:B])
+    if fp8:
+        q, k, v, qk_scale, ps, cs = _fp8_attn_case(2000 + Sq + Dh, B, Sq, Skv, H, Dh)
+        ref = O.fp8_attn(q, k, v, qk_scale=qk_scale, p_scale=ps, out_col_scale=cs, mask=mask, kv_len=kv_len)
+    else:
+        q, k, v, qk_scale, cs = _attn_case(700 + Sq + Dh, B, Sq, Skv, H, Dh)
+        ps = float(OL.S_P)
+        ref = O.int8_attn(q, k, v, qk_scale=qk_scale, p_scale=ps, out_col_scale=cs, mask=mask, kv_len=kv_len)
+    dq, dk, dv, dl = _repeated(reps, q, k, v, kv_len)
+    fn = hero.hero_fp8_attn if fp8 else hero.hero_int8_attn
+    got = fn(dq, dk, dv, qk_scale, ps, dev(cs), mask=mask, kv_len=dl).view(torch.uint8).reshape(reps, B * Sq, H * Dh)
+    assert torch.equal(got, got[:1].expand_as(got))
+    if fp8:
+        D = fp8_attn_flip_bound(q, k, v, qk_scale, ps, cs, mask=mask, kv_len=kv_len)
+        assert_fp8_attn_codes(to_np(got[0]), ref, O.e4m3_to_f32, "X_attn fp8", flip_bound=D)
+    else:
+        assert_codes(to_np(got[0].view(torch.int8)), ref, "X_attn")
 
 
 def test_fp8_attn_views_cache_one_query_and_errors(hero):
