@@ -660,14 +660,14 @@ def other_workloads(hero, seed):
     del st
     torch.cuda.empty_cache()
     out["bert-large-32x512_M1"]["cpu_baseline"], _ = cpu_baseline(sh, seed, "M1")
-    # ---- config 0: eager and as a HIP graph (9 launches of a few microseconds each)
+    # ---- config 0: eager and as a HIP graph (7 launches of a few microseconds each)
     log("[bench] config 0 (BERT-base 1 x 128): eager and HIP graph")
     sh = synth.CONFIGS[0]
     st = Stack(hero, sh, seed, HB.MODE_M3)
     ms, _ = time_stack(st, 50)
-    out["bert-base-1x128_eager"] = workload_record(st, ms, "M3", False, launches=9)
+    out["bert-base-1x128_eager"] = workload_record(st, ms, "M3", False, launches=7)
     ms, _ = time_stack(st, 50, graph=True)
-    out["bert-base-1x128_graph"] = workload_record(st, ms, "M3", True, launches=9)
+    out["bert-base-1x128_graph"] = workload_record(st, ms, "M3", True, launches=7)
     del st
     cb, _ = cpu_baseline(sh, seed, "M3")
     out["bert-base-1x128_eager"]["cpu_baseline"] = cb
