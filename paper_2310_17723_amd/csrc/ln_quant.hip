@@ -97,8 +97,8 @@ __device__ __forceinline__ void store_hp(const float (&v)[EPL], uint16_t* dst) {
     }
 }
 
-// four codes behind a LayerNorm.  E4M3: of the true quotient, |y / s| <= 448 (1 + 2^-23) clamped to the format's range;
-// INT8: |v * inv_sc| <= 127 (1 + 2^-22), so v * inv_sc + 128 rounds into 1 .. 255
+// four codes.  E4M3 (the variant of Sec. 2.1's 8-bit format): of the true quotient, |y / s| <= 448 (1 + 2^-23) clamped to the
+// format's range; INT8 behind a LayerNorm: |v * inv_sc| <= 127 (1 + 2^-22), so v * inv_sc + 128 rounds into 1 .. 255
 __device__ __forceinline__ uint32_t codes4(const float* v, float sc, float inv_sc, bool f8) {
     if (f8) return fp8x4_sat(__fdiv_rn(v[0], sc), __fdiv_rn(v[1], sc), __fdiv_rn(v[2], sc), __fdiv_rn(v[3], sc));
     uint32_t w = 0;
@@ -324,22 +324,11 @@ __global__ __launch_bounds__(64 * ln_max_waves(NCH)) void ln_quant_kernel(LnArgs
             const int64_t off = row * (int64_t)D + j0;
             uint32_t pk[EPL / 4];
             if (a.y_fp8) {
-                // FP8 output (the variant of Sec. 2.1's 8-bit format): E4M3 of the true quotient, round to
-                // nearest even; |y / s| <= 448 (1 + 2^-23) is clamped to the format's range
 #pragma unroll
-                for (int e4 = 0; e4 < EPL / 4; ++e4)
-                    pk[e4] = fp8x4_sat(__fdiv_rn(v[c][4 * e4], sc), __fdiv_rn(v[c][4 * e4 + 1], sc),
-                                       __fdiv_rn(v[c][4 * e4 + 2], sc), __fdiv_rn(v[c][4 * e4 + 3], sc));
+                for (int e4 = 0; e4 < EPL / 4; ++e4) pk[e4] = codes4(v[c] + 4 * e4, sc, inv_sc, true);
             } else if constexpr (HAS_LN) {
-                // |v * inv_sc| <= 127 (1 + 2^-22): v * inv_sc + 128 rounds into 1 .. 255
 #pragma unroll
-                for (int e4 = 0; e4 < EPL / 4; ++e4) {
-                    uint32_t w = 0;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(v[c][4 * e4 + t], inv_sc, 128.0f), t, w);
-                    pk[e4] = w ^ 0x80808080u;
-                }
+                for (int e4 = 0; e4 < EPL / 4; ++e4) pk[e4] = codes4(v[c] + 4 * e4, sc, inv_sc, false);
             } else {
                 // |v * inv_sc| <= 127 (absmax row scale), so no clamp is needed before the rounding add
                 float t[EPL];
