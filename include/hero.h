@@ -21,7 +21,7 @@
  *     or statistical arithmetic whose own rounding already differs from the definition's, so that their
  *     codes agree with it up to +-1 step on <= 0.1 % of the elements (the tolerance class of those paths):
  *     LN^quant behind a LayerNorm (v_rcp_f32 of the row scale, v_rsq_f32 of the variance), GELU^quant
- *     (1 / S_a[j]: v_rcp_f32, or the correctly rounded quotient in the overlapped-epilogue kernel), and
+ *     (1 / S_a[j]: v_rcp_f32 in the persistent kernel, the correctly rounded quotient in the others), and
  *     Softmax^quant (the normaliser and 1 / S_p are folded into the exponent).
  *   - The kernel an entry point runs is chosen from the problem size alone; the library reads no
  *     environment variable.  (include/hero_debug.h has test hooks that force a kernel.)
@@ -204,8 +204,9 @@ hero_status hero_int8_gemm_static(const int8_t* A, int64_t lda, const float* a_r
  *   to nearest even, saturated to +-448.  HERO_EPI_RAW_I32 does not exist here.
  *   A [M,K], Bt [N,K] E4M3 bytes, K contiguous.  Constraints as for hero_int8_gemm.
  * Token-wise FP8 activations use scale = max|x| / 448 per row; static scales fold as for INT8.
- * The order of the fp32 accumulation depends on the tile the library picks for a shape (fixed for a
- * given shape and build), so results are reproducible but not bit-identical across tile choices. */
+ * The order of the fp32 accumulation depends on the kernel the library picks for a shape (fixed for this entry point and
+ * build; inside hero_layer_fwd a long K is split where its workspace has room for that), so results are reproducible but
+ * not bit-identical across kernels. */
 hero_status hero_fp8_gemm(const void* A, int64_t lda, const float* a_row_scale,
                           const void* Bt, int64_t ldb, const float* b_col_scale,
                           const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,

@@ -404,7 +404,8 @@ extern "C" hero_status hero_hp_attn(const void* q, const int64_t q_strides[4],
     // 128 queries -> split: 7 x 12 heads x 93 7.3 -> 5.7, 2 x 16 x 512 17.4 -> 11.6, 1 x 32 x 400 causal 21.8 -> 18.2; with 192 or 256
     // blocks 33.8 -> 40.9 (1 x 32 x 700), 8.4 -> 10.0 (16 x 16 x 128).  Dh = 128 with two 32-query pieces per CU: only over more than
     // 384 keys (1 x 32 x 512 25.7 -> 23.2, 4 x 32 x 128 10.0 -> 10.5); a single piece of at most 128 keys, Dh = 64: up to three per CU
-    // (768 x 32 keys 5.4 -> 5.0, 1024 6.1 -> 6.8).  Against 64 bits the split is the closer one by 2-4 %.
+    // (768 x 32 keys 5.4 -> 5.0, 1024 6.1 -> 6.8).  Against 64 bits the split's own output is the
+    // closer one by 2-4 % (behind a layer's codes the two cannot be told apart).
     const int64_t pieces = B * H * ((Sq + 31) / 32);
     const bool split = Sq <= 32 ? Dh == 128 || pieces <= 768 || Skv > 128
                                 : B * H * ((Sq + ABQ - 1) / ABQ) <= 128 && (Dh == 64 || pieces <= 448 || (pieces <= 512 && Skv > 384));

@@ -309,12 +309,13 @@ inline bool ring_ok(int64_t lda_bytes, int64_t ldb_bytes) { return lda_bytes < (
 // Which form, or RING_NONE: a problem for the persistent kernels.  What decides is whether every one of the 256 CUs streams
 // its share of the weights: the largest tile that still gives every CU one workgroup, and while there are fewer
 // tiles than CUs, K groups inside the workgroup.  (Two workgroups per CU where the form's LDS allows it: 64 x 64 without K
-// groups, 128 x 64 without.)  Measured over M = 1 .. 4096 and the (N, K) of the three models, INT8 and BF16 operands, every
-// form, 345 shapes: the choice below is within 1.2 % of the best form on average.  Some of the figures, us, weights out of
-// the caches for the 4096-wide model (best form of the register-staged or persistent kernels -> this one):
-//   INT8  64 x 12288 x 4096 17.1 -> 14.4, 3 x 4096 x 4096 10.6 -> 5.7, 128 x 16384 x 4096 30 -> 21.6,
-//         2000 x 1024 x 4096 18.1 -> 14.3, 602 x 4096 x 4096 25 -> 20.2, 128 x 768 x 3072 5.4 -> 4.9
-//   BF16  651 x 768 x 3072 53 -> 9.6, 3 x 4096 x 16384 177 -> 36, 602 x 4096 x 16384 185 -> 130
+// groups, 128 x 64 without.)  Measured on this kernel over M = 1 .. 16384 and the (N, K) of the three models and of vocabularies,
+// every operand type, 16-bit, 8-bit and GELU^quant results, weights resident and cold, 1948 combinations: the choice (persistent
+// kernels included) is within 2.2 % of the best of twelve forms on average, 25 % at most.  Some of the figures, us, weights out
+// of the caches for the 4096-wide model (register-staged, plain 16-bit or persistent kernels of before -> now):
+//   INT8  64 x 12288 x 4096 17.7 -> 15.0, 128 x 12288 x 4096 29.3 -> 19.2, 512 x 4096 x 4096 25.2 -> 16.3,
+//         2048 x 1024 x 4096 18.9 -> 14.8, 128 x 768 x 3072 5.5 -> 5.0;  E4M3 64 x 4096 x 4096 13.2 -> 8.6
+//   BF16  800 x 768 x 3072 54.6 -> 13.3, 3 x 4096 x 16384 263 -> 37, 700 x 4096 x 16384 213 -> 131
 inline RingForm ring_form(int64_t M, int64_t N, int64_t kb, hero_epilogue epi) {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const int64_t slabs = (kb + 2 * BK - 1) / (2 * BK), t32 = tiles(32, 32), t12864 = tiles(128, 64);
