@@ -774,8 +774,8 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
 // ------------------------------------------------------------------------------------------
 constexpr int DEC_MAX_KEYS = 16384;
 
-// The value of lane ^ O (O a power of two), where every lane that agrees in the lower bits of log2 O already holds the same in
-// the bits above (a butterfly from the top down, or from the bottom up for O <= 2): data-parallel moves, no trip through LDS.
+// The value of lane ^ O by data-parallel moves, without a trip through LDS.  O = 4, 8: only where lanes that differ in no bit
+// below 2 O hold the same already (a butterfly from the top down), since the move is a rotation within 16 lanes.
 template <int O, typename T>
 __device__ __forceinline__ T lane_xor(T x) {
     const uint32_t b = __builtin_bit_cast(uint32_t, x);
