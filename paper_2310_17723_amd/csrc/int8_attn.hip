@@ -774,8 +774,8 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
 // ------------------------------------------------------------------------------------------
 constexpr int DEC_MAX_KEYS = 16384;
 
-// The value of lane ^ O by data-parallel moves, without a trip through LDS.  O = 4, 8: only where lanes that differ in no bit
-// below 2 O hold the same already (a butterfly from the top down), since the move is a rotation within 16 lanes.
+// The value of lane ^ O by data-parallel moves, without a trip through LDS.  O = 4 is a rotation within 16 lanes: only where lanes
+// that agree in their three lowest bits hold the same already (a butterfly from the top down).
 template <int O, typename T>
 __device__ __forceinline__ T lane_xor(T x) {
     const uint32_t b = __builtin_bit_cast(uint32_t, x);
