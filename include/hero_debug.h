@@ -41,7 +41,7 @@ hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void* Wt, int64_
 
 /* Which kernel hero_int8_gemm (dt HERO_I8), hero_fp8_gemm (HERO_F8E4M3) or hero_hp_gemm (HERO_BF16 / HERO_F16) runs for a
  * product without residual and without scratch, with the epilogue `epi`.  Returns a tile code as above (3 = 64x64 tile
- * staged through registers) or, for the ring kernel, 16 + its form: 0 = 32x32 with eight K groups, 1 = 32x32 with four,
+ * staged through registers, 4 = the weight-streaming kernel of few rows) or, for the ring kernel, 16 + its form: 0 = 32x32 with eight K groups, 1 = 32x32 with four,
  * 2 / 3 = 32x64 with two / four, 4 = 64x32 with four, 5 = 64x64 with two, 6 = 64x64, 7 = 128x64 with two, 8 = 128x64,
  * 9 = 128x128.  Launches nothing. */
 int hero_gemm_kernel(hero_dtype dt, hero_epilogue epi, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb);

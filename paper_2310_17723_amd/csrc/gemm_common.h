@@ -340,6 +340,16 @@ inline RingForm ring_form(int64_t M, int64_t N, int64_t kb, hero_epilogue epi) {
     if (t12864 <= 512 || (epi != HERO_EPI_REQUANT && !gelu && slabs <= 8 && t12864 <= 1024)) return RING_128x64;
     return RING_NONE;
 }
+// The weight-streaming kernel of few rows (gemm_skinny.hip): whole 16-column tiles, K in eight equal parts.  Beyond three tiles
+// per CU the ring's 64-column tiles stream as well (32-bit-per-lane offsets as there), and below 4 MB of weights a product is
+// a launch.  us, cold weights, ring (with the K split where it is one) -> this:
+//   INT8 3 x 4096 x 4096 7.3 -> 6.0, 3 x 4096 x 16384 18.6 -> 13.6, 24 rows 18.9 -> 16.1, 3 x 12288 x 4096 11.8 -> 11.2, 24 rows 12.3
+//   -> 12.3, 16 x 2560 x 10240 12.7 -> 10.4, 32 x 1024 x 4096 5.6 -> 4.8;  E4M3 24 x 4096 x 4096 8.4 -> 6.9;  BF16 3 x 4096 x 8192 39
+//   -> 26, 32 x 2048 x 4096 8.1 -> 6.6;  not taken: INT8 24 x 16384 x 4096 14.4 / 15.0, 3 x 32768 x 1024 8.6 / 10.9
+inline bool skinny_ok(int64_t M, int64_t N, int64_t kb, int64_t lda_bytes, int64_t ldb_bytes, int64_t max_n = 12288) {
+    return M <= 32 && N % 16 == 0 && N <= max_n && kb % (8 * 2 * BK) == 0 && N * kb >= (4 << 20) && ring_ok(lda_bytes, ldb_bytes);
+}
+hero_status launch_skinny(const GemmArgs& g, hero_dtype adt, hero_epilogue epi, hero_dtype c_dt, hipStream_t st);
 template <int ADT, int EPI, int CDT, int RDT, bool HALF> hero_status launch_ring_slabs(const GemmArgs& g, RingForm f, hipStream_t st);
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_ring(const GemmArgs& g, RingForm f, hipStream_t st) {

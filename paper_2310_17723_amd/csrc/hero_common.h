@@ -53,6 +53,11 @@ hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t 
                             void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt,
                             void* workspace, size_t workspace_bytes, void* stream);
 
+// LN^quant and the linear behind it in one launch (gemm_skinny.hip), or HERO_ERR_UNSUPPORTED
+hero_status hero_ln_gemm(const void* h, hero_dtype h_dt, const float* gamma, const float* beta, float eps,
+                         const void* Wt, const float* w_scale, const float* bias, hero_epilogue epi, const float* out_col_scale,
+                         void* C, hero_dtype c_dt, int64_t ldc, int64_t M, int64_t N, int64_t K, bool fp8, void* stream);
+
 // one decode step's attention, the new K / V rows appended to the cache by the same kernel (int8_attn.hip)
 hero_status hero_attn_decode_append(const int8_t* q, const int64_t q_strides[4], const int8_t* kn, const int8_t* vn, int64_t nstride,
                                     int8_t* kc, int8_t* vc, const int64_t c_strides[4], int64_t B, int64_t H, int64_t Smax, int64_t Dh,
@@ -155,6 +160,36 @@ __device__ __forceinline__ float gelu_erf(float x) {
     p = fmaf(p, z, -9.999930859e-01f);
     const float q = __builtin_amdgcn_exp2f(p);          // Phi(-|x|)
     return fmaf(-fabsf(x), q, fmaxf(x, 0.0f));
+}
+
+// four codes of LN^quant.  E4M3 (the variant of Sec. 2.1's 8-bit format): of the true quotient, |y / s| <= 448 (1 + 2^-23) clamped to the
+// format's range; INT8 behind a LayerNorm: |v * inv_sc| <= 127 (1 + 2^-22), so v * inv_sc + 128 rounds into 1 .. 255
+__device__ __forceinline__ uint32_t ln_codes4(const float* v, float sc, float inv_sc, bool f8) {
+    if (f8) return fp8x4_sat(__fdiv_rn(v[0], sc), __fdiv_rn(v[1], sc), __fdiv_rn(v[2], sc), __fdiv_rn(v[3], sc));
+    uint32_t w = 0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(v[t], inv_sc, 128.0f), t, w);
+    return w ^ 0x80808080u;
+}
+
+// ---- 64-lane reductions on the DPP network; the result is wave-uniform ---------------------------
+template <bool IS_MAX>
+__device__ __forceinline__ float dpp_step(float x, float y) { return IS_MAX ? fmaxf(x, y) : x + y; }
+template <bool IS_MAX>
+__device__ __forceinline__ float wave_reduce(float x) {
+    int xi;
+#define HERO_DPP(ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), ctrl, 0xF, 0xF, true))
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0xB1));      // quad_perm [1,0,3,2]
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0x4E));      // quad_perm [2,3,0,1]
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0x141));     // row_half_mirror: 8 lanes
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0x140));     // row_mirror: 16 lanes (every lane holds its row's value)
+#undef HERO_DPP
+    // rows 1,3 take lane 15 of the row before; then rows 2,3 take lane 31: lane 63 has all four rows
+    xi = __builtin_amdgcn_update_dpp(IS_MAX ? __builtin_bit_cast(int, -INFINITY) : 0, __builtin_bit_cast(int, x), 0x142, 0xA, 0xF, false);
+    x = dpp_step<IS_MAX>(x, __builtin_bit_cast(float, xi));
+    xi = __builtin_amdgcn_update_dpp(IS_MAX ? __builtin_bit_cast(int, -INFINITY) : 0, __builtin_bit_cast(int, x), 0x143, 0xC, 0xF, false);
+    x = dpp_step<IS_MAX>(x, __builtin_bit_cast(float, xi));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
 
 // ---- wave reductions (64 lanes) ---------------------------------------------------------

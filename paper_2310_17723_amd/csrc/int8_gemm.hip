@@ -9,7 +9,7 @@
 // lane l holds, for ONE output row m = l % 32, the columns n = 8g + 4(l/32) + t (register
 // 4g + t): the per-row scale is one register and a lane owns 4 consecutive columns.
 //
-// Four main loops share one epilogue (gemm_common.h):
+// The main loops; all but the skinny one's share one epilogue (gemm_common.h):
 //   * int8_gemm_persistent_kernel (large problems): 256x256 block tile, 8 waves of 128x64,
 //     slabs of 64 bytes of K copied global -> LDS directly (global_load_lds_dwordx4) through
 //     a ring of 4 stages; one workgroup per CU walks its tiles and the ring runs through the
@@ -18,6 +18,7 @@
 //     twice the L2 -> LDS traffic and is 10-15 % slower once every CU has work.
 //   * int8_gemm_dma_kernel: the same tile, one tile per workgroup (short K, huge strides).
 //   * int8_gemm_ring_kernel (gemm_ring.h; small and middling problems): 32x32 .. 128x128 tiles, 128-byte slabs, K groups.
+//   * skinny_gemm_kernel (gemm_skinny.hip; up to 32 rows): a stream of the weights.
 //   * int8_gemm_kernel (rows too far apart for 32-bit offsets; a short K that ends in half a slab, over many rows): 128x128 /
 //     64x64 tile staged through registers.
 // The epilogue works in registers: a lane-half exchange (v_permlane32_swap) gives every lane a
@@ -1075,7 +1076,7 @@ inline bool small_tile_fills_better(int64_t t256, int64_t t128) {
 }
 
 // What runs a product.  The codes of the kernels are those of the test hooks (include/hero_debug.h).
-enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_PERS256 = 7, K_PERS128 = 8, K_OVL = 9 };
+enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_SKINNY = 4, K_PERS256 = 7, K_PERS128 = 8, K_OVL = 9 };
 struct Choice { Kernel kernel; RingForm form; };
 
 // kb, lda, ldb in bytes; res: a fused residual.  tile: -1 chooses, otherwise the code a test hook
@@ -1100,6 +1101,7 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, bool res, int64_t M, int
         if (tile == K_RING || (tile == 0 && (adt == HERO_BF16 || adt == HERO_F16))) return small;
         return {tile == K_DMA256 ? K_DMA256 : K_REG128, RING_NONE};
     }
+    if (epi != HERO_EPI_RAW_I32 && skinny_ok(M, N, kb, lda, ldb)) return {K_SKINNY, RING_NONE};
     if (form != RING_NONE) return small;
     if (pers_ok) {
         if (t256 < 160 || small_tile_fills_better(t256, t128)) return {K_PERS128, RING_NONE};
@@ -1131,6 +1133,7 @@ hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
         if constexpr (ADT == HERO_I8) return launch_grid(g, 256, 256, 512, int8_gemm_dma_kernel<256, 256, 2, 4, 4, 2, EPI, CDT, RDT>, st);
         else return HERO_ERR_UNSUPPORTED;
     case K_RING: return launch_ring<ADT, EPI, CDT, RDT>(g, c.form, st);
+    case K_SKINNY: return launch_skinny(g, (hero_dtype)ADT, (hero_epilogue)EPI, (hero_dtype)CDT, st);
     case K_REG64: return launch_grid(g, 64, 64, 256, int8_gemm_kernel<64, 64, 2, 2, 2, 2, EPI, CDT, RDT, ADT>, st);
     default: return launch_grid(g, 128, 128, 256, int8_gemm_kernel<128, 128, 2, 2, 2, 2, EPI, CDT, RDT, ADT>, st);
     }
@@ -1139,8 +1142,9 @@ hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
     hero_status split;
-    if (tile < 0 && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
     const Choice c = choose((hero_dtype)ADT, (hero_epilogue)EPI, RDT >= 0, g.M, g.N, g.K, g.lda, g.ldb, tile);
+    // (a few column tiles of a very long K leave most CUs to the split: INT8 16 x 512 x 16384 10.5 us split, 11.6 as eight waves' work)
+    if (tile < 0 && (c.kernel != K_SKINNY || (g.N <= 512 && g.K > 8192)) && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
     return launch_choice<ADT, EPI, CDT, RDT>(g, c, st);
 }
 

@@ -205,14 +205,26 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                               (hero_mask)desc->mask, io->kv_len, attn, out_dt, d, stream);
     };
 
+    // A pre-LN layer's LN^quant and the 8-bit linear behind it (QKV, FC1) in one launch, where that takes the shape (few rows);
+    // HERO_ERR_UNSUPPORTED otherwise: the two are then launched one after the other.
+    auto ln_linear = [&](const float* lg, const float* lb, const void* wt, const float* ws_, const float* bias, hero_epilogue epi,
+                         const float* S_out, void* C, hero_dtype c_dt, int64_t N) -> hero_status {
+        if (!pre) return HERO_ERR_UNSUPPORTED;
+        return hero_ln_gemm(io->h, HP, lg, lb, desc->eps, wt, ws_, bias, epi, S_out, C, c_dt, N, T, N, d, (mode & HERO_M_FP8) != 0, stream);
+    };
+
     // ---- the FP8 variant (Sec. 2.1): the same chain with E4M3 codes in every 8-bit buffer
     if (mode & HERO_M_FP8) {
         const hero_dtype F8 = HERO_F8E4M3;
-        if (pre)
-            HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln1_g, w->ln1_b, desc->eps,
-                                       T, d, xin_q, xin_s, nullptr, HERO_BF16, stream));
-        HERO_TRY(hero_fp8_gemm_prefetching(xin_q, d, xin_s, w->w_qkv, d, w->w_qkv_s, w->b_qkv, nullptr, HERO_BF16, 0,
-                                           HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d, T, 3 * d, d, gws, gws_bytes, stream, w->w_o, (size_t)(d * d)));
+        hero_status fused = ln_linear(w->ln1_g, w->ln1_b, w->w_qkv, w->w_qkv_s, w->b_qkv, HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d);
+        if (fused != HERO_ERR_UNSUPPORTED) HERO_TRY(fused);
+        else {
+            if (pre)
+                HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln1_g, w->ln1_b, desc->eps,
+                                           T, d, xin_q, xin_s, nullptr, HERO_BF16, stream));
+            HERO_TRY(hero_fp8_gemm_prefetching(xin_q, d, xin_s, w->w_qkv, d, w->w_qkv_s, w->b_qkv, nullptr, HERO_BF16, 0,
+                                               HERO_EPI_REQUANT, nullptr, qkv, F8, 3 * d, T, 3 * d, d, gws, gws_bytes, stream, w->w_o, (size_t)(d * d)));
+        }
         HERO_TRY(attend8(true));
         if (!pre) {
             HERO_TRY(hero_fp8_gemm_prefetching(attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, nullptr, HERO_BF16, 0,
@@ -222,11 +234,16 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
         } else {
             HERO_TRY(hero_fp8_gemm_prefetching(attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, io->h, HERO_BF16, d,
                                                HERO_EPI_DEQUANT, nullptr, io->h, HERO_BF16, d, T, d, d, gws, gws_bytes, stream, w->w_1, (size_t)(f * d)));
-            HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
-                                       T, d, mid_q, mid_s, nullptr, HERO_BF16, stream));
         }
-        HERO_TRY(hero_fp8_gemm_prefetching(mid_q, d, mid_s, w->w_1, d, w->w_1_s, w->b_1, nullptr, HERO_BF16, 0,
-                                           HERO_EPI_GELU_REQUANT, w->S_a, act, F8, f, T, f, d, gws, gws_bytes, stream, w->w_2, (size_t)(d * f)));
+        fused = ln_linear(w->ln2_g, w->ln2_b, w->w_1, w->w_1_s, w->b_1, HERO_EPI_GELU_REQUANT, w->S_a, act, F8, f);
+        if (fused != HERO_ERR_UNSUPPORTED) HERO_TRY(fused);
+        else {
+            if (pre)
+                HERO_TRY(hero_ln_quant_fp8(io->h, HERO_BF16, nullptr, nullptr, F8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
+                                           T, d, mid_q, mid_s, nullptr, HERO_BF16, stream));
+            HERO_TRY(hero_fp8_gemm_prefetching(mid_q, d, mid_s, w->w_1, d, w->w_1_s, w->b_1, nullptr, HERO_BF16, 0,
+                                               HERO_EPI_GELU_REQUANT, w->S_a, act, F8, f, T, f, d, gws, gws_bytes, stream, w->w_2, (size_t)(d * f)));
+        }
         if (!pre) {
             HERO_TRY(hero_fp8_gemm_prefetching(act, f, nullptr, w->w_2, f, w->w_2_s, w->b_2, nullptr, HERO_BF16, 0,
                                                HERO_EPI_REQUANT, nullptr, x2, F8, d, T, d, f, gws, gws_bytes, stream, io->next_read, io->next_read_bytes));
@@ -240,14 +257,19 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     }
 
     // (1) PRE_LN: LN^quant of the residual stream (with its 16-bit copy when the QKV module is 16-bit)
-    if (pre)
+    const hero_epilogue epi_qkv = attn_i8 ? HERO_EPI_REQUANT : HERO_EPI_DEQUANT;
+    const hero_status fused1 = q_i8 ? ln_linear(w->ln1_g, w->ln1_b, w->w_qkv, w->w_qkv_s, w->b_qkv, epi_qkv, nullptr, qkv,
+                                                attn_i8 ? HERO_I8 : HP, 3 * d) : HERO_ERR_UNSUPPORTED;
+    const bool two1 = fused1 == HERO_ERR_UNSUPPORTED;
+    if (!two1) HERO_TRY(fused1);
+    if (pre && two1)
         HERO_TRY(hero_ln_quant(io->h, HP, nullptr, nullptr, HERO_I8, nullptr, w->ln1_g, w->ln1_b, desc->eps,
                                T, d, xin_q, xin_s, q_i8 ? nullptr : xin_hp, HP, stream));
     // (2) QKV: SQ codes for an INT8 attention (bare Round), 16-bit values otherwise
-    if (q_i8)
+    if (!two1) {}                                                        // (done with its LN^quant)
+    else if (q_i8)
         HERO_TRY(hero_int8_gemm_prefetching(xin_q, d, xin_s, w->w_qkv, d, w->w_qkv_s, w->b_qkv, nullptr, HP, 0,
-                                            attn_i8 ? HERO_EPI_REQUANT : HERO_EPI_DEQUANT, nullptr,
-                                            qkv, attn_i8 ? HERO_I8 : HP, 3 * d, T, 3 * d, d, gws, gws_bytes, stream,
+                                            epi_qkv, nullptr, qkv, attn_i8 ? HERO_I8 : HP, 3 * d, T, 3 * d, d, gws, gws_bytes, stream,
                                             o_i8 ? w->w_o : nullptr, (size_t)(d * d)));
     else
         HERO_TRY(hero_hp_gemm_ws(xin_hp, d, w->w_qkv_hp, d, w->b_qkv, nullptr, 0, 0, qkv, 3 * d, T, 3 * d, d, HP, gws, gws_bytes, stream));
@@ -263,6 +285,7 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
     // when FC1 is 16-bit
     const void* x1 = q_i8 ? (const void*)xin_q : (const void*)xin_hp;      // the layer input as LN^quant's first addend
     const hero_dtype x1_dt = q_i8 ? HERO_I8 : HP;
+    hero_status fused2 = HERO_ERR_UNSUPPORTED;
     if (!pre) {
         if (o_i8)
             HERO_TRY(hero_int8_gemm_prefetching((const int8_t*)attn, d, nullptr, w->w_o, d, w->w_o_s, w->b_o, nullptr, HP, 0,
@@ -279,11 +302,17 @@ extern "C" hero_status hero_layer_fwd(const hero_layer_desc* desc, const hero_la
                                                 fc1_i8 ? w->w_1 : nullptr, (size_t)(f * d)));
         else
             HERO_TRY(hero_hp_gemm_ws(attn, d, w->w_o_bf16, d, w->b_o, io->h, d, 0, io->h, d, T, d, d, HP, gws, gws_bytes, stream));
-        HERO_TRY(hero_ln_quant(io->h, HP, nullptr, nullptr, HERO_I8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
-                               T, d, mid_q, mid_s, fc1_i8 ? nullptr : mid_hp, HP, stream));
+        if (fc1_i8)
+            fused2 = ln_linear(w->ln2_g, w->ln2_b, w->w_1, w->w_1_s, w->b_1, fc2_i8 ? HERO_EPI_GELU_REQUANT : HERO_EPI_DEQUANT_GELU,
+                               w->S_a, act, fc2_i8 ? HERO_I8 : HP, f);
+        if (fused2 != HERO_ERR_UNSUPPORTED) HERO_TRY(fused2);
+        else
+            HERO_TRY(hero_ln_quant(io->h, HP, nullptr, nullptr, HERO_I8, nullptr, w->ln2_g, w->ln2_b, desc->eps,
+                                   T, d, mid_q, mid_s, fc1_i8 ? nullptr : mid_hp, HP, stream));
     }
     // (5) FC1 + GELU: GELU^quant codes for an INT8 FC2 (X_1 stays in registers), 16-bit values otherwise
-    if (fc1_i8)
+    if (fused2 != HERO_ERR_UNSUPPORTED) {}                               // (done with its LN^quant)
+    else if (fc1_i8)
         HERO_TRY(hero_int8_gemm_prefetching(mid_q, d, mid_s, w->w_1, d, w->w_1_s, w->b_1, nullptr, HP, 0,
                                             fc2_i8 ? HERO_EPI_GELU_REQUANT : HERO_EPI_DEQUANT_GELU, w->S_a,
                                             act, fc2_i8 ? HERO_I8 : HP, f, T, f, d, gws, gws_bytes, stream,

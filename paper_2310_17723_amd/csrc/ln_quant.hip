@@ -65,26 +65,6 @@ __device__ __forceinline__ void unpack4(int w, float (&o)[4], bool f8 = false) {
     }
 }
 
-// ---- 64-lane reductions on the DPP network; the result is wave-uniform ---------------------------
-template <bool IS_MAX>
-__device__ __forceinline__ float dpp_step(float x, float y) { return IS_MAX ? fmaxf(x, y) : x + y; }
-template <bool IS_MAX>
-__device__ __forceinline__ float wave_reduce(float x) {
-    int xi;
-#define HERO_DPP(ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), ctrl, 0xF, 0xF, true))
-    x = dpp_step<IS_MAX>(x, HERO_DPP(0xB1));      // quad_perm [1,0,3,2]
-    x = dpp_step<IS_MAX>(x, HERO_DPP(0x4E));      // quad_perm [2,3,0,1]
-    x = dpp_step<IS_MAX>(x, HERO_DPP(0x141));     // row_half_mirror: 8 lanes
-    x = dpp_step<IS_MAX>(x, HERO_DPP(0x140));     // row_mirror: 16 lanes (every lane holds its row's value)
-#undef HERO_DPP
-    // rows 1,3 take lane 15 of the row before; then rows 2,3 take lane 31: lane 63 has all four rows
-    xi = __builtin_amdgcn_update_dpp(IS_MAX ? __builtin_bit_cast(int, -INFINITY) : 0, __builtin_bit_cast(int, x), 0x142, 0xA, 0xF, false);
-    x = dpp_step<IS_MAX>(x, __builtin_bit_cast(float, xi));
-    xi = __builtin_amdgcn_update_dpp(IS_MAX ? __builtin_bit_cast(int, -INFINITY) : 0, __builtin_bit_cast(int, x), 0x143, 0xC, 0xF, false);
-    x = dpp_step<IS_MAX>(x, __builtin_bit_cast(float, xi));
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
-}
-
 template <int DT, int EPL>
 __device__ __forceinline__ void store_hp(const float (&v)[EPL], uint16_t* dst) {
 #pragma unroll
@@ -95,16 +75,6 @@ __device__ __forceinline__ void store_hp(const float (&v)[EPL], uint16_t* dst) {
             o[p] = (int)pack2_hp<DT>(v[8 * e8 + 2 * p], v[8 * e8 + 2 * p + 1]);
         *reinterpret_cast<v4i*>(dst + 8 * e8) = o;
     }
-}
-
-// four codes.  E4M3 (the variant of Sec. 2.1's 8-bit format): of the true quotient, |y / s| <= 448 (1 + 2^-23) clamped to the
-// format's range; INT8 behind a LayerNorm: |v * inv_sc| <= 127 (1 + 2^-22), so v * inv_sc + 128 rounds into 1 .. 255
-__device__ __forceinline__ uint32_t codes4(const float* v, float sc, float inv_sc, bool f8) {
-    if (f8) return fp8x4_sat(__fdiv_rn(v[0], sc), __fdiv_rn(v[1], sc), __fdiv_rn(v[2], sc), __fdiv_rn(v[3], sc));
-    uint32_t w = 0;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) w = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(v[t], inv_sc, 128.0f), t, w);
-    return w ^ 0x80808080u;
 }
 
 constexpr int ln_max_waves(int nch) { return nch <= 2 ? 16 : (nch == 4 ? 8 : 4); }   // per workgroup: the row must fit the registers
@@ -325,10 +295,10 @@ __global__ __launch_bounds__(64 * ln_max_waves(NCH)) void ln_quant_kernel(LnArgs
             uint32_t pk[EPL / 4];
             if (a.y_fp8) {
 #pragma unroll
-                for (int e4 = 0; e4 < EPL / 4; ++e4) pk[e4] = codes4(v[c] + 4 * e4, sc, inv_sc, true);
+                for (int e4 = 0; e4 < EPL / 4; ++e4) pk[e4] = ln_codes4(v[c] + 4 * e4, sc, inv_sc, true);
             } else if constexpr (HAS_LN) {
 #pragma unroll
-                for (int e4 = 0; e4 < EPL / 4; ++e4) pk[e4] = codes4(v[c] + 4 * e4, sc, inv_sc, false);
+                for (int e4 = 0; e4 < EPL / 4; ++e4) pk[e4] = ln_codes4(v[c] + 4 * e4, sc, inv_sc, false);
             } else {
                 // |v * inv_sc| <= 127 (absmax row scale), so no clamp is needed before the rounding add
                 float t[EPL];
@@ -469,7 +439,7 @@ __global__ __launch_bounds__(256) void ln_quant_row_kernel(LnArgs a) {
             const int64_t off = row * (int64_t)D + j0;
             uint32_t pk[2];
 #pragma unroll
-            for (int e4 = 0; e4 < 2; ++e4) pk[e4] = codes4(v[c] + 4 * e4, sc, inv_sc, a.y_fp8);
+            for (int e4 = 0; e4 < 2; ++e4) pk[e4] = ln_codes4(v[c] + 4 * e4, sc, inv_sc, a.y_fp8);
             *reinterpret_cast<v2i*>(a.y_q + off) = v2i{(int)pk[0], (int)pk[1]};
             if (a.hp_dt == HERO_BF16) store_hp<HERO_BF16, 8>(v[c], (uint16_t*)a.y_hp + off);
             else if (a.hp_dt == HERO_F16) store_hp<HERO_F16, 8>(v[c], (uint16_t*)a.y_hp + off);
