@@ -22,7 +22,7 @@
 // The kernel is bound by the plain-ALU work per score (exp2, conversion, rounding), not by
 // the matrix cores, so both passes are written to spend as few vector instructions per score
 // as possible (see the comment in front of pass 1).
-#include "hero_common.h"
+#include "gemm_common.h"          // direct global -> LDS loads
 #include <atomic>
 #include <type_traits>
 
@@ -534,6 +534,253 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
 }
 
 // ------------------------------------------------------------------------------------------
+// Up to 512 keys of 64 channels (the encoders): one pass.  The two-pass kernel above spends 15 vector slots per score, 8 of them the
+// two quarter-rate exp2, because a block's scores do not survive until the row sum is known.  Here they do: a wave takes 16 queries
+// at a time (v_mfma_*_16x16x64: lane l holds, for query l % 16, the keys 16 s + 4 (l / 16) + t of every 16-key step s), so that the
+// scores of up to 256 keys, later their exponentials, stay in 16 registers per 64 keys, and a code is one multiplication and one
+// packing conversion away: 10 slots per score (conversion, half a maximum, fma, exp2 (4), sum, product, packing conversion).  The
+// codes of a 64-key tile are the PV operand as they stand, V being staged transposed with its keys in the same order.
+// A block owns 128 queries of one (batch, head), in four groups of 32 (two sets of 16 each), and stages all of K (direct to LDS) and
+// V once.  KW waves share a group's keys: one up to 256 keys, then no barrier follows; two beyond (all scores of 512 keys in one wave's
+// registers leave two waves per SIMD, and 32 x 16 x 512 took 73 us, the two-pass kernel 69): the halves' maxima and sums meet in LDS,
+// and each wave ends with half of the channels.  The offset of the unsigned codes is removed by a second matrix instruction as in the
+// online variant, so o = -sum code * v.  Bound by the vector ALU; four waves per SIMD.
+// ------------------------------------------------------------------------------------------
+template <int ODT, int FMT, int NT, int KW>
+__global__ __launch_bounds__(256 * KW, 4) void int8_attn_keep_kernel(AttnArgs a) {
+    constexpr bool F8 = FMT == HERO_F8E4M3;
+    using V4 = typename std::conditional<F8, v4f, v4i>::type;
+    constexpr int DH = 64, NC = DH / 16, VLD = NT * 64, HG = 2, NW = 4 * KW, NH = NT / KW;       // NH: tiles of a wave
+    static_assert((NT == 2 || NT == 4 || NT == 8) && NH <= 4, "score registers");
+    __shared__ __attribute__((aligned(1024))) int8_t sK[NT * 64 * DH];       // 16-byte chunk c of key k at c ^ ((k >> 2) & 3)
+    // V transposed: key 64 i + 16 t + 4 g + j of a channel is byte 4 t + j of its 16-byte chunk 4 i + g, and chunk c of channel h lies at
+    // c ^ ((h ^ (h >> 4 << 2)) & 15): 16 channels' reads, and the transposed stores, fall into different banks
+    constexpr int VX = NT * 4 < 16 ? NT * 4 - 1 : 15;
+    __shared__ __attribute__((aligned(1024))) int8_t sVt[DH * VLD];
+    __shared__ __attribute__((aligned(16))) float scale[DH];
+    __shared__ float stat[KW == 1 ? 1 : 4 * KW * 32];                        // [group][half]: row maximum and row sum of 16 queries
+    __shared__ __attribute__((aligned(16))) V4 xch[KW == 1 ? 1 : 4 * 2 * 64];     // [group][2 channel groups][lane]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = wave & 3, kh = wave >> 2;
+    const int ql = lane & 15, gq = lane >> 4;
+    // blocks: order, rotation and the padding rule are those of the two-pass kernel
+    const int nqb = (a.Sq + BQ - 1) / BQ;
+    const int slot = blockIdx.x / 8, grp = (slot / (HG * nqb)) * 8 + (blockIdx.x % 8), within = slot % (HG * nqb);
+    const int bh = grp * HG + within / nqb;
+    if (bh >= a.B * a.H) return;
+    const uint32_t rot = ((uint32_t)(slot / (HG * nqb)) * 2654435761u) >> 20;
+    const int qb = (int)((within % nqb + rot) % (uint32_t)nqb);
+    const int b = bh / a.H, h = bh % a.H, q0 = qb * BQ;
+    const int len = a.kv_len ? min(max(a.kv_len[b], 0), a.Skv) : a.Skv;
+    const int shift = len - a.Sq;
+    const bool causal = a.mask == HERO_MASK_CAUSAL;
+    const int qlim = (a.mask == HERO_MASK_PADDING && a.Sq == a.Skv) ? len : a.Sq;
+    const int kmax = max(causal ? min(len, min(q0 + BQ, a.Sq) + shift) : len, 0);
+    const int ntiles = q0 < qlim ? (kmax + 63) / 64 : 0;
+    const int w0 = q0 + ((group + slot) & 3) * 32;                           // this wave's queries
+    v4i qf[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+        qf[s] = *reinterpret_cast<const v4i*>(a.q + (int64_t)b * a.qs[0] + (int64_t)min(w0 + s * 16 + ql, a.Sq - 1) * a.qs[1] + (int64_t)h * a.qs[2] + gq * 16);
+    const int8_t* const kbase = a.k + (int64_t)b * a.ks[0] + (int64_t)h * a.ks[2];
+    const int8_t* const vbase = a.v + (int64_t)b * a.vs[0] + (int64_t)h * a.vs[2];
+    {
+        // K: a load is 16 rows; lane l brings the chunk that belongs at position l % 4 of row l / 4.  V: wave w takes the tiles w, w + NW;
+        // a lane holds 16 channels of four keys.  Rows past the last key repeat it (masked below).
+        const int kr = lane >> 2, kc = ((lane & 3) ^ ((kr >> 2) & 3)) * 16;
+        const uint32_t kdst = __builtin_amdgcn_readfirstlane(hero_gemm::lds_offset(sK));
+        for (int u = wave; u < ntiles * 4; u += NW)
+            hero_gemm::dma16(kbase + (int64_t)min(u * 16 + kr, a.Skv - 1) * a.ks[1] + kc, kdst + u * 16 * DH);
+        constexpr int VU = (NT + NW - 1) / NW;
+        v4i rv[VU][4];
+        const int kg = lane >> 2, c4 = lane & 3;                             // four-key group of the tile, 16-channel group
+#pragma unroll
+        for (int u = 0; u < VU; ++u)
+            if (u * NW + wave < ntiles)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    rv[u][i] = *reinterpret_cast<const v4i*>(vbase + (int64_t)min((u * NW + wave) * 64 + kg * 4 + i, a.Skv - 1) * a.vs[1] + c4 * 16);
+#pragma unroll
+        for (int u = 0; u < VU; ++u)
+            if (u * NW + wave < ntiles) {
+                const int chunk = (u * NW + wave) * 4 + (kg & 3);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {                                // 4 x 4 byte transposes
+                    const uint32_t d0 = rv[u][0][w], d1 = rv[u][1][w], d2 = rv[u][2][w], d3 = rv[u][3][w];
+                    const uint32_t lo01 = __builtin_amdgcn_perm(d1, d0, 0x05010400u), hi01 = __builtin_amdgcn_perm(d1, d0, 0x07030602u);
+                    const uint32_t lo23 = __builtin_amdgcn_perm(d3, d2, 0x05010400u), hi23 = __builtin_amdgcn_perm(d3, d2, 0x07030602u);
+                    const uint32_t tr[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                                            __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        *reinterpret_cast<uint32_t*>(sVt + (c4 * 16 + w * 4 + j) * VLD + ((chunk ^ ((w * 4 + j) ^ (c4 << 2))) & VX) * 16 +
+                                                     (chunk & ~VX) * 16 + (kg >> 2) * 4) = tr[j];
+                }
+            }
+        if (tid < DH) scale[tid] = a.out_col_scale[a.scale_is_scalar ? 0 : h * DH + tid];
+        __builtin_amdgcn_s_waitcnt(hero_gemm::vmcnt_imm(0));                 // the direct loads are not the compiler's to wait for
+        __syncthreads();
+    }
+    const float c2 = a.qk_scale * 1.44269504088896340736f;
+    constexpr int MASKED = -0x40000000;
+    constexpr float FMASKED = -3.0e38f;
+    constexpr typename std::conditional<F8, float, int>::type HIDDEN = (typename std::conditional<F8, float, int>::type)(F8 ? FMASKED : (float)MASKED);
+    auto mfma = [](v4i x, v4i y, V4 c) {
+        if constexpr (F8) {                                                  // the upper half of K is zeros
+            const v8i x8 = {x[0], x[1], x[2], x[3], 0, 0, 0, 0}, y8 = {y[0], y[1], y[2], y[3], 0, 0, 0, 0};
+            return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x8, y8, c, 0, 0, 0, 0, 0, 0);
+        } else return __builtin_amdgcn_mfma_i32_16x16x64_i8(x, y, c, 0, 0, 0);
+    };
+    // a wave's i-th tile is KW i + kh.  Chunk 4 t + gq of channel 16 c + ql is at (gq ^ ql) ^ 4 (t ^ c) within its 16 (8): one of four (two)
+    // addresses per lane
+    constexpr int VK = VX == 15 ? 4 : 2;
+    const int8_t* const kf = sK + (kh * 64 + ql) * DH + ((gq ^ ((ql >> 2) & 3)) << 4);       // + 16 DH per step
+    int va[VK];
+#pragma unroll
+    for (int k = 0; k < VK; ++k) va[k] = ql * VLD + (((gq ^ ql ^ ((k ^ kh) << 2)) & VX) << 4);
+#pragma nounroll
+    for (int set = 0; set < 2; ++set) {
+        const v4i qs = set ? qf[1] : qf[0];
+        const int qfirst = w0 + set * 16, qi = qfirst + ql;
+        if (KW == 1 && qfirst >= a.Sq) break;                                    // (two halves meet at barriers: all sets run)
+        const int64_t orow = ((int64_t)b * a.Sq + qi) * a.ldo + (int64_t)h * DH;
+        const int nvis = max(causal ? min(len, qi + shift + 1) : len, 0);
+        // tiles this set sees, and the first of them that hides a key from one of its queries (both uniform)
+        const int last = max(causal ? min(len, min(qfirst + 16, a.Sq) + shift) : len, 0);
+        const int nt = qfirst < qlim ? (last + 63) / 64 : 0, edge = (max(causal ? min(len, qfirst + shift + 1) : len, 0)) / 64;
+        const int n = KW == 1 ? nt : (nt + 1 - kh) / 2;                          // this wave's tiles
+        V4 o[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) o[c] = V4{0, 0, 0, 0};
+        // `meet` turns this wave's maximum (log2 domain) and sum into the factor of its exponentials
+        auto meet = [&](float m2, float l) -> float {
+            if constexpr (KW == 1) return l > 0.0f ? __fdiv_rn(1.0f, l * a.p_scale) : 0.0f;       // a row that saw no key gets codes 0
+            else {
+                float* const st = stat + group * (KW * 32);
+                if (gq == 0) { st[kh * 32 + ql] = m2; st[kh * 32 + 16 + ql] = l; }
+                __syncthreads();
+                const float mo = st[(kh ^ 1) * 32 + ql], lo = st[(kh ^ 1) * 32 + 16 + ql], m = fmaxf(m2, mo);
+                if (!(m > -INFINITY)) return 0.0f;
+                const float f = __builtin_amdgcn_exp2f(m2 - m);
+                const float sum = kh == 0 ? fmaf(l, f, lo * __builtin_amdgcn_exp2f(mo - m)) : fmaf(lo, __builtin_amdgcn_exp2f(mo - m), l * f);
+                return __fdiv_rn(f, sum * a.p_scale);
+            }
+        };
+        auto run = [&](auto NTILE) {
+            constexpr int N = decltype(NTILE)::value;
+            V4 sc[N][4];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int t = KW * i + kh;
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    sc[i][s] = mfma(*reinterpret_cast<const v4i*>(kf + (KW * i * 4 + s) * 16 * DH), qs, V4{0, 0, 0, 0});
+                if (t >= edge) {
+                    const int lim = nvis - t * 64 - gq * 4;                      // key visible iff 16 s + j < lim
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) sc[i][s][j] = 16 * s + j < lim ? sc[i][s][j] : HIDDEN;
+                }
+            }
+            auto smax = sc[0][0][0];
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) smax = max(max(max(max(smax, sc[i][s][0]), sc[i][s][1]), sc[i][s][2]), sc[i][s][3]);
+            smax = max(smax, __shfl_xor(smax, 16));
+            smax = max(smax, __shfl_xor(smax, 32));
+            const bool any = F8 ? (float)smax > FMASKED : (int)smax > MASKED;    // the same in all lanes of a query
+            const float m2 = any ? (float)smax * c2 : 0.0f;                      // (nothing visible: every exponential is 0)
+            float l = 0.0f;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                float lt = 0.0f;
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float e = __builtin_amdgcn_exp2f(fmaf((float)sc[i][s][j], c2, -m2));
+                        if constexpr (F8) sc[i][s][j] = e; else sc[i][s][j] = __float_as_int(e);
+                        lt += e;
+                    }
+                l += lt;
+            }
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            const float r = meet(any ? m2 : -INFINITY, any ? l : 0.0f);
+            auto ev = [&](int i, int s, int j) { if constexpr (F8) return sc[i][s][j]; else return __int_as_float(sc[i][s][j]); };
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                v4i pf;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    if constexpr (F8) {
+                        const int w = __builtin_amdgcn_cvt_pk_fp8_f32(fminf(ev(i, s, 0) * r, 448.0f), fminf(ev(i, s, 1) * r, 448.0f), 0, false);
+                        pf[s] = __builtin_amdgcn_cvt_pk_fp8_f32(fminf(ev(i, s, 2) * r, 448.0f), fminf(ev(i, s, 3) * r, 448.0f), w, true);
+                    } else {
+                        uint32_t w = 0;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) w = __builtin_amdgcn_cvt_pk_u8_f32(ev(i, s, j) * r, j, w);
+                        pf[s] = (int)(w ^ 0x7f7f7f7fu);                          // 127 - code as signed bytes
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const v4i v = *reinterpret_cast<const v4i*>(sVt + va[(c ^ (KW * i)) & (VK - 1)] + c * 16 * VLD + (KW * i / VK) * VK * 64);
+                    o[c] = mfma(v, pf, o[c]);
+                    if constexpr (!F8) o[c] = mfma(v, v4i{(int)0x81818181u, (int)0x81818181u, (int)0x81818181u, (int)0x81818181u}, o[c]);    // * -127
+                }
+            }
+        };
+        if (n == 1) run(std::integral_constant<int, 1>{});
+        else if (n == 2) run(std::integral_constant<int, 2>{});
+        else if (NH > 2 && n == 3) run(std::integral_constant<int, (NH > 2 ? 3 : 1)>{});
+        else if (NH > 2 && n == 4) run(std::integral_constant<int, (NH > 2 ? 4 : 1)>{});
+        else meet(-INFINITY, 0.0f);
+        if constexpr (KW == 2) {
+            // halves of the keys -> halves of the channels
+            V4* const x = xch + group * 128 + lane;
+            if (kh == 1) { x[0] = o[0]; x[64] = o[1]; }
+            __syncthreads();
+            if (kh == 0) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const V4 p = x[c * 64];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) o[c][t] += p[t];
+                    x[c * 64] = o[2 + c];
+                }
+            }
+            __syncthreads();
+            if (kh == 1) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const V4 p = x[c * 64];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) o[c][t] = p[t] + o[2 + c][t];
+                }
+            }
+        }
+        if (qi >= a.Sq) continue;
+#pragma unroll
+        for (int c = 0; c < NC / KW; ++c) {
+            const int e0 = (kh * 2 + c) * 16 + gq * 4;
+            const v4f scl = *reinterpret_cast<const v4f*>(scale + e0);
+            float y[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                y[t] = (F8 ? (float)o[c][t] : (float)-o[c][t]) * scl[t];
+                if (qi >= qlim) y[t] = 0.0f;                                     // padded query: zeros
+            }
+            if (ODT == HERO_I8) *reinterpret_cast<uint32_t*>((int8_t*)a.out + orow + e0) = quant4_sat(y[0], y[1], y[2], y[3]);
+            else if (ODT == HERO_F8E4M3) *reinterpret_cast<uint32_t*>((int8_t*)a.out + orow + e0) = fp8x4_sat(y[0], y[1], y[2], y[3]);
+            else *reinterpret_cast<v2i*>((uint16_t*)a.out + orow + e0) = v2i{(int)pack2_hp<ODT>(y[0], y[1]), (int)pack2_hp<ODT>(y[2], y[3])};
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // Few query blocks (a short sentence, a prompt chunk of few users): the kernel above runs as one serial chain of two
 // passes over the keys per block of 128 queries, on as many CUs as there are blocks.  Here a block owns 32 queries and its
 // NW waves split the KEYS: wave w takes the 32-key steps w, w + NW, .., with K fragments straight from memory, V transposed
@@ -1033,6 +1280,24 @@ hero_status launch(const AttnArgs& a, hero_dtype out_dt, hipStream_t st) {
     return hero_launch_status();
 }
 
+template <int FMT>
+hero_status launch_keep(const AttnArgs& a, hero_dtype out_dt, hipStream_t st) {
+    const int64_t nqb = (a.Sq + BQ - 1) / BQ, hgroups = ((int64_t)a.B * a.H + 1) / 2, rounds = (hgroups + 7) / 8;
+    if (rounds * 16 * nqb > 0x7fffffffLL) return HERO_ERR_SHAPE;
+    auto go = [&](auto NT, auto KW) -> hero_status {
+        constexpr int nt = decltype(NT)::value, kw = decltype(KW)::value;
+        dim3 grid((unsigned)(rounds * 16 * nqb)), block(256 * kw);
+        if (out_dt == HERO_BF16) hipLaunchKernelGGL((int8_attn_keep_kernel<HERO_BF16, FMT, nt, kw>), grid, block, 0, st, a);
+        else if (out_dt == HERO_F16) hipLaunchKernelGGL((int8_attn_keep_kernel<HERO_F16, FMT, nt, kw>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((int8_attn_keep_kernel<FMT, FMT, nt, kw>), grid, block, 0, st, a);
+        return hero_launch_status();
+    };
+    constexpr std::integral_constant<int, 1> one;
+    if (a.Skv <= 128) return go(std::integral_constant<int, 2>{}, one);
+    if (a.Skv <= 256) return go(std::integral_constant<int, 4>{}, one);
+    return go(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
+}
+
 template <int DH, int FMT, int NW>
 hero_status launch_split(const AttnArgs& a, hero_dtype out_dt, hipStream_t st) {
     constexpr int HG = DH >= 128 ? 1 : 128 / DH;
@@ -1122,10 +1387,17 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     // 23.5 -> 26.0: there the chip is full and reading K / V four times as often costs more than the shorter chain gives.  With
     // Dh = 128 a CU holds fewer of its blocks, and it is full from three pieces of 32 queries on: 2 x 32 x 301 (640 pieces) above,
     // but 8 x 32 x 128 (1024) 12.3 -> 14.1, E4M3 4 x 32 x 200 (896) 13.9 -> 14.8.
-    if ((B * H * ((Sq + BQ - 1) / BQ) <= 256 && (Dh == 64 || B * H * ((Sq + 31) / 32) <= 768)) || Sq <= 32) {
+    // Up to 512 keys of 64 channels the one-pass kernel takes over from three quarters of the CUs on, and beyond from the two-pass
+    // kernel altogether: split -> one pass 128 blocks (8 x 16 x 100) 5.7 -> 6.3, 192 (12 x 16 x 128) 7.0 -> 6.6, 256 (4 x 16 x 512)
+    // 15.0 -> 10.7, (8 x 16 x 256) 10.5 -> 8.4; two passes -> one 32 x 16 x 512 padded 65 -> 56.5, 11 x 16 x 347 19.7 -> 14.4, 16 x 16 x 256
+    // 14.9 -> 10.4, 32 x 12 x 128 10.1 -> 7.6; E4M3 32 x 16 x 512 55.7 -> 56.8, 11 x 16 x 347 17.5 -> 13.8, 16 x 16 x 256 14.3 -> 11.1.
+    const int64_t blocks = B * H * ((Sq + BQ - 1) / BQ);
+    const bool keep = Dh == 64 && Skv <= 512;
+    if ((blocks <= (keep ? 191 : 256) && (Dh == 64 || B * H * ((Sq + 31) / 32) <= 768)) || Sq <= 32) {
         if (fp8) return Dh == 64 ? launch_split<64, HERO_F8E4M3, 4>(a, out_dt, st) : launch_split<128, HERO_F8E4M3, 4>(a, out_dt, st);
         return Dh == 64 ? launch_split<64, HERO_I8, 4>(a, out_dt, st) : launch_split<128, HERO_I8, 4>(a, out_dt, st);
     }
+    if (keep) return fp8 ? launch_keep<HERO_F8E4M3>(a, out_dt, st) : launch_keep<HERO_I8>(a, out_dt, st);
     if (fp8) return Dh == 64 ? launch<64, false, HERO_F8E4M3>(a, out_dt, st) : launch<128, false, HERO_F8E4M3>(a, out_dt, st);
     return Dh == 64 ? launch<64>(a, out_dt, st) : launch<128>(a, out_dt, st);
 }
