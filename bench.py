@@ -267,7 +267,7 @@ def fc1_roofline(hero, shape, seed, iters=40, tile=None):
     ms = float(np.median([ev[r].elapsed_time(ev[r + 1]) / iters for r in range(5)]))
     ops = 2.0 * M * N * K
     tops = ops / (ms * 1e-3) / 1e12
-    return {"bound": "mfma", "kernel": ("int8_gemm_ovl_kernel" if K < 2048 and tile in (None, 9) else "int8_gemm_persistent_kernel") + "<GELU_REQUANT> (FC1)", "shape_mnk": [M, N, K],
+    return {"bound": "mfma", "kernel": "int8_gemm_persistent_kernel<GELU_REQUANT> (FC1)", "shape_mnk": [M, N, K],
             "achieved": round(tops, 2), "peak": PEAK_INT8_TOPS, "unit": "TOP/s", "frac": round(tops / PEAK_INT8_TOPS, 4),
             "avg_launch_us": round(ms * 1e3, 2), "ops_per_launch": ops,
             "timing": f"median of 5 x {iters} back-to-back launches after 60 ms of them, HIP events; operands rotate over {n_a} / {n_w} / {n_c} buffers (A / W / C)",

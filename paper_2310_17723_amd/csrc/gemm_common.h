@@ -50,6 +50,18 @@ __device__ __forceinline__ ACC mfma_step(v4i a, v4i b, ACC c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a1, b1, c, 0, 0, 0);
     }
 }
+// The same on 16 x 16 tiles: one instruction takes a whole 64-byte slab of 16 rows of each operand.  At the clock the power limit allows
+// these sustain more than the 32 x 32 ones (half the accumulator traffic per multiply-add; registers only, random bytes: INT8 4.27
+// against 3.60 POP/s, BF16 2.17 against 1.91 PFLOP/s).
+template <int ADT> struct Acc4Of { using type = typename std::conditional<ADT == HERO_I8, v4i, v4f>::type; };
+template <int ADT, typename ACC>
+__device__ __forceinline__ ACC mfma16_step(v4i a, v4i b, ACC c) {
+    if constexpr (ADT == HERO_I8) return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+    else if constexpr (ADT == HERO_BF16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8hf, a), __builtin_bit_cast(v8hf, b), c, 0, 0, 0);
+}
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), in order
 template <int N, int I = 0, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -264,9 +276,101 @@ __device__ __forceinline__ void epilogue_direct(const GemmArgs& g, ACC (&acc)[BM
     }
 }
 
+// The epilogue behind 16 x 16 tiles whose weight rows were taken in the order 16 (r / 4) + 4 j + r % 4 (r: row of the instruction, j: its
+// tile of the wave's 64 columns): lane l then holds, for ONE output row (l % 16 of each of the TI tiles), the 16 consecutive columns
+// 16 (l / 16) .. + 15, column 4 j + t in acc[i][j][t], and nothing has to change lanes.
+template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT, bool UNIT, typename ACC, int TI>
+__device__ __forceinline__ void epilogue_rows16(const GemmArgs& g, ACC (&acc)[TI][4], const float* sv, const float (&rsr)[TI], int m0, int n0, int tid) {
+    static_assert(BN / WN == 64 && BM / WM == 16 * TI, "a wave owns 64 columns");
+    constexpr int ES = ElemSize<CDT>::v;
+    const int lane = tid & 63, wave = tid >> 6, wm = wave / WN, wn = wave % WN, nl = wn * 64 + (lane >> 4) * 16;
+    const int col0 = n0 + nl;
+    const bool has_rs = g.a_row_scale != nullptr, al16 = (g.ldc * ES) % 16 == 0, full = col0 + 16 <= g.N;
+    v4f cs[4], bs[4];
+    if (EPI != HERO_EPI_RAW_I32) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (!UNIT) cs[j] = *reinterpret_cast<const v4f*>(sv + nl + 4 * j);
+            bs[j] = *reinterpret_cast<const v4f*>(sv + BN + nl + 4 * j);
+        }
+    }
+    v4f os[4];                                                    // 1 / S_a
+    if (EPI == HERO_EPI_GELU_REQUANT) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) os[j] = *reinterpret_cast<const v4f*>(sv + 2 * BN + nl + 4 * j);
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        const int row = m0 + wm * TI * 16 + i * 16 + (lane & 15);
+        const bool ok = row < g.M && col0 < g.N;
+        if constexpr (EPI == HERO_EPI_RAW_I32) {
+            uint32_t d[16];                                       // int32 sums, or the bits of fp32 ones
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const auto v = acc[i][e >> 2][e & 3];
+                if constexpr (std::is_same<ACC, v4i>::value) d[e] = (uint32_t)v;
+                else d[e] = __float_as_uint(v);
+            }
+            if (ok) store_piece<4, 16>((int8_t*)g.C + ((int64_t)row * g.ldc + col0) * 4, d, col0, g.N, full, al16);
+        } else {
+            const float rs = rsr[i];
+            float y[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                float v = (float)acc[i][e >> 2][e & 3];
+                if (UNIT) v = v + bs[e >> 2][e & 3];
+                else {
+                    if (has_rs) v = v * rs;
+                    v = fmaf(v, cs[e >> 2][e & 3], bs[e >> 2][e & 3]);
+                }
+                if (EPI == HERO_EPI_DEQUANT_GELU || EPI == HERO_EPI_GELU_REQUANT) v = gelu_erf(v);
+                if (EPI == HERO_EPI_GELU_REQUANT) v = v * os[e >> 2][e & 3];      // the +-1 LSB class, see epilogue_direct
+                y[e] = v;
+            }
+            if constexpr (ES == 1) {
+                uint32_t d[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    d[j] = CDT == HERO_F8E4M3 ? fp8x4_sat(y[4 * j], y[4 * j + 1], y[4 * j + 2], y[4 * j + 3]) : quant4_sat(y[4 * j], y[4 * j + 1], y[4 * j + 2], y[4 * j + 3]);
+                if (ok) store_piece<1, 4>((int8_t*)g.C + (int64_t)row * g.ldc + col0, d, col0, g.N, full, al16);
+            } else if (ok) {
+                if constexpr (RDT >= 0) {
+                    const uint16_t* rp = (const uint16_t*)g.residual + (int64_t)row * g.ldr + col0;
+                    const bool rl16 = (g.ldr * 2) % 16 == 0 && ((uintptr_t)g.residual & 15) == 0;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        uint32_t r[4];
+                        if (full && rl16) {
+                            const v4i rv = *reinterpret_cast<const v4i*>(rp + 8 * q);
+                            r[0] = rv[0]; r[1] = rv[1]; r[2] = rv[2]; r[3] = rv[3];
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const int n = col0 + 8 * q + 2 * k;
+                                const uint32_t e0 = n < g.N ? rp[8 * q + 2 * k] : 0, e1 = n + 1 < g.N ? rp[8 * q + 2 * k + 1] : 0;
+                                r[k] = e0 | (e1 << 16);
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            y[8 * q + 2 * k] += hp_to_f32<RDT>(r[k] & 0xffffu);
+                            y[8 * q + 2 * k + 1] += hp_to_f32<RDT>(r[k] >> 16);
+                        }
+                    }
+                }
+                uint32_t d[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) d[k] = pack2_hp<CDT>(y[2 * k], y[2 * k + 1]);
+                store_piece<2, 8>((int8_t*)g.C + ((int64_t)row * g.ldc + col0) * 2, d, col0, g.N, full, al16);
+            }
+        }
+    }
+}
+
 // s_waitcnt immediate that waits only for vmcnt <= n (gfx9 encoding: vmcnt in bits 3:0 and 15:14,
 // expcnt 6:4 and lgkmcnt 11:8 left at their maxima).
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
+constexpr int vmcnt_lds_imm(int n) { return vmcnt_imm(n) & ~0x0F00; }        // .. and for every LDS access of this wave
 
 // One direct global->LDS load: 64 lanes x 16 bytes land at LDS address lds_base + lane * 16
 // (lds_base is wave-uniform and travels in M0).  Written as inline assembly on purpose: the

@@ -35,7 +35,6 @@ struct SkinnyArgs {
 
 constexpr int SKINNY_WAVES = 8, UNIT = 16 * 128;
 
-template <int ADT> struct SkinnyAcc { using type = typename std::conditional<ADT == HERO_I8, v4i, v4f>::type; };
 // both 16-byte fragments of a 128-byte step
 template <int ADT, typename ACC>
 __device__ __forceinline__ ACC mfma_16(const v4i (&w)[2], const v4i (&a)[2], ACC c) {
@@ -45,13 +44,7 @@ __device__ __forceinline__ ACC mfma_16(const v4i (&w)[2], const v4i (&a)[2], ACC
         return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(w8, a8, c, 0, 0, 0, 0, 0, 0);
     } else {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if constexpr (ADT == HERO_I8) c = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[s], a[s], c, 0, 0, 0);
-            else if constexpr (ADT == HERO_BF16)
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, w[s]), __builtin_bit_cast(v8bf, a[s]), c, 0, 0, 0);
-            else
-                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8hf, w[s]), __builtin_bit_cast(v8hf, a[s]), c, 0, 0, 0);
-        }
+        for (int s = 0; s < 2; ++s) c = mfma16_step<ADT>(w[s], a[s], c);
         return c;
     }
 }
@@ -68,7 +61,7 @@ __device__ __forceinline__ void unit_wait(int left) {
 // HDT: type of the rows in front of the fused LN^quant; -1: the activation rows are codes (or 16-bit values) in memory
 template <int ADT, int CT, int TM, int HDT>
 __global__ __launch_bounds__(SKINNY_WAVES * 64, 2) void skinny_gemm_kernel(SkinnyArgs sa) {
-    using ACC = typename SkinnyAcc<ADT>::type;
+    using ACC = typename Acc4Of<ADT>::type;
     const GemmArgs& g = sa.g;
     constexpr bool LN = HDT >= 0, HP = ADT == HERO_BF16 || ADT == HERO_F16;
     constexpr int LN_ROWS = 8, LN_K = 4096;                         // the fused form's limits

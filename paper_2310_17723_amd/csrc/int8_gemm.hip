@@ -4,25 +4,24 @@
 // Sec. 2.2.2 fused dequantization and the bare Round after folding; Sec. 2.2.3 GELU^quant).
 //
 // Both operands are K-contiguous ([M][K] activations, [N][K] weights), so every MFMA
-// operand fragment is one 128-bit LDS read.  MFMA: v_mfma_i32_32x32x32_i8 with the WEIGHT
-// fragment as first operand and the activation fragment as second, so the accumulator of
-// lane l holds, for ONE output row m = l % 32, the columns n = 8g + 4(l/32) + t (register
-// 4g + t): the per-row scale is one register and a lane owns 4 consecutive columns.
+// operand fragment is one 128-bit LDS read.  The WEIGHT fragment is the matrix instruction's first operand and the
+// activation fragment its second, so an accumulator holds, for ONE output row per lane, groups of 4 consecutive
+// columns: the per-row scale is one register.  The persistent kernel multiplies INT8 and 16-bit operands on 16 x 16 tiles
+// (mfma16_step), whose weight rows are taken in an order that gives a lane 16 consecutive columns; the others use 32 x 32
+// tiles (columns 8g + 4(l/32) + t of row l % 32) and exchange halves in the epilogue (v_permlane32_swap).
 //
 // The main loops; all but the skinny one's share one epilogue (gemm_common.h):
 //   * int8_gemm_persistent_kernel (large problems): 256x256 block tile, 8 waves of 128x64,
 //     slabs of 64 bytes of K copied global -> LDS directly (global_load_lds_dwordx4) through
 //     a ring of 4 stages; one workgroup per CU walks its tiles and the ring runs through the
 //     tile boundaries.  A second form, 128x128 with 4 waves of 64x64 and two workgroups per CU,
-//     serves the sizes at which the large tile would leave CUs idle; per tile area it needs
-//     twice the L2 -> LDS traffic and is 10-15 % slower once every CU has work.
+//     serves the sizes at which the large tile would leave CUs idle (twice the L2 -> LDS traffic per tile area).
 //   * int8_gemm_dma_kernel: the same tile, one tile per workgroup (short K, huge strides).
 //   * int8_gemm_ring_kernel (gemm_ring.h; small and middling problems): 32x32 .. 128x128 tiles, 128-byte slabs, K groups.
 //   * skinny_gemm_kernel (gemm_skinny.hip; up to 32 rows): a stream of the weights.
 //   * int8_gemm_kernel (rows too far apart for 32-bit offsets; a short K that ends in half a slab, over many rows): 128x128 /
 //     64x64 tile staged through registers.
-// The epilogue works in registers: a lane-half exchange (v_permlane32_swap) gives every lane a
-// contiguous piece of one output row, written with 128-bit stores.
+// The epilogue works in registers: every lane ends with a contiguous piece of one output row, written with 128-bit stores.
 #include "gemm_common.h"
 #include <atomic>
 #include <cstdlib>
@@ -298,12 +297,18 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void int8_gemm_dma_kernel(GemmA
 // epilogue vectors, fetched by the same direct loads into a double-buffered LDS area) are
 // already resident when the epilogue of the current tile ends.  Slab addresses are a wave-uniform tile base in SGPRs
 // plus a per-lane 32-bit offset, so advancing along K is scalar arithmetic.
+// The clock under matrix load is set by power, and 16 x 16 instructions multiply more per watt than 32 x 32 ones; their lanes also
+// write 16 (32) consecutive bytes next to their neighbours'.  us, 32 x 32 -> 16 x 16 tiles: INT8 16384 x 12288 x 4096 694 -> 642
+// (2.57 POP/s), 8192 x 4096 x 16384 451 -> 411, 8192 x 4096 x 4096 120 -> 111, 16384 x 4096 x 1024 REQUANT 71.5 -> 69.2, GELU^quant 16384 x
+// 16384 x 4096 1013 -> 921, 16-bit result 8192 x 4096 x 1024 53.9 -> 40.4;  BF16 8192 x 4096 x 4096 234 -> 208, 16384 x 4096 x 1024 156 -> 128.
+// (A kernel of its own for GELU^quant behind a short K, its epilogue spread over the next tile's main loop, fell behind with
+// that: 16384 x 4096 x 1024 91 -> 84 us, 16-bit result 152 -> 98.5, 2500 rows 27.9 -> 20.5.)
 // =====================================================================================
 template <int BM, int BN, int WM, int WN, int NS, int EPI, int CDT, int RDT, int ADT = HERO_I8>
 __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(GemmArgs g) {
-    using ACC = typename AccOf<ADT>::type;
     constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
-    constexpr bool WIDE = ADT == HERO_F8E4M3;
+    constexpr bool WIDE = ADT == HERO_F8E4M3;                       // 32 x 32 tiles; INT8 and 16 bits: 16 x 16 (mfma16_step)
+    using ACC = typename std::conditional<WIDE, v16f, typename Acc4Of<ADT>::type>::type;
     constexpr int NT = WM * WN * 64, NWAVE = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = A_BYTES + B_BYTES;
@@ -332,7 +337,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     // loader: unit u of wave w fills LDS granules [(u * NWAVE + w) * 64, +64) of the A (or B) part of
     // a stage; lane l owns row u * 128 + lrow, stored chunk l % 4 = global chunk (l % 4) ^ ((row >> 2) & 3).
     const int lrow = wave * 16 + (lane >> 2);
-    const uint32_t lc = (uint32_t)(((lane & 3) ^ ((lrow >> 2) & 3)) * 16);
+    // (16 x 16 tiles read the weight rows in another order: theirs are swizzled by row / 16)
+    const uint32_t lc = (uint32_t)(((lane & 3) ^ ((lrow >> 2) & 3)) * 16), lcb = WIDE ? lc : (uint32_t)(((lane & 3) ^ ((lrow >> 4) & 3)) * 16);
     const uint32_t wbase = __builtin_amdgcn_readfirstlane(lds_offset(smem) + wave * 1024);
     const uint32_t svbase = __builtin_amdgcn_readfirstlane(lds_offset(sv0));
 
@@ -348,7 +354,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
 #pragma unroll
         for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0i) * (uint32_t)g.lda + lc;
 #pragma unroll
-        for (int u = 0; u < B_UNITS; ++u) ob[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.N - 1 - n0i) * (uint32_t)g.ldb + lc;
+        for (int u = 0; u < B_UNITS; ++u) ob[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.N - 1 - n0i) * (uint32_t)g.ldb + lcb;
     };
     // The epilogue vectors of the issue stream's tile go out together with its FIRST pair, not when the stream
     // moves on to the tile: their buffer (parity of the tile) is still being read by the epilogue of the tile
@@ -395,6 +401,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
 
     // fragment offsets inside a stage (row rr, k-step ks, half hh): rr*64 + ((2ks+hh) ^ ((rr>>2)&3))*16
     const int hh = lane >> 5, ml = lane & 31;
+    // 16 x 16 tiles: row r = l % 16, chunk l / 16; weight row r of tile j is column 16 (r / 4) + 4 j + r % 4 of the wave's 64
+    constexpr int TI = 2 * TM, TJ = 2 * TN;
+    static_assert(WIDE || (TJ == 4 && TI % 2 == 0), "16 x 16 tiles: 64 columns per wave");
+    const int r16 = lane & 15, ch16 = ((lane >> 4) ^ ((r16 >> 2) & 3)) << 4;
+    const int foa = (wm * TI * 16 + r16) * 64 + ch16, fob = A_BYTES + (wn * 64 + 16 * (r16 >> 2) + (r16 & 3)) * 64 + ch16;
     int fo[2][NFR];
 #pragma unroll
     for (int t = 0; t < NFR; ++t) {
@@ -419,19 +430,27 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     for (;;) {
         int m0, n0;
         tile_from_seq<BM, BN>(g, seq, m0, n0);
-        ACC acc[TM][TN];
+        constexpr int CI = WIDE ? TM : TI, CJ = WIDE ? TN : TJ, CR = WIDE ? 16 : 4;
+        ACC acc[CI][CJ];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < CI; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < CJ; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-        v4i f0[NFR], f1[NFR];
+                for (int r = 0; r < CR; ++r) acc[i][j][r] = 0;
+        v4i f0[NFR], f1[NFR], fa[TI], fb[TJ];
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int t = 0; t < NFR; ++t) f0[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fo[0][t]);
-        if (WIDE)
+            for (int t = 0; t < NFR; ++t) {
+                f0[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fo[0][t]);
+                f1[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fo[1][t]);
+            }
+        } else {
 #pragma unroll
-            for (int t = 0; t < NFR; ++t) f1[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fo[1][t]);
+            for (int t = 0; t < TJ; ++t) fb[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fob + t * 256);
+#pragma unroll
+            for (int t = 0; t < TI; ++t) fa[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + foa + t * 1024);
+        }
 
         // One slab per iteration with the barrier in the middle (see int8_gemm_dma_kernel).  KT is even and the
         // ring holds two pairs: after the barrier of an ODD iteration i every wave has read the last fragment
@@ -441,7 +460,6 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         // out) and vmcnt(2 NW) in an even one (the younger pair may be out).
         auto iteration = [&](auto ODD) {
             constexpr bool odd = decltype(ODD)::value;
-            const int8_t* st = smem + stage * STAGE;
             const int nstage = stage + 1 == NS ? 0 : stage + 1;
             const int pstage = stage == 0 ? NS - 1 : stage - 1;
             const int8_t* stn = smem + nstage * STAGE;
@@ -478,28 +496,32 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
+                // 16 x 16 tiles: one instruction takes a whole slab of a row, so every fragment of a slab is read during the slab
+                // before, right after its register's last use: the first half of the rows (dead by the barrier) and the weights one by
+                // one as the second half is done with them, that half itself at the end.  Twelve instructions at least lie
+                // between a read and its use.
+                constexpr int HI = TI / 2, NH = HI * TJ;
 #pragma unroll
-                for (int n = 0; n < NM; ++n) {                         // k-step 0
-                    const int jj = n / TM, ii = n % TM;
-                    acc[ii][jj] = mfma_step<ADT>(f0[jj], f0[TN + ii], acc[ii][jj]);
-                    if (n < NFR / 2) {                                 // early: the reads must be back before the barrier
-                        f1[2 * n] = *reinterpret_cast<const v4i*>(st + fo[1][2 * n]);
-                        f1[2 * n + 1] = *reinterpret_cast<const v4i*>(st + fo[1][2 * n + 1]);
-                    }
+                for (int n = 0; n < NH; ++n) {
+                    const int jj = n / HI, ii = n % HI;
+                    acc[ii][jj] = mfma16_step<ADT>(fb[jj], fa[ii], acc[ii][jj]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm(odd ? 1 : 2 * NW));   // the next slab has landed (mine)
+                // the next slab has landed (mine); behind an odd slab the direct loads overwrite what this wave read last
+                __builtin_amdgcn_s_waitcnt(odd ? vmcnt_lds_imm(1) : vmcnt_imm(2 * NW));
                 __syncthreads();                                       // ... and everybody's
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int n = 0; n < NM; ++n) {                         // k-step 1
-                    const int jj = n / TM, ii = n % TM;
-                    acc[ii][jj] = mfma_step<ADT>(f1[jj], f1[TN + ii], acc[ii][jj]);
-                    if (n < NFR / 2) {
-                        f0[2 * n] = *reinterpret_cast<const v4i*>(stn + fo[0][2 * n]);
-                        f0[2 * n + 1] = *reinterpret_cast<const v4i*>(stn + fo[0][2 * n + 1]);
+                for (int n = 0; n < NH; ++n) {
+                    const int jj = n / HI, ii = HI + n % HI;
+                    acc[ii][jj] = mfma16_step<ADT>(fb[jj], fa[ii], acc[ii][jj]);
+                    if (n < HI) fa[n] = *reinterpret_cast<const v4i*>(stn + foa + n * 1024);
+                    if (n % HI == HI - 1) fb[jj] = *reinterpret_cast<const v4i*>(stn + fob + jj * 256);
+                    if (n >= NH - HI) fa[ii] = *reinterpret_cast<const v4i*>(stn + foa + ii * 1024);
+                    if (odd) {                                         // the units of the new pair, evenly over the half
+                        constexpr int EV = NH / NW;
+                        if (n % EV == 0 && n / EV < NW) { issue_pair(2 * (n / EV), pstage); issue_pair(2 * (n / EV) + 1, pstage); }
                     }
-                    if (odd && n < NW) { issue_pair(2 * n, pstage); issue_pair(2 * n + 1, pstage); }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -509,6 +531,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         for (int kt = 0; kt < KT; kt += 2) {
             iteration(std::false_type{});
             iteration(std::true_type{});
+            // S_a -> 1 / S_a once per tile (IEEE division): the vectors landed before the first barrier, KT >= 4 leaves another
+            if (!WIDE && EPI == HERO_EPI_GELU_REQUANT && kt == 0 && tid < BN) {
+                float* const s = sv0 + par * SVF + 2 * BN + tid;
+                *s = __fdiv_rn(1.0f, *s);
+            }
         }
         // Prefetch for the caller's next kernel: this tile's share of the lines, one dword of each, through the same
         // direct loads into a scratch corner of the LDS (no register is written, so nothing has to wait for them; the
@@ -525,369 +552,16 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         }
         // epilogue of this tile; the ring keeps filling with the next tile's slabs meanwhile
         const float* sv = sv0 + par * SVF;
-        float rsr[TM];
+        float rsr[CI];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * TM * 32 + i * 32 + ml] : 1.0f;
-        epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, true, UNIT>(g, acc, sv, rsr, m0, n0, tid);
+        for (int i = 0; i < CI; ++i)
+            rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * TM * 32 + i * (WIDE ? 32 : 16) + (WIDE ? ml : r16)] : 1.0f;
+        if constexpr (WIDE) epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, true, UNIT>(g, acc, sv, rsr, m0, n0, tid);
+        else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(g, acc, sv, rsr, m0, n0, tid);
         seq += nslot;
         par ^= 1;
         if (seq >= seq_end) break;
     }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));                      // the redundant tail loads
-}
-
-// =====================================================================================
-// Persistent kernel with the epilogue INSIDE the next tile's main loop (large problems, K >= 1024).
-// The vector ALU issues while the matrix pipe of the same SIMD is busy (measured: a wave that puts 4 fp32
-// instructions behind each of its v_mfma_i32_32x32x32_i8 runs 15 % longer than the matrix instructions alone,
-// not the 34 % the two take one after the other), but only if both kinds of work are there at the same
-// time.  Here a wave keeps TWO sets of accumulators: while the matrix instructions of tile t+1 fill one, the
-// dequantization / GELU / requantization / stores of tile t drain the other, a fixed handful of vector
-// instructions behind every matrix instruction (the epilogue of a tile is cut into 128 such steps, the first
-// 16 slabs of the next tile).  A 256 x 256 tile would need 2 x 128 accumulator registers per lane, which the
-// register file does not have beside everything else, so the tile is 256 x 128: 8 waves of 64 x 64 (4
-// accumulators, 2 x 64 registers).  The smaller tile needs 1.5 x the L2 -> LDS bytes per multiply-add; in exchange
-// a stage is 24 KB and the ring holds SIX slabs (three pairs), i.e. five slabs of lookahead instead of three.
-// The last tile of a workgroup has no successor: its epilogue runs after the loop, unhidden.
-// Measured (16384 x 4096 x 1024): the epilogue does disappear -- GELU^quant costs 7 us over the plain requantization
-// where it costs 25 us behind the 256 x 256 tile -- but the main loop of the smaller tile is slower by about as much
-// (92 us against 76 us: 1.33 x the LDS fragment reads per matrix instruction and 1.5 x the direct-load bytes on a
-// load stream that is latency-bound), so the two kernels end within 2 % of each other (99 / 101 us with
-// GELU^quant) when both are timed alone with operands that stay in the memory-side cache.  Inside a layer the
-// weights come from HBM, and there the deeper ring decides: this kernel is the tile choice's pick for a GELU epilogue
-// with K < 2048 (the numbers are beside the rule in choose()); the test entry point reaches it as tile code 9.
-// =====================================================================================
-// wait for vmcnt <= N and for every LDS access of this wave, then the workgroup barrier.  Inline assembly: the
-// kernel below has global stores inside its main loop, and a __syncthreads() there would make the compiler
-// wait for ALL outstanding vector-memory operations, the direct loads of the next slabs included.  The memory
-// clobber keeps the compiler from moving LDS accesses across the barrier.
-template <int N>
-__device__ __forceinline__ void wait_vm_barrier() {
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
-}
-
-template <int EPI, int CDT>
-__global__ __launch_bounds__(512, 2) void int8_gemm_ovl_kernel(GemmArgs g) {
-    constexpr int BM = 256, BN = 128, WN = 2, NS = 6, NWAVE = 8, NT = 512;
-    constexpr int TM = 2, TN = 2, NM = TM * TN, NFR = TM + TN;
-    constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = A_BYTES + B_BYTES;
-    constexpr int A_UNITS = A_BYTES / 16 / NT, B_UNITS = B_BYTES / 16 / NT, NW = A_UNITS + B_UNITS;
-    static_assert(A_UNITS == 2 && B_UNITS == 1 && NW <= NM && NFR == NM, "interleave plan");
-    constexpr int RING = NS * STAGE;
-    // per-tile epilogue vectors in LDS: column scale, bias, S_a (BN each), row scale (BM); three sets, because
-    // the set of tile t is read during tile t+1 while the issue stream already fetches the one of tile t+2
-    constexpr int SV_CS = 0, SV_BIAS = BN, SV_OS = 2 * BN, SV_RS = 3 * BN, SVF = 3 * BN + BM, NSV = 3;
-    constexpr int ES = ElemSize<CDT>::v;
-    constexpr bool GELU = EPI == HERO_EPI_DEQUANT_GELU || EPI == HERO_EPI_GELU_REQUANT;
-    constexpr int SPREAD = 16;                                   // slabs of the next tile the epilogue is spread over
-    constexpr int NSTEP = 16, NPIECE = 8;                        // 8 pieces of 8 outputs per lane, 16 steps each
-    static_assert(NPIECE * NSTEP == SPREAD * 2 * NM, "one epilogue step behind every matrix instruction");
-    constexpr int PF_OFF = RING + NSV * SVF * 4;                 // 256 bytes per wave where the prefetch requests land (never read)
-    static_assert(PF_OFF + NWAVE * 256 <= 160 * 1024, "LDS budget");
-    __shared__ __attribute__((aligned(1024))) int8_t smem[PF_OFF + NWAVE * 256];
-    float* const sv0 = reinterpret_cast<float*>(smem + RING);
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int hh = lane >> 5, ml = lane & 31;
-    const int xcd = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD, nslot = gridDim.x / NUM_XCD;
-    const int seq_end = min((xcd + 1) * g.per_xcd, g.ntm * g.ntn);
-    int seq = xcd * g.per_xcd + slot;                            // this workgroup's tiles: seq, seq + nslot, ...
-    if (seq >= seq_end) return;
-    const int KT = g.K / BK;                                     // even, >= SPREAD (the launch checks)
-    const bool has_rs = g.a_row_scale != nullptr, has_bias = g.bias != nullptr;
-    // absent vectors: the epilogue multiplies by 1 and adds 0 (both exact)
-    if (!has_bias) for (int c = tid; c < NSV * BN; c += NT) sv0[(c / BN) * SVF + SV_BIAS + c % BN] = 0.0f;
-    if (!has_rs) for (int c = tid; c < NSV * BM; c += NT) sv0[(c / BM) * SVF + SV_RS + c % BM] = 1.0f;
-
-    // loader: unit u of wave w fills LDS granules [(u * NWAVE + w) * 64, +64) of the A (or B) part of a stage;
-    // lane l owns row u * 128 + lrow, stored chunk l % 4 = global chunk (l % 4) ^ ((row >> 2) & 3)
-    const int lrow = wave * 16 + (lane >> 2);
-    const uint32_t lc = (uint32_t)(((lane & 3) ^ ((lrow >> 2) & 3)) * 16);
-    const uint32_t wbase = __builtin_amdgcn_readfirstlane(lds_offset(smem) + wave * 1024);
-    const uint32_t svbase = __builtin_amdgcn_readfirstlane(lds_offset(sv0));
-
-    // ---- issue stream: the tile / slab the next direct loads belong to (runs NS - 1 slabs ahead)
-    int iseq = seq, ikt = 0, ibuf = 0;
-    const int8_t* ia; const int8_t* ib;                          // wave-uniform: tile base + slab offset
-    uint32_t oa[A_UNITS], ob;
-    int m0i = 0, n0i = 0;
-    auto set_issue_tile = [&](int s) {
-        tile_from_seq<BM, BN>(g, s, m0i, n0i);
-        ia = g.A + (int64_t)m0i * g.lda;
-        ib = g.Bt + (int64_t)n0i * g.ldb;
-#pragma unroll
-        for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0i) * (uint32_t)g.lda + lc;
-        ob = (uint32_t)min(lrow, g.N - 1 - n0i) * (uint32_t)g.ldb + lc;
-    };
-    // The vectors of a tile are 10 chunks of 64 floats: 0-1 column scale, 2-3 bias, 4-5 S_a, 6-9 row scale.  Wave w
-    // fetches chunk w, waves 0 and 1 also chunks 8 and 9; what a wave fetches is fixed for the whole kernel, so
-    // it is worked out here once (source, clamp, destination) and the issue is one predicated load per chunk.
-    const int wu = __builtin_amdgcn_readfirstlane(wave);
-    const int vwhich = wu < 6 ? wu >> 1 : 3;                     // 0 column scale, 1 bias, 2 S_a, 3 row scale
-    const int vch = wu < 6 ? (wu & 1) * 64 : (wu - 6) * 64;
-    const float* const vsrc = vwhich == 0 ? g.b_col_scale : vwhich == 1 ? g.bias : vwhich == 2 ? g.out_col_scale : g.a_row_scale;
-    const bool von = EPI != HERO_EPI_RAW_I32 && (vwhich == 0 || (vwhich == 1 && has_bias) ||
-                                                 (vwhich == 2 && EPI == HERO_EPI_GELU_REQUANT) || (vwhich == 3 && has_rs));
-    const uint32_t vdst = svbase + (uint32_t)(vwhich * BN + vch) * 4;
-    const bool von2 = EPI != HERO_EPI_RAW_I32 && wu < 2 && has_rs;   // chunks 8, 9: rows 128 .. 255 of the row scale
-    const uint32_t vdst2 = svbase + (uint32_t)(SV_RS + 128 + wu * 64) * 4;
-    auto issue_tile_vectors = [&](int buf) {                     // when the stream enters a tile: older than all its slabs
-        const uint32_t bo = (uint32_t)buf * (SVF * 4);
-        if (von) {
-            const int lim = vwhich == 3 ? g.M - 1 - m0i : g.N - 1 - n0i, org = vwhich == 3 ? m0i : n0i;
-            dma4s((uint32_t)min(vch + lane, lim) * 4u, vsrc + org, vdst + bo);
-        }
-        if (von2) dma4s((uint32_t)min(128 + wu * 64 + lane, g.M - 1 - m0i) * 4u, g.a_row_scale + m0i, vdst2 + bo);
-        // the prefetch hint (see the persistent kernel): this tile's share of the lines the caller's next kernel reads.
-        // Like the vectors the requests are older than every slab of the tile, and five slabs pass before a wait
-        // asks for them.
-        if (g.pf_lines > 0 && wu * 64 < g.pf_lpt)
-            dma4s((uint32_t)min(iseq * g.pf_lpt + wu * 64 + lane, g.pf_lines - 1) * 128u, reinterpret_cast<const float*>(g.pf),
-                  __builtin_amdgcn_readfirstlane(lds_offset(smem + PF_OFF)) + (uint32_t)wu * 256u);
-    };
-    // The stream moves in PAIRS of slabs (128 bytes of every row = one cache line): load j of a pair is unit
-    // j / 2 of slab j % 2, so the two 64-byte halves of a line are requested back to back.
-    auto issue_pair = [&](int j, int stage0) {                   // stage0: the (even) stage of the pair's first slab
-        const int u = j >> 1;
-        const uint32_t lds = wbase + (stage0 + (j & 1)) * STAGE;
-        if (u < A_UNITS) dma16s(oa[u], ia + (j & 1) * BK, lds + u * NWAVE * 1024);
-        else dma16s(ob, ib + (j & 1) * BK, lds + A_BYTES);
-    };
-    // next pair; past the last tile the last pair repeats (never read).  The vectors of a tile go out the moment
-    // the stream enters it: their set (tile count mod 3) was last read by the epilogue of the tile three back,
-    // which ended before the current tile began.
-    auto advance = [&]() {
-        ikt += 2;
-        if (ikt < KT) { ia += 2 * BK; ib += 2 * BK; return; }
-        if (iseq + nslot < seq_end) {
-            iseq += nslot; ikt = 0; ibuf = ibuf == NSV - 1 ? 0 : ibuf + 1;
-            set_issue_tile(iseq);
-            issue_tile_vectors(ibuf);
-        } else {
-            ikt = KT - 2;
-        }
-    };
-
-    // fragment offsets inside a stage (row rr, k-step ks, half hh): rr*64 + ((2ks+hh) ^ ((rr>>2)&3))*16
-    int fo[2][NFR];
-#pragma unroll
-    for (int t = 0; t < NFR; ++t) {
-        const int rr = (t < TN ? wn * TN * 32 + t * 32 : wm * TM * 32 + (t - TN) * 32) + ml;
-        const int base = (t < TN ? A_BYTES : 0) + rr * 64;
-        fo[0][t] = base + (((0 + hh) ^ ((rr >> 2) & 3)) << 4);
-        fo[1][t] = base + (((2 + hh) ^ ((rr >> 2) & 3)) << 4);
-    }
-
-    // prologue: the first tile's vectors and the three pairs of the ring in flight, slab 0 landed
-    set_issue_tile(seq);
-    issue_tile_vectors(0);
-#pragma unroll
-    for (int p0 = 0; p0 < NS / 2; ++p0) {
-#pragma unroll
-        for (int j = 0; j < 2 * NW; ++j) issue_pair(j, 2 * p0);
-        advance();
-    }
-    wait_vm_barrier<(NS / 2 - 1) * 2 * NW + 1>();                 // only the last load of slab 1 and the two younger pairs may be out
-
-    v16i acc[TM][TN], prev[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { acc[i][j][r] = 0; prev[i][j][r] = 0; }
-    v4i f0[NFR], f1[NFR];
-#pragma unroll
-    for (int t = 0; t < NFR; ++t) f0[t] = *reinterpret_cast<const v4i*>(smem + fo[0][t]);
-
-    // ---- the tile whose epilogue is being drained: none yet (row origin M switches every store off)
-    int m0p = g.M, n0p = 0;
-    float* svp = sv0 + (NSV - 1) * SVF;
-    const bool al8 = g.ldc % 8 == 0;                             // rows of C start on 8-element boundaries
-    bool interior = false;                                       // the draining tile lies inside C and its rows are aligned: plain wide stores
-    // state of the piece in flight (8 outputs of one row per lane)
-    float ey[8], ez[8], ep[8];
-    v4f ecs[2], ebs[2], eos[2];
-    float ers = 1.0f;
-    // Step s of the epilogue of the previous tile.  Piece pc = s / 16 covers, for output row
-    // wm*64 + i*32 + ml (i = pc / 4), the 4-column groups q = pc % 4 of both accumulators of that row:
-    // columns wn*64 + 8q + 4hh + t and + 32.  After the lane-half exchange a lane owns 8 contiguous columns.
-    auto epi_step = [&](auto S) {
-        constexpr int s = decltype(S)::value, pc = s / NSTEP, st = s % NSTEP, i = pc / 4, qq = pc % 4;
-        const int rowl = wm * 64 + i * 32 + ml, c0 = wn * 64 + 8 * qq + 4 * hh;
-        if constexpr (s == 0 && EPI == HERO_EPI_GELU_REQUANT) {
-            // S_a -> 1 / S_a once per tile (IEEE division), published by the barrier in the middle of this slab;
-            // the first read is in step 10 of piece 0, well behind it
-            if (tid < BN) svp[SV_OS + tid] = __fdiv_rn(1.0f, svp[SV_OS + tid]);
-        }
-        if constexpr (EPI == HERO_EPI_RAW_I32) {
-            if constexpr (st == 1) {
-                const int row = m0p + rowl;
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int col = n0p + c0 + 32 * j;
-                    const uint32_t d[4] = {(uint32_t)prev[i][j][4 * qq], (uint32_t)prev[i][j][4 * qq + 1],
-                                           (uint32_t)prev[i][j][4 * qq + 2], (uint32_t)prev[i][j][4 * qq + 3]};
-                    int8_t* cp = (int8_t*)g.C + ((int64_t)row * g.ldc + col) * 4;
-                    if (interior) *reinterpret_cast<v4i*>(cp) = v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
-                    else if (row < g.M && col < g.N) store_piece<4, 4>(cp, d, col, g.N, col + 4 <= g.N, true);
-                }
-            }
-        } else {
-            if constexpr (st == 0) {
-                ecs[0] = *reinterpret_cast<const v4f*>(svp + SV_CS + c0);
-                ecs[1] = *reinterpret_cast<const v4f*>(svp + SV_CS + c0 + 32);
-                ebs[0] = *reinterpret_cast<const v4f*>(svp + SV_BIAS + c0);
-                ebs[1] = *reinterpret_cast<const v4f*>(svp + SV_BIAS + c0 + 32);
-                ers = svp[SV_RS + rowl];
-            } else if constexpr (st == 1) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ey[e] = (float)prev[i][e >> 2][4 * qq + (e & 3)];
-            } else if constexpr (st == 2) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ey[e] = ey[e] * ers;
-            } else if constexpr (st == 3) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ey[e] = fmaf(ey[e], ecs[e >> 2][e & 3], ebs[e >> 2][e & 3]);
-            } else if constexpr (GELU && st == 4) {               // erf-form GELU as in gelu_erf(), cut into steps
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { ez[e] = fminf(fabsf(ey[e]), 6.0f); ep[e] = fmaf(3.309558087e-05f, ez[e], -7.692443905e-04f); }
-            } else if constexpr (GELU && st == 5) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { ep[e] = fmaf(ep[e], ez[e], 8.080800064e-03f); ep[e] = fmaf(ep[e], ez[e], -5.341223627e-02f); }
-            } else if constexpr (GELU && st == 6) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { ep[e] = fmaf(ep[e], ez[e], -4.587708712e-01f); ep[e] = fmaf(ep[e], ez[e], -1.151201725e+00f); }
-            } else if constexpr (GELU && st == 7) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ep[e] = fmaf(ep[e], ez[e], -9.999930859e-01f);
-            } else if constexpr (GELU && st == 8) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ep[e] = __builtin_amdgcn_exp2f(ep[e]);
-            } else if constexpr (GELU && st == 9) {
-#pragma unroll
-                for (int e = 4; e < 8; ++e) ep[e] = __builtin_amdgcn_exp2f(ep[e]);
-            } else if constexpr (GELU && st == 10) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ez[e] = fmaxf(ey[e], 0.0f);
-                if constexpr (EPI == HERO_EPI_GELU_REQUANT) {
-                    eos[0] = *reinterpret_cast<const v4f*>(svp + SV_OS + c0);
-                    eos[1] = *reinterpret_cast<const v4f*>(svp + SV_OS + c0 + 32);
-                }
-            } else if constexpr (GELU && st == 11) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ey[e] = fmaf(-fabsf(ey[e]), ep[e], ez[e]);
-            } else if constexpr (EPI == HERO_EPI_GELU_REQUANT && st == 12) {
-                // GELU^quant is in the +-1 LSB class (fp32 GELU against the definition's fp64): the division by
-                // S_a[j] is a multiplication by the correctly rounded reciprocal
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ey[e] = ey[e] * eos[e >> 2][e & 3];
-            } else if constexpr (ES == 1 && st == 13) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ey[e] = __builtin_amdgcn_fmed3f(ey[e], -127.0f, 127.0f);
-            } else if constexpr (ES == 1 && st == 14) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ey[e] = ey[e] + 12582912.0f;   // rne_low_byte(): the low byte of the sum is the code
-            } else if constexpr (st == 15) {
-                const int row = m0p + rowl, col = n0p + wn * 64 + hh * 32 + 8 * qq;   // first of this lane's 8 columns
-                const bool ok = row < g.M && col < g.N, full = col + 8 <= g.N;   // (only looked at on the edge tiles)
-                if constexpr (ES == 1) {
-                    const uint32_t w0 = pack_low_bytes(__float_as_uint(ey[0]), __float_as_uint(ey[1]), __float_as_uint(ey[2]), __float_as_uint(ey[3]));
-                    const uint32_t w1 = pack_low_bytes(__float_as_uint(ey[4]), __float_as_uint(ey[5]), __float_as_uint(ey[6]), __float_as_uint(ey[7]));
-                    uint32_t d[2];
-                    swap32(w0, w1, d[0], d[1]);
-                    int8_t* cp = (int8_t*)g.C + (int64_t)row * g.ldc + col;
-                    if (interior) *reinterpret_cast<v2i*>(cp) = v2i{(int)d[0], (int)d[1]};
-                    else if (ok) store_piece<1, 2>(cp, d, col, g.N, full, false);
-                } else {
-                    uint32_t d[4];
-                    swap32(pack2_hp<CDT>(ey[0], ey[1]), pack2_hp<CDT>(ey[4], ey[5]), d[0], d[2]);
-                    swap32(pack2_hp<CDT>(ey[2], ey[3]), pack2_hp<CDT>(ey[6], ey[7]), d[1], d[3]);
-                    int8_t* cp = (int8_t*)g.C + ((int64_t)row * g.ldc + col) * 2;
-                    if (interior) *reinterpret_cast<v4i*>(cp) = v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
-                    else if (ok) store_piece<2, 4>(cp, d, col, g.N, full, false);
-                }
-            }
-        }
-    };
-
-    int stage = 0, buf = 0;
-    // One slab: the barrier sits in the middle (k-step 0 runs on fragments read during the previous slab, the
-    // barrier makes slab kt+1 visible, k-step 1 runs while its first fragments and, in odd slabs, the direct loads
-    // of the pair five slabs ahead are issued).  In program order the loads of a pair alternate between its two
-    // slabs, so "slab kt+1 has landed" is: at most the pair's last load and the two younger pairs outstanding in an
-    // odd slab, the two younger pairs in an even one.  The stores of the epilogue steps count in vmcnt as well; they
-    // can only make the wait longer, never shorter than needed (loads return in order among themselves).
-    auto iteration = [&](auto ODD, auto SLOT0, auto FIRST) {
-        constexpr bool odd = decltype(ODD)::value, first = decltype(FIRST)::value;
-        constexpr int s0 = decltype(SLOT0)::value;                   // first epilogue step of this slab; < 0: none
-        const int8_t* st = smem + stage * STAGE;
-        const int nstage = stage + 1 == NS ? 0 : stage + 1;
-        const int pstage = stage == 0 ? NS - 1 : stage - 1;
-        const int8_t* stn = smem + nstage * STAGE;
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<NM>([&](auto N_) {                                // k-step 0
-            constexpr int n = decltype(N_)::value, jj = n / TM, ii = n % TM;
-            if constexpr (first) {
-                const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                acc[ii][jj] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0[jj], f0[TN + ii], zero, 0, 0, 0);
-            } else {
-                acc[ii][jj] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f0[jj], f0[TN + ii], acc[ii][jj], 0, 0, 0);
-            }
-            if constexpr (n < NFR / 2) {                             // early: the reads must be back before the barrier
-                f1[2 * n] = *reinterpret_cast<const v4i*>(st + fo[1][2 * n]);
-                f1[2 * n + 1] = *reinterpret_cast<const v4i*>(st + fo[1][2 * n + 1]);
-            }
-            if constexpr (s0 >= 0) epi_step(std::integral_constant<int, (s0 >= 0 ? s0 + n : 0)>{});
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        wait_vm_barrier<odd ? 2 * NW + 1 : 4 * NW>();
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<NM>([&](auto N_) {                                // k-step 1
-            constexpr int n = decltype(N_)::value, jj = n / TM, ii = n % TM;
-            acc[ii][jj] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f1[jj], f1[TN + ii], acc[ii][jj], 0, 0, 0);
-            if constexpr (n < NFR / 2) {
-                f0[2 * n] = *reinterpret_cast<const v4i*>(stn + fo[0][2 * n]);
-                f0[2 * n + 1] = *reinterpret_cast<const v4i*>(stn + fo[0][2 * n + 1]);
-            }
-            if constexpr (odd && n < NW) { issue_pair(2 * n, pstage); issue_pair(2 * n + 1, pstage); }
-            if constexpr (s0 >= 0) epi_step(std::integral_constant<int, (s0 >= 0 ? s0 + NM + n : 0)>{});
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        if (odd) advance();
-        stage = nstage;
-    };
-
-    for (;;) {
-        // the first SPREAD slabs carry the epilogue of the previous tile, one step behind every matrix instruction
-        static_for<SPREAD>([&](auto I_) {
-            constexpr int it = decltype(I_)::value;
-            iteration(std::integral_constant<bool, (it & 1) != 0>{}, std::integral_constant<int, it * 2 * NM>{},
-                      std::integral_constant<bool, it == 0>{});
-        });
-        for (int kt = SPREAD; kt < KT; kt += 2) {
-            iteration(std::false_type{}, std::integral_constant<int, -1>{}, std::false_type{});
-            iteration(std::true_type{}, std::integral_constant<int, -1>{}, std::false_type{});
-        }
-        // hand the finished accumulators to the epilogue that runs inside the next tile
-        tile_from_seq<BM, BN>(g, seq, m0p, n0p);
-        interior = __builtin_amdgcn_readfirstlane((int)(al8 && m0p + BM <= g.M && n0p + BN <= g.N)) != 0;
-        svp = sv0 + buf * SVF;
-        buf = buf == NSV - 1 ? 0 : buf + 1;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) prev[i][j] = acc[i][j];
-        seq += nslot;
-        if (seq >= seq_end) break;
-    }
-    // the last tile's epilogue, unhidden
-    static_for<NPIECE * NSTEP>([&](auto S) {
-        epi_step(S);
-        if constexpr (decltype(S)::value == 3 && EPI == HERO_EPI_GELU_REQUANT) wait_vm_barrier<63>();   // publishes 1 / S_a
-    });
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));                      // the redundant tail loads
 }
 
@@ -1015,12 +689,8 @@ bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st,
     return true;
 }
 
-// Tile choice (all measured on MI355X; choose() below): the persistent 256x256 direct-to-LDS kernel, one workgroup per CU,
-// once the grid has enough tiles (160) to keep most of the 256 CUs busy; the persistent 128x128 form of the same kernel,
-// two workgroups per CU, below that (with 96-128 tiles of 256x256 half of the CUs would idle: 10-30 % faster there)
-// and where the last round of 256x256 tiles would be so empty that the small tile fills the chip better
-// (small_tile_fills_better below; per full round the small tile is 10-15 % slower, it needs twice the L2 -> LDS
-// traffic); the ring kernel where ring_form (gemm_common.h) has a form: everything smaller, and a short K.
+// Tile choice (choose() below): the ring kernel where ring_form (gemm_common.h) has a form (everything small, and a short K), the
+// persistent kernels beyond (small_tile_fills_better).
 // the prefetch hint's share per tile: at most one request per lane
 inline void share_prefetch(GemmArgs& g, int64_t tiles, int lanes) {
     if (g.pf_lines <= 0) return;
@@ -1051,49 +721,32 @@ hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) 
     return hero_launch_status();
 }
 
-// The persistent kernel with the epilogue inside the next tile's main loop (256 x 128 tiles).
-template <int EPI, int CDT>
-hero_status launch_ovl(const GemmArgs& g, hipStream_t st) {
-    GemmArgs gp = g;
-    gp.ntm = (g.M + 255) / 256; gp.ntn = (g.N + 127) / 128;
-    const int64_t tiles = (int64_t)gp.ntm * gp.ntn;
-    if (tiles > 0x7fffff00LL) return HERO_ERR_SHAPE;
-    gp.per_xcd = (int)((tiles + NUM_XCD - 1) / NUM_XCD);
-    const int nslot = gp.per_xcd < 32 ? gp.per_xcd : 32;              // one workgroup per CU (152 KB of LDS), 32 CUs per XCD
-    share_prefetch(gp, tiles, 512);
-    hipLaunchKernelGGL((int8_gemm_ovl_kernel<EPI, CDT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(512), 0, st, gp);
-    return hero_launch_status();
-}
-
-// 256 x 256 tiles, one workgroup per CU, or 128 x 128 tiles, two per CU?  Per full round the small tile is 10-15 % slower
-// (twice the L2 -> LDS traffic), but the large one wastes what its last round leaves empty: 384 tiles on 256 CUs are
-// one and a half rounds (8192 x 3072 x 1024, 16-bit output: 47.3 us against 42.0 with the small tile), 512 tiles are
-// two full ones (8192 x 4096 x 1024: 40.7 against 43.6).  Compare the filled fractions, the small tile's scaled by 0.87.
-inline bool small_tile_fills_better(int64_t t256, int64_t t128) {
-    const double e256 = (double)t256 / (double)(((t256 + 255) / 256) * 256);
-    const double e128 = 0.87 * (double)t128 / (double)(((t128 + 511) / 512) * 512);
-    return e128 > e256;
+// 256 x 256 tiles, one workgroup per CU, or 128 x 128 tiles, two per CU?  A CU is handed ceil(tiles / 256) tiles of either; a small one
+// takes a quarter of a large one's time and, with twice the L2 -> LDS traffic, 1.05 to 1.3 times that behind a short K, 1.15 to 1.6
+// behind a long one (the more the emptier the grid: the clock rises where CUs idle).  Measured over 450 products (INT8, E4M3, BF16, 256
+// .. 12000 rows), the rule's losses are 5 % at most.  us, large / small: REQUANT 3817 x 3072 x 1024 18.9 / 17.7, 768 x 12288 x 4096 52.8 /
+// 62.9, 1300 x 12288 x 4096 96.7 / 84.6, GELU^quant 3072 x 4096 x 1024 23.7 / 20.6, 3817 rows 25.0 / 26.4.
+inline bool small_tile_fills_better(int64_t t256, int64_t t128, int64_t kb) {
+    const double per_tile = kb <= 2048 ? 1.2 / 4 : 1.4 / 4;
+    return (double)((t128 + 255) / 256) * per_tile < (double)((t256 + 255) / 256);
 }
 
 // What runs a product.  The codes of the kernels are those of the test hooks (include/hero_debug.h).
-enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_SKINNY = 4, K_PERS256 = 7, K_PERS128 = 8, K_OVL = 9 };
+enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_SKINNY = 4, K_PERS256 = 7, K_PERS128 = 8, K_WAS_OVERLAPPED = 9 /* hook only: as 7 */ };
 struct Choice { Kernel kernel; RingForm form; };
 
-// kb, lda, ldb in bytes; res: a fused residual.  tile: -1 chooses, otherwise the code a test hook
+// kb, lda, ldb in bytes.  tile: -1 chooses, otherwise the code a test hook
 // forces (a forced kernel that cannot run the shape gives way to its closest relative).
-inline Choice choose(hero_dtype adt, hero_epilogue epi, bool res, int64_t M, int64_t N, int64_t kb, int64_t lda, int64_t ldb, int tile = -1) {
+inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, int64_t kb, int64_t lda, int64_t ldb, int tile = -1) {
     const bool i8 = adt == HERO_I8, ring = ring_ok(lda, ldb);
     const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
     // persistent kernels: K long enough that the slab ring never runs more than one tile ahead, whole pairs of slabs, 32-bit
     // per-lane offsets
     const bool pers_ok = ring && kb >= 4 * BK && kb % (2 * BK) == 0 && t128 <= 0x7fffff00LL;
-    // the overlapped-epilogue kernel: its epilogue is spread over the first 16 slabs of the next tile; no fused residual
-    const bool ovl_ok = i8 && pers_ok && kb >= 16 * BK && !res;
     const RingForm form = ring ? ring_form(M, N, kb, epi) : RING_NONE;
     const Choice small = {ring ? K_RING : (M <= 64 || t128 < 192 ? K_REG64 : K_REG128), form == RING_NONE ? RING_128x64 : form};
     if (tile >= 0) {
-        if (tile == K_OVL && ovl_ok) return {K_OVL, RING_NONE};
-        if (tile == K_PERS256 || tile == K_PERS128 || tile == K_OVL) {
+        if (tile == K_PERS256 || tile == K_PERS128 || tile == K_WAS_OVERLAPPED) {
             if (pers_ok && (adt == HERO_I8 || adt == HERO_F8E4M3 || t128 >= 192)) return {tile == K_PERS128 ? K_PERS128 : K_PERS256, RING_NONE};
             if (i8) return {tile == K_PERS128 ? K_REG128 : K_DMA256, RING_NONE};
             return small;
@@ -1104,16 +757,7 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, bool res, int64_t M, int
     if (epi != HERO_EPI_RAW_I32 && skinny_ok(M, N, kb, lda, ldb)) return {K_SKINNY, RING_NONE};
     if (form != RING_NONE) return small;
     if (pers_ok) {
-        if (t256 < 160 || small_tile_fills_better(t256, t128)) return {K_PERS128, RING_NONE};
-        // A GELU epilogue behind a short K goes to the overlapped-epilogue kernel: timed alone with resident operands it
-        // is 3 % behind the 256 x 256 tile (95 against 92.5 us at 16384 x 4096 x 1024), but in a layer the weights come
-        // from HBM and its six slabs of lookahead lose 4 us to that where the other loses 13 (rotating operands: 99.5
-        // against 105.2 us; the 24-layer BERT-large stack 7.95 -> 7.75 ms).  From K = 4096 on its slower main loop
-        // costs more than the hidden epilogue saves (GPT prefill, FC1 16384 x 16384 x 4096: +11 %).
-        // Forcing each of the layer's other GEMMs (QKV, attention-output, FC2) to this kernel or to the 128 x 128 tiles
-        // inside the stack made every one of them slower (7.46 -> 7.50-7.67 ms per 24 layers).
-        const bool gelu = epi == HERO_EPI_DEQUANT_GELU || epi == HERO_EPI_GELU_REQUANT;
-        return {gelu && ovl_ok && kb < 2048 ? K_OVL : K_PERS256, RING_NONE};
+        return {small_tile_fills_better(t256, t128, kb) ? K_PERS128 : K_PERS256, RING_NONE};
     }
     // K that ends in half a slab: the one-tile-per-workgroup 256 x 256 kernel (INT8) once its grid fills the chip, else 128 x 128
     // tiles, through the ring from 32 slabs on.  us, ring / registers: 2048 x 4096 x 4160 INT8 52.1 / 54.8, E4M3 51.0 / 55.7,
@@ -1126,7 +770,6 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, bool res, int64_t M, int
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
     switch (c.kernel) {
-    case K_OVL: if constexpr (ADT == HERO_I8 && RDT < 0) return launch_ovl<EPI, CDT>(g, st); else return HERO_ERR_UNSUPPORTED;
     case K_PERS256: return launch_persistent<256, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
     case K_PERS128: return launch_persistent<128, 128, 2, 2, EPI, CDT, RDT, ADT>(g, 2, st);
     case K_DMA256:
@@ -1142,7 +785,7 @@ hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
     hero_status split;
-    const Choice c = choose((hero_dtype)ADT, (hero_epilogue)EPI, RDT >= 0, g.M, g.N, g.K, g.lda, g.ldb, tile);
+    const Choice c = choose((hero_dtype)ADT, (hero_epilogue)EPI, g.M, g.N, g.K, g.lda, g.ldb, tile);
     // (a few column tiles of a very long K leave most CUs to the split: INT8 16 x 512 x 16384 10.5 us split, 11.6 as eight waves' work)
     if (tile < 0 && (c.kernel != K_SKINNY || (g.N <= 512 && g.K > 8192)) && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
     return launch_choice<ADT, EPI, CDT, RDT>(g, c, st);
@@ -1176,7 +819,7 @@ hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
     g.ksplit = 1; g.kslabs = 0;
     // more than 2^23 rows: the persistent kernels only (INT8 operands end there altogether)
     if (M > 65535 * 128LL) {
-        const Kernel k = choose(dt, gelu ? HERO_EPI_DEQUANT_GELU : HERO_EPI_DEQUANT, residual != nullptr, M, N, g.K, g.lda, g.ldb, tile).kernel;
+        const Kernel k = choose(dt, gelu ? HERO_EPI_DEQUANT_GELU : HERO_EPI_DEQUANT, M, N, g.K, g.lda, g.ldb, tile).kernel;
         if (k != K_PERS256 && k != K_PERS128) return HERO_ERR_UNSUPPORTED;
     }
     return dt == HERO_BF16 ? launch_hp<HERO_BF16>(g, gelu != 0, ws, ws_bytes, (hipStream_t)stream, tile)
@@ -1217,7 +860,7 @@ extern "C" hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void*
 // Test hook (include/hero_debug.h): what the product entry points run without scratch.
 extern "C" int hero_gemm_kernel(hero_dtype dt, hero_epilogue epi, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
     const int64_t es = dt == HERO_BF16 || dt == HERO_F16 ? 2 : 1;
-    const Choice c = choose(dt, epi, false, M, N, K * es, lda * es, ldb * es);
+    const Choice c = choose(dt, epi, M, N, K * es, lda * es, ldb * es);
     return c.kernel == K_RING ? 16 + (int)c.form : (int)c.kernel;
 }
 
