@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -17,3 +18,10 @@ def hero():
     """The HIP library binding; GPU tests fail loudly if it cannot be loaded."""
     import paper_2310_17723_amd as pkg
     return pkg.load()
+
+
+@pytest.fixture(autouse=True, scope="module")
+def _garbage_of_the_module_before():
+    """A pytest.raises block ties its frame into a cycle, the test's device tensors with it: collected here, not in the middle of a
+    test that counts device memory."""
+    gc.collect()
