@@ -449,6 +449,162 @@ __global__ __launch_bounds__(256) void ln_quant_row_kernel(LnArgs a) {
     }
 }
 
+// ---- embedding of many tokens, rows of 513 .. 1024 values: TWO rows per wave ------------------------------------
+// Bound by the vector ALU's issue slots, not by HBM: of the wave-per-row kernel's 410 instructions per row of 1024 values about 170 do
+// not depend on the row's length (three reductions across 64 lanes, the row's scalars, addresses, index lookups).  Here a half wave
+// owns a row (32 values per lane), so that one instruction serves two rows there: 320 per row.  The last step of a half-wave reduction is
+// one v_permlane16_swap, behind which every lane holds the result.  Persistent 16-wave workgroups, parameters in LDS, the next rows in
+// flight: as in ln_quant_kernel.  us, wave per row -> two rows: 1024 values, 6000 rows 8.4 -> 7.2, 8192 rows 8.9 -> 7.6, 12000 rows
+// 11.4 -> 11.2, 16384 rows 13.9 -> 11.8, 65536 rows 40.8 -> 32.5; 768 values, 6000 rows 8.2 -> 6.9, 16384 rows 13.4 -> 11.2.
+// (The form without lookups, two INT8 addends of 16384 x 1024, went from 12.8 to 14.3 us: fewer rows in flight cost it more.)
+template <bool IS_MAX>
+__device__ __forceinline__ float half_reduce(float x) {              // over the 32 lanes of a half wave, the result in every lane
+#define HERO_DPP(ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), ctrl, 0xF, 0xF, true))
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0xB1));      // quad_perm [1,0,3,2]
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0x4E));      // quad_perm [2,3,0,1]
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0x141));     // row_half_mirror
+    x = dpp_step<IS_MAX>(x, HERO_DPP(0x140));     // row_mirror
+#undef HERO_DPP
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);       // rows {0, 0, 2, 2} and {1, 1, 3, 3}
+    return dpp_step<IS_MAX>(__uint_as_float(r[0]), __uint_as_float(r[1]));      // (a bit cast of the element itself would read r[0] twice)
+}
+
+template <int RDT>
+__global__ __launch_bounds__(1024) void embed_pair_kernel(LnArgs a) {
+    constexpr int EPL = 16, CH = EPL * 32, NCH = 2;
+    __shared__ __attribute__((aligned(16))) float sp[2 * NCH * CH];      // gamma, beta
+    const int D = a.D, tid = threadIdx.x, hl = tid & 31, lane0 = hl * EPL;
+    const int64_t step = (int64_t)gridDim.x * 32;             // 16 waves, two rows each
+    int64_t row = (int64_t)blockIdx.x * 32 + (tid >> 5);
+    const bool has_r2 = a.r2 != nullptr;
+
+    v4i rx[NCH], rr[NCH][2], rs[NCH][2];
+    float xsr;
+    int gx, gr, g2 = 0;                                       // table rows of the next fetch; a half wave beyond the last row reads that one again
+    auto lookup = [&](int64_t rw) {
+        const int64_t i = rw < a.M ? rw : a.M - 1;
+        gx = min(max(a.x_idx[i], 0), a.x_rows - 1);
+        gr = min(max(a.r_idx[i], 0), a.r_rows - 1);
+        if (has_r2) g2 = min(max(a.r2_idx[i], 0), a.r2_rows - 1);
+    };
+    auto fetch = [&]() {
+        xsr = a.x_row_scale[gx];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int j0 = c * CH + lane0;
+            if (j0 < D) {
+                rx[c] = *reinterpret_cast<const v4i*>((const int8_t*)a.x + (int64_t)gx * D + j0);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) rr[c][k] = *reinterpret_cast<const v4i*>((const uint16_t*)a.r + (int64_t)gr * D + j0 + 8 * k);
+                if (has_r2)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) rs[c][k] = *reinterpret_cast<const v4i*>((const uint16_t*)a.r2 + (int64_t)g2 * D + j0 + 8 * k);
+            }
+        }
+    };
+    // lanes beyond D hold zeros throughout: nothing below asks for them until the results are written
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        rx[c] = v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) rr[c][k] = rs[c][k] = v4i{0, 0, 0, 0};
+    }
+    lookup(row);
+    fetch();
+    lookup(row + step);
+
+    // column j = chunk c, lane l, element 4 e4 + t  ->  [c][e4][l][t]: 32 consecutive 16-byte slots per read, the same for both halves
+    {
+        const int j = tid, w = j % CH, pos = (((j / CH) * (EPL / 4) + (w % EPL) / 4) * 32 + w / EPL) * 4 + (w % 4);
+        const bool in = j < D;
+        const float pg = in ? a.gamma[j] : 0.0f, pb = in && a.beta ? a.beta[j] : 0.0f;
+        sp[pos] = pg; sp[NCH * CH + pos] = pb;
+    }
+    __syncthreads();
+    const float inv_d = 1.0f / (float)D;
+    auto param = [&](int k, int c, int e4) { return *reinterpret_cast<const v4f*>(sp + k * NCH * CH + ((c * (EPL / 4) + e4) * 32 + hl) * 4); };
+    auto hp_at = [](const v4i (&w)[2], int e) { return hp_to_f32<RDT>(((uint32_t)w[e >> 3][(e & 7) >> 1] >> (16 * (e & 1))) & 0xffffu); };
+
+    // (wave-uniform: the wave's first row decides)
+    for (int64_t first = __builtin_amdgcn_readfirstlane(tid >> 6) * 2 + (int64_t)blockIdx.x * 32; first < a.M; first += step, row += step) {
+        asm volatile("" : "+v"(xsr));                         // nothing that reads the fetched registers may move above this point
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            asm volatile("" : "+v"(rx[c]));
+#pragma unroll
+            for (int k = 0; k < 2; ++k) { asm volatile("" : "+v"(rr[c][k])); asm volatile("" : "+v"(rs[c][k])); }
+        }
+        float v[NCH][EPL];
+        const float xs = xsr;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                float f[4];
+                unpack4(rx[c][e4], f);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[c][4 * e4 + t] = fmaf(f[t], xs, hp_at(rr[c], 4 * e4 + t));
+            }
+            if (has_r2)
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) v[c][e] += hp_at(rs[c], e);
+        }
+        if (first + step < a.M) {                             // the next rows' loads go out now, into the registers just unpacked
+            fetch();
+            lookup(row + 2 * step);
+        }
+
+        float s = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) s += v[c][e];
+        const float mean = half_reduce<false>(s) * inv_d;
+        float q = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const float mean_c = c * CH + lane0 < D ? mean : 0.0f;       // padding stays out of the squared deviations
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) {
+                v[c][e] -= mean_c;
+                q = fmaf(v[c][e], v[c][e], q);
+            }
+        }
+        const float rstd = __builtin_amdgcn_rsqf(half_reduce<false>(q) * inv_d + a.eps);
+        float amax = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e4 = 0; e4 < EPL / 4; ++e4) {
+                const v4f g = param(0, c, e4), b = param(1, c, e4);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {                 // (padded columns have gamma = beta = 0)
+                    v[c][4 * e4 + t] = fmaf(v[c][4 * e4 + t] * rstd, g[t], b[t]);
+                    amax = fmaxf(amax, fabsf(v[c][4 * e4 + t]));
+                }
+            }
+        amax = half_reduce<true>(amax);
+        const float sc = amax == 0.0f ? 1.0f : __fdiv_rn(amax, 127.0f), inv_sc = __builtin_amdgcn_rcpf(sc);
+        if (row < a.M) {
+            if (hl == 0) a.y_scale[row] = sc;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                const int j0 = c * CH + lane0;
+                if (j0 >= D) continue;
+                uint32_t pk[EPL / 4];
+#pragma unroll
+                for (int e4 = 0; e4 < EPL / 4; ++e4) pk[e4] = ln_codes4(v[c] + 4 * e4, sc, inv_sc, false);
+                *reinterpret_cast<v4i*>(a.y_q + row * (int64_t)D + j0) = v4i{(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
+            }
+        }
+    }
+}
+
+// Up to 4096 rows the wave-per-row kernel has one row per wave and is ahead (1024 values: 1024 rows 4.1 us against 6.6, 4096 rows
+// 6.0 against 7.1).
+constexpr int64_t EMBED_PAIR_ROWS = 4096;
+
 template <int XDT, int RDT, int NCH, bool GATHER = false>
 hero_status launch_nch(const LnArgs& a, hipStream_t st) {
     constexpr int CH = (XDT == HERO_I8 ? 16 : 8) * HERO_WAVE;
@@ -509,6 +665,11 @@ hero_status launch_r(const LnArgs& a, hipStream_t st) {
 template <int RDT>
 hero_status launch_gather(const LnArgs& a, hipStream_t st) {
     const int nch = (a.D + 16 * HERO_WAVE - 1) / (16 * HERO_WAVE);
+    if (a.D > 512 && a.D <= 1024 && a.M > EMBED_PAIR_ROWS) {
+        const unsigned blocks = (unsigned)(a.M < 256 * 32 ? (a.M + 31) / 32 : 256);
+        hipLaunchKernelGGL((embed_pair_kernel<RDT>), dim3(blocks), dim3(1024), 0, st, a);
+        return hero_launch_status();
+    }
     if (nch <= 1) return launch_nch<HERO_I8, RDT, 1, true>(a, st);
     if (nch <= 2) return launch_nch<HERO_I8, RDT, 2, true>(a, st);
     if (nch <= 4) return launch_nch<HERO_I8, RDT, 4, true>(a, st);

@@ -1,0 +1,51 @@
+"""The embedding with two rows per wave (513 .. 1024 values, more than 4096 tokens): a last wave with one row, one and several rounds of
+the grid, rows that end in either chunk of a lane, indices outside their tables, rows without variance and with infinities."""
+import pytest
+import torch
+
+import paper_2310_17723_amd as pkg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [528, 768, 784, 1008, 1024])
+@pytest.mark.parametrize("T", [4096, 4097, 8192, 8195, 16385])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("typed", [True, False])
+def test_embedding(D, T, dt, typed):
+    hero, g = pkg.load(), torch.Generator(device="cuda").manual_seed(D + T)
+    rnd = lambda *n: torch.randn(n, device="cuda", generator=g)
+    V, P, idx = 1000, 300, lambda n: torch.randint(-1, n + 1, (T,), dtype=torch.int32, device="cuda", generator=g)   # some outside: clamped
+    tok, ts = (rnd(V, D) * 40).round().clamp(-127, 127).to(torch.int8), torch.rand(V, device="cuda", generator=g) / 40 + 0.01
+    pos, typ, gamma, beta = rnd(P, D).to(dt), rnd(2, D).to(dt), 1 + 0.1 * rnd(D), 0.1 * rnd(D)
+    i, p, t = idx(V), idx(P), idx(2)
+    at = lambda table, k: table.double()[k.long().clamp(0, table.shape[0] - 1)]
+    v = at(tok, i) * at(ts, i)[:, None] + at(pos, p) + (at(typ, t) if typed else 0)
+    for b in (beta, None):
+        guard = torch.full((T + 2, D), 77, dtype=torch.int8, device="cuda")
+        q, s = hero.hero_embed_ln_quant(i, p, t if typed else None, tok, ts, pos, typ if typed else None, gamma, b, 1e-5, y_q=guard[:T])
+        ref = torch.nn.functional.layer_norm(v, (D,), gamma.double(), None if b is None else b.double(), 1e-5)
+        s_ref = ref.abs().amax(1) / 127
+        # fp32 statistics over D values of one magnitude: some 1e-6
+        assert float(((s.double() - s_ref).abs() / s_ref).max()) <= 1e-5
+        assert float((q.double() - ref / s_ref[:, None]).abs().max()) <= 0.501
+        assert bool((guard[T:] == 77).all())
+
+
+def test_rows_do_not_see_each_other():
+    hero, g, T, D = pkg.load(), torch.Generator(device="cuda").manual_seed(1), 8193, 1024
+    tok = torch.randint(-127, 128, (64, D), dtype=torch.int8, device="cuda", generator=g)
+    ts, pos = torch.rand(64, device="cuda", generator=g) + 0.5, torch.randn((8, D), device="cuda", generator=g).to(torch.bfloat16)
+    tok[1], pos[1], pos[2, 9] = 0, 0.0, float("inf")
+    i, p = torch.randint(2, 64, (T,), dtype=torch.int32, device="cuda", generator=g), torch.randint(3, 8, (T,), dtype=torch.int32, device="cuda", generator=g)
+    ones, zeros = torch.ones(D, device="cuda"), torch.zeros(D, device="cuda")
+    run = lambda: hero.hero_embed_ln_quant(i, p, None, tok, ts, pos, None, ones, zeros, 1e-5)
+    clean = run()
+    for r in (4, 8192):                                           # no variance
+        i[r], p[r] = 1, 1
+    p[7] = 2                                                      # an infinity
+    q, s = run()
+    keep = torch.ones(T, dtype=torch.bool, device="cuda")
+    keep[[4, 7, 8192]] = False
+    assert torch.equal(q[keep], clean[0][keep]) and torch.equal(s[keep], clean[1][keep])
+    assert bool((q[[4, 8192]] == 0).all()) and bool((s[[4, 8192]] == 1).all())
