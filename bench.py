@@ -51,7 +51,7 @@ def measured_traffic(key):
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
         e = dict(t["kernels"][key])
-        e["measured_at_commit"] = t.get("commit")
+        e.setdefault("measured_at_commit", t.get("commit"))
         return e
     except (OSError, KeyError, ValueError):
         return None
