@@ -549,9 +549,15 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
 // A block owns 128 queries of one (batch, head), in four groups of 32 (two sets of 16 each), and stages all of K (direct to LDS) and
 // V once.  KW waves share a group's keys: one up to 256 keys, then no barrier follows; two beyond (all scores of 512 keys in one wave's
 // registers leave two waves per SIMD, and 32 x 16 x 512 took 73 us, the two-pass kernel 69): the halves' maxima and sums meet in LDS,
-// and each wave ends with half of the channels.  The offset of the unsigned codes is removed by a second matrix instruction as in the
-// online variant, so o = -sum code * v.  Bound by the vector ALU; four waves per SIMD.
+// and each wave ends with half of the channels.  A hidden key is left out by the size of its masked score alone, which asks for a scale of
+// KEEP_MIN_QK or more; the two-pass kernel serves the others (selecting the exponentials here made the 256- and 512-key forms spill).
+// The offset of the unsigned codes is removed by a second matrix instruction as in the online variant, so o = -sum code * v.  Bound by
+// the vector ALU; four waves per SIMD.
 // ------------------------------------------------------------------------------------------
+// (2^30 - 2^20) * 2^-23 * log2(e) = 184: with the largest score, 64 * 128 * 128, on either side of the mask's value a hidden key's
+// exponential, below 2^-149, is 0 (E4M3: 3e38 beside 64 * 448 * 448)
+constexpr float KEEP_MIN_QK = 0x1p-23f;
+
 template <int ODT, int FMT, int NT, int KW>
 __global__ __launch_bounds__(256 * KW, 4) void int8_attn_keep_kernel(AttnArgs a) {
     constexpr bool F8 = FMT == HERO_F8E4M3;
@@ -1404,7 +1410,7 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     // 15.0 -> 10.7, (8 x 16 x 256) 10.5 -> 8.4; two passes -> one 32 x 16 x 512 padded 65 -> 56.5, 11 x 16 x 347 19.7 -> 14.4, 16 x 16 x 256
     // 14.9 -> 10.4, 32 x 12 x 128 10.1 -> 7.6; E4M3 32 x 16 x 512 55.7 -> 56.8, 11 x 16 x 347 17.5 -> 13.8, 16 x 16 x 256 14.3 -> 11.1.
     const int64_t blocks = B * H * ((Sq + BQ - 1) / BQ);
-    const bool keep = Dh == 64 && Skv <= 512;
+    const bool keep = Dh == 64 && Skv <= 512 && qk_scale >= KEEP_MIN_QK;
     if ((blocks <= (keep ? 191 : 256) && (Dh == 64 || B * H * ((Sq + 31) / 32) <= 768)) || Sq <= 32) {
         if (fp8) return Dh == 64 ? launch_split<64, HERO_F8E4M3, 4>(a, out_dt, st) : launch_split<128, HERO_F8E4M3, 4>(a, out_dt, st);
         return Dh == 64 ? launch_split<64, HERO_I8, 4>(a, out_dt, st) : launch_split<128, HERO_I8, 4>(a, out_dt, st);

@@ -15,7 +15,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("mask", [HB.MASK_PADDING, HB.MASK_CAUSAL])
 @pytest.mark.parametrize("qk", [2.0 ** -23, 1e-9, 1e-38, 0.0])
 @pytest.mark.parametrize("B,Sq,Skv,Dh", [(2, 513, 513, 64), (44, 97, 577, 64), (44, 97, 161, 128),
-                                         (2, 65, 65, 64), (3, 33, 200, 128), (2, 17, 600, 64)])
+                                         (2, 65, 65, 64), (3, 33, 200, 128), (2, 17, 600, 64),
+                                         # from here on: the one-pass kernel's sizes
+                                         (43, 65, 65, 64), (22, 129, 129, 64), (15, 257, 257, 64), (11, 509, 509, 64), (43, 33, 320, 64)])
 def test_hidden_keys_at_vanishing_scales(B, Sq, Skv, Dh, qk, mask, fp8):
     """With scores that tell no key from another a hidden key must be left out as such, not by the size of its score: padded keys and
     the future hold larger values than what a query sees.  S_p = 2^-8: no number of equal probabilities lies on a rounding tie."""
