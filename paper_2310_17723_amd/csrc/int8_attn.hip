@@ -894,32 +894,33 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
     auto stats = [&](v4i (&kf)[DS], int step) {
         SACC acc = scores(kf);
         if (step + 2 * NW < nsteps) load_k(kf, step + 2 * NW);
-        auto part = [&](auto EDGE) {
-            const int lim = nvis - (step * SK + hh * 4);         // key visible iff 8g + t < lim
-            if constexpr (decltype(EDGE)::value)
+        const bool edge = (step + 1) * SK > nvis_min;
+        const int lim = nvis - (step * SK + hh * 4);             // key visible iff 8g + t < lim
+        if (edge) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    if constexpr (F8) acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : FMASKED;
-                    else acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : MASKED;
-                }
-            auto smax = acc[0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) smax = max(smax, acc[r]);
-            smax = max(smax, __shfl_xor(smax, 32));
-            if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {
-                const float mn = fmaxf(m2, (float)smax * c2);
-                float sum = 0.0f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float e = __builtin_amdgcn_exp2f(fmaf((float)acc[r], c2, -mn));
-                    if constexpr (decltype(EDGE)::value) e = ((r >> 2) * 8 + (r & 3)) < lim ? e : 0.0f;
-                    sum += e;
-                }
-                l = fmaf(l, __builtin_amdgcn_exp2f(m2 - mn), sum);
-                m2 = mn;
+            for (int r = 0; r < 16; ++r) {
+                if constexpr (F8) acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : FMASKED;
+                else acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : MASKED;
             }
-        };
-        if ((step + 1) * SK > nvis_min) part(std::true_type{}); else part(std::false_type{});
+        }
+        auto smax = acc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) smax = max(smax, acc[r]);
+        smax = max(smax, __shfl_xor(smax, 32));
+        if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {
+            const float mn = fmaxf(m2, (float)smax * c2);
+            float e[16], sum = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(fmaf((float)acc[r], c2, -mn));
+            if (edge) {                                          // (as above: a hidden key counts for nothing)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) e[r] = ((r >> 2) * 8 + (r & 3)) < lim ? e[r] : 0.0f;
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum += e[r];
+            l = fmaf(l, __builtin_amdgcn_exp2f(m2 - mn), sum);
+            m2 = mn;
+        }
     };
     if (wave < nsteps) load_k(k0, wave);
     if (wave + NW < nsteps) load_k(k1, wave + NW);
