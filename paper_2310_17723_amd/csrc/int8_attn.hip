@@ -46,6 +46,18 @@ struct AttnArgs {
     const int8_t* kn; const int8_t* vn; int64_t nstride; int8_t* kc; int8_t* vc;
 };
 
+// the output rows of a block of BQ padded queries: zeros
+template <int DH, int ODT>
+__device__ __forceinline__ void zero_rows(const AttnArgs& a, int b, int h, int q0, int threads) {
+    constexpr int U = DH / 4;                                  // stores of 4 elements, as the kernels' own
+    const int rows = min(BQ, a.Sq - q0);
+    for (int idx = threadIdx.x; idx < rows * U; idx += threads) {
+        const int64_t e = ((int64_t)b * a.Sq + q0 + idx / U) * a.ldo + (int64_t)h * DH + (idx % U) * 4;
+        if (ODT == HERO_I8 || ODT == HERO_F8E4M3) *reinterpret_cast<uint32_t*>((int8_t*)a.out + e) = 0u;
+        else { v2i z = {0, 0}; *reinterpret_cast<v2i*>((uint16_t*)a.out + e) = z; }
+    }
+}
+
 // FMT = HERO_F8E4M3: the same flow with E4M3 codes (Sec. 2.1): q, k, v are E4M3 bytes, the scores and the PV sums
 // are fp32 accumulators of v_mfma_f32_32x32x64_f8f6f4, the probabilities are quantized to non-negative E4M3 codes
 // (saturating at 448 = p / S_p for p = 1 with S_p = 1/448), signed operands need no offset and no column sums.
@@ -98,16 +110,7 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
     // zeros.  A block with no real query writes them and leaves; a wave with no real query keeps staging K / V
     // and meeting the barriers (and adds its share of the column sums) but computes no score.
     const int qlim = (a.mask == HERO_MASK_PADDING && a.Sq == a.Skv) ? len : a.Sq;
-    if (q0 >= qlim) {
-        constexpr int U = DH / 4;                              // stores of 4 elements, as the output stage below
-        const int rows = min(BQ, a.Sq - q0);
-        for (int idx = tid; idx < rows * U; idx += 256) {
-            const int64_t e = ((int64_t)b * a.Sq + q0 + idx / U) * a.ldo + (int64_t)h * DH + (idx % U) * 4;
-            if (ODT == HERO_I8 || ODT == HERO_F8E4M3) *reinterpret_cast<uint32_t*>((int8_t*)a.out + e) = 0u;
-            else { v2i z = {0, 0}; *reinterpret_cast<v2i*>((uint16_t*)a.out + e) = z; }
-        }
-        return;
-    }
+    if (q0 >= qlim) { zero_rows<DH, ODT>(a, b, h, q0, 256); return; }
     const bool wact = __builtin_amdgcn_readfirstlane(q0 + wq * 32) < qlim;     // wave-uniform
 
     // ---- Q fragments (second MFMA operand), kept in registers -----------------------------
@@ -588,7 +591,8 @@ __global__ __launch_bounds__(256 * KW, 4) void int8_attn_keep_kernel(AttnArgs a)
     const bool causal = a.mask == HERO_MASK_CAUSAL;
     const int qlim = (a.mask == HERO_MASK_PADDING && a.Sq == a.Skv) ? len : a.Sq;
     const int kmax = max(causal ? min(len, min(q0 + BQ, a.Sq) + shift) : len, 0);
-    const int ntiles = q0 < qlim ? (kmax + 63) / 64 : 0;
+    if (q0 >= qlim) { zero_rows<DH, ODT>(a, b, h, q0, 256 * KW); return; }       // (before any barrier: the whole block leaves)
+    const int ntiles = (kmax + 63) / 64;
     const int w0 = q0 + ((group + slot) & 3) * 32;                           // this wave's queries
     v4i qf[2];
 #pragma unroll
