@@ -1413,10 +1413,19 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     // Up to 512 keys of 64 channels the one-pass kernel takes over from three quarters of the CUs on, and beyond from the two-pass
     // kernel altogether: split -> one pass 128 blocks (8 x 16 x 100) 5.7 -> 6.3, 192 (12 x 16 x 128) 7.0 -> 6.6, 256 (4 x 16 x 512)
     // 15.0 -> 10.7, (8 x 16 x 256) 10.5 -> 8.4; two passes -> one 32 x 16 x 512 padded 65 -> 56.5, 11 x 16 x 347 19.7 -> 14.4, 16 x 16 x 256
-    // 14.9 -> 10.4, 32 x 12 x 128 10.1 -> 7.6; E4M3 32 x 16 x 512 55.7 -> 56.8, 11 x 16 x 347 17.5 -> 13.8, 16 x 16 x 256 14.3 -> 11.1.
-    const int64_t blocks = B * H * ((Sq + BQ - 1) / BQ);
-    const bool keep = Dh == 64 && Skv <= 512 && qk_scale >= KEEP_MIN_QK;
-    if ((blocks <= (keep ? 191 : 256) && (Dh == 64 || B * H * ((Sq + 31) / 32) <= 768)) || Sq <= 32) {
+    // 14.9 -> 10.4, 32 x 12 x 128 10.1 -> 7.6; E4M3 11 x 16 x 347 18.0 -> 14.2, 16 x 16 x 256 14.0 -> 10.9.  Up to one block per CU it
+    // stays with the split kernel where the blocks are little more than half full (192 blocks of 129 padded keys 6.0 / 7.2, of 160
+    // 6.7 / 7.5; but of 192, three quarters full, 8.2 / 7.4), and where an XCD is handed more of the 512-key form's blocks than it has CUs (252
+    // blocks, 36 on some XCDs: 300 keys 12.1 / 12.8; 216 blocks, 30: 12.0 / 9.2).
+    const int64_t nqb = (Sq + BQ - 1) / BQ, blocks = B * H * nqb, pieces = B * H * ((Sq + 31) / 32), on_xcd = (B * H + 15) / 16 * 2 * nqb;
+    // E4M3 of more than 256 keys, from six blocks of the two-pass kernel per CU on: its wide matrix instruction takes 64 keys where the one-pass
+    // kernel's is half filled, and with many blocks that shows; padding, which ends its blocks early, adds to it.  Two passes / one, padded:
+    // 2064 blocks 260 keys 31.3 / 32.3, 320 36.0 / 37.2, 448 43.1 / 44.4, 480 47.8 / 48.7, 512 55.4 / 54.4, 3072 blocks 320 48.4 / 53.1, 512
+    // 71.3 / 72.2, but 1392 blocks 320 27.3 / 26.8;  full: 2064 blocks 320 43.3 / 46.5, 347 52.6 / 52.0, 448 54.1 / 51.1, 512 62.0 / 57.1.
+    const bool many_f8 = fp8 && blocks >= 1536 && Skv > 256 && Skv <= (mask == HERO_MASK_PADDING ? 480 : 352);
+    const bool few = blocks <= 191 || (blocks <= 256 && (2 * pieces <= 5 * blocks || (Skv > 256 && on_xcd > 32)));
+    const bool keep = Dh == 64 && Skv <= 512 && qk_scale >= KEEP_MIN_QK && !many_f8;
+    if (((keep ? few : blocks <= 256) && (Dh == 64 || pieces <= 768)) || Sq <= 32) {
         if (fp8) return Dh == 64 ? launch_split<64, HERO_F8E4M3, 4>(a, out_dt, st) : launch_split<128, HERO_F8E4M3, 4>(a, out_dt, st);
         return Dh == 64 ? launch_split<64, HERO_I8, 4>(a, out_dt, st) : launch_split<128, HERO_I8, 4>(a, out_dt, st);
     }

@@ -18,8 +18,20 @@ pytestmark = pytest.mark.gpu
                                         (256, 256, (256, 193)), (257, 257, (257, 0)), (33, 320, (320, 65)), (384, 384, (384, 321)),
                                         (100, 449, (449, 385)), (512, 512, (512, 448))])
 def test_against_oracle(Sq, Skv, lens, mask, fp8):
-    hero, H, Dh = pkg.load(), 6, 64
-    B = 256 // (H * ((Sq + 127) // 128)) + 1
+    H = 6
+    against_oracle(256 // (H * ((Sq + 127) // 128)) + 1, H, Sq, Skv, lens, mask, fp8)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("mask", [HB.MASK_NONE, HB.MASK_PADDING])
+@pytest.mark.parametrize("B,H,S,lens", [(48, 2, 160, (160, 129)), (48, 2, 161, (161, 100)), (21, 4, 320, (320, 161)), (20, 4, 320, (320, 161)),
+                                        (128, 4, 300, (300, 151)), (96, 4, 400, (400, 257)), (127, 4, 300, (300, 300))])
+def test_either_side_of_the_rules(B, H, S, lens, mask, fp8):
+    against_oracle(B, H, S, S, lens, mask, fp8)                      # little filled blocks, crowded XCDs, E4M3 of many blocks
+
+
+def against_oracle(B, H, Sq, Skv, lens, mask, fp8):
+    hero, Dh = pkg.load(), 64
     g = torch.Generator(device="cuda").manual_seed(Sq * 3 + Skv)
     dt = torch.float8_e4m3fn if fp8 else torch.int8
     qkv = [(torch.randn((B, s, 3, H, Dh), device="cuda", generator=g) * (40 if fp8 else 30)).clamp(-127, 127).to(dt) for s in (Sq, Skv)]
