@@ -27,6 +27,8 @@ using namespace hero_gemm;
 
 namespace {
 
+// the residual's rows: none, four elements as one vector, element by element (16-bit products take any stride and address)
+enum { RES_NONE = 0, RES_ALIGNED = 1, RES_ANY = 2 };
 struct SkinnyArgs {
     GemmArgs g;
     int epi, c_dt, has_res;
@@ -288,7 +290,10 @@ __global__ __launch_bounds__(SKINNY_WAVES * 64, 2) void skinny_gemm_kernel(Skinn
     }
     const bool bf = sa.c_dt == HERO_BF16;
     if (sa.has_res) {
-        const v2i r = *reinterpret_cast<const v2i*>((const uint16_t*)g.residual + (int64_t)m_e * g.ldr + n_e);
+        const uint16_t* const rp = (const uint16_t*)g.residual + (int64_t)m_e * g.ldr + n_e;
+        v2i r;
+        if (sa.has_res == RES_ALIGNED) r = *reinterpret_cast<const v2i*>(rp);
+        else r = v2i{(int)(rp[0] | (uint32_t)rp[1] << 16), (int)(rp[2] | (uint32_t)rp[3] << 16)};
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const uint32_t b = ((uint32_t)r[t >> 1] >> (16 * (t & 1))) & 0xffffu;
@@ -322,7 +327,8 @@ namespace hero_gemm {
 
 hero_status launch_skinny(const GemmArgs& g, hero_dtype adt, hero_epilogue epi, hero_dtype c_dt, hipStream_t st) {
     SkinnyArgs a;
-    a.g = g; a.epi = epi; a.c_dt = c_dt; a.has_res = g.residual != nullptr;
+    a.g = g; a.epi = epi; a.c_dt = c_dt;
+    a.has_res = !g.residual ? RES_NONE : (g.ldr % 4 == 0 && ((uintptr_t)g.residual & 7) == 0 ? RES_ALIGNED : RES_ANY);
     a.h = nullptr; a.gamma = a.beta = nullptr; a.eps = 0.0f;
     const bool one = g.M <= 16;
     switch (adt) {
@@ -348,7 +354,7 @@ hero_status hero_ln_gemm(const void* h, hero_dtype h_dt, const float* gamma, con
     g.Bt = (const int8_t*)Wt; g.ldb = K; g.b_col_scale = w_scale; g.bias = bias; g.residual = nullptr; g.ldr = 0;
     g.out_col_scale = out_col_scale; g.C = C; g.ldc = ldc; g.M = (int)M; g.N = (int)N; g.K = (int)K;
     g.ntm = g.ntn = g.per_xcd = 0; g.ksplit = 1; g.kslabs = 0;
-    a.epi = epi; a.c_dt = c_dt; a.has_res = 0; a.h = h; a.gamma = gamma; a.beta = beta; a.eps = eps;
+    a.epi = epi; a.c_dt = c_dt; a.has_res = RES_NONE; a.h = h; a.gamma = gamma; a.beta = beta; a.eps = eps;
     hipStream_t st = (hipStream_t)stream;
     if (fp8) return h_dt == HERO_BF16 ? launch_tiles<HERO_F8E4M3, 1, HERO_BF16>(a, st) : HERO_ERR_UNSUPPORTED;
     return h_dt == HERO_BF16 ? launch_tiles<HERO_I8, 1, HERO_BF16>(a, st) : launch_tiles<HERO_I8, 1, HERO_F16>(a, st);

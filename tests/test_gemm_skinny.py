@@ -71,6 +71,22 @@ def test_float(M, N, kb, dt):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dt", DTYPES[2:])
+@pytest.mark.parametrize("M,N", [(3, 4096), (32, 4112)])
+def test_residual_rows_anywhere(M, N, dt):
+    """The 16-bit product takes a residual of any row stride and address: the same bits as from aligned rows."""
+    hero, K, g = pkg.load(), 512, torch.Generator(device="cuda").manual_seed(M)
+    a, w = torch.randn((M, K), device="cuda", generator=g).to(dt), torch.randn((N, K), device="cuda", generator=g).to(dt)
+    res = torch.randn((M, N), device="cuda", generator=g).to(dt)
+    want = hero.hero_hp_gemm(a, w, residual=res)
+    for pad, off in ((1, 0), (3, 1), (4, 1), (4, 2), (2, 3), (0, 1)):
+        flat = torch.full((M * (N + pad) + 8,), float("nan"), dtype=dt, device="cuda")
+        view = flat[off:off + M * (N + pad)].view(M, N + pad)[:, :N]
+        view.copy_(res)
+        assert torch.equal(hero.hero_hp_gemm(a, w, residual=view), want), (pad, off)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("d,f,fmt", [(2048, 4160, "i8"), (4096, 16384, "i8"), (2048, 2048, "fp8"), (4096, 4096, "f16")])
 def test_fused_ln_quant(d, f, fmt):
     """A pre-LN layer of one token per sequence: with up to eight rows each LN^quant runs inside the linear behind it, with nine it
