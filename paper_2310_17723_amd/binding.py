@@ -112,7 +112,7 @@ class Hero:
             fn = getattr(self.lib, name)      # AttributeError if the library lacks the symbol
             fn.restype, fn.argtypes = res, args
         self._layer_fwd = self.lib["hero_layer_fwd"]                  # the same entry point, its io struct as packed bytes
-        self._layer_fwd.restype, self._layer_fwd.argtypes = i32, [vp, vp, vp, vp, C.c_size_t, vp]
+        self._layer_fwd.restype, self._layer_fwd.argtypes = i32, [C.POINTER(LayerDesc), C.POINTER(LayerWeights), vp, vp, C.c_size_t, vp]
 
     # ------------------------------------------------------------------ helpers
     def strerror(self, status: int) -> str:
@@ -365,5 +365,5 @@ class Hero:
         io = _LAYER_IO.pack(B, S, ptr(x_q), ptr(x_scale), ptr(out_q), ptr(out_scale), ptr(h), ptr(kv_len), ptr(k_cache), ptr(v_cache),
                             k_cache.shape[2] if k_cache is not None else 0, ptr(x_hp), ptr(out_hp),
                             ptr(next_read), 0 if next_read is None else next_read.nbytes)
-        st = self._layer_fwd(C.addressof(desc), C.addressof(weights), io, workspace.data_ptr(), workspace.nbytes, _stream(stream))
+        st = self._layer_fwd(C.byref(desc), C.byref(weights), io, workspace.data_ptr(), workspace.nbytes, _stream(stream))
         self._check(st)

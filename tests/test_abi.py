@@ -78,6 +78,19 @@ def test_argument_errors_come_before_any_launch(lib):
     assert "built-in scratch" in lib.strerror(5)
 
 
+def test_layer_fwd_refuses_a_structure_of_the_wrong_type(lib):
+    """Swapped or foreign structures are a Python error, before the library reads a byte of them."""
+    import types
+    import torch
+    from paper_2310_17723_amd.binding import LayerDesc, LayerIO, LayerWeights
+    d, w, ws = LayerDesc(0, 128, 2, 64, 256, 1e-5, 0, 31), LayerWeights(), torch.zeros(256, dtype=torch.uint8)
+    stream = types.SimpleNamespace(cuda_stream=0)
+    for pair in ((w, d), (d, d), (w, w), (d, LayerIO()), (C.c_int(0), w)):
+        with pytest.raises(C.ArgumentError):
+            lib.hero_layer_fwd(*pair, 0, 0, ws, stream=stream)
+    lib.hero_layer_fwd(d, w, 0, 0, ws, stream=stream)               # (no rows: nothing to do)
+
+
 def test_binding_structs_match_the_header_layout(tmp_path):
     """The three structs of hero_layer_fwd as gcc lays them out from include/hero.h against the binding's ctypes
     mirrors: size and the offset of every field (a field added to one side only would shift everything behind it)."""
