@@ -96,8 +96,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# (not a public name of torch: where a build lacks it, the public way)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    return _raw_stream(torch.cuda.current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
 
 
 def _strides4(t):

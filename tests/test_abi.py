@@ -91,6 +91,18 @@ def test_layer_fwd_refuses_a_structure_of_the_wrong_type(lib):
     lib.hero_layer_fwd(d, w, 0, 0, ws, stream=stream)               # (no rows: nothing to do)
 
 
+def test_the_current_stream_does_not_hang_on_a_private_name(monkeypatch):
+    import types
+    import torch
+    from paper_2310_17723_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=42))
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream() == 42 and binding._stream(types.SimpleNamespace(cuda_stream=7)) == 7
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 100 + device)
+    assert binding._stream() == 103
+
+
 def test_binding_structs_match_the_header_layout(tmp_path):
     """The three structs of hero_layer_fwd as gcc lays them out from include/hero.h against the binding's ctypes
     mirrors: size and the offset of every field (a field added to one side only would shift everything behind it)."""
