@@ -555,23 +555,23 @@ __global__ __launch_bounds__(1024) void embed_pair_kernel(LnArgs a) {
             lookup(row + 2 * step);
         }
 
-        float s = 0.0f;
+        // (four sums per lane: one chain of 32 values would be further from 64 bits than the wave-per-row kernel's 16)
+        float s[NCH][2], q[NCH][2];
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) s += v[c][e];
-        const float mean = half_reduce<false>(s) * inv_d;
-        float q = 0.0f;
+            for (int e = 0; e < EPL; ++e) s[c][e >> 3] = (e & 7) == 0 ? v[c][e] : s[c][e >> 3] + v[c][e];
+        const float mean = half_reduce<false>((s[0][0] + s[0][1]) + (s[1][0] + s[1][1])) * inv_d;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             const float mean_c = c * CH + lane0 < D ? mean : 0.0f;       // padding stays out of the squared deviations
 #pragma unroll
             for (int e = 0; e < EPL; ++e) {
                 v[c][e] -= mean_c;
-                q = fmaf(v[c][e], v[c][e], q);
+                q[c][e >> 3] = (e & 7) == 0 ? v[c][e] * v[c][e] : fmaf(v[c][e], v[c][e], q[c][e >> 3]);
             }
         }
-        const float rstd = __builtin_amdgcn_rsqf(half_reduce<false>(q) * inv_d + a.eps);
+        const float rstd = __builtin_amdgcn_rsqf(half_reduce<false>((q[0][0] + q[0][1]) + (q[1][0] + q[1][1])) * inv_d + a.eps);
         float amax = 0.0f;
 #pragma unroll
         for (int c = 0; c < NCH; ++c)

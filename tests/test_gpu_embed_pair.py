@@ -49,3 +49,26 @@ def test_rows_do_not_see_each_other():
     keep[[4, 7, 8192]] = False
     assert torch.equal(q[keep], clean[0][keep]) and torch.equal(s[keep], clean[1][keep])
     assert bool((q[[4, 8192]] == 0).all()) and bool((s[[4, 8192]] == 1).all())
+
+
+@pytest.mark.parametrize("D", [768, 1024])
+def test_no_further_from_64_bits_than_a_row_per_wave(D):
+    """The same tokens 16384 at a time (two rows per wave) and 4096 at a time (a row per wave): the token-wise scales' error against 64
+    bits.  Both are the fp32 roundings behind the statistics, some 6e-8; over 330000 rows their rms is good to 0.2 %, and sums in one
+    chain of 32 values stand out by 0.6 %."""
+    hero, T, eps = pkg.load(), 16384, 1e-12
+    err = [0.0, 0.0]
+    for seed in range(20):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        rnd = lambda *n: torch.randn(n, device="cuda", generator=g)
+        tok = rnd(2000, D) * 0.02
+        ts = tok.abs().amax(1) / 127
+        tok = (tok / ts[:, None]).round().to(torch.int8)
+        pos, typ, ga, be = (0.02 * rnd(512, D)).to(torch.bfloat16), (0.02 * rnd(2, D)).to(torch.bfloat16), 1 + 0.1 * rnd(D), 0.02 * rnd(D)
+        i, p, t = (torch.randint(0, n, (T,), dtype=torch.int32, device="cuda", generator=g) for n in (2000, 512, 2))
+        x = tok.double()[i.long()] * ts.double()[i.long()][:, None] + pos.double()[p.long()] + typ.double()[t.long()]
+        ref = torch.nn.functional.layer_norm(x, (D,), ga.double(), be.double(), eps).abs().amax(1) / 127
+        run = lambda a, b: hero.hero_embed_ln_quant(i[a:b], p[a:b], t[a:b], tok, ts, pos, typ, ga, be, eps)[1].double()
+        for k, s in enumerate((run(0, T), torch.cat([run(a, a + 4096) for a in range(0, T, 4096)]))):
+            err[k] += float((((s - ref) / ref) ** 2).sum())
+    assert (err[0] / err[1]) ** 0.5 <= 1.003, err
