@@ -767,6 +767,10 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, in
     return {M <= 64 || t128 < 192 ? K_REG64 : K_REG128, RING_NONE};
 }
 
+// May K be split over workgroups, given scratch?  Few rows stream the weights without that, but for a few column tiles of a very long
+// K, which leave most CUs to the split: INT8 16 x 512 x 16384 10.5 us split, 11.6 as eight waves' work.
+inline bool may_split(Kernel k, int64_t N, int64_t kb) { return k != K_SKINNY || (N <= 512 && kb > 8192); }
+
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
     switch (c.kernel) {
@@ -786,8 +790,7 @@ template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
     hero_status split;
     const Choice c = choose((hero_dtype)ADT, (hero_epilogue)EPI, g.M, g.N, g.K, g.lda, g.ldb, tile);
-    // (a few column tiles of a very long K leave most CUs to the split: INT8 16 x 512 x 16384 10.5 us split, 11.6 as eight waves' work)
-    if (tile < 0 && (c.kernel != K_SKINNY || (g.N <= 512 && g.K > 8192)) && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
+    if (tile < 0 && may_split(c.kernel, g.N, g.K) && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
     return launch_choice<ADT, EPI, CDT, RDT>(g, c, st);
 }
 
@@ -924,6 +927,11 @@ extern "C" size_t hero_int8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K
     const int64_t b = M <= 64 ? 64 : 128, tiles = (N + b - 1) / b, kt = K / BK, want = (512 + tiles - 1) / tiles;
     const int64_t kslabs = (kt + (want < 16 ? want : 16) - 1) / (want < 16 ? want : 16);
     return (size_t)((kt + kslabs - 1) / kslabs) * M * p.ldp * 4;
+}
+
+// What hero_layer_fwd insists on for an INT8 linear (contiguous rows): nothing where no plane is written.
+size_t hero_int8_gemm_scratch_needed(int64_t M, int64_t N, int64_t K) {
+    return may_split(choose(HERO_I8, HERO_EPI_DEQUANT, M, N, K, K, K).kernel, N, K) ? hero_int8_gemm_workspace_bytes(M, N, K) : 0;
 }
 
 extern "C" hero_status hero_int8_gemm(const int8_t* A, int64_t lda, const float* a_row_scale,

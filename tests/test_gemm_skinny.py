@@ -27,6 +27,24 @@ def test_route(dt):
         assert k(1, 4096, 4096, epi=HB.EPI_RAW_I32) != SKINNY
 
 
+@pytest.mark.parametrize("T,d,f,insists", [(1, 4096, 16384, False), (32, 4096, 16384, False), (33, 4096, 16384, True), (64, 4096, 16384, True),
+                                            (16, 512, 16384, True), (16, 1024, 8192, False)])
+def test_a_layer_insists_on_the_scratch_it_writes(T, d, f, insists):
+    """A decode layer of few rows streams its weights without a K split: a workspace without the planes of one is accepted (the call
+    goes on to the missing pointers), and refused where there are planes to write."""
+    import types
+    hero = pkg.load()
+    desc = hero.layer_desc(HB.ARCH_PRE_LN, d, d // 128, 128, f, 1e-5, HB.MASK_CAUSAL, HB.MODE_M3)
+    up = lambda n: (n + 255) // 256 * 256
+    acts = sum(up(n) for n in (T * d, 4 * T, 3 * T * d, T * d, T * d, 4 * T, T * f))
+    assert hero.hero_layer_workspace_bytes(desc, T, 1) > acts       # (what it can use keeps room for the split)
+    raw = torch.empty(acts + 256, dtype=torch.uint8)
+    ws = raw[-raw.data_ptr() % 256:][:acts]
+    with pytest.raises(HB.HeroError) as e:
+        hero.hero_layer_fwd(desc, HB.LayerWeights(), T, 1, ws, stream=types.SimpleNamespace(cuda_stream=0))
+    assert e.value.status == (5 if insists else 1)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", SHAPES)
 def test_int8(M, N, K):
