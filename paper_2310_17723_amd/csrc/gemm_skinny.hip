@@ -316,7 +316,9 @@ hero_status launch_tiles(const SkinnyArgs& sa, hipStream_t st) {
     case 1: hipLaunchKernelGGL((skinny_gemm_kernel<ADT, 1, TM, HDT>), grid, block, 0, st, a); break;
     case 2: hipLaunchKernelGGL((skinny_gemm_kernel<ADT, 2, TM, HDT>), grid, block, 0, st, a); break;
     case 3: hipLaunchKernelGGL((skinny_gemm_kernel<ADT, 3, TM, HDT>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((skinny_gemm_kernel<ADT, 4, TM, HDT>), grid, block, 0, st, a); break;
+    default:                                                        // beyond 12288 columns: the LN form only (skinny_ok)
+        if constexpr (HDT >= 0) hipLaunchKernelGGL((skinny_gemm_kernel<ADT, 4, TM, HDT>), grid, block, 0, st, a);
+        else return HERO_ERR_UNSUPPORTED;
     }
     return hero_launch_status();
 }
