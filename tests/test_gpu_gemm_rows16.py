@@ -1,5 +1,6 @@
 """The persistent GEMM's 16 x 16 tiles: a lane's 16 columns cut off by N at every place, rows by M, strides that are and are not multiples
-of 16 bytes, both tile sizes and every epilogue, against the ring kernel (INT8: the same bits) and 64 bits (16-bit operands)."""
+of 16 bytes, both tile sizes and every epilogue, against the ring kernel (INT8: the same bits) and 64 bits (16-bit operands); nothing is
+written beside or behind the result."""
 import pytest
 import torch
 
@@ -7,13 +8,17 @@ import paper_2310_17723_amd as pkg
 from paper_2310_17723_amd import binding as HB
 
 pytestmark = pytest.mark.gpu
-SHAPES = [(2049, 2056 + n, 256) for n in (4, 8, 12, 20, 60)] + [(1793, 2304, 1024), (2048, 2176, 384)]
+SHAPES = [(2049, 2048 + n, 256) for n in range(1, 16)] + [(2049, 2116, 256), (1793, 2304, 1024), (2048, 2176, 384)]
 
 
-def _strided(t, extra):
-    buf = torch.zeros((t.shape[0], t.shape[1] + extra), dtype=t.dtype, device=t.device)
-    buf[:, :t.shape[1]] = t
-    return buf[:, :t.shape[1]]
+def _canvas(M, N, dtype, step):
+    """M rows of N elements whose stride is a multiple of `step` elements (more than N), a row behind them, and what is beside them filled."""
+    buf = torch.full((M + 1, (N // step + 1) * step), 3, dtype=dtype, device="cuda")
+    return buf, buf[:M, :N]
+
+
+def _untouched(buf, M, N):
+    return bool((buf[:, N:] == 3).all()) and bool((buf[M:] == 3).all())
 
 
 @pytest.mark.parametrize("tile", [7, 8])
@@ -24,17 +29,18 @@ def test_int8(M, N, K, tile):
     a, w = (torch.randint(-127, 128, (n, K), device="cuda", generator=g, dtype=torch.int8) for n in (M, N))
     rs, cs = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) / (90 * K ** 0.5)
     bias, S = torch.randn(N, device="cuda", generator=g), torch.rand(N, device="cuda", generator=g) / 30 + 0.02
-    assert torch.equal(hero.hero_int8_gemm(a, w, tile=tile), hero.hero_int8_gemm(a, w, tile=2))
-    for e in (dict(epi=HB.EPI_REQUANT, out_dtype=torch.int8), dict(epi=HB.EPI_GELU_REQUANT, out_dtype=torch.int8, out_col_scale=S),
-              dict(epi=HB.EPI_DEQUANT, out_dtype=torch.float16), dict(epi=HB.EPI_DEQUANT_GELU, out_dtype=torch.bfloat16)):
-        for extra in (0, 4):
-            out = [_strided(torch.full((M, N), 3, dtype=e["out_dtype"], device="cuda"), extra) for _ in range(2)]
-            for o, t in zip(out, (tile, 2)):
-                hero.hero_int8_gemm(a, w, rs, cs, bias, C_out=o, tile=t, **e)
-            assert torch.equal(*out), (e, extra)
-    res = _strided(torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16), 4)
-    y = [hero.hero_int8_gemm(a, w, rs, cs, bias, residual=res, epi=HB.EPI_DEQUANT, out_dtype=torch.bfloat16, tile=t) for t in (tile, 2)]
-    assert torch.equal(*y)
+    res = _canvas(M, N, torch.bfloat16, 4)[1]
+    res.copy_(torch.randn((M, N), device="cuda", generator=g))
+    scaled = dict(a_row_scale=rs, b_col_scale=cs, bias=bias)
+    for e in (dict(epi=HB.EPI_RAW_I32, dt=torch.int32), dict(epi=HB.EPI_REQUANT, dt=torch.int8, **scaled),
+              dict(epi=HB.EPI_GELU_REQUANT, dt=torch.int8, out_col_scale=S, **scaled), dict(epi=HB.EPI_DEQUANT, dt=torch.float16, **scaled),
+              dict(epi=HB.EPI_DEQUANT_GELU, dt=torch.bfloat16, **scaled), dict(epi=HB.EPI_DEQUANT, dt=torch.bfloat16, residual=res, **scaled)):
+        dt = e.pop("dt")
+        for step in (4, 16):
+            (buf, out), (_, other) = _canvas(M, N, dt, step), _canvas(M, N, dt, step)
+            hero.hero_int8_gemm(a, w, C_out=out, tile=tile, **e)
+            hero.hero_int8_gemm(a, w, C_out=other, tile=2, **e)
+            assert torch.equal(out, other) and _untouched(buf, M, N), (e["epi"], step)
 
 
 @pytest.mark.parametrize("tile", [7, 8])
@@ -45,9 +51,12 @@ def test_16_bits(M, N, kb, dt, tile):
     g = torch.Generator(device="cuda").manual_seed(N + K)
     a, w = torch.randn((M, K), device="cuda", generator=g).to(dt), (torch.randn((N, K), device="cuda", generator=g) * K ** -0.5).to(dt)
     bias, res = torch.randn(N, device="cuda", generator=g), torch.randn((M, N), device="cuda", generator=g).to(dt)
-    y = hero.hero_hp_gemm(a, w, bias, residual=res, tile=tile)
     ref = a.double() @ w.double().t() + bias.double() + res.double()
     # fp32 sums of K products in any order: (K + 4) * 2^-24 of the sum of the magnitudes; then one rounding
     bound = (K + 4) * 2.0 ** -24 * (a.double().abs() @ w.double().abs().t() + bias.double().abs() + res.double().abs())
     ulp = 2.0 ** -8 if dt == torch.bfloat16 else 2.0 ** -11
-    assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * ulp).all())
+    for step, rows in ((4, res), (8, _canvas(M, N, dt, 1)[1])):      # the residual's rows on wide boundaries and on odd ones
+        rows.copy_(res)
+        buf, y = _canvas(M, N, dt, step)
+        hero.hero_hp_gemm(a, w, bias, residual=rows, C_out=y, tile=tile)
+        assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * ulp).all()) and _untouched(buf, M, N), step
