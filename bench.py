@@ -711,7 +711,7 @@ def main():
     ap.add_argument("--only", default=None, choices=["ln", "coissue", "fc1", "attention"],
                     help="run one leg alone and print its record (for rocprofv3 counter runs): the LN^quant bandwidth legs, "
                          "the MFMA + VALU co-issue probe, the FC1 GeMM^quant (with --tile), the attention kernels")
-    ap.add_argument("--tile", type=int, default=None, help="with --only fc1: force a GEMM kernel through the test hook (7, 8, 9)")
+    ap.add_argument("--tile", type=int, default=None, help="with --only fc1: force a GEMM kernel through the test hook (7, 8)")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a plain 256 MiB device copy 5 times (reference for the FETCH_SIZE / WRITE_SIZE counters)")
     args = ap.parse_args()

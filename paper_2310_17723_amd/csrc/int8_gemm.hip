@@ -732,7 +732,7 @@ inline bool small_tile_fills_better(int64_t t256, int64_t t128, int64_t kb) {
 }
 
 // What runs a product.  The codes of the kernels are those of the test hooks (include/hero_debug.h).
-enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_SKINNY = 4, K_PERS256 = 7, K_PERS128 = 8, K_WAS_OVERLAPPED = 9 /* hook only: as 7 */ };
+enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_SKINNY = 4, K_PERS256 = 7, K_PERS128 = 8 };
 struct Choice { Kernel kernel; RingForm form; };
 
 // kb, lda, ldb in bytes.  tile: -1 chooses, otherwise the code a test hook
@@ -746,7 +746,7 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, in
     const RingForm form = ring ? ring_form(M, N, kb, epi) : RING_NONE;
     const Choice small = {ring ? K_RING : (M <= 64 || t128 < 192 ? K_REG64 : K_REG128), form == RING_NONE ? RING_128x64 : form};
     if (tile >= 0) {
-        if (tile == K_PERS256 || tile == K_PERS128 || tile == K_WAS_OVERLAPPED) {
+        if (tile == K_PERS256 || tile == K_PERS128) {
             if (pers_ok && (adt == HERO_I8 || adt == HERO_F8E4M3 || t128 >= 192)) return {tile == K_PERS128 ? K_PERS128 : K_PERS256, RING_NONE};
             if (i8) return {tile == K_PERS128 ? K_REG128 : K_DMA256, RING_NONE};
             return small;
@@ -1071,7 +1071,8 @@ extern "C" hero_status hero_int8_gemm_tile(const int8_t* A, int64_t lda, const f
                                            hero_epilogue epi, const float* out_col_scale,
                                            void* C, hero_dtype c_dt, int64_t ldc,
                                            int64_t M, int64_t N, int64_t K, void* stream, int tile) {
-    if (tile != 0 && tile != 1 && tile != 2 && tile != 7 && tile != 8 && tile != 9) return HERO_ERR_UNSUPPORTED;
+    if (tile == 9) tile = K_PERS256;                                   // (a former kernel's code, still accepted)
+    if (tile != 0 && tile != 1 && tile != 2 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
     return run_int8_gemm(A, lda, a_row_scale, Bt, ldb, b_col_scale, bias, residual, res_dt, ldr, epi, out_col_scale,
                          C, c_dt, ldc, M, N, K, nullptr, 0, stream, tile);
 }

@@ -44,7 +44,7 @@ def test_split_scratch_is_asked_for_where_k_splits():
 def test_narrow_tiles_are_not_for_two_rounds_of_8_bit_results(dt):
     """128 x 64 tiles write half a line of an 8-bit result: beyond the first round of tiles the persistent kernel takes it (measured
     8-30 % ahead), likewise with a GELU epilogue; 16-bit results with a short K stay."""
-    PERSISTENT = (7, 8, 9)
+    PERSISTENT = (7, 8)
     for M, N, K in ((8192, 1024, 1024), (5400, 768, 768), (10240, 768, 768), (2048, 3072, 1024), (2500, 2304, 768), (1500, 3072, 1024)):
         assert kernel(dt, M, N, K, epi=HB.EPI_REQUANT) in PERSISTENT, (M, N, K)
         assert kernel(dt, M, N, K) == "128x64", (M, N, K)

@@ -251,8 +251,7 @@ def test_bert_large_layer_batch_slice(hero):
     assert np.allclose(gs, os_[valid], rtol=4e-3)
     assert np.abs(gq.astype(int) - oq[valid].astype(int)).max() <= 3
     assert np.mean(gq == oq[valid]) >= 0.999
-    # The same four sequences twice (8 x 512 rows: QKV now runs the 256 x 256 persistent tiles, FC1 the kernel with the
-    # overlapped epilogue, the other two GEMMs the 128 x 128 tiles), with the caller's hint about what it reads next: a
+    # The same four sequences twice (8 x 512 rows: larger tiles of the persistent kernel and of the ring kernel), with the caller's hint about what it reads next: a
     # sequence's result depends on nothing but the sequence, and the hint changes no value, so the two copies are equal
     # bit for bit; against the oracle they meet the same bar as the first run (GELU^quant of another kernel form may
     # round a code of the +-1 LSB class the other way).
