@@ -278,8 +278,9 @@ def fc1_roofline(hero, shape, seed, iters=40, tile=None):
 def measured_ceilings():
     """What this machine sustains, beside the nameplate peaks the fractions are quoted against, from the
     instruments of libhero_probe (a library of its own, loaded only here).  Matrix cores: a register-only INT8
-    MFMA loop on near-constant and on random operand bytes (the clock under the matrix cores is power-limited and
-    depends on the data), and the same loop with 4 / 8 fp32 vector instructions behind every matrix instruction of
+    MFMA loop (16 x 16 x 64, what the GEMM of large problems multiplies with; 32 x 32 x 32 beside it) on near-constant
+    and on random operand bytes (the clock under the matrix cores is power-limited and depends on the data), and a loop
+    of 32 x 32 x 32 with 4 / 8 fp32 vector instructions behind every matrix instruction of
     a wave, or in the other wave of the SIMD (does the vector ALU issue while the matrix pipe is busy?).  HBM: five
     instruments on 256 MiB buffers (read only, write only, copy with 1 and with 4 independent 16-byte loads in
     flight per lane, the runtime's device-to-device copy) and a copy of one LN^quant call's volume on rotating buffers."""
@@ -288,11 +289,12 @@ def measured_ceilings():
     pr = Probe()
     sink = torch.zeros(1, dtype=torch.int32, device="cuda")
     out = {}
-    for name, rnd in (("mfma_int8_constant_operands_tops", 0), ("mfma_int8_random_operands_tops", 1)):
+    for name, tile, rnd in (("mfma_int8_constant_operands_tops", 16, 0), ("mfma_int8_random_operands_tops", 16, 1),
+                            ("mfma_int8_32x32_random_operands_tops", 32, 1)):
         ops = [0.0]
 
         def fn():
-            ops[0] = pr.mfma_i8(rnd, 2048, sink)
+            ops[0] = pr.mfma_i8(tile, rnd, 2048 * 32 // tile, sink)
         ms = time_gpu(fn, 5, warmup=2, repeats=3)
         out[name] = round(ops[0] / (ms * 1e-3) / 1e12, 1)
     co = {}
@@ -444,9 +446,9 @@ def fp8_layer_leg(hero, shape, seed, iters=10):
 
 
 def attn_variants(hero, shape, seed, iters=20):
-    """The attention kernel alone at the workload's shape: the two-pass Softmax^quant of Sec. 2.2.2 (what the
-    layer runs) beside the single-sweep online variant (a different quantization of the probabilities) and the
-    FP8 variant of the two-pass flow."""
+    """The attention alone at the workload's shape: the Softmax^quant of Sec. 2.2.2 as the layer runs it (one pass over up to
+    512 keys of 64 channels, two beyond) beside the single-sweep online variant (a different quantization of the
+    probabilities) and the FP8 variant."""
     import torch
     from paper_2310_17723_amd import binding as HB
     g = torch.Generator(device="cuda").manual_seed(seed)
@@ -468,7 +470,7 @@ def attn_variants(hero, shape, seed, iters=20):
         res["real_pair_fraction"] = round(float((kvl.double() ** 2).mean().item()) / (S * S), 4)
     ms = time_gpu(lambda: hero.hero_int8_attn(v[:, :, 0], v[:, :, 1], v[:, :, 2], dt, 1 / 255, cs, mask=shape.mask,
                                               kv_len=kvl, out=out), iters)
-    res["two_pass_us"] = round(ms * 1e3, 2)
+    res["softmax_quant_us"] = round(ms * 1e3, 2)
     ms = time_gpu(lambda: hero.hero_int8_attn_online(v[:, :, 0], v[:, :, 1], v[:, :, 2], dth, 1 / 255, cs, mask=shape.mask,
                                                      kv_len=kvl, out=out), iters)
     res["online_us"] = round(ms * 1e3, 2)
@@ -477,7 +479,7 @@ def attn_variants(hero, shape, seed, iters=20):
     out8 = torch.empty((B * S, d), dtype=torch.float8_e4m3fn, device="cuda")
     ms = time_gpu(lambda: hero.hero_fp8_attn(v8[:, :, 0], v8[:, :, 1], v8[:, :, 2], 1.5 / (40 * 40 * Dh ** 0.5), 1 / 448, cs,
                                              mask=shape.mask, kv_len=kvl, out=out8), iters)
-    res["fp8_two_pass_us"] = round(ms * 1e3, 2)
+    res["fp8_softmax_quant_us"] = round(ms * 1e3, 2)
     return res
 
 
@@ -831,7 +833,7 @@ def main():
         rec["ln_quant_large"] = ln_bandwidth(hero, 65536, shape.d, nbuf=4)
         rec["embed_ln_quant"] = embed_bandwidth(hero, 32, 512, shape.d)
         if shape.S > 1:
-            log("[bench] attention alone: two-pass and online Softmax^quant")
+            log("[bench] attention alone: the layer's and the online Softmax^quant")
             rec["attention"] = attn_variants(hero, shape, args.seed)
         log("[bench] FP8 variant of the FC1 / FC2 GEMMs")
         rec["fp8_gemm"] = fp8_gemm_leg(hero, shape, args.seed)

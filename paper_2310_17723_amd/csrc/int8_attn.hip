@@ -3,9 +3,13 @@
 // with unsigned codes, X_attn,int8 S_attn = S_p S_v P_int8 X_v,int8).
 //
 // The softmax is normalised before it is quantized, so the row maximum and the row sum
-// must be known before the first code is produced: the kernel streams the keys twice
-// (pass 1: QK^T, row max / row sum; pass 2: QK^T again, codes, PV).  A and P never leave
-// the chip.
+// must be known before the first code is produced.  Four kernels (the rule: attn_entry):
+//   * int8_attn_kernel (described here) streams the keys twice (pass 1: QK^T, row max / row sum; pass 2: QK^T
+//     again, codes, PV), and in its online variant once;
+//   * int8_attn_keep_kernel: up to 512 keys of 64 channels, one pass, the scores kept in registers;
+//   * int8_attn_split_kernel: few queries, the keys split over a block's waves;
+//   * int8_attn_decode_kernel: one query per sequence, a stream of the cache.
+// A and P never leave the chip.
 //
 // Layout.  A block owns 128 queries of one (batch, head); each of its 4 waves owns 32 of them.
 // Scores are computed TRANSPOSED, S^T = K Q^T (v_mfma_i32_32x32x32_i8 with the key

@@ -1,6 +1,6 @@
 // libhero_probe: measuring instruments of bench.py, NOT part of the product library.  They establish, on the
 // machine at hand, the ceilings the kernels of libhero are compared with:
-//   * a register-only loop of v_mfma_i32_32x32x32_i8 (the matrix cores' rate at the clock the chip sustains under
+//   * a register-only loop of v_mfma_i32_16x16x64_i8 or v_mfma_i32_32x32x32_i8 (the matrix cores' rate at the clock the chip sustains under
 //     that load; the clock depends on how many operand bits toggle, so the operands are near-constant or random);
 //   * the same loop with fp32 vector instructions between the matrix instructions of a wave, or in the other wave
 //     of the SIMD (does the vector ALU issue while the matrix pipe is busy?);
@@ -20,7 +20,11 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 __device__ __forceinline__ unsigned lcg(unsigned& s) { s = s * 1664525u + 1013904223u; return s ^ (s >> 13) ^ (s << 7); }
 
+// TILE 16: v_mfma_i32_16x16x64_i8 (what the INT8 GEMM of large problems multiplies with), 32: v_mfma_i32_32x32x32_i8
+template <int TILE>
 __global__ __launch_bounds__(512) void probe_mfma_i8_kernel(int random_bytes, int iters, int* sink) {
+    constexpr int NR = TILE * TILE / 64;
+    typedef int ACC __attribute__((ext_vector_type(NR)));
     unsigned seed = threadIdx.x * 7919u + blockIdx.x * 104729u + 1u;
     v4i fa[4], fb[2];
 #pragma unroll
@@ -31,15 +35,16 @@ __global__ __launch_bounds__(512) void probe_mfma_i8_kernel(int random_bytes, in
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) fb[i][j] = random_bytes ? (int)lcg(seed) : 0x01010101;
-    v16i acc[8];
+    ACC acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0;
+        for (int r = 0; r < NR; ++r) acc[i][r] = 0;
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
         for (int n = 0; n < 16; ++n) {
-            acc[n & 7] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[(n >> 2) & 1], fa[n & 3], acc[n & 7], 0, 0, 0);
+            if constexpr (TILE == 16) acc[n & 7] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[(n >> 2) & 1], fa[n & 3], acc[n & 7], 0, 0, 0);
+            else acc[n & 7] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[(n >> 2) & 1], fa[n & 3], acc[n & 7], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -47,7 +52,7 @@ __global__ __launch_bounds__(512) void probe_mfma_i8_kernel(int random_bytes, in
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[i][r];
+        for (int r = 0; r < NR; ++r) s += acc[i][r];
     if (s == 0x7fffffff) sink[0] = s;                     // keeps the loop alive; never true for these operands' sums
 }
 
@@ -146,14 +151,17 @@ __global__ __launch_bounds__(256) void probe_write_kernel(v4i* __restrict__ dst,
 
 }  // namespace
 
-extern "C" int hero_probe_mfma_i8(int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream) {
+extern "C" int hero_probe_mfma_i8(int tile, int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream) {
     if (iters <= 0 || iters > 0x7fffffffLL) return 2;
+    if (tile != 16 && tile != 32) return 2;
     if (!sink) return 1;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         return 6;
-    hipLaunchKernelGGL(probe_mfma_i8_kernel, dim3((unsigned)cus), dim3(512), 0, (hipStream_t)stream, random_bytes, (int)iters, sink);
-    if (ops) *ops = (double)cus * 8.0 * (double)iters * 16.0 * 65536.0;      // 8 waves x 16 instructions x 2*32*32*32 per iteration
+    if (tile == 16) hipLaunchKernelGGL(probe_mfma_i8_kernel<16>, dim3((unsigned)cus), dim3(512), 0, (hipStream_t)stream, random_bytes, (int)iters, sink);
+    else hipLaunchKernelGGL(probe_mfma_i8_kernel<32>, dim3((unsigned)cus), dim3(512), 0, (hipStream_t)stream, random_bytes, (int)iters, sink);
+    // 8 waves x 16 instructions x 2*16*16*64 (2*32*32*32) per iteration
+    if (ops) *ops = (double)cus * 8.0 * (double)iters * 16.0 * (tile == 16 ? 32768.0 : 65536.0);
     return launch_status();
 }
 
