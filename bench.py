@@ -294,7 +294,7 @@ def measured_ceilings():
         ops = [0.0]
 
         def fn():
-            ops[0] = pr.mfma_i8(tile, rnd, 2048 * 32 // tile, sink)
+            ops[0] = pr.mfma_i8(rnd, 2048 * 32 // tile, sink, tile=tile)
         ms = time_gpu(fn, 5, warmup=2, repeats=3)
         out[name] = round(ops[0] / (ms * 1e-3) / 1e12, 1)
     co = {}

@@ -12,10 +12,11 @@
 extern "C" {
 #endif
 
-/* Register-only loop of v_mfma_i32_16x16x64_i8 (tile 16) or v_mfma_i32_32x32x32_i8 (tile 32): one 512-thread workgroup per
- * CU, `iters` x 16 instructions per wave, on near-constant (random_bytes == 0) or random operand bytes.  *ops (host, may be NULL) receives the
+/* Register-only loop of v_mfma_i32_32x32x32_i8 (.._16: v_mfma_i32_16x16x64_i8): one 512-thread workgroup per CU,
+ * `iters` x 16 instructions per wave, on near-constant (random_bytes == 0) or random operand bytes.  *ops (host, may be NULL) receives the
  * integer operations the launch performs; sink is one device int32 the kernel may write. */
-int hero_probe_mfma_i8(int tile, int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream);
+int hero_probe_mfma_i8(int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream);
+int hero_probe_mfma_i8_16(int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream);
 
 /* Matrix and vector instructions on one SIMD.  mode 0: every wave issues, `iters` times, 8 x (one matrix
  * instruction, valu_per_mfma fp32 fma); mode 1: the fma alone; mode 2: the same work split by wave (one wave of

@@ -12,7 +12,8 @@ LIB_PATH = os.path.join(os.path.dirname(_HERE), "libhero_probe.so")
 
 vp, i64, i32 = C.c_void_p, C.c_int64, C.c_int
 SYMBOLS = {
-    "hero_probe_mfma_i8": (i32, [i32, i32, i64, vp, C.POINTER(C.c_double), vp]),
+    "hero_probe_mfma_i8": (i32, [i32, i64, vp, C.POINTER(C.c_double), vp]),
+    "hero_probe_mfma_i8_16": (i32, [i32, i64, vp, C.POINTER(C.c_double), vp]),
     "hero_probe_coissue": (i32, [i32, i32, i64, vp, C.POINTER(C.c_double), C.POINTER(C.c_double), vp]),
     "hero_probe_copy": (i32, [vp, vp, i64, i32, vp]),
     "hero_probe_read": (i32, [vp, i64, vp, vp]),
@@ -39,9 +40,10 @@ class Probe:
         if rc != 0:
             raise RuntimeError(f"libhero_probe: status {rc}")
 
-    def mfma_i8(self, tile, random_bytes, iters, sink) -> float:
+    def mfma_i8(self, random_bytes, iters, sink, tile=32) -> float:
         ops = C.c_double(0.0)
-        self._check(self.lib.hero_probe_mfma_i8(int(tile), int(bool(random_bytes)), int(iters), sink.data_ptr(), C.byref(ops), _stream()))
+        fn = {16: self.lib.hero_probe_mfma_i8_16, 32: self.lib.hero_probe_mfma_i8}[tile]
+        self._check(fn(int(bool(random_bytes)), int(iters), sink.data_ptr(), C.byref(ops), _stream()))
         return ops.value
 
     def coissue(self, mode, valu_per_mfma, iters, sink):

@@ -151,18 +151,25 @@ __global__ __launch_bounds__(256) void probe_write_kernel(v4i* __restrict__ dst,
 
 }  // namespace
 
-extern "C" int hero_probe_mfma_i8(int tile, int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream) {
+template <int TILE>
+static int launch_mfma_i8(int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream) {
     if (iters <= 0 || iters > 0x7fffffffLL) return 2;
-    if (tile != 16 && tile != 32) return 2;
     if (!sink) return 1;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         return 6;
-    if (tile == 16) hipLaunchKernelGGL(probe_mfma_i8_kernel<16>, dim3((unsigned)cus), dim3(512), 0, (hipStream_t)stream, random_bytes, (int)iters, sink);
-    else hipLaunchKernelGGL(probe_mfma_i8_kernel<32>, dim3((unsigned)cus), dim3(512), 0, (hipStream_t)stream, random_bytes, (int)iters, sink);
+    hipLaunchKernelGGL(probe_mfma_i8_kernel<TILE>, dim3((unsigned)cus), dim3(512), 0, (hipStream_t)stream, random_bytes, (int)iters, sink);
     // 8 waves x 16 instructions x 2*16*16*64 (2*32*32*32) per iteration
-    if (ops) *ops = (double)cus * 8.0 * (double)iters * 16.0 * (tile == 16 ? 32768.0 : 65536.0);
+    if (ops) *ops = (double)cus * 8.0 * (double)iters * 16.0 * (TILE == 16 ? 32768.0 : 65536.0);
     return launch_status();
+}
+
+extern "C" int hero_probe_mfma_i8(int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream) {
+    return launch_mfma_i8<32>(random_bytes, iters, sink, ops, stream);
+}
+
+extern "C" int hero_probe_mfma_i8_16(int random_bytes, int64_t iters, int32_t* sink, double* ops, void* stream) {
+    return launch_mfma_i8<16>(random_bytes, iters, sink, ops, stream);
 }
 
 extern "C" int hero_probe_coissue(int mode, int valu_per_mfma, int64_t iters, int32_t* sink, double* mfma_ops,
