@@ -51,8 +51,8 @@ __device__ __forceinline__ ACC mfma_step(v4i a, v4i b, ACC c) {
     }
 }
 // The same on 16 x 16 tiles: one instruction takes a whole 64-byte slab of 16 rows of each operand.  At the clock the power limit allows
-// these sustain more than the 32 x 32 ones (half the accumulator traffic per multiply-add; registers only, random bytes: INT8 4.27
-// against 3.60 POP/s, BF16 2.17 against 1.91 PFLOP/s).
+// these sustain more than the 32 x 32 ones (half the accumulator traffic per multiply-add; hero_probe_mfma_i8, registers only, random
+// bytes: INT8 4.15 against 3.48 POP/s).
 template <int ADT> struct Acc4Of { using type = typename std::conditional<ADT == HERO_I8, v4i, v4f>::type; };
 template <int ADT, typename ACC>
 __device__ __forceinline__ ACC mfma16_step(v4i a, v4i b, ACC c) {

@@ -547,19 +547,20 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
 }
 
 // ------------------------------------------------------------------------------------------
-// Up to 512 keys of 64 channels (the encoders): one pass.  The two-pass kernel above spends 15 vector slots per score, 8 of them the
-// two quarter-rate exp2, because a block's scores do not survive until the row sum is known.  Here they do: a wave takes 16 queries
+// Up to 512 keys of 64 channels (the encoders): one pass.  The core of the two-pass kernel above takes 15 vector slots per score, 8 of
+// them the two quarter-rate exp2, because a block's scores do not survive until the row sum is known.  Here they do: a wave takes 16 queries
 // at a time (v_mfma_*_16x16x64: lane l holds, for query l % 16, the keys 16 s + 4 (l / 16) + t of every 16-key step s), so that the
 // scores of up to 256 keys, later their exponentials, stay in 16 registers per 64 keys, and a code is one multiplication and one
-// packing conversion away: 10 slots per score (conversion, half a maximum, fma, exp2 (4), sum, product, packing conversion).  The
+// packing conversion away: 10 slots per score (conversion, half a maximum, fma, exp2 (4), sum, product, packing conversion; counted with
+// staging, masks and results 13.4 instructions or 16.4 slots per score, the two-pass kernel 15.0 or 21).  The
 // codes of a 64-key tile are the PV operand as they stand, V being staged transposed with its keys in the same order.
 // A block owns 128 queries of one (batch, head), in four groups of 32 (two sets of 16 each), and stages all of K (direct to LDS) and
 // V once.  KW waves share a group's keys: one up to 256 keys, then no barrier follows; two beyond (all scores of 512 keys in one wave's
 // registers leave two waves per SIMD, and 32 x 16 x 512 took 73 us, the two-pass kernel 69): the halves' maxima and sums meet in LDS,
 // and each wave ends with half of the channels.  A hidden key is left out by the size of its masked score alone, which asks for a scale of
 // KEEP_MIN_QK or more; the two-pass kernel serves the others (selecting the exponentials here made the 256- and 512-key forms spill).
-// The offset of the unsigned codes is removed by a second matrix instruction as in the online variant, so o = -sum code * v.  Bound by
-// the vector ALU; four waves per SIMD.
+// The offset of the unsigned codes is removed by a second matrix instruction as in the online variant, so o = -sum code * v.  The vector
+// ALU is the largest term (32 x 16 x 512 padded: 58 % of the cycles with exp2 weighted, the matrix pipe 11 %); four waves per SIMD.
 // ------------------------------------------------------------------------------------------
 // (2^30 - 2^20) * 2^-23 * log2(e) = 184: with the largest score, 64 * 128 * 128, on either side of the mask's value a hidden key's
 // exponential, below 2^-149, is 0 (E4M3: 3e38 beside 64 * 448 * 448)

@@ -450,9 +450,9 @@ __global__ __launch_bounds__(256) void ln_quant_row_kernel(LnArgs a) {
 }
 
 // ---- embedding of many tokens, rows of 513 .. 1024 values: TWO rows per wave ------------------------------------
-// Bound by the vector ALU's issue slots, not by HBM: of the wave-per-row kernel's 410 instructions per row of 1024 values about 170 do
-// not depend on the row's length (three reductions across 64 lanes, the row's scalars, addresses, index lookups).  Here a half wave
-// owns a row (32 values per lane), so that one instruction serves two rows there: 320 per row.  The last step of a half-wave reduction is
+// The vector ALU's issue slots are the largest term, not HBM: a good part of the wave-per-row kernel's 360 instructions per row of 1024
+// values does not depend on the row's length (three reductions across 64 lanes, the row's scalars, addresses, index lookups).  Here a
+// half wave owns a row (32 values per lane), so that one instruction serves two rows there: 281 per row (both counted).  The last step of a half-wave reduction is
 // one v_permlane16_swap, behind which every lane holds the result.  Persistent 16-wave workgroups, parameters in LDS, the next rows in
 // flight: as in ln_quant_kernel.  us, wave per row -> two rows: 1024 values, 6000 rows 8.4 -> 7.2, 8192 rows 8.9 -> 7.6, 12000 rows
 // 11.4 -> 11.2, 16384 rows 13.9 -> 11.8, 65536 rows 40.8 -> 32.5; 768 values, 6000 rows 8.2 -> 6.9, 16384 rows 13.4 -> 11.2.
