@@ -767,9 +767,22 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, in
     return {M <= 64 || t128 < 192 ? K_REG64 : K_REG128, RING_NONE};
 }
 
-// May K be split over workgroups, given scratch?  Few rows stream the weights without that, but for a few column tiles of a very long
-// K, which leave most CUs to the split: INT8 16 x 512 x 16384 10.5 us split, 11.6 as eight waves' work.
-inline bool may_split(Kernel k, int64_t N, int64_t kb) { return k != K_SKINNY || (N <= 512 && kb > 8192); }
+// May K be split over workgroups, given scratch?  Few rows stream the weights without that, unless K is long (in bytes beyond 8192, all
+// that N <= 512 asks) and the columns few: a workgroup of the weight-streaming kernel takes the whole K of its columns and of all
+// rows, so that its time grows with both and most CUs are idle, while the split's grows with the slabs of a range, more so where an XCD
+// is handed more of its workgroups than it has CUs.  Two estimates in us, fitted to 800 products of 576 .. 4096 columns, and the split
+// where they are close (within 7 %, up to 2048 columns): 1 % behind the better one on average, nowhere 5 % behind the split.  us, split / whole K: INT8 16 x 512 x 16384 10.5 / 11.6, 32 x 640 x 16384 11.1 / 15.5, 32 x 1024 x 16384 12.0 / 15.2, 8
+// rows 11.2 / 10.4, 24 x 2048 x 24576 16.8 / 20.2, 32 x 1280 x 16384 (36 workgroups on an XCD) 15.2 / 14.3;  BF16 32 x 1024 x 8192 11.8 / 14.9.
+inline bool may_split(Kernel kernel, int64_t M, int64_t N, int64_t kb) {
+    if (kernel != K_SKINNY) return true;
+    if (kb <= 8192) return false;
+    if (N <= 512) return true;
+    const SplitK p = splitk_plan(M, N, kb);
+    const double k = (double)kb / 1024, on_xcd = (double)((N + 511) / 512) * p.ksplit;
+    const double whole = 4.7 + k * (0.28 + 0.009 * (double)M + (M > 16 ? 0.06 : 0.0)) + (double)N * k * 4e-5;
+    const double split = 7.0 + 0.35e-3 * (double)N + 0.09 * p.ksplit + p.kslabs * (on_xcd > 32 ? 0.46 : 0.29) + (on_xcd > 32 ? 1.8 : 0.0);
+    return split < (N <= 2048 ? 1.07 : 1.0) * whole;
+}
 
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
@@ -790,7 +803,7 @@ template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_epi(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, int tile) {
     hero_status split;
     const Choice c = choose((hero_dtype)ADT, (hero_epilogue)EPI, g.M, g.N, g.K, g.lda, g.ldb, tile);
-    if (tile < 0 && may_split(c.kernel, g.N, g.K) && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
+    if (tile < 0 && may_split(c.kernel, g.M, g.N, g.K) && launch_splitk<EPI, CDT, RDT, ADT>(g, ws, ws_bytes, st, &split)) return split;
     return launch_choice<ADT, EPI, CDT, RDT>(g, c, st);
 }
 
@@ -931,7 +944,7 @@ extern "C" size_t hero_int8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K
 
 // What hero_layer_fwd insists on for an INT8 linear (contiguous rows): nothing where no plane is written.
 size_t hero_int8_gemm_scratch_needed(int64_t M, int64_t N, int64_t K) {
-    return may_split(choose(HERO_I8, HERO_EPI_DEQUANT, M, N, K, K, K).kernel, N, K) ? hero_int8_gemm_workspace_bytes(M, N, K) : 0;
+    return may_split(choose(HERO_I8, HERO_EPI_DEQUANT, M, N, K, K, K).kernel, M, N, K) ? hero_int8_gemm_workspace_bytes(M, N, K) : 0;
 }
 
 extern "C" hero_status hero_int8_gemm(const int8_t* A, int64_t lda, const float* a_row_scale,

@@ -28,7 +28,7 @@ def test_route(dt):
 
 
 @pytest.mark.parametrize("T,d,f,insists", [(1, 4096, 16384, False), (32, 4096, 16384, False), (33, 4096, 16384, True), (64, 4096, 16384, True),
-                                            (16, 512, 16384, True), (16, 1024, 8192, False)])
+                                            (16, 512, 16384, True), (16, 1024, 8192, False), (32, 1024, 16384, True), (1, 1024, 16384, False)])
 def test_a_layer_insists_on_the_scratch_it_writes(T, d, f, insists):
     """A decode layer of few rows streams its weights without a K split: a workspace without the planes of one is accepted (the call
     goes on to the missing pointers), and refused where there are planes to write."""
@@ -63,6 +63,18 @@ def test_int8(M, N, K):
                   dict(epi=HB.EPI_DEQUANT, out_dtype=torch.bfloat16, residual=res), dict(epi=HB.EPI_DEQUANT_GELU, out_dtype=torch.bfloat16),
                   dict(epi=HB.EPI_GELU_REQUANT, out_dtype=torch.int8, out_col_scale=S)):
             assert torch.equal(hero.hero_int8_gemm(a, w, **kw, **e), hero.hero_int8_gemm(a, w, **kw, **e, tile=2)), (row is None, e)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(8, 1024, 16384), (32, 1024, 16384), (17, 592, 12288), (24, 2048, 24576), (32, 1280, 16384), (16, 512, 9216)])
+def test_with_scratch_for_a_split(M, N, K):
+    """Few rows of a very long K, on either side of the rule that splits it where there is scratch: the same bits."""
+    hero, g = pkg.load(), torch.Generator(device="cuda").manual_seed(K)
+    a, w = (torch.randint(-127, 128, (n, K), device="cuda", generator=g, dtype=torch.int8) for n in (M, N))
+    rs, cs, bias = torch.rand(M, device="cuda", generator=g) + 0.5, torch.rand(N, device="cuda", generator=g) / 9000, torch.randn(N, device="cuda", generator=g)
+    ws = torch.full((hero.hero_int8_gemm_workspace_bytes(M, N, K),), 0xA5, dtype=torch.uint8, device="cuda")
+    for e in (dict(epi=HB.EPI_DEQUANT, out_dtype=torch.bfloat16), dict(epi=HB.EPI_REQUANT, out_dtype=torch.int8)):
+        assert torch.equal(hero.hero_int8_gemm(a, w, rs, cs, bias, workspace=ws, **e), hero.hero_int8_gemm(a, w, rs, cs, bias, **e))
 
 
 @pytest.mark.gpu
