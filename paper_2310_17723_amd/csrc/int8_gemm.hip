@@ -725,10 +725,13 @@ hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) 
 // takes a quarter of a large one's time and, with twice the L2 -> LDS traffic, 1.05 to 1.3 times that behind a short K, 1.15 to 1.6
 // behind a long one (the more the emptier the grid: the clock rises where CUs idle).  Measured over 450 products (INT8, E4M3, BF16, 256
 // .. 12000 rows), the rule's losses are 5 % at most.  us, large / small: REQUANT 3817 x 3072 x 1024 18.9 / 17.7, 768 x 12288 x 4096 52.8 /
-// 62.9, 1300 x 12288 x 4096 96.7 / 84.6, GELU^quant 3072 x 4096 x 1024 23.7 / 20.6, 3817 rows 25.0 / 26.4.
-inline bool small_tile_fills_better(int64_t t256, int64_t t128, int64_t kb) {
-    const double per_tile = kb <= 2048 ? 1.2 / 4 : 1.4 / 4;
-    return (double)((t128 + 255) / 256) * per_tile < (double)((t256 + 255) / 256);
+// 62.9, 1300 x 12288 x 4096 96.7 / 84.6, GELU^quant 3072 x 4096 x 1024 23.7 / 20.6, 3817 rows 25.0 / 26.4.  E4M3 behind a long K, whose large
+// tile has no 16 x 16 instructions, is nearer to the small one's rate from the second round on: GELU^quant 3072 x 12288 x 4096 161 / 144, 6144 x
+// 4096 x 4096 106.6 / 99.6, 16-bit result 151 / 142, but 2500 x 16384 x 4096 163 / 171 and, in one round, 768 x 12288 x 4096 REQUANT 46.8 / 49.0.
+inline bool small_tile_fills_better(int64_t t256, int64_t t128, int64_t kb, bool f8) {
+    const int64_t n256 = (t256 + 255) / 256, n128 = (t128 + 255) / 256;
+    const double per_tile = (kb <= 2048 ? 1.2 : f8 && n256 > 1 ? 1.3 : 1.4) / 4;
+    return (double)n128 * per_tile < (double)n256;
 }
 
 // What runs a product.  The codes of the kernels are those of the test hooks (include/hero_debug.h).
@@ -757,7 +760,7 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, in
     if (epi != HERO_EPI_RAW_I32 && skinny_ok(M, N, kb, lda, ldb)) return {K_SKINNY, RING_NONE};
     if (form != RING_NONE) return small;
     if (pers_ok) {
-        return {small_tile_fills_better(t256, t128, kb) ? K_PERS128 : K_PERS256, RING_NONE};
+        return {small_tile_fills_better(t256, t128, kb, adt == HERO_F8E4M3) ? K_PERS128 : K_PERS256, RING_NONE};
     }
     // K that ends in half a slab: the one-tile-per-workgroup 256 x 256 kernel (INT8) once its grid fills the chip, else 128 x 128
     // tiles, through the ring from 32 slabs on.  us, ring / registers: 2048 x 4096 x 4160 INT8 52.1 / 54.8, E4M3 51.0 / 55.7,

@@ -54,6 +54,15 @@ def test_narrow_tiles_are_not_for_two_rounds_of_8_bit_results(dt):
     assert kernel(dt, 3000, 1024, 1024, epi=HB.EPI_REQUANT) == "128x64"
 
 
+def test_e4m3_of_a_long_k_and_several_rounds_takes_small_tiles():
+    """Three rounds of 128 x 128 tiles for one of 256 x 256: ahead for E4M3 from the second large round on (up to 12 %), not for INT8."""
+    f8, i8 = torch.float8_e4m3fn, torch.int8
+    for M, N, K in ((3072, 12288, 4096), (6144, 4096, 4096), (1500, 16384, 4096), (12000, 2048, 8192)):
+        assert kernel(f8, M, N, K) == 8 and kernel(i8, M, N, K) == 7, (M, N, K)
+    for M, N, K in ((768, 12288, 4096), (2500, 16384, 4096), (16384, 12288, 4096)):
+        assert kernel(f8, M, N, K) == 7, (M, N, K)
+
+
 @pytest.mark.parametrize("dt", DTYPES)
 def test_few_rows_of_many_columns_keep_small_tiles(dt):
     """A product of at most 64 rows never runs tiles of 128 or 256 rows, however many columns it has."""
