@@ -602,8 +602,8 @@ __global__ __launch_bounds__(1024) void embed_pair_kernel(LnArgs a) {
 }
 
 // Up to 4096 rows the wave-per-row kernel has one row per wave and is ahead (1024 values: 1024 rows 4.1 us against 6.6, 4096 rows
-// 6.0 against 7.1).
-constexpr int64_t EMBED_PAIR_ROWS = 4096;
+// 6.0 against 7.1), and still with a second row in half a workgroup's waves (4104 rows 6.65 / 7.1, 4108 7.0 / 7.1, 4112 7.9 / 7.1).
+constexpr int64_t EMBED_PAIR_ROWS = 4104;
 
 template <int XDT, int RDT, int NCH, bool GATHER = false>
 hero_status launch_nch(const LnArgs& a, hipStream_t st) {

@@ -1,4 +1,4 @@
-"""The embedding with two rows per wave (513 .. 1024 values, more than 4096 tokens): a last wave with one row, one and several rounds of
+"""The embedding with two rows per wave (513 .. 1024 values, more than 4104 tokens): a last wave with one row, one and several rounds of
 the grid, rows that end in either chunk of a lane, indices outside their tables, rows without variance and with infinities."""
 import pytest
 import torch
@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D", [528, 768, 784, 1008, 1024])
-@pytest.mark.parametrize("T", [4096, 4097, 8192, 8195, 16385])
+@pytest.mark.parametrize("T", [4096, 4104, 4105, 8192, 8195, 16385])
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("typed", [True, False])
 def test_embedding(D, T, dt, typed):
