@@ -1427,7 +1427,10 @@ hero_status attn_entry(const int8_t* q, const int64_t q_strides[4],
     // kernel's is half filled, and with many blocks that shows; padding, which ends its blocks early, adds to it.  Two passes / one, padded:
     // 2064 blocks 260 keys 31.3 / 32.3, 320 36.0 / 37.2, 448 43.1 / 44.4, 480 47.8 / 48.7, 512 55.4 / 54.4, 3072 blocks 320 48.4 / 53.1, 512
     // 71.3 / 72.2, but 1392 blocks 320 27.3 / 26.8;  full: 2064 blocks 320 43.3 / 46.5, 347 52.6 / 52.0, 448 54.1 / 51.1, 512 62.0 / 57.1.
-    const bool many_f8 = fp8 && blocks >= 1536 && Skv > 256 && Skv <= (mask == HERO_MASK_PADDING ? 480 : 352);
+    // Heads of few queries, whose blocks are short and take both of a CU's places in one pass, cross earlier (full, 64 queries: 504
+    // blocks 400 keys 0.87 of the two-pass time, 516 blocks 1.12, 1032 1.28; 96 queries: 768 blocks 0.94, 1032 1.06).
+    const bool many_f8 = fp8 && Skv > 256 && ((blocks >= 1536 && Skv <= (mask == HERO_MASK_PADDING ? 480 : 352)) ||
+                                              (Sq <= 64 && blocks > 512) || (Sq <= 96 && blocks > 1024));
     const bool few = blocks <= 191 || (blocks <= 256 && (2 * pieces <= 5 * blocks || (Skv > 256 && on_xcd > 32)));
     const bool keep = Dh == 64 && Skv <= 512 && qk_scale >= KEEP_MIN_QK && !many_f8;
     if (((keep ? few : blocks <= 256) && (Dh == 64 || pieces <= 768)) || Sq <= 32) {

@@ -24,10 +24,11 @@ def test_against_oracle(Sq, Skv, lens, mask, fp8):
 
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("mask", [HB.MASK_NONE, HB.MASK_PADDING])
-@pytest.mark.parametrize("B,H,S,lens", [(48, 2, 160, (160, 129)), (48, 2, 161, (161, 100)), (21, 4, 320, (320, 161)), (20, 4, 320, (320, 161)),
-                                        (128, 4, 300, (300, 151)), (96, 4, 400, (400, 257)), (127, 4, 300, (300, 300))])
-def test_either_side_of_the_rules(B, H, S, lens, mask, fp8):
-    against_oracle(B, H, S, S, lens, mask, fp8)                      # little filled blocks, crowded XCDs, E4M3 of many blocks
+@pytest.mark.parametrize("B,H,Sq,Skv,lens", [(48, 2, 160, 160, (160, 129)), (48, 2, 161, 161, (161, 100)), (21, 4, 320, 320, (320, 161)),
+                                             (20, 4, 320, 320, (320, 161)), (128, 4, 300, 300, (300, 151)), (96, 4, 400, 400, (400, 257)),
+                                             (127, 4, 300, 300, (300, 300)), (128, 4, 64, 400, (400, 65)), (129, 4, 64, 400, (400, 65)), (257, 4, 96, 260, (260, 250))])
+def test_either_side_of_the_rules(B, H, Sq, Skv, lens, mask, fp8):
+    against_oracle(B, H, Sq, Skv, lens, mask, fp8)                   # little filled blocks, crowded XCDs, E4M3 of many blocks or few queries
 
 
 def against_oracle(B, H, Sq, Skv, lens, mask, fp8):
