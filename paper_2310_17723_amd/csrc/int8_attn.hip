@@ -684,7 +684,7 @@ __global__ __launch_bounds__(256 * KW, 4) void int8_attn_keep_kernel(AttnArgs a)
                 if (!(m > -INFINITY)) return 0.0f;
                 const float f = __builtin_amdgcn_exp2f(m2 - m);
                 const float sum = kh == 0 ? fmaf(l, f, lo * __builtin_amdgcn_exp2f(mo - m)) : fmaf(lo, __builtin_amdgcn_exp2f(mo - m), l * f);
-                return __fdiv_rn(f, sum * a.p_scale);
+                return sum > 0.0f ? __fdiv_rn(f, sum * a.p_scale) : 0.0f;       // (E4M3: a row with a NaN among its scores, as one wave's)
             }
         };
         auto run = [&](auto NTILE) {

@@ -67,3 +67,22 @@ def against_oracle(B, H, Sq, Skv, lens, mask, fp8):
         # a probability code that parts moves an output by one |v| <= 127 times the scale; the result is rounded to 16 bits
         d = np.abs(hp[sel].float().cpu().numpy().reshape(refh.shape) - refh)
         assert np.all(d <= 127.5 * sn[0] + 2.0 ** -8 * np.abs(refh)) and np.mean(d > 2.0 ** -8 * np.abs(refh) + 1e-5) <= 1e-3
+
+
+@pytest.mark.parametrize("Skv", [200, 300, 513])
+def test_a_nan_code_stays_with_its_key(Skv):
+    """E4M3, one pass (200 and 300 keys) and two (513): a key that holds a NaN code gets the largest probability code and the row's other
+    keys code 0, for the row has no sum to divide by.  Rows that do not see it are untouched."""
+    hero, H, Dh, B = pkg.load(), 6, 64, 20
+    g = torch.Generator(device="cuda").manual_seed(Skv)
+    q, k, v = ((torch.randn((B, Skv, H, Dh), device="cuda", generator=g) * 40).to(torch.float8_e4m3fn) for _ in range(3))
+    scale = torch.full((H * Dh,), 1 / 448 / 64, device="cuda")
+    run = lambda key: hero.hero_fp8_attn(q, key, v, 1.5 / (1600 * 8), 1 / 448, scale).view(torch.int8).reshape(B, Skv, H, Dh)
+    ref = run(k)
+    bad = k.clone()
+    bad.view(torch.int8)[3, 17, 2, 5] = 0x7F
+    want = (448 * v[3, 17, 2].float() * scale[0]).to(torch.float8_e4m3fn).view(torch.int8)
+    got = run(bad)
+    assert bool((got[3, :, 2] == want).all())
+    got[3, :, 2] = ref[3, :, 2]
+    assert torch.equal(got, ref)
