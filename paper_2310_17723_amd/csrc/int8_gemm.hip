@@ -337,8 +337,13 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     // loader: unit u of wave w fills LDS granules [(u * NWAVE + w) * 64, +64) of the A (or B) part of
     // a stage; lane l owns row u * 128 + lrow, stored chunk l % 4 = global chunk (l % 4) ^ ((row >> 2) & 3).
     const int lrow = wave * 16 + (lane >> 2);
-    // (16 x 16 tiles read the weight rows in another order: theirs are swizzled by row / 16)
-    const uint32_t lc = (uint32_t)(((lane & 3) ^ ((lrow >> 2) & 3)) * 16), lcb = WIDE ? lc : (uint32_t)(((lane & 3) ^ ((lrow >> 4) & 3)) * 16);
+    // 16 x 16 tiles swizzle by swz4(row / 4), the weight rows, taken in another order, by swz4(row / 16).  The LDS serves a 128-bit
+    // read in four turns of 16 lanes, lanes 0-3, 12-15 and 20-27 in the first, so a turn meets rows 0-3 and 12-15 of one chunk and rows 4-11 of
+    // the chunk beside it; with row / 4 itself half of every read's cycles were bank conflicts, with 0, 3, 2, 1 there are none.
+    // us: BERT-large layer 32 x 512 292.0 -> 290.4, in M1 394.9 -> 390.8, GPT prefill 8 x 2048 3245 -> 3232.
+    auto swz4 = [](int q) { return (q ^ (q << 1)) & 3; };
+    const uint32_t lc = (uint32_t)(((lane & 3) ^ (WIDE ? (lrow >> 2) & 3 : swz4(lrow >> 2))) * 16);
+    const uint32_t lcb = WIDE ? lc : (uint32_t)(((lane & 3) ^ swz4(lrow >> 4)) * 16);
     const uint32_t wbase = __builtin_amdgcn_readfirstlane(lds_offset(smem) + wave * 1024);
     const uint32_t svbase = __builtin_amdgcn_readfirstlane(lds_offset(sv0));
 
@@ -404,7 +409,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     // 16 x 16 tiles: row r = l % 16, chunk l / 16; weight row r of tile j is column 16 (r / 4) + 4 j + r % 4 of the wave's 64
     constexpr int TI = 2 * TM, TJ = 2 * TN;
     static_assert(WIDE || (TJ == 4 && TI % 2 == 0), "16 x 16 tiles: 64 columns per wave");
-    const int r16 = lane & 15, ch16 = ((lane >> 4) ^ ((r16 >> 2) & 3)) << 4;
+    const int r16 = lane & 15, ch16 = ((lane >> 4) ^ swz4(r16 >> 2)) << 4;
     const int foa = (wm * TI * 16 + r16) * 64 + ch16, fob = A_BYTES + (wn * 64 + 16 * (r16 >> 2) + (r16 & 3)) * 64 + ch16;
     int fo[2][NFR];
 #pragma unroll
