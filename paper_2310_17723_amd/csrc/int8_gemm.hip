@@ -13,8 +13,8 @@
 // The main loops; all but the skinny one's share one epilogue (gemm_common.h):
 //   * int8_gemm_persistent_kernel (large problems): 256x256 block tile, 8 waves of 128x64,
 //     slabs of 64 bytes of K copied global -> LDS directly (global_load_lds_dwordx4) through
-//     a ring of 4 stages; one workgroup per CU walks its tiles and the ring runs through the
-//     tile boundaries.  A second form, 128x128 with 4 waves of 64x64 and two workgroups per CU,
+//     two rings, of four slots for the activations and five for the weights; one workgroup per CU walks its tiles and the
+//     rings run through the tile boundaries.  A second form, 128x128 with 4 waves of 64x64 and two workgroups per CU,
 //     serves the sizes at which the large tile would leave CUs idle (twice the L2 -> LDS traffic per tile area).
 //   * int8_gemm_dma_kernel: the same tile, one tile per workgroup (short K, huge strides).
 //   * int8_gemm_ring_kernel (gemm_ring.h; small and middling problems): 32x32 .. 128x128 tiles, 128-byte slabs, K groups.
@@ -297,6 +297,11 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void int8_gemm_dma_kernel(GemmA
 // epilogue vectors, fetched by the same direct loads into a double-buffered LDS area) are
 // already resident when the epilogue of the current tile ends.  Slab addresses are a wave-uniform tile base in SGPRs
 // plus a per-lane 32-bit offset, so advancing along K is scalar arithmetic.
+// A and B have rings of their own, of four and five slots (144 KB), and take turns: B's pair of slabs goes out in even iterations and has
+// three to arrive in, A's in odd ones and has two.  One ring of four slots for both sent 64 KB at once and then waited for the last of them: a
+// pair of slabs took the time from its first load to its last one's arrival, 2500 to 3200 clocks against 2048 of matrix instructions.  us,
+// one ring -> two: INT8 16384 x 12288 x 4096 641 -> 610 (2.70 POP/s), 16384 x 4096 x 16384 888 -> 815, 16384 x 1024 x 4096 55.3 -> 53.2, 16384 x
+// 3072 x 1024 49.8 -> 48.8;  BF16 8192 x 4096 x 4096 208 -> 199;  E4M3 8192 x 4096 x 4096 111 -> 102.  (Both operands in the same iteration: -7 %.)
 // The clock under matrix load is set by power, and 16 x 16 instructions multiply more per watt than 32 x 32 ones; their lanes also
 // write 16 (32) consecutive bytes next to their neighbours'.  us, 32 x 32 -> 16 x 16 tiles: INT8 16384 x 12288 x 4096 694 -> 642
 // (2.57 POP/s), 8192 x 4096 x 16384 451 -> 411, 8192 x 4096 x 4096 120 -> 111, 16384 x 4096 x 1024 REQUANT 71.5 -> 69.2, GELU^quant 16384 x
@@ -304,26 +309,42 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void int8_gemm_dma_kernel(GemmA
 // (A kernel of its own for GELU^quant behind a short K, its epilogue spread over the next tile's main loop, fell behind with
 // that: 16384 x 4096 x 1024 91 -> 84 us, 16-bit result 152 -> 98.5, 2500 rows 27.9 -> 20.5.)
 // =====================================================================================
-template <int BM, int BN, int WM, int WN, int NS, int EPI, int CDT, int RDT, int ADT = HERO_I8>
+// How many of a wave's direct loads may be out when the barrier of an iteration publishes the next slab: those issued behind the ones
+// that bring it.  la, lb: loads of a pair of A, B.  Times are iterations before this one (0); a ring of n slots is given a pair for the slabs
+// n - 1 and n ahead in odd iterations (n even) or even ones (n odd), B before A.  Behind an odd iteration the pair's first slab is
+// needed, whose loads alternate with the second one's, so that the very last may be out as well.
+constexpr int pair_loads_behind(bool odd, int na, int nb, int la, int lb) {
+    const int first = odd ? 2 : 1;
+    const int last = 2 * (first - na) + 1 > 2 * (first - nb) ? 2 * (first - na) + 1 : 2 * (first - nb);     // 2 * time (+ 1: A)
+    int c = odd ? 1 : 0;
+    for (int t = -6; t < 0; ++t) {
+        const bool t_odd = ((t + (odd ? 1 : 0)) & 1) != 0;
+        if ((nb % 2 == 0) == t_odd && 2 * t > last) c += lb;
+        if ((na % 2 == 0) == t_odd && 2 * t + 1 > last) c += la;
+    }
+    return c;
+}
+
+template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT = HERO_I8>
 __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(GemmArgs g) {
     constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
     constexpr bool WIDE = ADT == HERO_F8E4M3;                       // 32 x 32 tiles; INT8 and 16 bits: 16 x 16 (mfma16_step)
     using ACC = typename std::conditional<WIDE, v16f, typename Acc4Of<ADT>::type>::type;
     constexpr int NT = WM * WN * 64, NWAVE = WM * WN;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = A_BYTES + B_BYTES;
-    constexpr int A_UNITS = A_BYTES / 16 / NT, B_UNITS = B_BYTES / 16 / NT, NW = A_UNITS + B_UNITS;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;            // (32 x 32 tiles)
+    constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK;
+    constexpr int A_UNITS = BM / 16 / NWAVE, B_UNITS = BN / 16 / NWAVE;      // 1 KB loads per wave and slab: 16 rows each
     constexpr int NM = TM * TN, NFR = TM + TN;
-    static_assert(NS == 4 && NW <= NM && NFR <= 2 * NM && NFR % 2 == 0, "ring / interleave plan");
-    constexpr int RING = NS * STAGE;
+    static_assert(NSA >= 4 && NSA <= 6 && NSB >= 4 && NSB <= 6 && BM % (16 * NWAVE) == 0 && BN % (16 * NWAVE) == 0 && (!WIDE || (NFR <= 2 * NM && BM % (32 * WM) == 0)), "rings / interleave plan");
+    constexpr int A_RING = NSA * A_BYTES, B_RING = NSB * B_BYTES, RING = A_RING + B_RING;
     constexpr int SVF = 4 * BN;                                  // floats per vector set: column scale, bias, S_a, row scale
-    static_assert(BM == BN, "the row-scale vector shares the column vectors' length");
+    static_assert(BM <= BN, "the row-scale vector shares the column vectors' length");
     constexpr int PF_OFF = RING + 2 * SVF * 4;                   // 256 bytes per wave where the prefetch requests land (never read)
     static_assert(PF_OFF + NWAVE * 256 <= 160 * 1024, "LDS budget");
     __shared__ __attribute__((aligned(1024))) int8_t smem[PF_OFF + NWAVE * 256];
     float* const sv0 = reinterpret_cast<float*>(smem + RING);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int xcd = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD, nslot = gridDim.x / NUM_XCD;
     const int seq_end = min((xcd + 1) * g.per_xcd, g.ntm * g.ntn);
@@ -334,8 +355,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     if (!has_bias)                                               // the bias vectors are read by the epilogue either way
         for (int c = tid; c < 2 * BN; c += NT) sv0[(c / BN) * SVF + BN + c % BN] = 0.0f;
 
-    // loader: unit u of wave w fills LDS granules [(u * NWAVE + w) * 64, +64) of the A (or B) part of
-    // a stage; lane l owns row u * 128 + lrow, stored chunk l % 4 = global chunk (l % 4) ^ ((row >> 2) & 3).
+    // loader: unit u of wave w fills LDS granules [(u * NWAVE + w) * 64, +64) of a slot of A (or B); lane l owns row u * 128 + lrow, stored chunk l % 4 = global chunk (l % 4) ^ ((row >> 2) & 3).
     const int lrow = wave * 16 + (lane >> 2);
     // 16 x 16 tiles swizzle by swz4(row / 4), the weight rows, taken in another order, by swz4(row / 16).  The LDS serves a 128-bit
     // read in four turns of 16 lanes, lanes 0-3, 12-15 and 20-27 in the first, so a turn meets rows 0-3 and 12-15 of one chunk and rows 4-11 of
@@ -347,91 +367,116 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     const uint32_t wbase = __builtin_amdgcn_readfirstlane(lds_offset(smem) + wave * 1024);
     const uint32_t svbase = __builtin_amdgcn_readfirstlane(lds_offset(sv0));
 
-    // ---- issue stream: the tile / slab the next direct loads belong to (runs NS-1 slabs ahead)
-    int iseq = seq, ikt = 0, ipar = 0;
+    // ---- the two issue streams, of A and of B: the tile / slab their next direct loads belong to
+    int aseq = seq, akt = 0, bseq = seq, bkt = 0, bpar = 0;
     const int8_t* ia; const int8_t* ib;                          // wave-uniform: tile base + slab offset
     uint32_t oa[A_UNITS], ob[B_UNITS];
-    int m0i = 0, n0i = 0;                                        // origin of the issue stream's tile
-    auto set_issue_tile = [&](int s) {
-        tile_from_seq<BM, BN>(g, s, m0i, n0i);
-        ia = g.A + (int64_t)m0i * g.lda;
-        ib = g.Bt + (int64_t)n0i * g.ldb;
+    int m0b = 0, n0b = 0;                                        // origin of B's tile
+    auto set_tile_a = [&](int s) {
+        int m0, n0;
+        tile_from_seq<BM, BN>(g, s, m0, n0);
+        ia = g.A + (int64_t)m0 * g.lda;
 #pragma unroll
-        for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0i) * (uint32_t)g.lda + lc;
-#pragma unroll
-        for (int u = 0; u < B_UNITS; ++u) ob[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.N - 1 - n0i) * (uint32_t)g.ldb + lcb;
+        for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0) * (uint32_t)g.lda + lc;
     };
-    // The epilogue vectors of the issue stream's tile go out together with its FIRST pair, not when the stream
+    auto set_tile_b = [&](int s) {
+        tile_from_seq<BM, BN>(g, s, m0b, n0b);
+        ib = g.Bt + (int64_t)n0b * g.ldb;
+#pragma unroll
+        for (int u = 0; u < B_UNITS; ++u) ob[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.N - 1 - n0b) * (uint32_t)g.ldb + lcb;
+    };
+    // The epilogue vectors of B's tile go out together with its FIRST pair, not when the stream
     // moves on to the tile: their buffer (parity of the tile) is still being read by the epilogue of the tile
     // two back until every wave has started the tile in between.
     auto issue_tile_vectors = [&](int par) {
         // wave w fetches 64 entries (chunk w % CH) of vectors w / CH and 2 + w / CH
         constexpr int CH = BN / 64;
         static_assert(NWAVE == 2 * CH, "two vectors per wave");
-        const int wu = __builtin_amdgcn_readfirstlane(wave);
-        const int ch = (wu % CH) * 64, which = wu / CH;
+        const int ch = (wave % CH) * 64, which = wave / CH;
         const uint32_t dst = svbase + par * SVF * 4 + ch * 4;
-        const uint32_t cn = (uint32_t)min(ch + lane, g.N - 1 - n0i) * 4u, cm = (uint32_t)min(ch + lane, g.M - 1 - m0i) * 4u;
+        const uint32_t cn = (uint32_t)min(ch + lane, g.N - 1 - n0b) * 4u, cm = (uint32_t)min(ch + lane, g.M - 1 - m0b) * 4u;
         if (EPI == HERO_EPI_RAW_I32) return;
         if (which == 0) {
-            if (!UNIT) dma4s(cn, g.b_col_scale + n0i, dst);
-            if (EPI == HERO_EPI_GELU_REQUANT) dma4s(cn, g.out_col_scale + n0i, dst + 2 * BN * 4);
+            if (!UNIT) dma4s(cn, g.b_col_scale + n0b, dst);
+            if (EPI == HERO_EPI_GELU_REQUANT) dma4s(cn, g.out_col_scale + n0b, dst + 2 * BN * 4);
         } else {
-            if (has_bias) dma4s(cn, g.bias + n0i, dst + BN * 4);
-            if (has_rs) dma4s(cm, g.a_row_scale + m0i, dst + 3 * BN * 4);
+            if (has_bias) dma4s(cn, g.bias + n0b, dst + BN * 4);
+            if (has_rs) dma4s(cm, g.a_row_scale + m0b, dst + 3 * BN * 4);
         }
     };
-    // The issue stream moves in PAIRS of slabs (128 bytes of every row = one cache line): the j-th direct load
-    // of a pair is unit j / 2 of slab j % 2, so the two 64-byte halves of a line are requested back to back and
-    // the second one is served by the line the first one brought in.  A CU pulls 48 B/clk from the L2 that way,
+    // A stream moves in PAIRS of slabs (128 bytes of every row = one cache line): the two 64-byte halves of a line are requested back
+    // to back and the second one is served by the line the first one brought in.  A CU pulls 48 B/clk from the L2 that way,
     // against 30 B/clk when the halves are requested one slab apart (measured; a 256 x 256 tile needs 32).
-    auto issue_pair = [&](int j, int stage0) {                   // stage0: the (even) stage of the pair's first slab
-        if (j == 0 && ikt == 0) issue_tile_vectors(ipar);
-        const int u = j >> 1;
-        const uint32_t lds = wbase + (stage0 + (j & 1)) * STAGE;
+    // issue_a(u) / issue_b(u): unit u of both slabs; wra, wrb: LDS offset of the pair's first slot (the second is the next one, round the ring).
+    uint32_t wra = 0, wrb = 0;
+    auto next_slot = [](uint32_t o, uint32_t bytes, uint32_t ring) { const uint32_t n = o + bytes; return n == ring ? 0u : n; };
+    auto issue_a = [&](int u) {
+        dma16s(oa[u], ia, wbase + wra + u * NWAVE * 1024);
         // (the second slab through its own scalar base: an instruction offset would move the LDS side too)
-        if (u < A_UNITS) dma16s(oa[u], ia + (j & 1) * BK, lds + u * NWAVE * 1024);
-        else dma16s(ob[u - A_UNITS], ib + (j & 1) * BK, lds + A_BYTES + (u - A_UNITS) * NWAVE * 1024);
+        dma16s(oa[u], ia + BK, wbase + next_slot(wra, A_BYTES, A_RING) + u * NWAVE * 1024);
     };
-    auto advance = [&]() {                                       // next pair; past the last tile the last pair repeats (never read)
-        ikt += 2;
-        if (ikt < KT) { ia += 2 * BK; ib += 2 * BK; return; }
-        if (iseq + nslot < seq_end) {
-            iseq += nslot; ikt = 0; ipar ^= 1;
-            set_issue_tile(iseq);
-        } else {
-            ikt = KT - 2;
-        }
+    auto issue_b = [&](int u) {
+        if (u == 0 && bkt == 0) issue_tile_vectors(bpar);
+        dma16s(ob[u], ib, wbase + A_RING + wrb + u * NWAVE * 1024);
+        dma16s(ob[u], ib + BK, wbase + A_RING + next_slot(wrb, B_BYTES, B_RING) + u * NWAVE * 1024);
+    };
+    auto advance_a = [&]() {                                     // next pair; past the last tile the last pair repeats (never read)
+        wra = next_slot(next_slot(wra, A_BYTES, A_RING), A_BYTES, A_RING);
+        akt += 2;
+        if (akt < KT) { ia += 2 * BK; return; }
+        if (aseq + nslot < seq_end) {
+            aseq += nslot; akt = 0;
+            set_tile_a(aseq);
+        } else akt = KT - 2;
+    };
+    auto advance_b = [&]() {
+        wrb = next_slot(next_slot(wrb, B_BYTES, B_RING), B_BYTES, B_RING);
+        bkt += 2;
+        if (bkt < KT) { ib += 2 * BK; return; }
+        if (bseq + nslot < seq_end) {
+            bseq += nslot; bkt = 0; bpar ^= 1;
+            set_tile_b(bseq);
+        } else bkt = KT - 2;
     };
 
-    // fragment offsets inside a stage (row rr, k-step ks, half hh): rr*64 + ((2ks+hh) ^ ((rr>>2)&3))*16
+    // fragment offsets inside a slot (row rr, k-step ks, half hh): rr*64 + ((2ks+hh) ^ ((rr>>2)&3))*16
     const int hh = lane >> 5, ml = lane & 31;
     // 16 x 16 tiles: row r = l % 16, chunk l / 16; weight row r of tile j is column 16 (r / 4) + 4 j + r % 4 of the wave's 64
-    constexpr int TI = 2 * TM, TJ = 2 * TN;
-    static_assert(WIDE || (TJ == 4 && TI % 2 == 0), "16 x 16 tiles: 64 columns per wave");
+    constexpr int TI = BM / WM / 16, TJ = 2 * TN;
+    static_assert(WIDE || TJ == 4, "16 x 16 tiles: 64 columns per wave");
     const int r16 = lane & 15, ch16 = ((lane >> 4) ^ swz4(r16 >> 2)) << 4;
-    const int foa = (wm * TI * 16 + r16) * 64 + ch16, fob = A_BYTES + (wn * 64 + 16 * (r16 >> 2) + (r16 & 3)) * 64 + ch16;
+    const int foa = (wm * TI * 16 + r16) * 64 + ch16, fob = A_RING + (wn * 64 + 16 * (r16 >> 2) + (r16 & 3)) * 64 + ch16;
     int fo[2][NFR];
 #pragma unroll
     for (int t = 0; t < NFR; ++t) {
         const int rr = (t < TN ? wn * TN * 32 + t * 32 : wm * TM * 32 + (t - TN) * 32) + ml;
-        const int base = (t < TN ? A_BYTES : 0) + rr * 64;
+        const int base = (t < TN ? A_RING : 0) + rr * 64;
         fo[0][t] = base + (((0 + hh) ^ ((rr >> 2) & 3)) << 4);
         fo[1][t] = base + (((2 + hh) ^ ((rr >> 2) & 3)) << 4);
     }
 
-    // prologue: vectors of the first tile, both pairs of the ring in flight, slab 0 landed
-    set_issue_tile(seq);
+    // prologue: what the iterations before the first would have issued, in their order; slab 0 landed
+    constexpr int LA = 2 * A_UNITS, LB = 2 * B_UNITS;
+    set_tile_a(seq);
+    set_tile_b(seq);
 #pragma unroll
-    for (int p0 = 0; p0 < 2; ++p0) {
+    for (int t = -5; t < 0; ++t) {
+        const int pb = t + NSB - 1, pa = t + NSA - 1;              // twice the pair whose turn it is
+        if (pb >= 0 && pb % 2 == 0) {
 #pragma unroll
-        for (int j = 0; j < 2 * NW; ++j) issue_pair(j, 2 * p0);
-        advance();
+            for (int u = 0; u < B_UNITS; ++u) issue_b(u);
+            advance_b();
+        }
+        if (pa >= 0 && pa % 2 == 0) {
+#pragma unroll
+            for (int u = 0; u < A_UNITS; ++u) issue_a(u);
+            advance_a();
+        }
     }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NW + 1));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(pair_loads_behind(false, NSA, NSB, LA, LB) + 1));
     __syncthreads();
 
-    int stage = 0, par = 0;
+    int rda = 0, rdb = 0, par = 0;                                  // LDS offsets of the current slab
     for (;;) {
         int m0, n0;
         tile_from_seq<BM, BN>(g, seq, m0, n0);
@@ -447,27 +492,29 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         if constexpr (WIDE) {
 #pragma unroll
             for (int t = 0; t < NFR; ++t) {
-                f0[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fo[0][t]);
-                f1[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fo[1][t]);
+                f0[t] = *reinterpret_cast<const v4i*>(smem + (t < TN ? rdb : rda) + fo[0][t]);
+                f1[t] = *reinterpret_cast<const v4i*>(smem + (t < TN ? rdb : rda) + fo[1][t]);
             }
         } else {
 #pragma unroll
-            for (int t = 0; t < TJ; ++t) fb[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + fob + t * 256);
+            for (int t = 0; t < TJ; ++t) fb[t] = *reinterpret_cast<const v4i*>(smem + rdb + fob + t * 256);
 #pragma unroll
-            for (int t = 0; t < TI; ++t) fa[t] = *reinterpret_cast<const v4i*>(smem + stage * STAGE + foa + t * 1024);
+            for (int t = 0; t < TI; ++t) fa[t] = *reinterpret_cast<const v4i*>(smem + rda + foa + t * 1024);
         }
 
-        // One slab per iteration with the barrier in the middle (see int8_gemm_dma_kernel).  KT is even and the
-        // ring holds two pairs: after the barrier of an ODD iteration i every wave has read the last fragment
-        // of the pair (i-1, i), whose two stages then take the pair (i+3, i+4) of the stream, which may
-        // already belong to the next tile.  In program order the loads of a pair alternate between its slabs,
-        // so "slab i+1 has landed" is vmcnt(1) in an odd iteration (only the last load of slab i+2 may be
-        // out) and vmcnt(2 NW) in an even one (the younger pair may be out).
+        // One slab per iteration with the barrier in the middle (see int8_gemm_dma_kernel).  Behind the barrier of iteration i every
+        // wave has read the last fragment of slab i (lgkmcnt(0) in front of it), so both its slots are free: a ring of five slots has
+        // one to spare and takes the pair (i + 4, i + 5) in even iterations, rings of four and six wait for the odd one
+        // and take (i + 3, i + 4), (i + 5, i + 6).  The pairs may already belong to the next tile.
         auto iteration = [&](auto ODD) {
             constexpr bool odd = decltype(ODD)::value;
-            const int nstage = stage + 1 == NS ? 0 : stage + 1;
-            const int pstage = stage == 0 ? NS - 1 : stage - 1;
-            const int8_t* stn = smem + nstage * STAGE;
+            constexpr bool put_a = odd == (NSA % 2 == 0), put_b = odd == (NSB % 2 == 0);
+            constexpr int NU = (put_a ? A_UNITS : 0) + (put_b ? B_UNITS : 0);      // units to issue: B's, then A's
+            const int nda = rda + A_BYTES == A_RING ? 0 : rda + A_BYTES, ndb = rdb + B_BYTES == B_RING ? 0 : rdb + B_BYTES;
+            auto issue_unit = [&](int u) { if (put_b && u < B_UNITS) issue_b(u); else issue_a(u - (put_b ? B_UNITS : 0)); };
+            auto wait_next_slab = [&]() {                             // slab i + 1 has landed (mine), slab i has been read
+                __builtin_amdgcn_s_waitcnt(vmcnt_lds_imm(pair_loads_behind(odd, NSA, NSB, LA, LB)));
+            };
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (WIDE) {
                 // FP8: one 32x32x64 matrix instruction per accumulator and slab (both k halves of a fragment
@@ -479,7 +526,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
                     const int jj = n / TM, ii = n % TM;
                     acc[ii][jj] = mfma_wide_f8(f0[jj], f1[jj], f0[TN + ii], f1[TN + ii], acc[ii][jj]);
                     if (n == TM - 1) {
-                        __builtin_amdgcn_s_waitcnt(vmcnt_imm(odd ? 1 : 2 * NW));
+                        wait_next_slab();
                         __syncthreads();
                     }
                     if (n >= TM - 1) {
@@ -487,16 +534,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
                         for (int t = 0; t < NFR; ++t) {
                             const int last = t < TN ? t * TM + TM - 1 : (TN - 1) * TM + (t - TN);
                             if ((last < TM - 1 ? TM - 1 : last) == n) {
-                                f0[t] = *reinterpret_cast<const v4i*>(stn + fo[0][t]);
-                                f1[t] = *reinterpret_cast<const v4i*>(stn + fo[1][t]);
+                                f0[t] = *reinterpret_cast<const v4i*>(smem + (t < TN ? ndb : nda) + fo[0][t]);
+                                f1[t] = *reinterpret_cast<const v4i*>(smem + (t < TN ? ndb : nda) + fo[1][t]);
                             }
                         }
-                        if (odd) {                                     // PPS units of the new pair per instruction slot
-                            constexpr int SLOTS = NM - TM + 1, PPS = (NW + SLOTS - 1) / SLOTS;
+                        constexpr int SLOTS = NM - TM + 1, PPS = (NU + SLOTS - 1) / SLOTS;      // units per instruction slot
 #pragma unroll
-                            for (int u = (n - (TM - 1)) * PPS; u < (n - (TM - 1) + 1) * PPS; ++u)
-                                if (u < NW) { issue_pair(2 * u, pstage); issue_pair(2 * u + 1, pstage); }
-                        }
+                        for (int u = (n - (TM - 1)) * PPS; u < (n - (TM - 1) + 1) * PPS; ++u)
+                            if (u < NU) issue_unit(u);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -505,33 +550,34 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
                 // before, right after its register's last use: the first half of the rows (dead by the barrier) and the weights one by
                 // one as the second half is done with them, that half itself at the end.  Twelve instructions at least lie
                 // between a read and its use.
-                constexpr int HI = TI / 2, NH = HI * TJ;
+                constexpr int HI = TI / 2, HS = TI - HI, NH = HS * TJ;
+                static_assert(NU <= NH, "a slot of the second half for every unit");
 #pragma unroll
-                for (int n = 0; n < NH; ++n) {
+                for (int n = 0; n < HI * TJ; ++n) {
                     const int jj = n / HI, ii = n % HI;
                     acc[ii][jj] = mfma16_step<ADT>(fb[jj], fa[ii], acc[ii][jj]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                // the next slab has landed (mine); behind an odd slab the direct loads overwrite what this wave read last
-                __builtin_amdgcn_s_waitcnt(odd ? vmcnt_lds_imm(1) : vmcnt_imm(2 * NW));
+                wait_next_slab();
                 __syncthreads();                                       // ... and everybody's
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int n = 0; n < NH; ++n) {
-                    const int jj = n / HI, ii = HI + n % HI;
+                    const int jj = n / HS, ii = HI + n % HS;
                     acc[ii][jj] = mfma16_step<ADT>(fb[jj], fa[ii], acc[ii][jj]);
-                    if (n < HI) fa[n] = *reinterpret_cast<const v4i*>(stn + foa + n * 1024);
-                    if (n % HI == HI - 1) fb[jj] = *reinterpret_cast<const v4i*>(stn + fob + jj * 256);
-                    if (n >= NH - HI) fa[ii] = *reinterpret_cast<const v4i*>(stn + foa + ii * 1024);
-                    if (odd) {                                         // the units of the new pair, evenly over the half
-                        constexpr int EV = NH / NW;
-                        if (n % EV == 0 && n / EV < NW) { issue_pair(2 * (n / EV), pstage); issue_pair(2 * (n / EV) + 1, pstage); }
+                    if (n < HI) fa[n] = *reinterpret_cast<const v4i*>(smem + nda + foa + n * 1024);
+                    if (n % HS == HS - 1) fb[jj] = *reinterpret_cast<const v4i*>(smem + ndb + fob + jj * 256);
+                    if (n >= NH - HS) fa[ii] = *reinterpret_cast<const v4i*>(smem + nda + foa + ii * 1024);
+                    if constexpr (NU > 0) {                            // evenly over the half
+                        constexpr int EV = NH / NU;
+                        if (n % EV == 0 && n / EV < NU) issue_unit(n / EV);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            if (odd) advance();
-            stage = nstage;
+            if (put_b) advance_b();
+            if (put_a) advance_a();
+            rda = nda; rdb = ndb;
         };
         for (int kt = 0; kt < KT; kt += 2) {
             iteration(std::false_type{});
@@ -548,7 +594,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         // longer than a miss).  What the request brings is the line: into this XCD's L2 and, on its way, into the
         // memory-side cache, where the next kernel's first tiles would otherwise all miss at once.
         if (g.pf_lines > 0) {
-            const int w0 = __builtin_amdgcn_readfirstlane(wave) * 64;
+            const int w0 = wave * 64;
             if (w0 < g.pf_lpt) {
                 const uint32_t line = (uint32_t)min(seq * g.pf_lpt + w0 + lane, g.pf_lines - 1);
                 dma4s(line * 128u, reinterpret_cast<const float*>(g.pf),
@@ -560,7 +606,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         float rsr[CI];
 #pragma unroll
         for (int i = 0; i < CI; ++i)
-            rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * TM * 32 + i * (WIDE ? 32 : 16) + (WIDE ? ml : r16)] : 1.0f;
+            rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * (BM / WM) + i * (WIDE ? 32 : 16) + (WIDE ? ml : r16)] : 1.0f;
         if constexpr (WIDE) epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, true, UNIT>(g, acc, sv, rsr, m0, n0, tid);
         else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(g, acc, sv, rsr, m0, n0, tid);
         seq += nslot;
@@ -722,7 +768,7 @@ hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) 
     share_prefetch(gp, tiles, WM * WN * 64);
     const int cap = 32 * wg_per_cu;                                   // 32 CUs per XCD
     const int nslot = gp.per_xcd < cap ? gp.per_xcd : cap;
-    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
+    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, 5, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
     return hero_launch_status();
 }
 
