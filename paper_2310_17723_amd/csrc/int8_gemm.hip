@@ -14,8 +14,8 @@
 //   * int8_gemm_persistent_kernel (large problems): 256x256 block tile, 8 waves of 128x64,
 //     slabs of 64 bytes of K copied global -> LDS directly (global_load_lds_dwordx4) through
 //     two rings, of four slots for the activations and five for the weights; one workgroup per CU walks its tiles and the
-//     rings run through the tile boundaries.  A second form, 128x128 with 4 waves of 64x64 and two workgroups per CU,
-//     serves the sizes at which the large tile would leave CUs idle (twice the L2 -> LDS traffic per tile area).
+//     rings run through the tile boundaries.  Tiles of 224, 192 and 160 rows and a second form, 128x128 with 4 waves of 64x64 and two workgroups per CU,
+//     serve the sizes at which the large tile would leave CUs idle (128x128: twice the L2 -> LDS traffic per tile area).
 //   * int8_gemm_dma_kernel: the same tile, one tile per workgroup (short K, huge strides).
 //   * int8_gemm_ring_kernel (gemm_ring.h; small and middling problems): 32x32 .. 128x128 tiles, 128-byte slabs, K groups.
 //   * skinny_gemm_kernel (gemm_skinny.hip; up to 32 rows): a stream of the weights.
@@ -333,9 +333,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     constexpr int NT = WM * WN * 64, NWAVE = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;            // (32 x 32 tiles)
     constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK;
-    constexpr int A_UNITS = BM / 16 / NWAVE, B_UNITS = BN / 16 / NWAVE;      // 1 KB loads per wave and slab: 16 rows each
+    // 1 KB loads per wave and slab: 16 rows each; with BM no multiple of 128 the last one is for the first A_LAST waves only
+    constexpr int A_UNITS = (BM / 16 + NWAVE - 1) / NWAVE, A_LAST = BM / 16 - (A_UNITS - 1) * NWAVE, B_UNITS = BN / 16 / NWAVE;
+    constexpr bool A_EVEN = A_LAST == NWAVE;
     constexpr int NM = TM * TN, NFR = TM + TN;
-    static_assert(NSA >= 4 && NSA <= 6 && NSB >= 4 && NSB <= 6 && BM % (16 * NWAVE) == 0 && BN % (16 * NWAVE) == 0 && (!WIDE || (NFR <= 2 * NM && BM % (32 * WM) == 0)), "rings / interleave plan");
+    static_assert(NSA >= 4 && NSA <= 6 && NSB >= 4 && NSB <= 6 && BM % (16 * WM) == 0 && BN % (16 * NWAVE) == 0 && (!WIDE || (NFR <= 2 * NM && BM % (32 * WM) == 0)), "rings / interleave plan");
     constexpr int A_RING = NSA * A_BYTES, B_RING = NSB * B_BYTES, RING = A_RING + B_RING;
     constexpr int SVF = 4 * BN;                                  // floats per vector set: column scale, bias, S_a, row scale
     static_assert(BM <= BN, "the row-scale vector shares the column vectors' length");
@@ -351,6 +353,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     int seq = xcd * g.per_xcd + slot;                            // this workgroup's tiles: seq, seq + nslot, ...
     if (seq >= seq_end) return;
     const int KT = g.K / BK;
+    const bool has_last = A_EVEN || wave < A_LAST;
     const bool has_rs = g.a_row_scale != nullptr, has_bias = g.bias != nullptr;
     if (!has_bias)                                               // the bias vectors are read by the epilogue either way
         for (int c = tid; c < 2 * BN; c += NT) sv0[(c / BN) * SVF + BN + c % BN] = 0.0f;
@@ -411,9 +414,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     uint32_t wra = 0, wrb = 0;
     auto next_slot = [](uint32_t o, uint32_t bytes, uint32_t ring) { const uint32_t n = o + bytes; return n == ring ? 0u : n; };
     auto issue_a = [&](int u) {
-        dma16s(oa[u], ia, wbase + wra + u * NWAVE * 1024);
-        // (the second slab through its own scalar base: an instruction offset would move the LDS side too)
-        dma16s(oa[u], ia + BK, wbase + next_slot(wra, A_BYTES, A_RING) + u * NWAVE * 1024);
+        if (A_EVEN || u + 1 < A_UNITS || has_last) {
+            dma16s(oa[u], ia, wbase + wra + u * NWAVE * 1024);
+            // (the second slab through its own scalar base: an instruction offset would move the LDS side too)
+            dma16s(oa[u], ia + BK, wbase + next_slot(wra, A_BYTES, A_RING) + u * NWAVE * 1024);
+        }
     };
     auto issue_b = [&](int u) {
         if (u == 0 && bkt == 0) issue_tile_vectors(bpar);
@@ -473,7 +478,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
             advance_a();
         }
     }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(pair_loads_behind(false, NSA, NSB, LA, LB) + 1));
+    if (has_last) __builtin_amdgcn_s_waitcnt(vmcnt_imm(pair_loads_behind(false, NSA, NSB, LA, LB) + 1));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(pair_loads_behind(false, NSA, NSB, LA - 2, LB) + 1));
     __syncthreads();
 
     int rda = 0, rdb = 0, par = 0;                                  // LDS offsets of the current slab
@@ -513,7 +519,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
             const int nda = rda + A_BYTES == A_RING ? 0 : rda + A_BYTES, ndb = rdb + B_BYTES == B_RING ? 0 : rdb + B_BYTES;
             auto issue_unit = [&](int u) { if (put_b && u < B_UNITS) issue_b(u); else issue_a(u - (put_b ? B_UNITS : 0)); };
             auto wait_next_slab = [&]() {                             // slab i + 1 has landed (mine), slab i has been read
-                __builtin_amdgcn_s_waitcnt(vmcnt_lds_imm(pair_loads_behind(odd, NSA, NSB, LA, LB)));
+                if (has_last) __builtin_amdgcn_s_waitcnt(vmcnt_lds_imm(pair_loads_behind(odd, NSA, NSB, LA, LB)));
+                else __builtin_amdgcn_s_waitcnt(vmcnt_lds_imm(pair_loads_behind(odd, NSA, NSB, LA - 2, LB)));
             };
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (WIDE) {
@@ -741,7 +748,7 @@ bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st,
 }
 
 // Tile choice (choose() below): the ring kernel where ring_form (gemm_common.h) has a form (everything small, and a short K), the
-// persistent kernels beyond (small_tile_fills_better).
+// persistent kernels beyond (persistent_choice).
 // the prefetch hint's share per tile: at most one request per lane
 inline void share_prefetch(GemmArgs& g, int64_t tiles, int lanes) {
     if (g.pf_lines <= 0) return;
@@ -758,6 +765,9 @@ inline void set_prefetch(GemmArgs& g, const void* prefetch, size_t prefetch_byte
     }
 }
 
+// Slots of the two rings, A and B, for a tile of BM rows: what 160 KB hold (128 x 128: two workgroups per CU).  Both operands in the same
+// iteration lose what the slots give: 2500 x 4096 x 4096 in tiles of 192 rows 48.0 us with five and five, 42.9 with four and five.
+template <int BM> struct PersRing { static constexpr int A = BM == 160 ? 5 : 4, B = BM == 160 ? 6 : 5; };
 template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT, int ADT>
 hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) {
     GemmArgs gp = g;
@@ -768,26 +778,41 @@ hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) 
     share_prefetch(gp, tiles, WM * WN * 64);
     const int cap = 32 * wg_per_cu;                                   // 32 CUs per XCD
     const int nslot = gp.per_xcd < cap ? gp.per_xcd : cap;
-    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, 4, 5, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
+    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, PersRing<BM>::A, PersRing<BM>::B, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
     return hero_launch_status();
-}
-
-// 256 x 256 tiles, one workgroup per CU, or 128 x 128 tiles, two per CU?  A CU is handed ceil(tiles / 256) tiles of either; a small one
-// takes a quarter of a large one's time and, with twice the L2 -> LDS traffic, 1.05 to 1.3 times that behind a short K, 1.15 to 1.6
-// behind a long one (the more the emptier the grid: the clock rises where CUs idle).  Measured over 450 products (INT8, E4M3, BF16, 256
-// .. 12000 rows), the rule's losses are 5 % at most.  us, large / small: REQUANT 3817 x 3072 x 1024 18.9 / 17.7, 768 x 12288 x 4096 52.8 /
-// 62.9, 1300 x 12288 x 4096 96.7 / 84.6, GELU^quant 3072 x 4096 x 1024 23.7 / 20.6, 3817 rows 25.0 / 26.4.  E4M3 behind a long K, whose large
-// tile has no 16 x 16 instructions, is nearer to the small one's rate from the second round on: GELU^quant 3072 x 12288 x 4096 161 / 144, 6144 x
-// 4096 x 4096 106.6 / 99.6, 16-bit result 151 / 142, but 2500 x 16384 x 4096 163 / 171 and, in one round, 768 x 12288 x 4096 REQUANT 46.8 / 49.0.
-inline bool small_tile_fills_better(int64_t t256, int64_t t128, int64_t kb, bool f8) {
-    const int64_t n256 = (t256 + 255) / 256, n128 = (t128 + 255) / 256;
-    const double per_tile = (kb <= 2048 ? 1.2 : f8 && n256 > 1 ? 1.3 : 1.4) / 4;
-    return (double)n128 * per_tile < (double)n256;
 }
 
 // What runs a product.  The codes of the kernels are those of the test hooks (include/hero_debug.h).
 enum Kernel { K_REG128 = 0, K_DMA256 = 1, K_RING = 2, K_REG64 = 3, K_SKINNY = 4, K_PERS256 = 7, K_PERS128 = 8 };
-struct Choice { Kernel kernel; RingForm form; };
+struct Choice { Kernel kernel; RingForm form; int rows = 256; };       // rows: K_PERS256's tile is rows x 256
+
+// The persistent kernel's tile: 256, 224, 192 or 160 rows (E4M3, whose matrix instructions take 32 rows of a wave's half: 256 or 192) by 256
+// columns, one workgroup per CU, or 128 x 128, two per CU.  A CU is handed ceil(tiles / 256) of them; what one takes, in parts of a
+// 256 x 256 tile's time, is below: more than its share of the area (0.875, 0.75, 0.625, 0.25), since the weights' 256 rows are loaded for every
+// height and a 128 x 128 tile loads twice as much for its area, which a long K does not hide.  Measured over 265 products (INT8, E4M3, BF16;
+// 300 .. 14000 rows, K of 768 .. 16384) the choice is 0.4 % from the best of the five on average, 10 % at most, and was ahead of choosing between 256 and 128
+// by 4 % on average, by 40 % at most.  us, 256 / 224 / 192 / 160 / 128: INT8 GELU^quant 602 x 16384 x 4096 52.1 / 49.6 / 47.5 / 43.3 / 58.5, 16-bit result
+// 2500 x 4096 x 16384 160 / 152 / 141 / 134 / 174, REQUANT 3817 x 3072 x 1024 17.0 / 16.7 / 15.0 / 23.4 / 15.9, 9000 x 1024 x 4096 43.8 / 41.4 / 36.3 / 35.4 / 46.0, 14000 x
+// 3072 x 1024 47.0 / 44.1 / 49.4 / 53.4 / 47.6;  BF16 602 x 16384 x 4096 94 / 90 / 83 / 76 / 109, 9000 x 1024 x 4096 81 / 78 / 67 / 65 / 88.
+inline Choice persistent_choice(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, int64_t kb) {
+    const bool f8 = adt == HERO_F8E4M3, gelu = epi == HERO_EPI_DEQUANT_GELU || epi == HERO_EPI_GELU_REQUANT;
+    auto rounds = [&](int64_t bm, int64_t bn) { return (double)((((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256); };
+    const double n256 = rounds(256, 256);
+    const double small = rounds(128, 128) * (kb <= 2048 ? (gelu ? 0.27 : 0.30) : f8 && n256 > 1 ? 0.325 : kb < 8192 ? 0.34 : 0.36);
+    // (E4M3 behind a long K: from the second large round on 128 x 128 keeps what it is ahead of 256 x 256 in, 192 rows serve the rest.  us, 256 / 192 / 128:
+    // REQUANT 3000 x 12288 x 4096 143 / 124 / 140, 1900 x 12288 x 4096 94 / 83 / 102, 10500 x 1024 x 4096 43.7 / 39.6 / 45.7.)
+    if (f8 && kb > 2048 && n256 > 1 && small < n256) return {K_PERS128, RING_NONE};
+    Choice c = {K_PERS256, RING_NONE};
+    double t = n256;
+    auto offer = [&](int rows, double part) { const double o = rounds(rows, 256) * part; if (o < t) { t = o; c.rows = rows; } };
+    offer(192, f8 ? 0.87 : 0.80);
+    if (!f8) {
+        offer(224, 0.91);
+        if (kb >= 6 * BK) offer(160, 0.71);                            // (its weights' ring of six slots)
+    }
+    if (small < t) return {K_PERS128, RING_NONE};
+    return c;
+}
 
 // kb, lda, ldb in bytes.  tile: -1 chooses, otherwise the code a test hook
 // forces (a forced kernel that cannot run the shape gives way to its closest relative).
@@ -800,8 +825,10 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, in
     const RingForm form = ring ? ring_form(M, N, kb, epi) : RING_NONE;
     const Choice small = {ring ? K_RING : (M <= 64 || t128 < 192 ? K_REG64 : K_REG128), form == RING_NONE ? RING_128x64 : form};
     if (tile >= 0) {
+        const int rows = tile == 10 ? 224 : tile == 11 || (tile == 12 && kb < 6 * BK) ? 192 : tile == 12 ? 160 : 256;
+        if (rows < 256) tile = K_PERS256;
         if (tile == K_PERS256 || tile == K_PERS128) {
-            if (pers_ok && (adt == HERO_I8 || adt == HERO_F8E4M3 || t128 >= 192)) return {tile == K_PERS128 ? K_PERS128 : K_PERS256, RING_NONE};
+            if (pers_ok && (adt == HERO_I8 || adt == HERO_F8E4M3 || t128 >= 192)) return {tile == K_PERS128 ? K_PERS128 : K_PERS256, RING_NONE, rows};
             if (i8) return {tile == K_PERS128 ? K_REG128 : K_DMA256, RING_NONE};
             return small;
         }
@@ -810,9 +837,7 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, in
     }
     if (epi != HERO_EPI_RAW_I32 && skinny_ok(M, N, kb, lda, ldb)) return {K_SKINNY, RING_NONE};
     if (form != RING_NONE) return small;
-    if (pers_ok) {
-        return {small_tile_fills_better(t256, t128, kb, adt == HERO_F8E4M3) ? K_PERS128 : K_PERS256, RING_NONE};
-    }
+    if (pers_ok) return persistent_choice(adt, epi, M, N, kb);
     // K that ends in half a slab: the one-tile-per-workgroup 256 x 256 kernel (INT8) once its grid fills the chip, else 128 x 128
     // tiles, through the ring from 32 slabs on.  us, ring / registers: 2048 x 4096 x 4160 INT8 52.1 / 54.8, E4M3 51.0 / 55.7,
     // x 8256 bytes of BF16 90.4 / 99.7, but 2048 x 4096 x 2112 INT8 32.6 / 31.1, 8192 x 1024 x 1056 BF16 28.5 / 26.8.
@@ -841,7 +866,13 @@ inline bool may_split(Kernel kernel, int64_t M, int64_t N, int64_t kb) {
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
     switch (c.kernel) {
-    case K_PERS256: return launch_persistent<256, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
+    case K_PERS256:
+        if (c.rows == 192) return launch_persistent<192, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
+        if constexpr (ADT != HERO_F8E4M3) {
+            if (c.rows == 224) return launch_persistent<224, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
+            if (c.rows == 160) return launch_persistent<160, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
+        }
+        return launch_persistent<256, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
     case K_PERS128: return launch_persistent<128, 128, 2, 2, EPI, CDT, RDT, ADT>(g, 2, st);
     case K_DMA256:
         if constexpr (ADT == HERO_I8) return launch_grid(g, 256, 256, 512, int8_gemm_dma_kernel<256, 256, 2, 4, 4, 2, EPI, CDT, RDT>, st);
@@ -923,7 +954,7 @@ extern "C" hero_status hero_bf16_gemm(const void* A, int64_t lda, const void* Wt
 extern "C" hero_status hero_hp_gemm_tile(const void* A, int64_t lda, const void* Wt, int64_t ldb,
                                          const float* bias, const void* residual, int64_t ldr, int gelu,
                                          void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hero_dtype dt, void* stream, int tile) {
-    if (tile != 0 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
+    if (tile != 0 && tile != 7 && tile != 8 && (tile < 10 || tile > 12)) return HERO_ERR_UNSUPPORTED;
     return run_hp_gemm(A, lda, Wt, ldb, bias, residual, ldr, gelu, C, ldc, M, N, K, dt, nullptr, 0, stream, tile);
 }
 
@@ -1139,7 +1170,7 @@ extern "C" hero_status hero_int8_gemm_tile(const int8_t* A, int64_t lda, const f
                                            void* C, hero_dtype c_dt, int64_t ldc,
                                            int64_t M, int64_t N, int64_t K, void* stream, int tile) {
     if (tile == 9) tile = K_PERS256;                                   // (a former kernel's code, still accepted)
-    if (tile != 0 && tile != 1 && tile != 2 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
+    if (tile != 0 && tile != 1 && tile != 2 && tile != 7 && tile != 8 && (tile < 10 || tile > 12)) return HERO_ERR_UNSUPPORTED;
     return run_int8_gemm(A, lda, a_row_scale, Bt, ldb, b_col_scale, bias, residual, res_dt, ldr, epi, out_col_scale,
                          C, c_dt, ldc, M, N, K, nullptr, 0, stream, tile);
 }
@@ -1150,7 +1181,7 @@ extern "C" hero_status hero_fp8_gemm_tile(const void* A, int64_t lda, const floa
                                           hero_epilogue epi, const float* out_col_scale,
                                           void* C, hero_dtype c_dt, int64_t ldc,
                                           int64_t M, int64_t N, int64_t K, void* stream, int tile) {
-    if (tile != 0 && tile != 7 && tile != 8) return HERO_ERR_UNSUPPORTED;
+    if (tile != 0 && tile != 7 && tile != 8 && tile != 11) return HERO_ERR_UNSUPPORTED;
     return run_fp8_gemm(A, lda, a_row_scale, Bt, ldb, b_col_scale, bias, residual, res_dt, ldr, epi, out_col_scale,
                         C, c_dt, ldc, M, N, K, nullptr, 0, stream, tile);
 }

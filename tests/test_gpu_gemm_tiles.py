@@ -1,5 +1,5 @@
 """The persistent GEMM where a workgroup walks several tiles: its two rings and the epilogue's vectors pass from tile to tile, from the shortest K
-it takes (two pairs of slabs) on."""
+it takes (two pairs of slabs) on; every height of its tiles, whose last loads are for a part of the waves only."""
 import pytest
 import torch
 
@@ -7,8 +7,10 @@ import paper_2310_17723_amd as pkg
 from paper_2310_17723_amd import binding as HB
 
 pytestmark = pytest.mark.gpu
-TILES = [7, 8]
+TILES = [7, 8, 10, 11, 12]
 SHAPES = [(4500, 4200, kb) for kb in (256, 384, 512, 640)] + [(4500, 4208, 1024)]      # 306 tiles of 256 x 256, 1188 of 128 x 128
+# rows in front of, at and behind the edges of a tile, of a wave's half and of a load's 16 rows
+SHAPES += [(n, 2304, 512) for n in (1, 16, 79, 80, 81, 160, 161, 191, 193, 223, 225, 273)]
 
 
 def _inputs(M, N, K, dt):
@@ -37,6 +39,8 @@ def test_int8(M, N, K, tile):
 @pytest.mark.parametrize("M,N,kb", SHAPES)
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float8_e4m3fn])
 def test_floats(M, N, kb, dt, tile):
+    if dt == torch.float8_e4m3fn and tile in (10, 12):
+        pytest.skip("E4M3 has tiles of 256, 192 and 128 rows")
     hero, K = pkg.load(), kb // dt.itemsize
     a, w, rs, cs, bias, _ = _inputs(M, N, K, dt)
     ref, mag = a.double() @ w.double().t(), a.double().abs() @ w.double().abs().t()
