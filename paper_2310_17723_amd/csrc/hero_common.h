@@ -47,6 +47,7 @@ hero_status hero_fp8_gemm_prefetching(const void* A, int64_t lda, const float* a
 // scratch for the K split of an E4M3 product (0: it does not split); the 16-bit product with scratch for the K split of a skinny
 // or middling problem, and that scratch's size
 size_t hero_int8_gemm_scratch_needed(int64_t M, int64_t N, int64_t K);     // INT8: 0 where the split is not taken either
+size_t hero_int8_gemm_split_bytes(int64_t M, int64_t N, int64_t K);        // INT8: what the split of a middling problem takes too
 size_t hero_fp8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 size_t hero_hp_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t ldb,

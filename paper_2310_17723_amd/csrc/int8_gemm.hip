@@ -311,21 +311,21 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void int8_gemm_dma_kernel(GemmA
 // =====================================================================================
 // How many of a wave's direct loads may be out when the barrier of an iteration publishes the next slab: those issued behind the ones
 // that bring it.  la, lb: loads of a pair of A, B.  Times are iterations before this one (0); a ring of n slots is given a pair for the slabs
-// n - 1 and n ahead in odd iterations (n even) or even ones (n odd), B before A.  Behind an odd iteration the pair's first slab is
+// n - 1 and n ahead in odd iterations (n even) or even ones (n odd), A before B.  Behind an odd iteration the pair's first slab is
 // needed, whose loads alternate with the second one's, so that the very last may be out as well.
 constexpr int pair_loads_behind(bool odd, int na, int nb, int la, int lb) {
     const int first = odd ? 2 : 1;
-    const int last = 2 * (first - na) + 1 > 2 * (first - nb) ? 2 * (first - na) + 1 : 2 * (first - nb);     // 2 * time (+ 1: A)
+    const int last = 2 * (first - nb) + 1 > 2 * (first - na) ? 2 * (first - nb) + 1 : 2 * (first - na);     // 2 * time (+ 1: B)
     int c = odd ? 1 : 0;
     for (int t = -6; t < 0; ++t) {
         const bool t_odd = ((t + (odd ? 1 : 0)) & 1) != 0;
-        if ((nb % 2 == 0) == t_odd && 2 * t > last) c += lb;
-        if ((na % 2 == 0) == t_odd && 2 * t + 1 > last) c += la;
+        if ((nb % 2 == 0) == t_odd && 2 * t + 1 > last) c += lb;
+        if ((na % 2 == 0) == t_odd && 2 * t > last) c += la;
     }
     return c;
 }
 
-template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT = HERO_I8>
+template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT = HERO_I8, bool PART = false>
 __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(GemmArgs g) {
     constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
     constexpr bool WIDE = ADT == HERO_F8E4M3;                       // 32 x 32 tiles; INT8 and 16 bits: 16 x 16 (mfma16_step)
@@ -338,6 +338,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     constexpr bool A_EVEN = A_LAST == NWAVE;
     constexpr int NM = TM * TN, NFR = TM + TN;
     static_assert(NSA >= 4 && NSA <= 6 && NSB >= 4 && NSB <= 6 && BM % (16 * WM) == 0 && BN % (16 * NWAVE) == 0 && (!WIDE || (NFR <= 2 * NM && BM % (32 * WM) == 0)), "rings / interleave plan");
+    static_assert(!PART || (EPI == HERO_EPI_RAW_I32 && !WIDE), "a part writes raw accumulators");
     constexpr int A_RING = NSA * A_BYTES, B_RING = NSB * B_BYTES, RING = A_RING + B_RING;
     constexpr int SVF = 4 * BN;                                  // floats per vector set: column scale, bias, S_a, row scale
     static_assert(BM <= BN, "the row-scale vector shares the column vectors' length");
@@ -349,10 +350,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int xcd = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD, nslot = gridDim.x / NUM_XCD;
-    const int seq_end = min((xcd + 1) * g.per_xcd, g.ntm * g.ntn);
+    const int ntiles = g.ntm * g.ntn;
+    const int seq_end = min((xcd + 1) * g.per_xcd, PART ? ntiles * g.ksplit : ntiles);
     int seq = xcd * g.per_xcd + slot;                            // this workgroup's tiles: seq, seq + nslot, ...
     if (seq >= seq_end) return;
-    const int KT = g.K / BK;
+    // PART: sequence number s is tile s % ntiles of K range s / ntiles (g.kslabs pairs of slabs, the last range may be shorter)
+    auto range_slabs = [&](int s) { return PART ? 2 * min(g.kslabs, g.K / (2 * BK) - s / ntiles * g.kslabs) : g.K / BK; };
     const bool has_last = A_EVEN || wave < A_LAST;
     const bool has_rs = g.a_row_scale != nullptr, has_bias = g.bias != nullptr;
     if (!has_bias)                                               // the bias vectors are read by the epilogue either way
@@ -371,20 +374,23 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     const uint32_t svbase = __builtin_amdgcn_readfirstlane(lds_offset(sv0));
 
     // ---- the two issue streams, of A and of B: the tile / slab their next direct loads belong to
-    int aseq = seq, akt = 0, bseq = seq, bkt = 0, bpar = 0;
+    int aseq = seq, akt = 0, aKT, bseq = seq, bkt = 0, bKT, bpar = 0;
     const int8_t* ia; const int8_t* ib;                          // wave-uniform: tile base + slab offset
     uint32_t oa[A_UNITS], ob[B_UNITS];
     int m0b = 0, n0b = 0;                                        // origin of B's tile
+    auto range_start = [&](int s) { return PART ? (int64_t)(s / ntiles) * g.kslabs * (2 * BK) : (int64_t)0; };
     auto set_tile_a = [&](int s) {
         int m0, n0;
-        tile_from_seq<BM, BN>(g, s, m0, n0);
-        ia = g.A + (int64_t)m0 * g.lda;
+        tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0, n0);
+        aKT = range_slabs(s);
+        ia = g.A + (int64_t)m0 * g.lda + range_start(s);
 #pragma unroll
         for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0) * (uint32_t)g.lda + lc;
     };
     auto set_tile_b = [&](int s) {
-        tile_from_seq<BM, BN>(g, s, m0b, n0b);
-        ib = g.Bt + (int64_t)n0b * g.ldb;
+        tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0b, n0b);
+        bKT = range_slabs(s);
+        ib = g.Bt + (int64_t)n0b * g.ldb + range_start(s);
 #pragma unroll
         for (int u = 0; u < B_UNITS; ++u) ob[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.N - 1 - n0b) * (uint32_t)g.ldb + lcb;
     };
@@ -428,20 +434,20 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     auto advance_a = [&]() {                                     // next pair; past the last tile the last pair repeats (never read)
         wra = next_slot(next_slot(wra, A_BYTES, A_RING), A_BYTES, A_RING);
         akt += 2;
-        if (akt < KT) { ia += 2 * BK; return; }
+        if (akt < aKT) { ia += 2 * BK; return; }
         if (aseq + nslot < seq_end) {
             aseq += nslot; akt = 0;
             set_tile_a(aseq);
-        } else akt = KT - 2;
+        } else akt = aKT - 2;
     };
     auto advance_b = [&]() {
         wrb = next_slot(next_slot(wrb, B_BYTES, B_RING), B_BYTES, B_RING);
         bkt += 2;
-        if (bkt < KT) { ib += 2 * BK; return; }
+        if (bkt < bKT) { ib += 2 * BK; return; }
         if (bseq + nslot < seq_end) {
             bseq += nslot; bkt = 0; bpar ^= 1;
             set_tile_b(bseq);
-        } else bkt = KT - 2;
+        } else bkt = bKT - 2;
     };
 
     // fragment offsets inside a slot (row rr, k-step ks, half hh): rr*64 + ((2ks+hh) ^ ((rr>>2)&3))*16
@@ -467,15 +473,15 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
 #pragma unroll
     for (int t = -5; t < 0; ++t) {
         const int pb = t + NSB - 1, pa = t + NSA - 1;              // twice the pair whose turn it is
-        if (pb >= 0 && pb % 2 == 0) {
-#pragma unroll
-            for (int u = 0; u < B_UNITS; ++u) issue_b(u);
-            advance_b();
-        }
         if (pa >= 0 && pa % 2 == 0) {
 #pragma unroll
             for (int u = 0; u < A_UNITS; ++u) issue_a(u);
             advance_a();
+        }
+        if (pb >= 0 && pb % 2 == 0) {
+#pragma unroll
+            for (int u = 0; u < B_UNITS; ++u) issue_b(u);
+            advance_b();
         }
     }
     if (has_last) __builtin_amdgcn_s_waitcnt(vmcnt_imm(pair_loads_behind(false, NSA, NSB, LA, LB) + 1));
@@ -485,7 +491,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     int rda = 0, rdb = 0, par = 0;                                  // LDS offsets of the current slab
     for (;;) {
         int m0, n0;
-        tile_from_seq<BM, BN>(g, seq, m0, n0);
+        tile_from_seq<BM, BN>(g, PART ? seq % ntiles : seq, m0, n0);
+        const int KT = range_slabs(seq);
         constexpr int CI = WIDE ? TM : TI, CJ = WIDE ? TN : TJ, CR = WIDE ? 16 : 4;
         ACC acc[CI][CJ];
 #pragma unroll
@@ -509,18 +516,22 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         }
 
         // One slab per iteration with the barrier in the middle (see int8_gemm_dma_kernel).  Behind the barrier of iteration i every
-        // wave has read the last fragment of slab i (lgkmcnt(0) in front of it), so both its slots are free: a ring of five slots has
+        // wave has read the last fragment of slab i, so both its slots are free: a ring of five slots has
         // one to spare and takes the pair (i + 4, i + 5) in even iterations, rings of four and six wait for the odd one
         // and take (i + 3, i + 4), (i + 5, i + 6).  The pairs may already belong to the next tile.
         auto iteration = [&](auto ODD) {
             constexpr bool odd = decltype(ODD)::value;
             constexpr bool put_a = odd == (NSA % 2 == 0), put_b = odd == (NSB % 2 == 0);
-            constexpr int NU = (put_a ? A_UNITS : 0) + (put_b ? B_UNITS : 0);      // units to issue: B's, then A's
+            constexpr int NU = (put_a ? A_UNITS : 0) + (put_b ? B_UNITS : 0);      // units to issue: A's, then B's
             const int nda = rda + A_BYTES == A_RING ? 0 : rda + A_BYTES, ndb = rdb + B_BYTES == B_RING ? 0 : rdb + B_BYTES;
-            auto issue_unit = [&](int u) { if (put_b && u < B_UNITS) issue_b(u); else issue_a(u - (put_b ? B_UNITS : 0)); };
-            auto wait_next_slab = [&]() {                             // slab i + 1 has landed (mine), slab i has been read
-                if (has_last) __builtin_amdgcn_s_waitcnt(vmcnt_lds_imm(pair_loads_behind(odd, NSA, NSB, LA, LB)));
-                else __builtin_amdgcn_s_waitcnt(vmcnt_lds_imm(pair_loads_behind(odd, NSA, NSB, LA - 2, LB)));
+            auto issue_unit = [&](int u) { if (put_a && u < A_UNITS) issue_a(u); else issue_b(u - (put_a ? A_UNITS : 0)); };
+            // slab i + 1 has landed (mine); what the loads behind the barrier overwrite has been read.  (16 x 16 tiles: the last of the weights'
+            // fragments was an operand in front of the barrier, a row's may still be under way.)
+            auto wait_next_slab = [&]() {
+                constexpr int all = pair_loads_behind(odd, NSA, NSB, LA, LB), part = pair_loads_behind(odd, NSA, NSB, LA - 2, LB);
+                constexpr bool lds = put_a || WIDE;
+                if (has_last) __builtin_amdgcn_s_waitcnt(lds ? vmcnt_lds_imm(all) : vmcnt_imm(all));
+                else __builtin_amdgcn_s_waitcnt(lds ? vmcnt_lds_imm(part) : vmcnt_imm(part));
             };
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (WIDE) {
@@ -615,7 +626,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         for (int i = 0; i < CI; ++i)
             rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * (BM / WM) + i * (WIDE ? 32 : 16) + (WIDE ? ml : r16)] : 1.0f;
         if constexpr (WIDE) epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, true, UNIT>(g, acc, sv, rsr, m0, n0, tid);
-        else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(g, acc, sv, rsr, m0, n0, tid);
+        else if constexpr (PART) {
+            GemmArgs gp = g;
+            gp.C = (int32_t*)g.C + (int64_t)(seq / ntiles) * g.M * g.ldc;
+            epilogue_rows16<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(gp, acc, sv, rsr, m0, n0, tid);
+        } else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(g, acc, sv, rsr, m0, n0, tid);
         seq += nslot;
         par ^= 1;
         if (seq >= seq_end) break;
@@ -632,7 +647,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
 // kernel measured 4x slower than no split at all).  Measured with cold weights, one pass -> split: INT8 64 x 4096 x 16384
 // 23.6 -> 19.7 us, 3 rows 19.7 -> 17.6, 100 rows 26.3 -> 24.1; BF16 64 rows 44.4 -> 35.6, 3 rows 36.2 -> 30.5; with
 // K = 4096 the second launch costs more than the split gives.
-struct SplitK { int ksplit, kslabs; int64_t ldp; size_t bytes; };      // ranges, 128-byte slabs of each, the planes' stride and size
+struct SplitK { int ksplit, kslabs; int64_t ldp; size_t bytes; int rows = 0; };      // ranges, 128-byte slabs of each, the planes' stride and size; rows: below
 inline SplitK split_ranges(int64_t M, int64_t N, int64_t kb, int64_t want) {
     const int64_t slabs = (kb + 2 * BK - 1) / (2 * BK), kslabs = (slabs + want - 1) / want;
     SplitK p;
@@ -649,17 +664,45 @@ inline SplitK splitk_plan(int64_t M, int64_t N, int64_t kb) {           // kb: b
     return split_ranges(M, N, kb, want < 16 ? want : 16);
 }
 
-// A middling 16-bit product with a very long K (FC2 of a prompt chunk, 256 slabs or more): one round of 128 x 128 tiles leaves
-// a part of the CUs without work, and their 32 x 64 wave tiles are bound by LDS reads.  Tiles of 128 x 256 (64 x 128 per wave:
-// 0.56 of the LDS bytes per multiply-add) times as many K ranges as fill the 256 CUs, at least three.  Measured, BF16,
-// N = 4096, K = 16384, best form in one pass -> split: M = 150 67 -> 52 us, 300 83 -> 69, 512 94 -> 87, 602 131 -> 108; with
-// half the slabs (INT8 codes) the planes cost what the split gives (300 rows 44.7 -> 43.3, 400 47 -> 51).
-inline SplitK mid_split_plan(int64_t M, int64_t N, int64_t kb) {
-    const int64_t tiles = ((M + 127) / 128) * ((N + 255) / 256);
-    if (M <= 128 || kb < 256 * 2 * BK || tiles <= 0 || tiles * 3 > 256) return SplitK{1, 0, 0, 0};
-    return split_ranges(M, N, kb, 256 / tiles < 8 ? 256 / tiles : 8);
+// A middling product with a very long K (FC2 of a prompt chunk, 16 KB and more): one round of 128 x 128 tiles leaves a part of the CUs
+// without work, and so do few large ones.  Tiles of `rows` x 256 of the persistent kernel, or 16-bit ones of 128 x 256 of the ring's (rows 0; 256 slabs or
+// more), times as many K ranges as fill the 256 CUs, where an estimate in us says so: a range's share of a 256 x 256 tile's time over the
+// whole K, 9.4 ns per byte of it, plus the planes' way out and back, 0.9 us per MB, and 6 us for the second launch and the ranges' start, against 128 x 128
+// tiles in one round (0.43) or two (0.8), or large ones.  Measured, N = 4096, K = 16384, best form in one pass -> split: BF16 M = 150 67 -> 52 us (ring), 300 83 -> 69
+// (ring), 602 128 -> 93 (ring 99), 700 124 -> 108, 900 135 -> 131, 1100 236 -> 153, 1400 231 -> 180;  INT8 602 68 -> 63, 1100 119 -> 93, 1400
+// 118 -> 112, but 900 74 -> 83;  a quarter of that K: nowhere ahead (INT8 602 20.8 -> 38, BF16 1100 64 -> 60).
+inline SplitK mid_split_plan(int64_t M, int64_t N, int64_t kb, bool hp) {
+    SplitK best{1, 0, 0, 0};
+    if (M <= 128 || N <= 0 || kb % BK != 0) return best;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const int64_t t128 = tiles(128, 256);
+    const double whole = 9.4e-3 * (double)kb;
+    double t = 0;
+    auto offer = [&](int rows, double part) {
+        const int64_t n = tiles(rows ? rows : 128, 256);
+        if (n > 128) return;
+        SplitK p = split_ranges(M, N, kb, 256 / n < 8 ? 256 / n : 8);
+        p.rows = rows;
+        if (p.ksplit < 2 || (rows && kb / (2 * BK) - (int64_t)(p.ksplit - 1) * p.kslabs < 3)) return;      // (the rings: six slabs or more)
+        const double e = part * whole * (double)p.kslabs * (2 * BK) / (double)kb + 0.9e-6 * (double)p.bytes + 6;
+        if (best.ksplit == 1 || e < t) { t = e; best = p; }
+    };
+    const bool ring = hp && kb >= 256 * 2 * BK && t128 * 3 <= 256;
+    if (ring) offer(0, 0.66);
+    const RingForm form = ring_form(M, N, kb, HERO_EPI_DEQUANT);
+    if ((form != RING_NONE && form != RING_128x128) || kb < 128 * 2 * BK || kb % (2 * BK) != 0) return best;
+    const int64_t small = tiles(128, 128);
+    auto rounds = [&](int64_t bm) { return (double)((tiles(bm, 256) + 255) / 256); };
+    double one = small <= 256 ? 0.43 : small <= 512 ? 0.8 : 1e9;
+    for (const double o : {rounds(256), 0.91 * rounds(224), 0.80 * rounds(192), 0.71 * rounds(160)}) one = o < one ? o : one;
+    offer(160, 0.70);
+    offer(192, 0.82);
+    offer(224, 0.95);
+    offer(256, 1.00);
+    if (!ring && t > 0.93 * one * whole) return SplitK{1, 0, 0, 0};
+    return best;
 }
-inline SplitK hp_split_plan(int64_t M, int64_t N, int64_t kb) { return M <= 128 ? splitk_plan(M, N, kb) : mid_split_plan(M, N, kb); }
+inline SplitK split_plan(bool hp, int64_t M, int64_t N, int64_t kb) { return M <= 128 ? splitk_plan(M, N, kb) : mid_split_plan(M, N, kb, hp); }
 
 // Pass 2 of split-K: one thread per 4 consecutive columns of a row.
 // Integer sums are exact in any order; fp32 partial sums (E4M3 and 16-bit operands) are added in the fixed order of the
@@ -725,18 +768,38 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const in
     }
 }
 
+// Slots of the two rings, A and B, for a tile of BM x 256: what 160 KB hold.  Both operands in the same
+// iteration lose what the slots give: 2500 x 4096 x 4096 in tiles of 192 rows 48.0 us with five and five, 42.9 with four and five.
+template <int BM> struct PersRing { static constexpr int A = BM == 160 ? 5 : 4, B = BM == 160 ? 6 : 5; };
+// Pass 1 by the persistent kernel: g.ksplit ranges of g.kslabs slabs (of 128 bytes) into planes of g.C, tiles of BM x 256.
+template <int BM, int ADT>
+hero_status launch_persistent_part(GemmArgs g, hipStream_t st) {
+    g.ntm = (g.M + BM - 1) / BM; g.ntn = (g.N + 255) / 256;
+    g.per_xcd = (g.ntm * g.ntn * g.ksplit + NUM_XCD - 1) / NUM_XCD;
+    const int nslot = g.per_xcd < 32 ? g.per_xcd : 32;
+    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, 256, 2, 4, PersRing<BM>::A, PersRing<BM>::B, HERO_EPI_RAW_I32, HERO_I32, -1, ADT, true>),
+                       dim3((unsigned)(nslot * NUM_XCD)), dim3(512), 0, st, g);
+    return hero_launch_status();
+}
+
 // Runs the split where it is one (true: *status is the outcome).
 template <int EPI, int CDT, int RDT, int ADT>
 bool launch_splitk(const GemmArgs& g, void* ws, size_t ws_bytes, hipStream_t st, hero_status* status) {
     if (!ws || !ring_ok(g.lda, g.ldb)) return false;
-    const SplitK p = ADT == HERO_BF16 || ADT == HERO_F16 ? hp_split_plan(g.M, g.N, g.K) : splitk_plan(g.M, g.N, g.K);
+    const SplitK p = ADT == HERO_F8E4M3 ? splitk_plan(g.M, g.N, g.K) : split_plan(ADT != HERO_I8, g.M, g.N, g.K);
     if (p.ksplit <= 1 || ws_bytes < p.bytes) return false;
     const RingForm f = g.M > 128 ? RING_128x256 : (g.M <= 64 ? RING_64x64_K2 : RING_128x64_K2);     // skinny: 64 columns, one workgroup per CU
     GemmArgs g1 = g;                                                   // pass 1: raw partial planes in the scratch
     g1.a_row_scale = nullptr; g1.b_col_scale = nullptr; g1.bias = nullptr; g1.residual = nullptr; g1.out_col_scale = nullptr;
     g1.C = ws; g1.ldc = p.ldp;
     g1.kslabs = p.kslabs; g1.ksplit = p.ksplit;
-    *status = launch_ring_part<ADT>(g1, f, st);
+    if constexpr (ADT != HERO_F8E4M3) {
+        if (p.rows == 160) *status = launch_persistent_part<160, ADT>(g1, st);
+        else if (p.rows == 192) *status = launch_persistent_part<192, ADT>(g1, st);
+        else if (p.rows == 224) *status = launch_persistent_part<224, ADT>(g1, st);
+        else if (p.rows == 256) *status = launch_persistent_part<256, ADT>(g1, st);
+    }
+    if (!p.rows) *status = launch_ring_part<ADT>(g1, f, st);
     if (*status != HERO_OK) return true;
     GemmArgs g2 = g;                                                   // pass 2: sum of the planes + epilogue
     g2.ksplit = p.ksplit;
@@ -765,10 +828,7 @@ inline void set_prefetch(GemmArgs& g, const void* prefetch, size_t prefetch_byte
     }
 }
 
-// Slots of the two rings, A and B, for a tile of BM rows: what 160 KB hold (128 x 128: two workgroups per CU).  Both operands in the same
-// iteration lose what the slots give: 2500 x 4096 x 4096 in tiles of 192 rows 48.0 us with five and five, 42.9 with four and five.
-template <int BM> struct PersRing { static constexpr int A = BM == 160 ? 5 : 4, B = BM == 160 ? 6 : 5; };
-template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT, int ADT>
+template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT>
 hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) {
     GemmArgs gp = g;
     gp.ntm = (g.M + BM - 1) / BM; gp.ntn = (g.N + BN - 1) / BN;
@@ -778,7 +838,7 @@ hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) 
     share_prefetch(gp, tiles, WM * WN * 64);
     const int cap = 32 * wg_per_cu;                                   // 32 CUs per XCD
     const int nslot = gp.per_xcd < cap ? gp.per_xcd : cap;
-    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, PersRing<BM>::A, PersRing<BM>::B, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
+    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, NSA, NSB, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
     return hero_launch_status();
 }
 
@@ -863,17 +923,27 @@ inline bool may_split(Kernel kernel, int64_t M, int64_t N, int64_t kb) {
     return split < (N <= 2048 ? 1.07 : 1.0) * whole;
 }
 
+template <int BM, int EPI, int CDT, int RDT, int ADT>
+hero_status launch_persistent_wide(const GemmArgs& g, hipStream_t st) {
+    return launch_persistent<BM, 256, 2, 4, PersRing<BM>::A, PersRing<BM>::B, EPI, CDT, RDT, ADT>(g, 1, st);
+}
+
 template <int ADT, int EPI, int CDT, int RDT>
 hero_status launch_choice(const GemmArgs& g, Choice c, hipStream_t st) {
     switch (c.kernel) {
     case K_PERS256:
-        if (c.rows == 192) return launch_persistent<192, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
+        if (c.rows == 192) return launch_persistent_wide<192, EPI, CDT, RDT, ADT>(g, st);
         if constexpr (ADT != HERO_F8E4M3) {
-            if (c.rows == 224) return launch_persistent<224, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
-            if (c.rows == 160) return launch_persistent<160, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
+            if (c.rows == 224) return launch_persistent_wide<224, EPI, CDT, RDT, ADT>(g, st);
+            if (c.rows == 160) return launch_persistent_wide<160, EPI, CDT, RDT, ADT>(g, st);
         }
-        return launch_persistent<256, 256, 2, 4, EPI, CDT, RDT, ADT>(g, 1, st);
-    case K_PERS128: return launch_persistent<128, 128, 2, 2, EPI, CDT, RDT, ADT>(g, 2, st);
+        return launch_persistent_wide<256, EPI, CDT, RDT, ADT>(g, st);
+    // While a workgroup has one tile, four slots each: it waits for its weights as long either way, and both operands in one go (the
+    // activations first: the other order +3 to 9 %) take fewer requests at a time.  us, four and four / five and four: BF16 301 x 12288 x 4096 62.0 /
+    // 65.0, 1100 x 4096 x 4096 59.1 / 62.1, INT8 34.1 / 35.0, 32.2 / 32.3;  12500 x 4096 x 1024 BF16 118.4 / 112.7, INT8 73.0 / 69.4.
+    case K_PERS128:
+        if (((int64_t)(g.M + 127) / 128) * ((g.N + 127) / 128) <= 512) return launch_persistent<128, 128, 2, 2, 4, 4, EPI, CDT, RDT, ADT>(g, 2, st);
+        return launch_persistent<128, 128, 2, 2, 5, 4, EPI, CDT, RDT, ADT>(g, 2, st);
     case K_DMA256:
         if constexpr (ADT == HERO_I8) return launch_grid(g, 256, 256, 512, int8_gemm_dma_kernel<256, 256, 2, 4, 4, 2, EPI, CDT, RDT>, st);
         else return HERO_ERR_UNSUPPORTED;
@@ -928,7 +998,7 @@ hero_status run_hp_gemm(const void* A, int64_t lda, const void* Wt, int64_t ldb,
 }
 }  // namespace
 
-size_t hero_hp_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) { return hp_split_plan(M, N, 2 * K).bytes; }
+size_t hero_hp_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) { return split_plan(true, M, N, 2 * K).bytes; }
 
 // hero_hp_gemm with scratch for the K split (hero_layer_fwd).  Not part of the C ABI.
 hero_status hero_hp_gemm_ws(const void* A, int64_t lda, const void* Wt, int64_t ldb,
@@ -1026,6 +1096,9 @@ extern "C" size_t hero_int8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K
     const int64_t kslabs = (kt + (want < 16 ? want : 16) - 1) / (want < 16 ? want : 16);
     return (size_t)((kt + kslabs - 1) / kslabs) * M * p.ldp * 4;
 }
+
+// What hero_layer_fwd offers an INT8 linear: as much as any split of it takes.
+size_t hero_int8_gemm_split_bytes(int64_t M, int64_t N, int64_t K) { return M <= 128 ? hero_int8_gemm_workspace_bytes(M, N, K) : split_plan(false, M, N, K).bytes; }
 
 // What hero_layer_fwd insists on for an INT8 linear (contiguous rows): nothing where no plane is written.
 size_t hero_int8_gemm_scratch_needed(int64_t M, int64_t N, int64_t K) {

@@ -41,7 +41,7 @@ Workspace plan(const hero_layer_desc* d, int64_t T) {
     w.a = take((size_t)T * d->f * e_a);
     w.x2 = take(pre ? 0 : (size_t)T * d->d * e_a);
     // split-K scratch of the skinny (decode) and long-K GEMMs, shared (stream order): the largest of the four shapes.  A call is
-    // refused only without what an INT8 linear splits into; what E4M3 or 16-bit linears can use beyond that is taken if it is there,
+    // refused only without what an INT8 linear of up to 128 rows splits into; what the others can use beyond that is taken if it is there,
     // and they run in one pass otherwise.  (It exists for bands of T only: a workspace sized for a larger T may not have it.)
     const int64_t D = d->d, F = d->f, nk[4][2] = {{3 * D, D}, {D, D}, {F, D}, {D, F}};
     const uint32_t bit[4] = {HERO_M_QKV, HERO_M_ATTN_OUT, HERO_M_FC1, HERO_M_FC2};
@@ -50,7 +50,7 @@ Workspace plan(const hero_layer_desc* d, int64_t T) {
     for (int l = 0; l < 4; ++l) {
         if (!fp8) {
             needed = std::max(needed, hero_int8_gemm_scratch_needed(T, nk[l][0], nk[l][1]));
-            any = std::max(any, hero_int8_gemm_workspace_bytes(T, nk[l][0], nk[l][1]));
+            any = std::max(any, hero_int8_gemm_split_bytes(T, nk[l][0], nk[l][1]));
         }
         if (fp8) any = std::max(any, hero_fp8_gemm_workspace_bytes(T, nk[l][0], nk[l][1]));
         else if (!(d->mode_mask & bit[l])) any = std::max(any, hero_hp_gemm_workspace_bytes(T, nk[l][0], nk[l][1]));

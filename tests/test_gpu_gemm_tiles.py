@@ -52,3 +52,39 @@ def test_floats(M, N, kb, dt, tile):
         ref = ref * s + bias.double()
         bound = (2.0 ** -12 + (K + 4) * 2.0 ** -24) * (mag * s + bias.double().abs())     # products kept to 13 bits of the largest of eight
     assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * 2.0 ** -8).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(1100, 4096, 16384), (1053, 4100, 16512)])
+def test_int8_k_split_of_a_middling_product(M, N, K):
+    """Two K ranges in tiles of 160 rows, the second one shorter: the sums are exact, through scratch that is dirty and no larger than it has to be."""
+    hero = pkg.load()
+    a, w, rs, cs, bias, _ = _inputs(M, N, K, torch.int8)
+    kw = dict(a_row_scale=rs, b_col_scale=cs / (90 * K ** 0.5), bias=bias, epi=HB.EPI_REQUANT, out_dtype=torch.int8)
+    ws = torch.full((2 * M * N * 4 + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    out = hero.hero_int8_gemm(a, w, workspace=ws[:-256], **kw)
+    assert torch.equal(out, hero.hero_int8_gemm(a, w, **kw))
+    assert not bool((ws[:4096] == 0xA5).all()) and bool((ws[-256:] == 0xA5).all())
+    assert torch.equal(hero.hero_int8_gemm(a, w, workspace=ws[:-256]), hero.hero_int8_gemm(a, w))
+
+
+@pytest.mark.parametrize("mode", [HB.MODE_M2, HB.MODE_M2 | HB.M_F16])
+def test_16_bit_k_split_of_a_middling_product(mode, monkeypatch):
+    """A chunk's FC2 in 16 bits, split where the workspace has room: the sums part by their fp32 order, a rounding at most behind them."""
+    import test_gpu_workspace as TW
+    monkeypatch.setattr(TW, "D", 4096)
+    monkeypatch.setattr(TW, "H", 32)
+    hero = pkg.load()
+    keep, W, desc = TW._layer(hero, mode, 8192, 5)
+    dt = torch.float16 if mode & HB.M_F16 else torch.bfloat16
+    keep["w_2_bf16"] = keep["w_2_bf16"].to(dt)
+    W = hero.layer_weights(keep, 2e-4, 1 / 255)
+    B, S = 2, 550
+    full = hero.hero_layer_workspace_bytes(desc, B, S)
+    h0 = torch.randn((B * S, 4096), device="cuda", generator=torch.Generator(device="cuda").manual_seed(6)).to(dt)
+    res = []
+    for nbytes in (full, full - 2 * B * S * 4096 * 4):               # two planes
+        h, ws = h0.clone(), torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+        hero.hero_layer_fwd(desc, W, B, S, ws, h=h)
+        res.append(h.float())
+    assert bool(torch.isfinite(res[0]).all())
+    assert float((res[0] - res[1]).norm() / res[0].norm()) <= 2.0 ** -8
