@@ -453,6 +453,9 @@ inline RingForm ring_form(int64_t M, int64_t N, int64_t kb, hero_epilogue epi) {
 inline bool skinny_ok(int64_t M, int64_t N, int64_t kb, int64_t lda_bytes, int64_t ldb_bytes, int64_t max_n = 12288) {
     return M <= 32 && N % 16 == 0 && N <= max_n && kb % (8 * 2 * BK) == 0 && N * kb >= (4 << 20) && ring_ok(lda_bytes, ldb_bytes);
 }
+// the persistent kernel (gemm_persistent.h): a tile of `rows` x 256 or, with 128, of 128 x 128; and a K split's planes
+template <int ADT, int EPI, int CDT, int RDT> hero_status launch_persistent_tile(const GemmArgs& g, int rows, hipStream_t st);
+template <int ADT> hero_status launch_persistent_part(const GemmArgs& g, int rows, hipStream_t st);
 hero_status launch_skinny(const GemmArgs& g, hero_dtype adt, hero_epilogue epi, hero_dtype c_dt, hipStream_t st);
 template <int ADT, int EPI, int CDT, int RDT, bool HALF> hero_status launch_ring_slabs(const GemmArgs& g, RingForm f, hipStream_t st);
 template <int ADT, int EPI, int CDT, int RDT>
