@@ -50,6 +50,14 @@ struct AttnArgs {
     const int8_t* kn; const int8_t* vn; int64_t nstride; int8_t* kc; int8_t* vc;
 };
 
+// the larger of lane l's and lane l ^ 32's value
+template <typename T>
+__device__ __forceinline__ T pair_max(T x) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return max(__builtin_bit_cast(T, r[0]), __builtin_bit_cast(T, r[1]));
+}
+
 // the output rows of a block of BQ padded queries: zeros
 template <int DH, int ODT>
 __device__ __forceinline__ void zero_rows(const AttnArgs& a, int b, int h, int q0, int threads) {
@@ -371,6 +379,10 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
     }
 
     // ---- pass 1: row max and row sum ------------------------------------------------------------
+    // One maximum per tile, the two lanes of a query exchange theirs by v_permlane32_swap.  us, an exchange through LDS every 32 keys -> this:
+    // 8 x 32 x 2048 x 128 causal 455 -> 435, E4M3 376 -> 342, 2 x 32 x 2048 without a mask 195 -> 183, 169 -> 159, 8 x 32 x 200 behind 1300 keys 84 -> 80, 68
+    // -> 63.5, 8 x 16 x 1000 x 64 74 -> 71, 63 -> 61.  (Maxima of a lane's own keys, joined behind the last tile: another 2 %, but their factors' errors
+    // showed where all probabilities are equal.)
     float m2 = -INFINITY, l = 0.0f;           // running max (log2 domain) and sum of 2^(a2 - m2), this lane's keys
     constexpr float FMASKED = -3.0e38f;       // E4M3 scores are floats: the mask value of that variant
     if (ntiles > 0) { load_k(0); store_k(0); }
@@ -380,35 +392,41 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
         if (tile + 1 < ntiles) load_k(tile + 1);
         const bool edge = (tile + 1) * BKV > nvis_min;
         auto pass1_tile = [&](auto EDGE) {
+            const int lim = nvis - (tile * BKV + hh * 4);                       // key visible iff 32s + 8g + t < lim
+            SACC acc[BKV / 32];
 #pragma unroll
             for (int s = 0; s < BKV / 32; ++s) {
-                SACC acc = scores(buf, s);
-                if constexpr (decltype(EDGE)::value) {
-                    const int lim = nvis - (tile * BKV + s * 32 + hh * 4);      // key visible iff 8g + t < lim
+                acc[s] = scores(buf, s);
+                if constexpr (decltype(EDGE)::value)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        if constexpr (F8) acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : FMASKED;
-                        else acc[r] = ((r >> 2) * 8 + (r & 3)) < lim ? acc[r] : MASKED;
+                        if constexpr (F8) acc[s][r] = s * 32 + (r >> 2) * 8 + (r & 3) < lim ? acc[s][r] : FMASKED;
+                        else acc[s][r] = s * 32 + (r >> 2) * 8 + (r & 3) < lim ? acc[s][r] : MASKED;
                     }
-                }
-                auto smax = acc[0];
+            }
+            auto smax = acc[0][0];
 #pragma unroll
-                for (int r = 1; r < 16; ++r) smax = max(smax, acc[r]);
-                smax = max(smax, __shfl_xor(smax, 32));
-                if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {          // same decision in both lanes of a query
-                    const float mn = fmaxf(m2, (float)smax * c2);
-                    float sum = 0.0f;
-                    const int lim = nvis - (tile * BKV + s * 32 + hh * 4);
+            for (int s = 0; s < BKV / 32; ++s)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) smax = max(smax, acc[s][r]);
+            smax = pair_max(smax);
+            if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {              // same decision in both lanes of a query
+                const float mn = fmaxf(m2, (float)smax * c2);
+                float sum = 0.0f;
+#pragma unroll
+                for (int s = 0; s < BKV / 32; ++s) {
+                    float part = 0.0f;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        float e = __builtin_amdgcn_exp2f(fmaf((float)acc[r], c2, -mn));
+                        float e = __builtin_amdgcn_exp2f(fmaf((float)acc[s][r], c2, -mn));
                         // (a hidden key counts for nothing at any scale of the scores, also where c2 brings the mask's value back into range)
-                        if constexpr (decltype(EDGE)::value) e = ((r >> 2) * 8 + (r & 3)) < lim ? e : 0.0f;
-                        sum += e;
+                        if constexpr (decltype(EDGE)::value) e = s * 32 + (r >> 2) * 8 + (r & 3) < lim ? e : 0.0f;
+                        part += e;
                     }
-                    l = fmaf(l, __builtin_amdgcn_exp2f(m2 - mn), sum);
-                    m2 = mn;
+                    sum += part;
                 }
+                l = fmaf(l, __builtin_amdgcn_exp2f(m2 - mn), sum);
+                m2 = mn;
             }
         };
         if (!wact) {} else if (edge) pass1_tile(std::true_type{}); else pass1_tile(std::false_type{});
@@ -816,8 +834,12 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
     using SACC = typename std::conditional<F8, v16f, v16i>::type;
     using ST = typename std::conditional<F8, float, int>::type;
     using V4 = typename std::conditional<F8, v4f, v4i>::type;
-    constexpr int SQ = 32, SK = 32, VLD = SK + 16, DS = DH / 32, VU = (SK / 4) * (DH / 4) / 64, TLD = 36;
-    __shared__ __attribute__((aligned(16))) int8_t pool[NW * DH * VLD > NW * SQ * TLD * 4 ? NW * DH * VLD : NW * SQ * TLD * 4];
+    constexpr int SQ = 32, SK = 32, VLD = SK + 16, DS = DH / 32, TLD = 36;
+    // V: a unit is 4 keys x CW channels; with 16 of them a load is 128 bits, and every 16 channels lie 32 bytes further on (the stores of eight
+    // units' same channel fall into different banks that way; GPT layer, 2 x 301 tokens behind 900 keys, 253.3 -> 251.2 us).  64 channels have
+    // half as many of those as a wave has lanes: 4 each.
+    constexpr int CW = DH >= 128 ? 16 : 4, VU = (SK / 4) * (DH / CW) / 64, VPAD = DH >= 128 ? 32 : 0, VT = DH * VLD + DH / 16 * VPAD;
+    __shared__ __attribute__((aligned(16))) int8_t pool[NW * VT > NW * SQ * TLD * 4 ? NW * VT : NW * SQ * TLD * 4];
     __shared__ float sm[NW][SQ], sl[NW][SQ];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, ql = lane & 31;
@@ -845,36 +867,46 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
     }
     const int8_t* const kbase = a.k + (int64_t)b * a.ks[0] + (int64_t)h * a.ks[2] + hh * 16;
     const int8_t* const vbase = a.v + (int64_t)b * a.vs[0] + (int64_t)h * a.vs[2];
-    int8_t* const sv = pool + wave * DH * VLD;
+    int8_t* const sv = pool + wave * VT;
     v4i k0[DS], k1[DS];                                          // two steps in flight in pass 1
-    int rv[VU][4];
+    int rv[VU][4][CW / 4];
     auto load_k = [&](v4i (&kf)[DS], int step) {                                // lane: key row ql of the step, its 16-byte pieces of half hh
         const int8_t* p = kbase + (int64_t)min(step * SK + ql, a.Skv - 1) * a.ks[1];
 #pragma unroll
         for (int d = 0; d < DS; ++d) kf[d] = *reinterpret_cast<const v4i*>(p + d * 32);
     };
-    // V unit: 4 keys x 4 channels; eight consecutive lanes read 32 contiguous bytes of one key row
+    // eight consecutive lanes read 128 (32) contiguous bytes of one key row
     auto load_v = [&](int step) {
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
             const int kg = (lane >> 3) & 7, cg = (lane & 7) + 8 * u;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                rv[u][i] = *reinterpret_cast<const int*>(vbase + (int64_t)min(step * SK + kg * 4 + i, a.Skv - 1) * a.vs[1] + cg * 4);
+            for (int i = 0; i < 4; ++i) {
+                const int8_t* p = vbase + (int64_t)min(step * SK + kg * 4 + i, a.Skv - 1) * a.vs[1] + cg * CW;
+                if constexpr (CW == 16) {
+                    const v4i w = *reinterpret_cast<const v4i*>(p);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) rv[u][i][c] = w[c];
+                } else rv[u][i][0] = *reinterpret_cast<const int*>(p);
+            }
         }
     };
     auto store_v = [&]() {
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
             const int kg = (lane >> 3) & 7, cg = (lane & 7) + 8 * u;
-            const uint32_t d0 = rv[u][0], d1 = rv[u][1], d2 = rv[u][2], d3 = rv[u][3];
-            const uint32_t lo01 = __builtin_amdgcn_perm(d1, d0, 0x05010400u), hi01 = __builtin_amdgcn_perm(d1, d0, 0x07030602u);
-            const uint32_t lo23 = __builtin_amdgcn_perm(d3, d2, 0x05010400u), hi23 = __builtin_amdgcn_perm(d3, d2, 0x07030602u);
-            const uint32_t t[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
-                                   __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
             const int pos = (kg & 1) * 16 + (kg >> 1) * 4;       // the key order of the PV fragment (see the kernel above)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) *reinterpret_cast<uint32_t*>(&sv[(cg * 4 + j) * VLD + pos]) = t[j];
+            for (int c = 0; c < CW / 4; ++c) {
+                const uint32_t d0 = rv[u][0][c], d1 = rv[u][1][c], d2 = rv[u][2][c], d3 = rv[u][3][c];
+                const uint32_t lo01 = __builtin_amdgcn_perm(d1, d0, 0x05010400u), hi01 = __builtin_amdgcn_perm(d1, d0, 0x07030602u);
+                const uint32_t lo23 = __builtin_amdgcn_perm(d3, d2, 0x05010400u), hi23 = __builtin_amdgcn_perm(d3, d2, 0x07030602u);
+                const uint32_t t[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                                       __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<uint32_t*>(&sv[(cg * CW + c * 4 + j) * VLD + (VPAD ? cg * VPAD : 0) + pos]) = t[j];
+            }
         }
     };
     auto scores = [&](const v4i (&kf)[DS]) {
@@ -915,7 +947,7 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
         auto smax = acc[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) smax = max(smax, acc[r]);
-        smax = max(smax, __shfl_xor(smax, 32));
+        smax = pair_max(smax);
         if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {
             const float mn = fmaxf(m2, (float)smax * c2);
             float e[16], sum = 0.0f;
@@ -988,7 +1020,7 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int c = 0; c < DS; ++c) {
-            const v4i vf = *reinterpret_cast<const v4i*>(&sv[(c * 32 + ql) * VLD + hh * 16]);
+            const v4i vf = *reinterpret_cast<const v4i*>(&sv[(c * 32 + ql) * VLD + (c * 2 + (ql >> 4)) * VPAD + hh * 16]);
             if constexpr (F8) o[c] = mfma_wide_f8(vf, zero, pf, zero, o[c]);
             else {
                 o[c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf, o[c], 0, 0, 0);
