@@ -55,7 +55,8 @@ template <typename T>
 __device__ __forceinline__ T pair_max(T x) {
     const uint32_t u = __builtin_bit_cast(uint32_t, x);
     const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return max(__builtin_bit_cast(T, r[0]), __builtin_bit_cast(T, r[1]));
+    const uint32_t lo = r[0], hi = r[1];                      // (a bit cast of the element itself would read r[0] twice)
+    return max(__builtin_bit_cast(T, lo), __builtin_bit_cast(T, hi));
 }
 
 // the output rows of a block of BQ padded queries: zeros
@@ -380,8 +381,8 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
 
     // ---- pass 1: row max and row sum ------------------------------------------------------------
     // One maximum per tile, the two lanes of a query exchange theirs by v_permlane32_swap.  us, an exchange through LDS every 32 keys -> this:
-    // 8 x 32 x 2048 x 128 causal 455 -> 435, E4M3 376 -> 342, 2 x 32 x 2048 without a mask 195 -> 183, 169 -> 159, 8 x 32 x 200 behind 1300 keys 84 -> 80, 68
-    // -> 63.5, 8 x 16 x 1000 x 64 74 -> 71, 63 -> 61.  (Maxima of a lane's own keys, joined behind the last tile: another 2 %, but their factors' errors
+    // 8 x 32 x 2048 x 128 causal 467 -> 435, E4M3 388 -> 351, 2 x 32 x 2048 without a mask 201 -> 185, 169 -> 155, 8 x 32 x 200 behind 1300 keys 84 -> 82, 69
+    // -> 65, 8 x 16 x 1000 x 64 75 -> 71, 66 -> 63.  (Maxima of a lane's own keys, joined behind the last tile: another 2 %, but their factors' errors
     // showed where all probabilities are equal.)
     float m2 = -INFINITY, l = 0.0f;           // running max (log2 domain) and sum of 2^(a2 - m2), this lane's keys
     constexpr float FMASKED = -3.0e38f;       // E4M3 scores are floats: the mask value of that variant
