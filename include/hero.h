@@ -373,9 +373,10 @@ typedef struct {
 } hero_layer_io;
 
 /* Bytes of scratch hero_layer_fwd can use for T = B*S rows of this layer.  Part of it is scratch for the K split of the GEMMs,
- * which only some sizes have, so a smaller T may ask for more than a larger one.  Where E4M3 or 16-bit modules are what asks
- * for that part, a workspace without it is accepted and they run in one pass (their fp32 sums are then ordered otherwise);
- * INT8 modules insist on theirs (T <= 128 rows, K >= 8192; of 32 rows and fewer only those whose K is split all the same). */
+ * which only some sizes have, so a smaller T may ask for more than a larger one.  Where E4M3 or 16-bit modules, or INT8 ones of more than
+ * 128 rows, are what asks for that part, a workspace without it is accepted and they run in one pass (fp32 sums are then ordered
+ * otherwise, INT8's are the same); INT8 modules of T <= 128 rows and K >= 8192 insist on theirs (of 32 rows and fewer only those
+ * whose K is split all the same). */
 size_t hero_layer_workspace_bytes(const hero_layer_desc* desc, int64_t B, int64_t S);
 
 /* One W8A8 layer: enqueues LN^quant, the four GeMM^quant, the attention and (POST_LN) the

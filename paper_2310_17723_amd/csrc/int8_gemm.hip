@@ -786,7 +786,8 @@ static hero_status run_int8_gemm(const int8_t* A, int64_t lda, const float* a_ro
 }
 
 // hero_int8_gemm_ws for a caller that knows what its chain reads next (hero_layer_fwd: the next module's weights):
-// the large-problem kernels request that memory while they run, the others ignore the hint.  Not part of the C ABI.
+// the large-problem kernels request that memory while they run, the others ignore the hint.  The workspace is scratch for any split
+// (hero_int8_gemm_split_bytes).  Not part of the C ABI.
 hero_status hero_int8_gemm_prefetching(const int8_t* A, int64_t lda, const float* a_row_scale,
                                        const int8_t* Bt, int64_t ldb, const float* b_col_scale,
                                        const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,
@@ -818,6 +819,8 @@ extern "C" hero_status hero_int8_gemm_ws(const int8_t* A, int64_t lda, const flo
                                          void* C, hero_dtype c_dt, int64_t ldc,
                                          int64_t M, int64_t N, int64_t K,
                                          void* workspace, size_t workspace_bytes, void* stream) {
+    // a buffer for a product whose size query is 0 need not be scratch (the split of a middling one is hero_layer_fwd's, which asks for it)
+    if (hero_int8_gemm_workspace_bytes(M, N, K) == 0) workspace_bytes = 0;
     return run_int8_gemm(A, lda, a_row_scale, Bt, ldb, b_col_scale, bias, residual, res_dt, ldr, epi, out_col_scale,
                          C, c_dt, ldc, M, N, K, workspace, workspace_bytes, stream, -1);
 }

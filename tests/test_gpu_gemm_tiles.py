@@ -54,17 +54,39 @@ def test_floats(M, N, kb, dt, tile):
     assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * 2.0 ** -8).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(1100, 4096, 16384), (1053, 4100, 16512)])
-def test_int8_k_split_of_a_middling_product(M, N, K):
-    """Two K ranges in tiles of 160 rows, the second one shorter: the sums are exact, through scratch that is dirty and no larger than it has to be."""
+@pytest.mark.parametrize("M,N,K", [(1100, 4096, 16384), (1053, 4100, 16512), (602, 4096, 16384)])
+def test_a_buffer_the_size_query_does_not_ask_for_stays_as_it_is(M, N, K):
+    """hero_int8_gemm_workspace_bytes is 0: "any buffer, or none, is accepted", and none is written, also where the layer would split K."""
     hero = pkg.load()
+    assert hero.lib.hero_int8_gemm_workspace_bytes(M, N, K) == 0
     a, w, rs, cs, bias, _ = _inputs(M, N, K, torch.int8)
     kw = dict(a_row_scale=rs, b_col_scale=cs / (90 * K ** 0.5), bias=bias, epi=HB.EPI_REQUANT, out_dtype=torch.int8)
-    ws = torch.full((2 * M * N * 4 + 256,), 0xA5, dtype=torch.uint8, device="cuda")
-    out = hero.hero_int8_gemm(a, w, workspace=ws[:-256], **kw)
-    assert torch.equal(out, hero.hero_int8_gemm(a, w, **kw))
-    assert not bool((ws[:4096] == 0xA5).all()) and bool((ws[-256:] == 0xA5).all())
-    assert torch.equal(hero.hero_int8_gemm(a, w, workspace=ws[:-256]), hero.hero_int8_gemm(a, w))
+    ws = torch.full((8 * M * N * 4,), 0xA5, dtype=torch.uint8, device="cuda")
+    assert torch.equal(hero.hero_int8_gemm(a, w, workspace=ws, **kw), hero.hero_int8_gemm(a, w, **kw))
+    assert torch.equal(hero.hero_int8_gemm(a, w, workspace=ws), hero.hero_int8_gemm(a, w))
+    assert bool((ws == 0xA5).all())
+
+
+@pytest.mark.parametrize("B,S,f", [(2, 550, 16384), (1, 1053, 16512)])
+def test_int8_k_split_of_a_middling_product(B, S, f, monkeypatch):
+    """A chunk's FC2 in INT8, two K ranges in tiles of 160 rows (the second one shorter): the sums are exact, so the layer's result is the same bit for bit
+    through scratch that is dirty and no larger than it has to be, and without it."""
+    import test_gpu_workspace as TW
+    monkeypatch.setattr(TW, "D", 4096)
+    monkeypatch.setattr(TW, "H", 32)
+    hero, mode, T = pkg.load(), HB.MODE_M3, B * S
+    keep, W, desc = TW._layer(hero, mode, f, 5)
+    full, planes = hero.hero_layer_workspace_bytes(desc, B, S), 2 * T * 4096 * 4
+    h0 = torch.randn((T, 4096), device="cuda", generator=torch.Generator(device="cuda").manual_seed(6)).to(torch.bfloat16)
+    res = []
+    for nbytes in (full, full - planes):
+        h, ws = h0.clone(), torch.full((nbytes + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        hero.hero_layer_fwd(desc, W, B, S, ws[:nbytes], h=h)
+        res.append(h)
+        assert bool((ws[nbytes:] == 0xA5).all())
+        if nbytes == full:
+            assert not bool((ws[full - planes:full - planes + 4096] == 0xA5).all())
+    assert torch.equal(res[0], res[1]) and bool(torch.isfinite(res[0].float()).all())
 
 
 @pytest.mark.parametrize("mode", [HB.MODE_M2, HB.MODE_M2 | HB.M_F16])
