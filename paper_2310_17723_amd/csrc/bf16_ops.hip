@@ -216,7 +216,8 @@ __global__ __launch_bounds__(256) void bf16_attn_kernel(BAttnArgs a) {
     }
     l += __shfl_xor(l, 32);
     if (qi >= a.Sq) return;
-    const float inv_l = l > 0.0f ? 1.0f / l : 0.0f;
+    // (a score beyond fp32: the fma's exponent is -inf where the product alone, minus the maximum, was NaN)
+    const float inv_l = m2 == INFINITY ? __builtin_nanf("") : (l > 0.0f ? 1.0f / l : 0.0f);
     const int64_t orow = ((int64_t)b * a.Sq + qi) * a.ldo + (int64_t)h * DH;
 #pragma unroll
     for (int c = 0; c < CT; ++c)

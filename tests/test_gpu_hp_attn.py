@@ -68,3 +68,17 @@ def test_small_probabilities(dt):
     q, k, v = torch.zeros((40, 128, 16, 64), device="cuda"), torch.zeros((40, 500, 16, 64), device="cuda"), torch.randn((40, 500, 16, 64), device="cuda", generator=g)
     q[..., 0], k[:, 77, :, 0], v[:, 77] = 1.0, 10.0, 0.0
     _check(q.to(dt), k.to(dt), (v + 1).to(dt), 1.0, HB.MASK_NONE, None)
+
+
+@pytest.mark.parametrize("dt,unit,scale", [(torch.bfloat16, 1e19, 4.0), (torch.float16, 3e4, 4e29)])
+@pytest.mark.parametrize("key", [5, 40, 99])
+def test_a_score_beyond_fp32_is_not_silent(dt, unit, scale, key):
+    """A sum that fp32 holds, times a scale that takes it beyond: the row has no maximum to subtract, and is NaN (as softmax of fp32 scores is), not zeros."""
+    g = torch.Generator(device="cuda").manual_seed(9)
+    q, k, v = torch.zeros((40, 100, 16, 64), device="cuda"), torch.zeros((40, 100, 16, 64), device="cuda"), torch.randn((40, 100, 16, 64), device="cuda", generator=g)
+    q[3, 17, 2, 0], k[3, key, 2, 0] = unit, unit
+    bad = torch.zeros(q.shape, device="cuda", dtype=torch.bool)
+    bad[3, 17, 2] = True
+    for n in (slice(0, 40), slice(3, 4)):                           # many query blocks, few
+        y = pkg.load().hero_hp_attn(q[n].to(dt), k[n].to(dt), v[n].to(dt), scale, HB.MASK_NONE, None)
+        assert torch.equal(torch.isnan(y).reshape(bad[n].shape), bad[n])
