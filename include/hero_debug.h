@@ -17,7 +17,8 @@ extern "C" {
 /* GeMM^quant (Sec. 2.1, 2.2.2, 2.2.3) with the kernel forced.  tile: 0 = 128x128 tile staged through registers,
  * 1 = 256x256 direct-to-LDS, one tile per workgroup, 2 = the ring kernel (small and middling problems), 7 = 256x256
  * persistent, 8 = 128x128 persistent (two workgroups per CU), 10 / 11 / 12 = persistent of 224 / 192 / 160 rows by 256 columns;
- * 9, the code of a former kernel, runs as 7.  Never splits K. */
+ * 9, the code of a former kernel, runs as 7.  The persistent kernels, here and below, run every M and N whose K is a multiple of 128 bytes,
+ * 256 or more (160 rows: 384 or more, else as 192), and whose rows lie less than 16 MB apart.  Never splits K. */
 hero_status hero_int8_gemm_tile(const int8_t* A, int64_t lda, const float* a_row_scale,
                                 const int8_t* Bt, int64_t ldb, const float* b_col_scale,
                                 const float* bias, const void* residual, hero_dtype res_dt, int64_t ldr,

@@ -17,7 +17,6 @@ __device__ __forceinline__ v16f mfma_hp(v4i a, v4i b, v16f c) {
 }
 
 // s + the two 16-bit values of pk (v_dot2_f32_bf16 / _f16 against ones)
-typedef short v2s __attribute__((ext_vector_type(2)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 template <int DT>
 __device__ __forceinline__ float add_pair(uint32_t pk, float s) {

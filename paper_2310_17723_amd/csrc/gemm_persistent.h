@@ -280,8 +280,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
             } else {
                 // 16 x 16 tiles: one instruction takes a whole slab of a row, so every fragment of a slab is read during the slab
                 // before, right after its register's last use: the first half of the rows (dead by the barrier) and the weights one by
-                // one as the second half is done with them, that half itself at the end.  Twelve instructions at least lie
-                // between a read and its use.
+                // one as the second half is done with them, that half itself at the end.  At least three times TI / 2, rounded down, instructions lie
+                // between a read and its use: twelve with 256 rows, nine with 224 and 192, six with 160 and in 128 x 128 tiles.
                 constexpr int HI = TI / 2, HS = TI - HI, NH = HS * TJ;
                 static_assert(NU <= NH, "a slot of the second half for every unit");
 #pragma unroll

@@ -501,7 +501,7 @@ inline Choice choose(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, in
         const int rows = tile == 10 ? 224 : tile == 11 || (tile == 12 && kb < 6 * BK) ? 192 : tile == 12 ? 160 : 256;
         if (rows < 256) tile = K_PERS256;
         if (tile == K_PERS256 || tile == K_PERS128) {
-            if (pers_ok && (adt == HERO_I8 || adt == HERO_F8E4M3 || t128 >= 192)) return {tile == K_PERS128 ? K_PERS128 : K_PERS256, RING_NONE, rows};
+            if (pers_ok) return {tile == K_PERS128 ? K_PERS128 : K_PERS256, RING_NONE, rows};
             if (i8) return {tile == K_PERS128 ? K_REG128 : K_DMA256, RING_NONE};
             return small;
         }
