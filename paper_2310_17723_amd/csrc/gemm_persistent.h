@@ -50,6 +50,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     // 1 KB loads per wave and slab: 16 rows each; with BM no multiple of 128 the last one is for the first A_LAST waves only
     constexpr int A_UNITS = (BM / 16 + NWAVE - 1) / NWAVE, A_LAST = BM / 16 - (A_UNITS - 1) * NWAVE, B_UNITS = BN / 16 / NWAVE;
     constexpr bool A_EVEN = A_LAST == NWAVE;
+    constexpr bool ONE = NSA == NSB && BM == BN;                    // rings alike, filled in the same iterations: B's stream and offsets are A's too
     constexpr int NM = TM * TN, NFR = TM + TN;
     static_assert(NSA >= 4 && NSA <= 6 && NSB >= 4 && NSB <= 6 && BM % (16 * WM) == 0 && BN % (16 * NWAVE) == 0 && (!WIDE || (NFR <= 2 * NM && BM % (32 * WM) == 0)), "rings / interleave plan");
     static_assert(!PART || (EPI == HERO_EPI_RAW_I32 && !WIDE), "a part writes raw accumulators");
@@ -93,16 +94,21 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     uint32_t oa[A_UNITS], ob[B_UNITS];
     int m0b = 0, n0b = 0;                                        // origin of B's tile
     auto range_start = [&](int s) { return PART ? (int64_t)(s / ntiles) * g.kslabs * (2 * BK) : (int64_t)0; };
-    auto set_tile_a = [&](int s) {
-        int m0, n0;
-        tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0, n0);
-        aKT = range_slabs(s);
+    auto set_rows = [&](int s, int m0) {
         ia = g.A + (int64_t)m0 * g.lda + range_start(s);
 #pragma unroll
         for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0) * (uint32_t)g.lda + lc;
     };
+    auto set_tile_a = [&](int s) {
+        if (ONE) return;
+        int m0, n0;
+        tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0, n0);
+        aKT = range_slabs(s);
+        set_rows(s, m0);
+    };
     auto set_tile_b = [&](int s) {
         tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0b, n0b);
+        if (ONE) set_rows(s, m0b);
         bKT = range_slabs(s);
         ib = g.Bt + (int64_t)n0b * g.ldb + range_start(s);
 #pragma unroll
@@ -135,9 +141,10 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     auto next_slot = [](uint32_t o, uint32_t bytes, uint32_t ring) { const uint32_t n = o + bytes; return n == ring ? 0u : n; };
     auto issue_a = [&](int u) {
         if (A_EVEN || u + 1 < A_UNITS || has_last) {
-            dma16s(oa[u], ia, wbase + wra + u * NWAVE * 1024);
+            const uint32_t w = ONE ? wrb : wra;
+            dma16s(oa[u], ia, wbase + w + u * NWAVE * 1024);
             // (the second slab through its own scalar base: an instruction offset would move the LDS side too)
-            dma16s(oa[u], ia + BK, wbase + next_slot(wra, A_BYTES, A_RING) + u * NWAVE * 1024);
+            dma16s(oa[u], ia + BK, wbase + next_slot(w, A_BYTES, A_RING) + u * NWAVE * 1024);
         }
     };
     auto issue_b = [&](int u) {
@@ -146,6 +153,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         dma16s(ob[u], ib + BK, wbase + A_RING + next_slot(wrb, B_BYTES, B_RING) + u * NWAVE * 1024);
     };
     auto advance_a = [&]() {                                     // next pair; past the last tile the last pair repeats (never read)
+        if (ONE) return;
         wra = next_slot(next_slot(wra, A_BYTES, A_RING), A_BYTES, A_RING);
         akt += 2;
         if (akt < aKT) { ia += 2 * BK; return; }
@@ -157,7 +165,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     auto advance_b = [&]() {
         wrb = next_slot(next_slot(wrb, B_BYTES, B_RING), B_BYTES, B_RING);
         bkt += 2;
-        if (bkt < bKT) { ib += 2 * BK; return; }
+        if (bkt < bKT) { ib += 2 * BK; if (ONE) ia += 2 * BK; return; }
         if (bseq + nslot < seq_end) {
             bseq += nslot; bkt = 0; bpar ^= 1;
             set_tile_b(bseq);
@@ -237,7 +245,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
             constexpr bool odd = decltype(ODD)::value;
             constexpr bool put_a = odd == (NSA % 2 == 0), put_b = odd == (NSB % 2 == 0);
             constexpr int NU = (put_a ? A_UNITS : 0) + (put_b ? B_UNITS : 0);      // units to issue: A's, then B's
-            const int nda = rda + A_BYTES == A_RING ? 0 : rda + A_BYTES, ndb = rdb + B_BYTES == B_RING ? 0 : rdb + B_BYTES;
+            const int nda = rda + A_BYTES == A_RING ? 0 : rda + A_BYTES, ndb = ONE ? nda : (rdb + B_BYTES == B_RING ? 0 : rdb + B_BYTES);
             auto issue_unit = [&](int u) { if (put_a && u < A_UNITS) issue_a(u); else issue_b(u - (put_a ? A_UNITS : 0)); };
             // slab i + 1 has landed (mine); what the loads behind the barrier overwrite has been read.  (16 x 16 tiles: the last of the weights'
             // fragments was an operand in front of the barrier, a row's may still be under way.)
@@ -389,9 +397,11 @@ hero_status launch_persistent_tile(const GemmArgs& g, int rows, hipStream_t st) 
         if (rows == 160) return wide(std::integral_constant<int, 160>{});
     }
     if (rows != 128) return HERO_ERR_UNSUPPORTED;
-    // While a workgroup has one tile, four slots each: it waits for its weights as long either way, and both operands in one go (the
-    // activations first: the other order +3 to 9 %) take fewer requests at a time.  us, four and four / five and four: BF16 301 x 12288 x 4096 62.0 /
-    // 65.0, 1100 x 4096 x 4096 59.1 / 62.1, INT8 34.1 / 35.0, 32.2 / 32.3;  12500 x 4096 x 1024 BF16 118.4 / 112.7, INT8 73.0 / 69.4.
+    // While a workgroup has one tile, four slots each, filled by one stream: it waits for its weights as long either way, and both operands in one go (the
+    // activations first: the other order +3 to 9 %) take fewer requests at a time.  us, weights and activations from memory, four and four / five and four: BF16
+    // 301 x 12288 x 4096 61.5 / 65.7, 1100 x 4096 x 4096 60.4 / 63.4, 1310 x 4096 x 16384 224 / 244, INT8 33.7 / 35.0, 33.2 / 34.4, 112 / 118;  beyond, E4M3 6144 x
+    // 4096 x 4096 100.8 / 99.6, 12500 x 4096 x 1024 62.0 / 61.5, INT8 60.8 / 61.1, BF16 112.0 / 113.4.  (Two streams for the four and four: E4M3 1693 x 4096 x 16384
+    // in cache 121.1 us, one 117.4, BF16 1395 x 4096 x 4096 56.7 and 55.3.)
     if (((int64_t)(g.M + 127) / 128) * ((g.N + 127) / 128) <= 512) return launch_persistent<128, 128, 2, 2, 4, 4, EPI, CDT, RDT, ADT>(g, 2, st);
     return launch_persistent<128, 128, 2, 2, 5, 4, EPI, CDT, RDT, ADT>(g, 2, st);
 }
