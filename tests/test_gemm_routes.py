@@ -64,6 +64,16 @@ def test_e4m3_of_a_long_k_and_several_rounds_takes_small_tiles():
 
 
 @pytest.mark.parametrize("dt", DTYPES)
+def test_small_tiles_of_a_long_k_while_all_are_resident(dt):
+    """257 to 512 tiles of 128 x 128 (two on a CU) behind a K of 8 KB or more: ahead of tiles of 160 rows (weights from memory, up to 15 % for 16 bits), which
+    would leave most CUs without work; beyond that the taller tiles."""
+    for M, N, kb in ((5943, 768, 16384), (301, 12288, 8192), (4637, 1024, 8192), (7859, 1024, 8192), (1313, 4096, 16384), (1310, 4096, 32768)):
+        assert kernel(dt, M, N, kb) == 8, (M, N, kb)
+    for M, N, kb in ((705, 12288, 8192), (633, 16384, 8192), (2438, 4096, 32768)):
+        assert kernel(dt, M, N, kb) == 7, (M, N, kb)
+
+
+@pytest.mark.parametrize("dt", DTYPES)
 def test_few_rows_of_many_columns_keep_small_tiles(dt):
     """A product of at most 64 rows never runs tiles of 128 or 256 rows, however many columns it has."""
     for N in (33000, 36864, 50304, 131072):
