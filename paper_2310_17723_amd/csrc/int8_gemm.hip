@@ -463,8 +463,9 @@ struct Choice { Kernel kernel; RingForm form; int rows = 256; };       // rows: 
 // columns, one workgroup per CU, or 128 x 128, two per CU.  A CU is handed ceil(tiles / 256) of them; what one takes, in parts of a
 // 256 x 256 tile's time, is below: more than its share of the area (0.875, 0.75, 0.625, 0.25), since the weights' 256 rows are loaded for every
 // height and a 128 x 128 tile loads twice as much for its area, which a long K does not hide.  Measured over 265 products (INT8, E4M3, BF16;
-// 300 .. 14000 rows, K of 768 .. 16384) the choice is 0.4 % from the best of the five on average, 10 % at most, and was ahead of choosing between 256 and 128
-// by 4 % on average, by 40 % at most.  us, 256 / 224 / 192 / 160 / 128: INT8 GELU^quant 602 x 16384 x 4096 52.1 / 49.6 / 47.5 / 43.3 / 58.5, 16-bit result
+// 300 .. 14000 rows, K of 768 .. 16384) the choice is 0.4 % from the best of the five on average and was ahead of choosing between 256 and 128
+// by 4 % on average, by 40 % at most.  Single ones are further off: behind a short K how full the last round is counts too (8-bit operands, 16-bit result, 160 x 256 /
+// 128 x 128: 4184 x 4096 x 1024 26.7 / 30.5, but 4931 rows 31.0 / 28.7, 6616 x 3072 x 1024 29.9 / 27.7; 8187 x 3072 x 768 is best in 224 rows, 28.5 / 33.4).  us, 256 / 224 / 192 / 160 / 128: INT8 GELU^quant 602 x 16384 x 4096 52.1 / 49.6 / 47.5 / 43.3 / 58.5, 16-bit result
 // 2500 x 4096 x 16384 160 / 152 / 141 / 134 / 174, REQUANT 3817 x 3072 x 1024 17.0 / 16.7 / 15.0 / 23.4 / 15.9, 9000 x 1024 x 4096 43.8 / 41.4 / 36.3 / 35.4 / 46.0, 14000 x
 // 3072 x 1024 47.0 / 44.1 / 49.4 / 53.4 / 47.6;  BF16 602 x 16384 x 4096 94 / 90 / 83 / 76 / 109, 9000 x 1024 x 4096 81 / 78 / 67 / 65 / 88.
 inline Choice persistent_choice(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, int64_t kb) {
