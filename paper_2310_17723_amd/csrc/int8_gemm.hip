@@ -472,10 +472,14 @@ inline Choice persistent_choice(hero_dtype adt, hero_epilogue epi, int64_t M, in
     const bool f8 = adt == HERO_F8E4M3, gelu = epi == HERO_EPI_DEQUANT_GELU || epi == HERO_EPI_GELU_REQUANT;
     auto rounds = [&](int64_t bm, int64_t bn) { return (double)((((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256); };
     const double n256 = rounds(256, 256);
-    // (Behind a K of 8 KB and more 128 x 128 tiles are nearer to their share of the area while all are resident at once, 512 at most, than one after another.
-    // us, weights and activations from memory, 160 x 256 / 128 x 128: BF16 5943 x 768 x 8192 126 / 111, 301 x 12288 x 4096 70.8 / 61.5, 4637 x 1024 x 4096 71.0 / 60.5, 7859
-    // rows 73.1 / 68.0, 332 x 16384 x 4096 68.9 / 68.3, INT8 1313 x 4096 x 16384 123 / 112, 7705 x 1024 x 8192 72.5 / 68.6;  in cache 0 .. 9 %, INT8 -2 .. 4 %.)
-    const double n128 = rounds(128, 128), small = n128 * (kb <= 2048 ? (gelu ? 0.27 : 0.30) : f8 && n256 > 1 ? 0.325 : kb < 8192 || n128 <= 2 ? 0.34 : 0.36);
+    // Behind a K of 8 KB and more 128 x 128 tiles are nearer to their share of the area while all are resident at once (512 at most) and an eighth of the CUs have one only.
+    // us, weights and activations from memory, 160 x 256 / 128 x 128: BF16 5943 x 768 x 8192 126 / 111, 301 x 12288 x 4096 70.8 / 61.5, 4637 x 1024 x 4096 71.0 / 60.5, INT8
+    // 1313 x 4096 x 16384 123 / 112;  GPT layer, 1300 and 1700 tokens, M3 396 / 387, 442 / 436.  Not with more of them (480: 630 tokens, M0 327 / 332; 512: 2040 tokens, M2 600 / 619), nor with four or eight rows of
+    // tiles, the last one more than half full (BF16 431 x 12288 x 4096 70.0 / 68.5, 480 rows 71.8 / 74.4, 505 rows 69.9 / 79.2, 1000 x 8192 x 4096 69.0 / 75.2;
+    // layer, 505 tokens, M0 293 / 314): consecutive workgroups then differ in their row of tiles in steps of four, which is slower by a fifth than with six.
+    const int64_t m128 = (M + 127) / 128;
+    const bool resident = m128 * ((N + 127) / 128) <= 448 && !(m128 % 4 == 0 && m128 <= 8 && (M - 1) % 128 >= 64);
+    const double small = rounds(128, 128) * (kb <= 2048 ? (gelu ? 0.27 : 0.30) : f8 && n256 > 1 ? 0.325 : kb < 8192 || resident ? 0.34 : 0.36);
     // (E4M3 behind a long K: from the second large round on 128 x 128 keeps what it is ahead of 256 x 256 in, 192 rows serve the rest.  us, 256 / 192 / 128:
     // REQUANT 3000 x 12288 x 4096 143 / 124 / 140, 1900 x 12288 x 4096 94 / 83 / 102, 10500 x 1024 x 4096 43.7 / 39.6 / 45.7.)
     if (f8 && kb > 2048 && n256 > 1 && small < n256) return {K_PERS128, RING_NONE};
