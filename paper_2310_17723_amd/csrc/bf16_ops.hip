@@ -33,7 +33,7 @@ __device__ __forceinline__ float add_pair(uint32_t pk, float s) {
 // scales and subtracts, exp2 (four slots), half a packing conversion and half a v_dot2 that sums the packed values.  Keys are compared with
 // the limit only in tiles that hide one, a wave leaves out tiles of which it sees nothing.  us, with a multiplication, a comparison and a
 // select per score and sums of unpacked values -> this: 8 x 16 x 512 padded 24.5 -> 21.5, 16 x 16 x 300 causal 19.9 -> 17.2, 4 x 32 x 1024 x 128
-// causal 120 -> 107 (FP16 126 -> 113), 8 x 32 x 256 behind 2048 keys 156 -> 130;  BERT-large layer 32 x 512 in M1 356.7 -> 347.7.  (The maximum raised once
+// causal 120 -> 107 (FP16 126 -> 113), 8 x 32 x 256 behind 2048 keys 156 -> 130;  BERT-large layer 32 x 512 in M1 385 -> 379.  (The maximum raised once
 // per 64 keys: another 2-5 %, but an error larger by 0.1 .. 0.6 %, since fewer probabilities are exactly 1.)
 // ------------------------------------------------------------------------------------------
 constexpr int ABQ = 128, ABKV = 64;

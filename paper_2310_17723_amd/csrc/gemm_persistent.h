@@ -14,7 +14,7 @@ namespace hero_gemm {
 // A and B have rings of their own, of four and five slots (144 KB), and take turns: B's pair of slabs goes out in even iterations and has
 // three to arrive in, A's in odd ones and has two.  One ring of four slots for both sent 64 KB at once and then waited for the last of them: a
 // pair of slabs took the time from its first load to its last one's arrival, 2500 to 3200 clocks against 2048 of matrix instructions.  us,
-// one ring -> two: INT8 16384 x 12288 x 4096 641 -> 610 (2.70 POP/s), 16384 x 4096 x 16384 888 -> 815, 16384 x 1024 x 4096 55.3 -> 53.2, 16384 x
+// one ring -> two: BERT-large layer 32 x 512 300 both ways, in M1 404 -> 385, GPT prefill 8 x 2048 3387 -> 3263;  INT8 16384 x 12288 x 4096 641 -> 610 (2.70 POP/s), 16384 x 4096 x 16384 888 -> 815, 16384 x 1024 x 4096 55.3 -> 53.2, 16384 x
 // 3072 x 1024 49.8 -> 48.8;  BF16 8192 x 4096 x 4096 208 -> 199;  E4M3 8192 x 4096 x 4096 111 -> 102.  (Both operands in the same iteration: -7 %.)
 // The clock under matrix load is set by power, and 16 x 16 instructions multiply more per watt than 32 x 32 ones; their lanes also
 // write 16 (32) consecutive bytes next to their neighbours'.  us, 32 x 32 -> 16 x 16 tiles: INT8 16384 x 12288 x 4096 694 -> 642
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     // 16 x 16 tiles swizzle by swz4(row / 4), the weight rows, taken in another order, by swz4(row / 16).  The LDS serves a 128-bit
     // read in four turns of 16 lanes, lanes 0-3, 12-15 and 20-27 in the first, so a turn meets rows 0-3 and 12-15 of one chunk and rows 4-11 of
     // the chunk beside it; with row / 4 itself half of every read's cycles were bank conflicts, with 0, 3, 2, 1 there are none.
-    // us: BERT-large layer 32 x 512 292.0 -> 290.4, in M1 394.9 -> 390.8, GPT prefill 8 x 2048 3245 -> 3232.
+    // us: BERT-large layer 32 x 512 304 -> 300, in M1 405 both ways, GPT prefill 8 x 2048 3418 -> 3376.
     auto swz4 = [](int q) { return (q ^ (q << 1)) & 3; };
     const uint32_t lc = (uint32_t)(((lane & 3) ^ (WIDE ? (lrow >> 2) & 3 : swz4(lrow >> 2))) * 16);
     const uint32_t lcb = WIDE ? lc : (uint32_t)(((lane & 3) ^ swz4(lrow >> 4)) * 16);
@@ -134,8 +134,9 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         }
     };
     // A stream moves in PAIRS of slabs (128 bytes of every row = one cache line): the two 64-byte halves of a line are requested back
-    // to back and the second one is served by the line the first one brought in.  A CU pulls 48 B/clk from the L2 that way,
-    // against 30 B/clk when the halves are requested one slab apart (measured; a 256 x 256 tile needs 32).
+    // to back and the second one is served by the line the first one brought in.  In a loop of nothing else, as many workgroups sharing panels as here, a CU
+    // takes 57 B/clk from its L2 that way, 43 with the halves one slab apart, 60 in whole lines;  38, 28 and 46 where the panels come from beyond the L2, at any
+    // depth from 16 KB per wave on (a 256 x 256 tile needs 32 at the matrix cores' peak, a 128 x 128 tile 64).
     // issue_a(u) / issue_b(u): unit u of both slabs; wra, wrb: LDS offset of the pair's first slot (the second is the next one, round the ring).
     uint32_t wra = 0, wrb = 0;
     auto next_slot = [](uint32_t o, uint32_t bytes, uint32_t ring) { const uint32_t n = o + bytes; return n == ring ? 0u : n; };
