@@ -380,10 +380,11 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
     }
 
     // ---- pass 1: row max and row sum ------------------------------------------------------------
-    // One maximum per tile, the two lanes of a query exchange theirs by v_permlane32_swap.  us, an exchange through LDS every 32 keys -> this:
-    // 8 x 32 x 2048 x 128 causal 467 -> 435, E4M3 388 -> 351, 2 x 32 x 2048 without a mask 201 -> 185, 169 -> 155, 8 x 32 x 200 behind 1300 keys 84 -> 82, 69
-    // -> 65, 8 x 16 x 1000 x 64 75 -> 71, 66 -> 63.  (Maxima of a lane's own keys, joined behind the last tile: another 2 %, but their factors' errors
-    // showed where all probabilities are equal.)
+    // One maximum per tile, or per 32 keys in tiles that hide some (a block that is hidden altogether is left out); the two lanes of a query exchange
+    // theirs by v_permlane32_swap.  us, an exchange through LDS every 32 keys -> this: 8 x 32 x 2048 x 128 causal 394 -> 387, E4M3 332 -> 324, 2 x 32 x 2048
+    // without a mask 178 -> 174, 150 -> 145, 8 x 32 x 200 behind 1300 keys 76 -> 74, 62.6 -> 59.9, 8 x 16 x 1000 x 64 64 -> 63, 58.2 -> 56.5, 3 x 32 x 290 causal 20.6 -> 20.2.
+    // (64 keys to a maximum in every tile: 21.2 there, 17 x 32 x 92 16.8 -> 17.6.  Maxima of a lane's own keys, joined behind the last tile: another 2 %, but their
+    // factors' errors showed where all probabilities are equal.)
     float m2 = -INFINITY, l = 0.0f;           // running max (log2 domain) and sum of 2^(a2 - m2), this lane's keys
     constexpr float FMASKED = -3.0e38f;       // E4M3 scores are floats: the mask value of that variant
     if (ntiles > 0) { load_k(0); store_k(0); }
@@ -394,40 +395,44 @@ __global__ __launch_bounds__(256, ONLINE ? (DH == 64 ? 3 : 2) : (DH == 64 ? 4 : 
         const bool edge = (tile + 1) * BKV > nvis_min;
         auto pass1_tile = [&](auto EDGE) {
             const int lim = nvis - (tile * BKV + hh * 4);                       // key visible iff 32s + 8g + t < lim
-            SACC acc[BKV / 32];
+            constexpr int G = decltype(EDGE)::value ? 1 : BKV / 32;             // 32-key blocks to a maximum
 #pragma unroll
-            for (int s = 0; s < BKV / 32; ++s) {
-                acc[s] = scores(buf, s);
-                if constexpr (decltype(EDGE)::value)
+            for (int s0 = 0; s0 < BKV / 32; s0 += G) {
+                SACC acc[G];
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        if constexpr (F8) acc[s][r] = s * 32 + (r >> 2) * 8 + (r & 3) < lim ? acc[s][r] : FMASKED;
-                        else acc[s][r] = s * 32 + (r >> 2) * 8 + (r & 3) < lim ? acc[s][r] : MASKED;
-                    }
-            }
-            auto smax = acc[0][0];
+                for (int s = 0; s < G; ++s) {
+                    acc[s] = scores(buf, s0 + s);
+                    if constexpr (decltype(EDGE)::value)
 #pragma unroll
-            for (int s = 0; s < BKV / 32; ++s)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) smax = max(smax, acc[s][r]);
-            smax = pair_max(smax);
-            if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {              // same decision in both lanes of a query
-                const float mn = fmaxf(m2, (float)smax * c2);
-                float sum = 0.0f;
-#pragma unroll
-                for (int s = 0; s < BKV / 32; ++s) {
-                    float part = 0.0f;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        float e = __builtin_amdgcn_exp2f(fmaf((float)acc[s][r], c2, -mn));
-                        // (a hidden key counts for nothing at any scale of the scores, also where c2 brings the mask's value back into range)
-                        if constexpr (decltype(EDGE)::value) e = s * 32 + (r >> 2) * 8 + (r & 3) < lim ? e : 0.0f;
-                        part += e;
-                    }
-                    sum += part;
+                        for (int r = 0; r < 16; ++r) {
+                            if constexpr (F8) acc[s][r] = s0 * 32 + (r >> 2) * 8 + (r & 3) < lim ? acc[s][r] : FMASKED;
+                            else acc[s][r] = s0 * 32 + (r >> 2) * 8 + (r & 3) < lim ? acc[s][r] : MASKED;
+                        }
                 }
-                l = fmaf(l, __builtin_amdgcn_exp2f(m2 - mn), sum);
-                m2 = mn;
+                auto smax = acc[0][0];
+#pragma unroll
+                for (int s = 0; s < G; ++s)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) smax = max(smax, acc[s][r]);
+                smax = pair_max(smax);
+                if (F8 ? (float)smax > FMASKED : (int)smax > MASKED) {          // same decision in both lanes of a query
+                    const float mn = fmaxf(m2, (float)smax * c2);
+                    float sum = 0.0f;
+#pragma unroll
+                    for (int s = 0; s < G; ++s) {
+                        float part = 0.0f;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            float e = __builtin_amdgcn_exp2f(fmaf((float)acc[s][r], c2, -mn));
+                            // (a hidden key counts for nothing at any scale of the scores, also where c2 brings the mask's value back into range)
+                            if constexpr (decltype(EDGE)::value) e = s0 * 32 + (r >> 2) * 8 + (r & 3) < lim ? e : 0.0f;
+                            part += e;
+                        }
+                        sum += part;
+                    }
+                    l = fmaf(l, __builtin_amdgcn_exp2f(m2 - mn), sum);
+                    m2 = mn;
+                }
             }
         };
         if (!wact) {} else if (edge) pass1_tile(std::true_type{}); else pass1_tile(std::false_type{});
