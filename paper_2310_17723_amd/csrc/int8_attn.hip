@@ -834,7 +834,7 @@ __global__ __launch_bounds__(256 * KW, 4) void int8_attn_keep_kernel(AttnArgs a)
 // L2 for a quarter of the chain; bound by latency.  Same codes by the same formulas as above; the offset of the unsigned codes is
 // removed by a second matrix instruction as in the online variant, so o = -sum code * v.
 // ------------------------------------------------------------------------------------------
-template <int DH, int ODT, int FMT, int NW>
+template <int DH, int ODT, int FMT, int NW, int CW>
 __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
     constexpr bool F8 = FMT == HERO_F8E4M3;
     using SACC = typename std::conditional<F8, v16f, v16i>::type;
@@ -842,9 +842,9 @@ __global__ __launch_bounds__(64 * NW) void int8_attn_split_kernel(AttnArgs a) {
     using V4 = typename std::conditional<F8, v4f, v4i>::type;
     constexpr int SQ = 32, SK = 32, VLD = SK + 16, DS = DH / 32, TLD = 36;
     // V: a unit is 4 keys x CW channels; with 16 of them a load is 128 bits, and every 16 channels lie 32 bytes further on (the stores of eight
-    // units' same channel fall into different banks that way; GPT layer, 2 x 301 tokens behind 900 keys, 253.3 -> 251.2 us).  64 channels have
-    // half as many of those as a wave has lanes: 4 each.
-    constexpr int CW = DH >= 128 ? 16 : 4, VU = (SK / 4) * (DH / CW) / 64, VPAD = DH >= 128 ? 32 : 0, VT = DH * VLD + DH / 16 * VPAD;
+    // units' same channel fall into different banks that way; GPT layer, 2 x 301 tokens behind 900 keys, 253.3 -> 251.2 us; launch_split has the rule).
+    static_assert(CW == 4 || (CW == 16 && DH >= 128), "64 channels have half as many units of 16 as a wave has lanes");
+    constexpr int VU = (SK / 4) * (DH / CW) / 64, VPAD = CW == 16 ? 32 : 0, VT = DH * VLD + DH / 16 * VPAD;
     __shared__ __attribute__((aligned(16))) int8_t pool[NW * VT > NW * SQ * TLD * 4 ? NW * VT : NW * SQ * TLD * 4];
     __shared__ float sm[NW][SQ], sl[NW][SQ];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1370,9 +1370,22 @@ hero_status launch_split(const AttnArgs& a, hero_dtype out_dt, hipStream_t st) {
     const int64_t nqb = (a.Sq + 31) / 32, hgroups = ((int64_t)a.B * a.H + HG - 1) / HG, rounds = (hgroups + 7) / 8;
     if (rounds * 8 * HG * nqb > 0x7fffffffLL) return HERO_ERR_SHAPE;
     dim3 grid((unsigned)(rounds * 8 * HG * nqb)), block(64 * NW);
-    if (out_dt == HERO_BF16) hipLaunchKernelGGL((int8_attn_split_kernel<DH, HERO_BF16, FMT, NW>), grid, block, 0, st, a);
-    else if (out_dt == HERO_F16) hipLaunchKernelGGL((int8_attn_split_kernel<DH, HERO_F16, FMT, NW>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((int8_attn_split_kernel<DH, FMT, FMT, NW>), grid, block, 0, st, a);
+    auto go = [&](auto W) {
+        constexpr int CW = decltype(W)::value;
+        if (out_dt == HERO_BF16) hipLaunchKernelGGL((int8_attn_split_kernel<DH, HERO_BF16, FMT, NW, CW>), grid, block, 0, st, a);
+        else if (out_dt == HERO_F16) hipLaunchKernelGGL((int8_attn_split_kernel<DH, HERO_F16, FMT, NW, CW>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((int8_attn_split_kernel<DH, FMT, FMT, NW, CW>), grid, block, 0, st, a);
+    };
+    // V in 128-bit loads (128 channels), but not for E4M3 with at most one block per CU and 1024 keys or more, whose steps, shorter by a matrix instruction, wait
+    // longer for four such loads than for sixteen of 32 bits.  us, 32 / 128 bits: E4M3 32 blocks x 2165 keys 23.3 / 24.5, 112 x 1553 19.5 / 20.2, 224 x 1694 21.8 /
+    // 22.2, 128 x 820 12.4 / 12.6, but padded 64 x 831 11.7 / 11.4, 128 x 498 9.8 / 9.6, 384 x 1837 26.6 / 24.8, 640 x 1338 38.0 / 36.3;  INT8 64 x 1969 17.6 / 17.4, 320 x 859 20.0 / 18.9.
+    if constexpr (DH >= 128) {
+        if (FMT != HERO_F8E4M3 || (int64_t)a.B * a.H * nqb > 256 || a.Skv < 1024) {
+            go(std::integral_constant<int, 16>{});
+            return hero_launch_status();
+        }
+    }
+    if constexpr (DH < 128 || FMT == HERO_F8E4M3) go(std::integral_constant<int, 4>{});
     return hero_launch_status();
 }
 

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("Dh", [64, 128])
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("mask", [HB.MASK_NONE, HB.MASK_PADDING, HB.MASK_CAUSAL])
-@pytest.mark.parametrize("Sq,Skv", [(20, 150), (130, 600), (577, 577)])
+@pytest.mark.parametrize("Sq,Skv", [(20, 150), (130, 600), (577, 577), (20, 1023), (90, 1024)])
 def test_one_key_far_ahead(Dh, fp8, mask, Sq, Skv):
     """Query i asks for channel i % Dh, in which one key leads the others by 100 or 300 units of the softmax's exponent: that key's probability is 1, the others' 0,
     and the output is its V, code for code.  From 88.7 units (2^128) on a maximum that misses the key makes the row's sum infinite."""
