@@ -94,21 +94,23 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     uint32_t oa[A_UNITS], ob[B_UNITS];
     int m0b = 0, n0b = 0;                                        // origin of B's tile
     auto range_start = [&](int s) { return PART ? (int64_t)(s / ntiles) * g.kslabs * (2 * BK) : (int64_t)0; };
-    auto set_rows = [&](int s, int m0) {
-        ia = g.A + (int64_t)m0 * g.lda + range_start(s);
-#pragma unroll
-        for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0) * (uint32_t)g.lda + lc;
-    };
     auto set_tile_a = [&](int s) {
-        if (ONE) return;
-        int m0, n0;
-        tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0, n0);
-        aKT = range_slabs(s);
-        set_rows(s, m0);
+        if constexpr (!ONE) {
+            int m0, n0;
+            tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0, n0);
+            aKT = range_slabs(s);
+            ia = g.A + (int64_t)m0 * g.lda + range_start(s);
+#pragma unroll
+            for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0) * (uint32_t)g.lda + lc;
+        }
     };
     auto set_tile_b = [&](int s) {
         tile_from_seq<BM, BN>(g, PART ? s % ntiles : s, m0b, n0b);
-        if (ONE) set_rows(s, m0b);
+        if constexpr (ONE) {
+            ia = g.A + (int64_t)m0b * g.lda + range_start(s);
+#pragma unroll
+            for (int u = 0; u < A_UNITS; ++u) oa[u] = (uint32_t)min(lrow + u * (NWAVE * 16), g.M - 1 - m0b) * (uint32_t)g.lda + lc;
+        }
         bKT = range_slabs(s);
         ib = g.Bt + (int64_t)n0b * g.ldb + range_start(s);
 #pragma unroll
@@ -142,10 +144,9 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     auto next_slot = [](uint32_t o, uint32_t bytes, uint32_t ring) { const uint32_t n = o + bytes; return n == ring ? 0u : n; };
     auto issue_a = [&](int u) {
         if (A_EVEN || u + 1 < A_UNITS || has_last) {
-            const uint32_t w = ONE ? wrb : wra;
-            dma16s(oa[u], ia, wbase + w + u * NWAVE * 1024);
+            dma16s(oa[u], ia, wbase + (ONE ? wrb : wra) + u * NWAVE * 1024);
             // (the second slab through its own scalar base: an instruction offset would move the LDS side too)
-            dma16s(oa[u], ia + BK, wbase + next_slot(w, A_BYTES, A_RING) + u * NWAVE * 1024);
+            dma16s(oa[u], ia + BK, wbase + next_slot(ONE ? wrb : wra, A_BYTES, A_RING) + u * NWAVE * 1024);
         }
     };
     auto issue_b = [&](int u) {
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         dma16s(ob[u], ib + BK, wbase + A_RING + next_slot(wrb, B_BYTES, B_RING) + u * NWAVE * 1024);
     };
     auto advance_a = [&]() {                                     // next pair; past the last tile the last pair repeats (never read)
-        if (ONE) return;
+        if constexpr (ONE) return;
         wra = next_slot(next_slot(wra, A_BYTES, A_RING), A_BYTES, A_RING);
         akt += 2;
         if (akt < aKT) { ia += 2 * BK; return; }
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     auto advance_b = [&]() {
         wrb = next_slot(next_slot(wrb, B_BYTES, B_RING), B_BYTES, B_RING);
         bkt += 2;
-        if (bkt < bKT) { ib += 2 * BK; if (ONE) ia += 2 * BK; return; }
+        if (bkt < bKT) { ib += 2 * BK; if constexpr (ONE) ia += 2 * BK; return; }
         if (bseq + nslot < seq_end) {
             bseq += nslot; bkt = 0; bpar ^= 1;
             set_tile_b(bseq);
