@@ -292,11 +292,16 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
                 // before, right after its register's last use: the first half of the rows (dead by the barrier) and the weights one by
                 // one as the second half is done with them, that half itself at the end.  At least three times TI / 2, rounded down, instructions lie
                 // between a read and its use: twelve with 256 rows, nine with 224 and 192, six with 160 and in 128 x 128 tiles.
+                // The rows run there and back, so that an instruction shares an operand with the one before it: nothing changes but what toggles, and the clock
+                // is what the power limit allows.  us, rows always upwards / this: INT8 16384 x 12288 x 4096 600.8 / 594.0, GELU^quant 16384 x 4096 x 1024
+                // 82.8 / 81.8, BF16 109.6 / 108.9;  BERT-large layer 32 x 512 270.9 / 269.0 (282.4 / 280.1 on another card), in M1 357.0 / 356.3, GPT prefill 0 to 1 %
+                // by the card.  (The columns there and back as well, over the two iterations of a pair: 631 / 623 us for the first of these, no gain.)
+                auto there_and_back = [](int jj, int r, int rows) { return jj & 1 ? rows - 1 - r : r; };
                 constexpr int HI = TI / 2, HS = TI - HI, NH = HS * TJ;
                 static_assert(NU <= NH, "a slot of the second half for every unit");
 #pragma unroll
                 for (int n = 0; n < HI * TJ; ++n) {
-                    const int jj = n / HI, ii = n % HI;
+                    const int jj = n / HI, ii = there_and_back(jj, n % HI, HI);
                     acc[ii][jj] = mfma16_step<ADT>(fb[jj], fa[ii], acc[ii][jj]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -305,7 +310,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int n = 0; n < NH; ++n) {
-                    const int jj = n / HS, ii = HI + n % HS;
+                    const int jj = n / HS, ii = HI + there_and_back(jj, n % HS, HS);
                     acc[ii][jj] = mfma16_step<ADT>(fb[jj], fa[ii], acc[ii][jj]);
                     if (n < HI) fa[n] = *reinterpret_cast<const v4i*>(smem + nda + foa + n * 1024);
                     if (n % HS == HS - 1) fb[jj] = *reinterpret_cast<const v4i*>(smem + ndb + fob + jj * 256);
