@@ -350,16 +350,21 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         }
         // epilogue of this tile; the ring keeps filling with the next tile's slabs meanwhile
         const float* sv = sv0 + par * SVF;
+        // 16-bit results: what hangs on the lane's number is worked out per tile, from a number the compiler cannot carry over the main loop
+        constexpr bool HP = !WIDE && ElemSize<CDT>::v == 2;
+        int el = lane;
+        if constexpr (HP) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(el));
         float rsr[CI];
 #pragma unroll
         for (int i = 0; i < CI; ++i)
-            rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * (BM / WM) + i * (WIDE ? 32 : 16) + (WIDE ? ml : r16)] : 1.0f;
+            rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * (BM / WM) + i * (WIDE ? 32 : 16) + (HP ? el & 15 : WIDE ? ml : r16)] : 1.0f;
         if constexpr (WIDE) epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, true, UNIT>(g, acc, sv, rsr, m0, n0, tid);
+        else if constexpr (HP) epilogue_rows16_hp<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(g, acc, sv, rsr, m0, n0, wave, el);
         else if constexpr (PART) {
             GemmArgs gp = g;
             gp.C = (int32_t*)g.C + (int64_t)(seq / ntiles) * g.M * g.ldc;
-            epilogue_rows16<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(gp, acc, sv, rsr, m0, n0, tid);
-        } else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(g, acc, sv, rsr, m0, n0, tid);
+            epilogue_rows16<BM, BN, WM, WN, EPI, CDT, UNIT>(gp, acc, sv, rsr, m0, n0, tid);
+        } else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, UNIT>(g, acc, sv, rsr, m0, n0, tid);
         seq += nslot;
         par ^= 1;
         if (seq >= seq_end) break;

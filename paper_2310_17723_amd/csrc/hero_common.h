@@ -164,6 +164,36 @@ __device__ __forceinline__ float gelu_erf(float x) {
     return fmaf(-fabsf(x), q, fmaxf(x, 0.0f));
 }
 
+// The same for eight values side by side, step by step: an empty asm statement that takes all eight ends a step.  Left to itself the compiler
+// runs one value's chain of twelve dependent instructions after the other's.
+__device__ __forceinline__ void step_end(float (&v)[8]) {
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
+}
+__device__ __forceinline__ void gelu_erf8(float (&x)[8]) {
+    constexpr float C[7] = {3.309558087e-05f, -7.692443905e-04f, 8.080800064e-03f, -5.341223627e-02f, -4.587708712e-01f, -1.151201725e+00f, -9.999930859e-01f};
+    float z[8], p[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) z[t] = fminf(fabsf(x[t]), 6.0f);
+    step_end(z);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) p[t] = fmaf(C[0], z[t], C[1]);
+    step_end(p);
+#pragma unroll
+    for (int k = 2; k < 7; ++k) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) p[t] = fmaf(p[t], z[t], C[k]);
+        step_end(p);
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) p[t] = __builtin_amdgcn_exp2f(p[t]);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) z[t] = fmaxf(x[t], 0.0f);
+    step_end(z);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = fmaf(-fabsf(x[t]), p[t], z[t]);
+    step_end(x);
+}
+
 // four codes of LN^quant.  E4M3 (the variant of Sec. 2.1's 8-bit format): of the true quotient, |y / s| <= 448 (1 + 2^-23) clamped to the
 // format's range; INT8 behind a LayerNorm: |v * inv_sc| <= 127 (1 + 2^-22), so v * inv_sc + 128 rounds into 1 .. 255
 __device__ __forceinline__ uint32_t ln_codes4(const float* v, float sc, float inv_sc, bool f8) {

@@ -60,3 +60,21 @@ def test_16_bits(M, N, kb, dt, tile):
         buf, y = _canvas(M, N, dt, step)
         hero.hero_hp_gemm(a, w, bias, residual=rows, C_out=y, tile=tile)
         assert bool(((y.double() - ref).abs() <= bound + (ref.abs() + bound) * ulp).all()) and _untouched(buf, M, N), step
+
+
+@pytest.mark.parametrize("tile", [7, 8, 10, 11, 12])
+@pytest.mark.parametrize("M,N", [(2048, 2304), (2047, 2304), (2049, 2303), (1793, 2312)])
+def test_16_bit_results_whole_and_cut_tiles(M, N, tile):
+    """Tiles whose rows all exist take a path of their own, without a row scale and bias as with them: the ring kernel's bits."""
+    hero, K = pkg.load(), 384
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a, w = (torch.randint(-127, 128, (n, K), device="cuda", generator=g, dtype=torch.int8) for n in (M, N))
+    rs, cs = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) / (90 * K ** 0.5)
+    for dt in (torch.float16, torch.bfloat16):
+        for epi in (HB.EPI_DEQUANT, HB.EPI_DEQUANT_GELU):
+            for kw in (dict(a_row_scale=rs, bias=cs * 30), dict()):
+                for step in (4, 8):
+                    (buf, out), (_, other) = _canvas(M, N, dt, step), _canvas(M, N, dt, step)
+                    hero.hero_int8_gemm(a, w, b_col_scale=cs, epi=epi, C_out=out, tile=tile, **kw)
+                    hero.hero_int8_gemm(a, w, b_col_scale=cs, epi=epi, C_out=other, tile=2, **kw)
+                    assert torch.equal(out, other) and _untouched(buf, M, N), (dt, epi, bool(kw), step)
