@@ -39,7 +39,7 @@ constexpr int pair_loads_behind(bool odd, int na, int nb, int la, int lb) {
     return c;
 }
 
-template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT = HERO_I8, bool PART = false>
+template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT = HERO_I8, bool PART = false, bool STEADY = false>
 __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(GemmArgs g) {
     constexpr bool UNIT = ADT == HERO_BF16 || ADT == HERO_F16;      // 16-bit operands: no scales, y = acc + bias
     constexpr bool WIDE = ADT == HERO_F8E4M3;                       // 32 x 32 tiles; INT8 and 16 bits: 16 x 16 (mfma16_step)
@@ -150,13 +150,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         }
     };
     auto issue_b = [&](int u) {
-        if (u == 0 && bkt == 0) issue_tile_vectors(bpar);
+        if (!STEADY && u == 0 && bkt == 0) issue_tile_vectors(bpar);
         dma16s(ob[u], ib, wbase + A_RING + wrb + u * NWAVE * 1024);
         dma16s(ob[u], ib + BK, wbase + A_RING + next_slot(wrb, B_BYTES, B_RING) + u * NWAVE * 1024);
     };
     auto advance_a = [&]() {                                     // next pair; past the last tile the last pair repeats (never read)
         if constexpr (ONE) return;
         wra = next_slot(next_slot(wra, A_BYTES, A_RING), A_BYTES, A_RING);
+        if constexpr (STEADY) { ia += 2 * BK; return; }
         akt += 2;
         if (akt < aKT) { ia += 2 * BK; return; }
         if (aseq + nslot < seq_end) {
@@ -166,6 +167,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
     };
     auto advance_b = [&]() {
         wrb = next_slot(next_slot(wrb, B_BYTES, B_RING), B_BYTES, B_RING);
+        if constexpr (STEADY) { ib += 2 * BK; return; }
         bkt += 2;
         if (bkt < bKT) { ib += 2 * BK; if constexpr (ONE) ia += 2 * BK; return; }
         if (bseq + nslot < seq_end) {
@@ -203,6 +205,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
             advance_a();
         }
         if (pb >= 0 && pb % 2 == 0) {
+            if (STEADY && pb == 0) issue_tile_vectors(0);
 #pragma unroll
             for (int u = 0; u < B_UNITS; ++u) issue_b(u);
             advance_b();
@@ -326,7 +329,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
             if (put_a) advance_a();
             rda = nda; rdb = ndb;
         };
-        for (int kt = 0; kt < KT; kt += 2) {
+        // STEADY: the streams are D pairs ahead, so that the last D pairs of iterations, in front of which they move on to the next tile, are code of their own
+        // and the loop of the others holds no branch but its own.  Past the last tile the last pair repeats (never read).
+        constexpr int D = STEADY ? NSA / 2 : 0;
+        static_assert(!STEADY || (NSB / 2 == D && !ONE && !WIDE && EPI != HERO_EPI_GELU_REQUANT), "both streams move on together");
+        const int KS = KT - 2 * D;
+        for (int kt = 0; kt < KS; kt += 2) {
             iteration(std::false_type{});
             iteration(std::true_type{});
             // S_a -> 1 / S_a once per tile (IEEE division): the vectors landed before the first barrier, KT >= 4 leaves another
@@ -334,6 +342,21 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
                 float* const s = sv0 + par * SVF + 2 * BN + tid;
                 *s = __fdiv_rn(1.0f, *s);
             }
+        }
+        if constexpr (STEADY) {
+            const bool last = seq + nslot >= seq_end;
+            const int back = last ? 2 * BK : 0;
+            if (!last) {
+                bpar ^= 1;
+                set_tile_a(seq + nslot);
+                set_tile_b(seq + nslot);
+                issue_tile_vectors(bpar);                              // (every wave is past the epilogue that read their buffer)
+            }
+            static_for<D>([&](auto) {
+                ia -= back; ib -= back;
+                iteration(std::false_type{});
+                iteration(std::true_type{});
+            });
         }
         // Prefetch for the caller's next kernel: this tile's share of the lines, one dword of each, through the same
         // direct loads into a scratch corner of the LDS (no register is written, so nothing has to wait for them; the
@@ -350,21 +373,21 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         }
         // epilogue of this tile; the ring keeps filling with the next tile's slabs meanwhile
         const float* sv = sv0 + par * SVF;
-        // 16-bit results: what hangs on the lane's number is worked out per tile, from a number the compiler cannot carry over the main loop
+        // 16-bit results and STEADY: what hangs on the lane's number is worked out per tile, from a number the compiler cannot carry over the main loop
         constexpr bool HP = !WIDE && ElemSize<CDT>::v == 2;
         int el = lane;
-        if constexpr (HP) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(el));
+        if constexpr (HP || STEADY) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(el));
         float rsr[CI];
 #pragma unroll
         for (int i = 0; i < CI; ++i)
-            rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * (BM / WM) + i * (WIDE ? 32 : 16) + (HP ? el & 15 : WIDE ? ml : r16)] : 1.0f;
+            rsr[i] = (EPI != HERO_EPI_RAW_I32 && has_rs) ? sv[3 * BN + wm * (BM / WM) + i * (WIDE ? 32 : 16) + (HP || STEADY ? el & 15 : WIDE ? ml : r16)] : 1.0f;
         if constexpr (WIDE) epilogue_direct<BM, BN, WM, WN, EPI, CDT, RDT, true, UNIT>(g, acc, sv, rsr, m0, n0, tid);
         else if constexpr (HP) epilogue_rows16_hp<BM, BN, WM, WN, EPI, CDT, RDT, UNIT>(g, acc, sv, rsr, m0, n0, wave, el);
         else if constexpr (PART) {
             GemmArgs gp = g;
             gp.C = (int32_t*)g.C + (int64_t)(seq / ntiles) * g.M * g.ldc;
             epilogue_rows16<BM, BN, WM, WN, EPI, CDT, UNIT>(gp, acc, sv, rsr, m0, n0, tid);
-        } else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, UNIT>(g, acc, sv, rsr, m0, n0, tid);
+        } else epilogue_rows16<BM, BN, WM, WN, EPI, CDT, UNIT>(g, acc, sv, rsr, m0, n0, STEADY ? wave * 64 + el : tid);
         seq += nslot;
         par ^= 1;
         if (seq >= seq_end) break;
@@ -381,7 +404,7 @@ inline void share_prefetch(GemmArgs& g, int64_t tiles, int lanes) {
 // Slots of the two rings, A and B, for a tile of BM x 256: what 160 KB hold.  Both operands in the same
 // iteration lose what the slots give: 2500 x 4096 x 4096 in tiles of 192 rows 48.0 us with five and five, 42.9 with four and five.
 template <int BM> struct PersRing { static constexpr int A = BM == 160 ? 5 : 4, B = BM == 160 ? 6 : 5; };
-template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT>
+template <int BM, int BN, int WM, int WN, int NSA, int NSB, int EPI, int CDT, int RDT, int ADT, bool STEADY = false>
 hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) {
     GemmArgs gp = g;
     gp.ntm = (g.M + BM - 1) / BM; gp.ntn = (g.N + BN - 1) / BN;
@@ -391,7 +414,7 @@ hero_status launch_persistent(const GemmArgs& g, int wg_per_cu, hipStream_t st) 
     share_prefetch(gp, tiles, WM * WN * 64);
     const int cap = 32 * wg_per_cu;                                   // 32 CUs per XCD
     const int nslot = gp.per_xcd < cap ? gp.per_xcd : cap;
-    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, NSA, NSB, EPI, CDT, RDT, ADT>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
+    hipLaunchKernelGGL((int8_gemm_persistent_kernel<BM, BN, WM, WN, NSA, NSB, EPI, CDT, RDT, ADT, false, STEADY>), dim3((unsigned)(nslot * NUM_XCD)), dim3(WM * WN * 64), 0, st, gp);
     return hero_launch_status();
 }
 
@@ -402,6 +425,14 @@ hero_status launch_persistent_tile(const GemmArgs& g, int rows, hipStream_t st) 
         constexpr int BM = decltype(R)::value;
         return launch_persistent<BM, 256, 2, 4, PersRing<BM>::A, PersRing<BM>::B, EPI, CDT, RDT, ADT>(g, 1, st);
     };
+    // The branch-free loop where a launch has four tiles per CU and more of 64 slabs and more.  It takes 1223 cycles per slab of 1024 cycles of matrix instructions
+    // where the other takes 1405 (the same at any clock: what waits is not memory), and the clock falls by half of that.  us, other / this: INT8 16384 x
+    // 12288 x 4096 608.8 / 584.0 (2.82 POP/s), 16-bit result 16384 x 4096 x 4096 217.8 / 211.3, x 16384 829.7 / 796.5, BF16 16384 x 12288 x 4096 1188 /
+    // 1149;  GPT prefill 8 x 2048 3055 / 3004.  Not for less: with K = 1024 (four tiles) a launch is as long, and the BERT-large layer, whose other kernels pay for
+    // the clock, was 2 % slower with it.  GELU^quant: spills.
+    if constexpr (ADT != HERO_F8E4M3 && EPI != HERO_EPI_GELU_REQUANT)
+        if (rows == 256 && g.K >= 64 * BK && ((int64_t)(g.M + 255) / 256) * ((g.N + 255) / 256) >= 4 * 256)
+            return launch_persistent<256, 256, 2, 4, PersRing<256>::A, PersRing<256>::B, EPI, CDT, RDT, ADT, true>(g, 1, st);
     if (rows == 256) return wide(std::integral_constant<int, 256>{});
     if (rows == 192) return wide(std::integral_constant<int, 192>{});
     if constexpr (ADT != HERO_F8E4M3) {

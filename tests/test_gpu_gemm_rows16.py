@@ -78,3 +78,33 @@ def test_16_bit_results_whole_and_cut_tiles(M, N, tile):
                     hero.hero_int8_gemm(a, w, b_col_scale=cs, epi=epi, C_out=out, tile=tile, **kw)
                     hero.hero_int8_gemm(a, w, b_col_scale=cs, epi=epi, C_out=other, tile=2, **kw)
                     assert torch.equal(out, other) and _untouched(buf, M, N), (dt, epi, bool(kw), step)
+
+
+@pytest.mark.parametrize("M,N,K", [(8065, 8200, 4096), (7936, 8448, 4224), (16384, 4097, 4096)])
+def test_the_branch_free_loop(M, N, K):
+    """1024 tiles of 256 x 256 and more, each of 64 slabs or more: the last iterations of a tile are code of their own there.  INT8 against the
+    ring kernel's bits, 16 bits against 64 on rows of several tiles."""
+    hero = pkg.load()
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a, w = (torch.randint(-127, 128, (n, K), device="cuda", generator=g, dtype=torch.int8) for n in (M, N))
+    rs, cs = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) / (90 * K ** 0.5)
+    bias, res = torch.randn(N, device="cuda", generator=g), torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16)
+    scaled = dict(a_row_scale=rs, b_col_scale=cs, bias=bias)
+    kinds = [dict(epi=HB.EPI_RAW_I32, dt=torch.int32), dict(epi=HB.EPI_REQUANT, dt=torch.int8, **scaled), dict(epi=HB.EPI_DEQUANT_GELU, dt=torch.float16, **scaled)]
+    if N % 4 == 0:
+        kinds.append(dict(epi=HB.EPI_DEQUANT, dt=torch.bfloat16, residual=res, **scaled))
+    for e in kinds:
+        dt = e.pop("dt")
+        (buf, out), (_, other) = _canvas(M, N, dt, 16), _canvas(M, N, dt, 16)
+        hero.hero_int8_gemm(a, w, C_out=out, tile=7, **e)
+        hero.hero_int8_gemm(a, w, C_out=other, tile=2, **e)
+        assert torch.equal(out, other) and _untouched(buf, M, N), e["epi"]
+    rows = torch.tensor([0, 255, 256, M // 2, M - 257, M - 1], device="cuda")
+    for dt, ulp in ((torch.bfloat16, 2.0 ** -8), (torch.float16, 2.0 ** -11)):
+        x, y = torch.randn((M, K // 2), device="cuda", generator=g).to(dt), (torch.randn((N, K // 2), device="cuda", generator=g) * K ** -0.5).to(dt)
+        buf, out = _canvas(M, N, dt, 8)
+        hero.hero_hp_gemm(x, y, bias, C_out=out, tile=7)             # half of K: 64 slabs of 16 bits
+        xs = x[rows].double()
+        ref = xs @ y.double().t() + bias.double()
+        bound = (K + 4) * 2.0 ** -24 * (xs.abs() @ y.double().abs().t() + bias.double().abs())
+        assert bool(((out[rows].double() - ref).abs() <= bound + (ref.abs() + bound) * ulp).all()) and _untouched(buf, M, N), dt
