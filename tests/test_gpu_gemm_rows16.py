@@ -80,6 +80,31 @@ def test_16_bit_results_whole_and_cut_tiles(M, N, tile):
                     assert torch.equal(out, other) and _untouched(buf, M, N), (dt, epi, bool(kw), step)
 
 
+@pytest.mark.parametrize("tile", [7, 8, 10, 11, 12])
+@pytest.mark.parametrize("M,N", [(2049, 2312), (1793, 2307)])
+def test_residual_off_wide_boundaries(M, N, tile):
+    """Pieces whose 16 columns all exist, and ones that N cuts, of a residual that lies on 2, 4 and 8 bytes: the bits of one that lies on 16."""
+    hero, K = pkg.load(), 384
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a, w = (torch.randint(-127, 128, (n, K), device="cuda", generator=g, dtype=torch.int8) for n in (M, N))
+    rs, cs = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) / (90 * K ** 0.5)
+    bias, r = torch.randn(N, device="cuda", generator=g), torch.randn((M, N), device="cuda", generator=g)
+    for dt in (torch.float16, torch.bfloat16):
+        x, y = torch.randn((M, K), device="cuda", generator=g).to(dt), (torch.randn((N, K), device="cuda", generator=g) * K ** -0.5).to(dt)
+        first = {}
+        for ldr, off in ((2320, 0), (2324, 0), (2320, 1), (2320, 4), (2321, 0), (2322, 2)):
+            res = torch.full((M * ldr + off,), 9, dtype=dt, device="cuda")[off:].view(M, ldr)[:, :N]
+            res.copy_(r)
+            calls = {"linear": lambda c: hero.hero_hp_gemm(x, y, bias, residual=res, C_out=c, tile=tile),
+                     "gelu": lambda c: hero.hero_hp_gemm(x, y, bias, residual=res, gelu=True, C_out=c, tile=tile)}
+            if ldr % 4 == 0 and off == 0:                                # all that 8-bit operands come with
+                calls["i8"] = lambda c: hero.hero_int8_gemm(a, w, rs, cs, bias, residual=res, epi=HB.EPI_DEQUANT, C_out=c, tile=tile)
+            for name, call in calls.items():
+                buf, out = _canvas(M, N, dt, 16)
+                call(out)
+                assert torch.equal(first.setdefault(name, out), out) and _untouched(buf, M, N), (dt, name, ldr, off)
+
+
 @pytest.mark.parametrize("M,N,K", [(8065, 8200, 4096), (7936, 8448, 4224), (16384, 4097, 4096)])
 def test_the_branch_free_loop(M, N, K):
     """1024 tiles of 256 x 256 and more, each of 64 slabs or more: the last iterations of a tile are code of their own there.  INT8 against the
