@@ -105,31 +105,41 @@ def test_residual_off_wide_boundaries(M, N, tile):
                 assert torch.equal(first.setdefault(name, out), out) and _untouched(buf, M, N), (dt, name, ldr, off)
 
 
-@pytest.mark.parametrize("M,N,K", [(8065, 8200, 4096), (7936, 8448, 4224), (16384, 4097, 4096)])
+@pytest.mark.parametrize("M,N,K", [(8065, 8200, 4096), (7937, 8448, 4224), (16384, 4097, 4096)])
 def test_the_branch_free_loop(M, N, K):
-    """1024 tiles of 256 x 256 and more, each of 64 slabs or more: the last iterations of a tile are code of their own there.  INT8 against the
-    ring kernel's bits, 16 bits against 64 on rows of several tiles."""
+    """1024 tiles of 256 x 256 and more, each of 64 slabs or more (66: the activations' ring of four slots starts the next tile at another one): the
+    last iterations of a tile are code of their own there.  INT8 against the ring kernel's bits, 16 bits against 64 on rows of several tiles."""
+    assert -(-M // 256) * -(-N // 256) >= 1024 and K >= 64 * 64      # what launch_persistent_tile asks for
     hero = pkg.load()
     g = torch.Generator(device="cuda").manual_seed(M + K)
     a, w = (torch.randint(-127, 128, (n, K), device="cuda", generator=g, dtype=torch.int8) for n in (M, N))
     rs, cs = torch.rand(M, device="cuda", generator=g) + 0.5, (torch.rand(N, device="cuda", generator=g) + 0.5) / (90 * K ** 0.5)
-    bias, res = torch.randn(N, device="cuda", generator=g), torch.randn((M, N), device="cuda", generator=g).to(torch.bfloat16)
+    bias, res = torch.randn(N, device="cuda", generator=g), {}
+    for dt in (torch.bfloat16, torch.float16):
+        res[dt] = _canvas(M, N, dt, 16)[1]
+        res[dt].copy_(torch.randn((M, N), device="cuda", generator=g))
     scaled = dict(a_row_scale=rs, b_col_scale=cs, bias=bias)
-    kinds = [dict(epi=HB.EPI_RAW_I32, dt=torch.int32), dict(epi=HB.EPI_REQUANT, dt=torch.int8, **scaled), dict(epi=HB.EPI_DEQUANT_GELU, dt=torch.float16, **scaled)]
-    if N % 4 == 0:
-        kinds.append(dict(epi=HB.EPI_DEQUANT, dt=torch.bfloat16, residual=res, **scaled))
+    kinds = [dict(epi=HB.EPI_RAW_I32, dt=torch.int32), dict(epi=HB.EPI_REQUANT, dt=torch.int8, **scaled)]
+    for dt in res:
+        kinds += [dict(epi=HB.EPI_DEQUANT, dt=dt, **scaled), dict(epi=HB.EPI_DEQUANT_GELU, dt=dt, **scaled), dict(epi=HB.EPI_DEQUANT, dt=dt, residual=res[dt], **scaled)]
     for e in kinds:
         dt = e.pop("dt")
         (buf, out), (_, other) = _canvas(M, N, dt, 16), _canvas(M, N, dt, 16)
         hero.hero_int8_gemm(a, w, C_out=out, tile=7, **e)
         hero.hero_int8_gemm(a, w, C_out=other, tile=2, **e)
-        assert torch.equal(out, other) and _untouched(buf, M, N), e["epi"]
+        assert torch.equal(out, other) and _untouched(buf, M, N), (e["epi"], dt, "residual" in e)
     rows = torch.tensor([0, 255, 256, M // 2, M - 257, M - 1], device="cuda")
     for dt, ulp in ((torch.bfloat16, 2.0 ** -8), (torch.float16, 2.0 ** -11)):
         x, y = torch.randn((M, K // 2), device="cuda", generator=g).to(dt), (torch.randn((N, K // 2), device="cuda", generator=g) * K ** -0.5).to(dt)
-        buf, out = _canvas(M, N, dt, 8)
-        hero.hero_hp_gemm(x, y, bias, C_out=out, tile=7)             # half of K: 64 slabs of 16 bits
-        xs = x[rows].double()
-        ref = xs @ y.double().t() + bias.double()
-        bound = (K + 4) * 2.0 ** -24 * (xs.abs() @ y.double().abs().t() + bias.double().abs())
-        assert bool(((out[rows].double() - ref).abs() <= bound + (ref.abs() + bound) * ulp).all()) and _untouched(buf, M, N), dt
+        xs, rr = x[rows].double(), res[dt][rows].double()
+        lin = xs @ y.double().t() + bias.double()
+        sums = (K + 4) * 2.0 ** -24 * (xs.abs() @ y.double().abs().t() + bias.double().abs())
+        for gelu in (False, True):
+            for r in (None, res[dt]):
+                buf, out = _canvas(M, N, dt, 8)
+                hero.hero_hp_gemm(x, y, bias, residual=r, gelu=gelu, C_out=out, tile=7)      # half of K: the same slabs of 16 bits
+                act = torch.nn.functional.gelu(lin) if gelu else lin
+                ref = act + (rr if r is not None else 0)
+                # GELU's slope is at most 1.13, its fp32 form within 1.1e-7 and a rounding; the residual's sum rounds once
+                bound = (1.13 * sums + 1.1e-7 + 2.0 ** -24 * act.abs() if gelu else sums) + (2.0 ** -24 * ref.abs() if r is not None else 0)
+                assert bool(((out[rows].double() - ref).abs() <= bound + (ref.abs() + bound) * ulp).all()) and _untouched(buf, M, N), (dt, gelu, r is not None)
