@@ -342,9 +342,10 @@ __device__ __forceinline__ void epilogue_rows16(const GemmArgs& g, ACC (&acc)[TI
 // 47.5 -> 46.8, GPT prefill 8 x 2048 3112 -> 3101, chunk 2 x 301 unchanged.
 // (8-bit results keep the other form: theirs is ahead by 2 to 4 % launched by itself, REQUANT 16384 x 3072 x 1024 50.1 -> 48.3, but the BERT-large layer is
 // up to 2 % slower: its clock falls by more than the cycles.)
-// A residual off 16-byte boundaries comes element by element, with a test in front of each only where N cuts the piece: a test is a branch, and every
-// second element was waited for by itself.  us, a test everywhere (before this form of the epilogue) -> now: INT8 16384 x 1024 x 1024, rows 1028 apart, 40.4 (40.0) -> 24.8,
-// BF16 16384 x 3076 x 1024 171.3 (168.8) -> 118.8, 3000 x 4100 x 1024 45.1 (44.7) -> 32.4;  on 16-byte boundaries unchanged.
+// A residual off 16-byte boundaries, and that of a piece that N cuts, comes element by element without a test (columns past the last one read the last one and
+// are not stored): a test is a branch, and every second element was waited for by itself, row after row of the tile that ends the launch.  us, a test per element
+// before this form of the epilogue, with it -> now: off 16 bytes INT8 16384 x 1024 x 1024 (rows 1028 apart) 40.0, 40.4 -> 24.8, BF16 16384 x 3076 x 1024 168.8, 171.3 -> 118.8;
+// cut FP16 + GELU 2049 x 2303 x 512 15.6, 16.1 -> 14.6, INT8 -> BF16 3000 x 3000 x 1024 21.4, 21.6 -> 20.3, 7000 x 1500 x 1024 25.1, 25.4 -> 23.6.
 template <int BM, int BN, int WM, int WN, int EPI, int CDT, int RDT, bool UNIT, typename ACC, int TI>
 __device__ __forceinline__ void epilogue_rows16_hp(const GemmArgs& g, ACC (&acc)[TI][4], const float* sv, const float (&rsr)[TI], int m0, int n0, int wave, int lane) {
     static_assert(BN / WN == 64 && BM / WM == 16 * TI && ElemSize<CDT>::v == 2, "a wave owns 64 columns, 16-bit results");
@@ -391,12 +392,9 @@ __device__ __forceinline__ void epilogue_rows16_hp(const GemmArgs& g, ACC (&acc)
 #pragma unroll
                         for (int k = 0; k < 4; ++k) r[k] = rp[8 * q + 2 * k] | ((uint32_t)rp[8 * q + 2 * k + 1] << 16);
                     } else {
+                        const int last = g.N - 1 - col0;
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const int n = col0 + 8 * q + 2 * k;
-                            const uint32_t e0 = n < g.N ? rp[8 * q + 2 * k] : 0, e1 = n + 1 < g.N ? rp[8 * q + 2 * k + 1] : 0;
-                            r[k] = e0 | (e1 << 16);
-                        }
+                        for (int k = 0; k < 4; ++k) r[k] = rp[min(8 * q + 2 * k, last)] | ((uint32_t)rp[min(8 * q + 2 * k + 1, last)] << 16);
                     }
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {

@@ -81,9 +81,10 @@ def test_16_bit_results_whole_and_cut_tiles(M, N, tile):
 
 
 @pytest.mark.parametrize("tile", [7, 8, 10, 11, 12])
-@pytest.mark.parametrize("M,N", [(2049, 2312), (1793, 2307)])
+@pytest.mark.parametrize("M,N", [(2049, 2312), (1793, 2307), (300, 2305)])
 def test_residual_off_wide_boundaries(M, N, tile):
-    """Pieces whose 16 columns all exist, and ones that N cuts, of a residual that lies on 2, 4 and 8 bytes: the bits of one that lies on 16."""
+    """Pieces whose 16 columns all exist, and ones that N cuts, of a residual that lies on 2, 4 and 8 bytes: the bits of one that lies on 16, and
+    (INT8) those of the ring kernel."""
     hero, K = pkg.load(), 384
     g = torch.Generator(device="cuda").manual_seed(M + N)
     a, w = (torch.randint(-127, 128, (n, K), device="cuda", generator=g, dtype=torch.int8) for n in (M, N))
@@ -103,6 +104,10 @@ def test_residual_off_wide_boundaries(M, N, tile):
                 buf, out = _canvas(M, N, dt, 16)
                 call(out)
                 assert torch.equal(first.setdefault(name, out), out) and _untouched(buf, M, N), (dt, name, ldr, off)
+            if "i8" in calls:
+                _, other = _canvas(M, N, dt, 16)
+                hero.hero_int8_gemm(a, w, rs, cs, bias, residual=res, epi=HB.EPI_DEQUANT, C_out=other, tile=2)
+                assert torch.equal(first["i8"], other), (dt, ldr, off)
 
 
 @pytest.mark.parametrize("M,N,K", [(8065, 8200, 4096), (7937, 8448, 4224), (16384, 4097, 4096)])
