@@ -428,8 +428,11 @@ hero_status launch_persistent_tile(const GemmArgs& g, int rows, hipStream_t st) 
     // The branch-free loop where a launch has four tiles per CU and more of 64 slabs and more.  It takes 1223 cycles per slab of 1024 cycles of matrix instructions
     // where the other takes 1405 (the same at any clock: what waits is not memory), and the clock falls by half of that.  us, other / this: INT8 16384 x
     // 12288 x 4096 608.8 / 584.0 (2.82 POP/s), 16-bit result 16384 x 4096 x 4096 217.8 / 211.3, x 16384 829.7 / 796.5, BF16 16384 x 12288 x 4096 1188 /
-    // 1149;  GPT prefill 8 x 2048 3055 / 3004.  Not for less: with K = 1024 (four tiles) a launch is as long, and the BERT-large layer, whose other kernels pay for
-    // the clock, was 2 % slower with it.  GELU^quant: spills.
+    // 1149;  GPT prefill 8 x 2048 3055 / 3004.  Not for less, though by itself it is ahead there too (one to eight tiles per CU of 16 slabs 0.96 to 1.01 of the other's time,
+    // of 32 and more 0.94 to 0.98: REQUANT 16384 x 1024 x 4096 55.6 / 53.5, x 16384 209.0 / 201.8, 16384 x 3072 x 2048 88.1 / 83.0): the BERT-large layer, whose other kernels pay for
+    // the clock, was 2 % slower with it everywhere, and with it for FC2 alone (one tile per CU, 64 slabs; in M1 128) 284.9 / 286.6, in M1 361.0 / 360.9.
+    // GELU^quant 16384 x 16384 x 4096 921 / 900 by itself, but GPT prefill as long with it.  All but one of the twelve INT8 and BF16 forms spill two to six registers,
+    // which come back where the streams move on to the next tile and wait there for the loads under way (GPT's QKV writes 202.9 MB, its result is 201.3).
     if constexpr (ADT != HERO_F8E4M3 && EPI != HERO_EPI_GELU_REQUANT)
         if (rows == 256 && g.K >= 64 * BK && ((int64_t)(g.M + 255) / 256) * ((g.N + 255) / 256) >= 4 * 256)
             return launch_persistent<256, 256, 2, 4, PersRing<256>::A, PersRing<256>::B, EPI, CDT, RDT, ADT, true>(g, 1, st);

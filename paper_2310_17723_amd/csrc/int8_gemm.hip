@@ -468,6 +468,7 @@ struct Choice { Kernel kernel; RingForm form; int rows = 256; };       // rows: 
 // 128 x 128: 4184 x 4096 x 1024 26.7 / 30.5, but 4931 rows 31.0 / 28.7, 6616 x 3072 x 1024 29.9 / 27.7; 8187 x 3072 x 768 is best in 224 rows, 28.5 / 33.4).  us, 256 / 224 / 192 / 160 / 128: INT8 GELU^quant 602 x 16384 x 4096 52.1 / 49.6 / 47.5 / 43.3 / 58.5, 16-bit result
 // 2500 x 4096 x 16384 160 / 152 / 141 / 134 / 174, REQUANT 3817 x 3072 x 1024 17.0 / 16.7 / 15.0 / 23.4 / 15.9, 9000 x 1024 x 4096 43.8 / 41.4 / 36.3 / 35.4 / 46.0, 14000 x
 // 3072 x 1024 47.0 / 44.1 / 49.4 / 53.4 / 47.6;  BF16 602 x 16384 x 4096 94 / 90 / 83 / 76 / 109, 9000 x 1024 x 4096 81 / 78 / 67 / 65 / 88.
+// (256 rows by the loop with branches.  Where launch_persistent_tile takes the one without, they take 0.94 to 0.98 of that, which is not weighed here.)
 inline Choice persistent_choice(hero_dtype adt, hero_epilogue epi, int64_t M, int64_t N, int64_t kb) {
     const bool f8 = adt == HERO_F8E4M3, gelu = epi == HERO_EPI_DEQUANT_GELU || epi == HERO_EPI_GELU_REQUANT;
     auto rounds = [&](int64_t bm, int64_t bn) { return (double)((((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256); };
