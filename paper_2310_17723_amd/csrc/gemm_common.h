@@ -338,7 +338,7 @@ __device__ __forceinline__ void epilogue_rows16(const GemmArgs& g, ACC (&acc)[TI
 
 // The same for 16-bit results.  WHOLE: all of the wave's rows and columns exist and its pieces lie on 16 bytes (uniform), so that neither a row nor
 // a store asks again and a row's address is the one above it plus a constant: four branches and 64-bit products per row were a tenth of the epilogue.
-// us, asked per row -> once, what the lane's number enters worked out per tile, GELU of eight values side by side (of the three it is the first that counts: INT8 -> FP16 GELU 16384 x 4096
+// us, asked per row -> once, what the lane's number enters worked out per tile (where the kernel still does), GELU of eight values side by side (of the three it is the first that counts: INT8 -> FP16 GELU 16384 x 4096
 // x 1024 85.8 before, 84.6 with the other two, 82.7 with all; FP16 16384 x 4096 x 512 74.5, 74.4, 73.3): BERT-large layer 32 x 512 in M1 362.0 -> 358.5, GELU 602 x 16384 x 4096
 // 47.5 -> 46.8, GPT prefill 8 x 2048 3112 -> 3101, chunk 2 x 301 unchanged.
 // (8-bit results keep the other form: theirs is ahead by 2 to 4 % launched by itself, REQUANT 16384 x 3072 x 1024 50.1 -> 48.3, but the BERT-large layer is

@@ -373,10 +373,13 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void int8_gemm_persistent_kernel(G
         }
         // epilogue of this tile; the ring keeps filling with the next tile's slabs meanwhile
         const float* sv = sv0 + par * SVF;
-        // 16-bit results and STEADY: what hangs on the lane's number is worked out per tile, from a number the compiler cannot carry over the main loop
-        constexpr bool HP = !WIDE && ElemSize<CDT>::v == 2;
+        // STEADY, 16-bit results behind GELU or of 128 x 128 tiles: what hangs on the lane's number is worked out per tile, from a number the compiler cannot carry over
+        // the main loop.  Not in front of other 16-bit results: no gain, and it is what a short launch ends with.  us, before the path for whole tiles / per tile / this: FP16
+        // 7000 x 1500 x 512 18.4 / 18.6 / 18.4, 9000 x 1000 x 512 17.6 / 17.8 / 17.6, INT8 -> FP16 4000 x 4100 x 4096 68.1 / 68.8 / 68.4, BF16 with a residual 4000 x 4100 x 2048 70.6 / 71.1 /
+        // 69.6;  GELU the other way round (FP16 1500 x 3001 x 512 12.4 / 12.4 / 12.5), 128 x 128 too (INT8 -> BF16 1500 x 3001 x 4096 29.3 / 29.3 / 29.4).
+        constexpr bool HP = !WIDE && ElemSize<CDT>::v == 2, ANEW = STEADY || (HP && (EPI == HERO_EPI_DEQUANT_GELU || BM == 128));
         int el = lane;
-        if constexpr (HP || STEADY) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(el));
+        if constexpr (ANEW) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(el));
         float rsr[CI];
 #pragma unroll
         for (int i = 0; i < CI; ++i)
